@@ -165,23 +165,80 @@ def _coords(dims, nnz, skew, gen):
     return coords[::-1]
 
 
-def prepare(case, seed):
+def _inputs(case, seed):
+    """Sorted host coordinates, values and factors, from the seed alone."""
     dims, ranks, skew = _fields(case)
-    kind = case["kind"]
-    cfg = dict(kind=kind, dims=dims, ranks=ranks, dtype=case["dtype"], nnz=case["nnz"])
+    cfg = dict(kind=case["kind"], dims=dims, ranks=ranks, dtype=case["dtype"], nnz=case["nnz"])
     dt = torch.float64 if case["dtype"] == "f64" else torch.float32
     gen = torch.Generator(device=DEVICE)
     gen.manual_seed(seed)
     coords = _coords(dims, case["nnz"], skew, gen)
     vals = (torch.rand(case["nnz"], dtype=dt, device=DEVICE, generator=gen) * 2 - 1).cpu().numpy()
     factors = [torch.randn(shape, dtype=dt, device=DEVICE, generator=gen).cpu().numpy() for shape in synth.factor_shapes(cfg)]
+    return cfg, coords, vals, factors
+
+
+def prepare(case, seed):
+    cfg, coords, vals, factors = _inputs(case, seed)
+    kind = cfg["kind"]
     sched = sc.schedule(case["schedule"], deterministic=case["deterministic"])
-    return Contraction(synth.KINDS[kind][0], coords, vals, dims, factors, sched, synth.output_shape(cfg))
+    return Contraction(synth.KINDS[kind][0], coords, vals, cfg["dims"], factors, sched, synth.output_shape(cfg))
 
 
 def run(state):
     state.run()
     return state.out
+
+
+def _add_up(count, width, into, part):
+    """Row into[e] of the result is the sum of part(e) over all e, in chunks that fit the memory."""
+    out = torch.zeros(count, width, dtype=torch.float64, device=DEVICE)
+    step = max(1, (1 << 28) // width)
+    for lo in range(0, into.numel(), step):
+        at = slice(lo, lo + step)
+        out.index_add_(0, into[at], part(at))
+    return out
+
+
+def exact(case, seed):
+    """The output in double precision: sums over the last mode first, as the expressions factor."""
+    cfg, coords, vals, factors = _inputs(case, seed)
+    kind, dims = cfg["kind"], cfg["dims"]
+    idx = [torch.from_numpy(c).to(DEVICE).long() for c in coords]
+    v = torch.from_numpy(vals).to(DEVICE).double()
+    f = [torch.from_numpy(x).to(DEVICE).double() for x in factors]
+    if kind.startswith("sddmm"):
+        i, j = idx
+        out = _add_up(dims[0], f[2].shape[1], i,
+                      lambda at: (v[at] * (f[0][i[at]] * f[1][j[at]]).sum(1))[:, None] * f[2][j[at]])
+        return out @ f[3] if kind.endswith("gemm") else out
+    # the factors on the modes 1, 2, ... from the leaf upwards: a row per (i, j, k), then a row per (i, j)
+    lead = f[0] if kind == "ttmc_all" else None
+    on = f[1:] if lead is not None else f[:len(dims) - 1]
+    key = idx[0]
+    for n, x in zip(dims[1:-1], idx[1:-1]):
+        key = key * n + x
+    nodes, up = torch.unique_consecutive(key, return_inverse=True)
+    leaf = idx[-1]
+    rows = _add_up(nodes.numel(), on[-1].shape[1], up, lambda at: v[at, None] * on[-1][leaf[at]])
+    for mode in range(len(dims) - 2, 0, -1):
+        here, key = nodes % dims[mode], nodes // dims[mode]
+        if mode > 1:
+            nodes, up = torch.unique_consecutive(key, return_inverse=True)
+            count = nodes.numel()
+        else:
+            up, count = key, dims[0]
+        below, g = rows, on[mode - 1]
+        if kind.startswith("mttkrp"):
+            rows = _add_up(count, g.shape[1], up, lambda at: g[here[at]] * below[at])
+        else:
+            rows = _add_up(count, g.shape[1] * below.shape[1], up,
+                           lambda at: (g[here[at]][:, :, None] * below[at][:, None, :]).flatten(1))
+    if lead is not None:
+        rows = lead.t().contiguous() @ rows
+    elif kind == "mttkrp_gemm":
+        rows = rows @ f[2]
+    return rows.reshape(synth.output_shape(cfg))
 
 
 def _expected_prefixes(dims, skew, nnz):
