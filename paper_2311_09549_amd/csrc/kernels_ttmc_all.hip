@@ -81,49 +81,88 @@ __global__ void __launch_bounds__(NT) mode0_reduce_kernel(K5Args a)
     }
 }
 
-// The same partial sums on the matrix cores, fp32, L = 16 LT in {16, 32, 64, 128}, M N a multiple of 64: a workgroup takes all of L
-// for 64 columns (a wavefront for 16 of them), so S is read once instead of once per 16 values of l; four slices per
-// v_mfma_f32_16x16x4_f32 with C^T as operand A (l along the rows) and S as operand B, both straight from global memory
-// (a lane's 16 neighbours read 64 contiguous bytes of a row).
+// The same partial sums on the matrix cores, fp32, L = 16 LT in {16, 32, 64, 128}, M N a multiple of 64: a wavefront takes all of L
+// for 64 columns, so S is read once; four slices per v_mfma_f32_16x16x4_f32 with C^T as operand A (l along the rows) and S
+// as operand B, both straight from global memory.  Which l and which column a tile's rows and columns stand for is free, so
+// a lane reads 16 adjacent bytes of a row of S (one column in each of the wavefront's four column tiles) and up to 16 of a row
+// of C (one l in each of four l tiles): three loads per 4 LT MFMAs at L = 128.  With 4-byte loads, nine per LT MFMAs, the L1
+// address path bound the kernel (2606 us = 66 TFLOP/s on 40,000 slices at 128 x 128 x 128, where the fp32 matrix rate of a large
+// library product is 149; 1532 us = 110 now).  The reads of the next UK steps are in flight while this batch is multiplied; the wavefronts
+// of a workgroup read the same rows of C.
 typedef float k5_floatx4 __attribute__((ext_vector_type(4)));
 template <int LT>
-__global__ void __launch_bounds__(NT) mode0_reduce_mfma_kernel(K5Args a)
+__global__ void __launch_bounds__(NT, 2) mode0_reduce_mfma_kernel(K5Args a)
 {
-    constexpr int UK = 4;   // steps of four slices whose operand reads are issued together
+    constexpr int UK = LT >= 8 ? 2 : 4;    // steps of four slices per batch of reads
+    constexpr int CW = LT < 4 ? LT : 4;    // adjacent values of l a lane reads at once ...
+    constexpr int CN = LT / CW;            // ... in CN pieces, 16 CW values of l apart
     const int tid = threadIdx.x;
     const int wave = tid / 64, lane = tid % 64, kk = lane / 16, col = lane % 16;
-    const int c = blockIdx.y * 64 + wave * 16 + col;   // < M N: the launch has M N / 64 workgroups along y
+    const int c = ((int)blockIdx.y * ((int)blockDim.x / 64) + wave) * 64 + 4 * col;   // < M N: the launch has M N / 64 wavefronts along y
     const int64_t r0 = (int64_t)blockIdx.x * a.chunk, r1 = min(r0 + a.chunk, a.rows);
-    const float *C = static_cast<const float *>(a.C) + col;
+    const float *C = static_cast<const float *>(a.C) + CW * col;
     const float *S = static_cast<const float *>(a.S) + c;
-    k5_floatx4 acc[LT];
-#pragma unroll
-    for (int lt = 0; lt < LT; ++lt) acc[lt] = k5_floatx4{0.f, 0.f, 0.f, 0.f};
-    for (int64_t rb = r0; rb < r1; rb += 4 * UK) {
-        float sv[UK], cv[UK][LT];
+    struct Batch {
+        k5_floatx4 s[UK];
+        Pack<float, CW> v[UK][CN];
+    };
+    auto load = [&](Batch &b, int64_t rb) {
 #pragma unroll
         for (int u = 0; u < UK; ++u) {
-            const int64_t row = rb + 4 * u + kk, rc = min(row, r1 - 1);   // lanes past the chunk read its last slice and are zeroed
-            const bool ok = row < r1;
-            const float s = S[rc * (int64_t)a.MN];
-            sv[u] = ok ? s : 0.f;
+            const int64_t row = rb + 4 * u + kk;
+            b.s[u] = *reinterpret_cast<const k5_floatx4 *>(S + row * a.MN);
 #pragma unroll
-            for (int lt = 0; lt < LT; ++lt) {
-                const float v = C[rc * a.ldC + lt * 16];
-                cv[u][lt] = ok ? v : 0.f;
-            }
+            for (int h = 0; h < CN; ++h) b.v[u][h] = *reinterpret_cast<const Pack<float, CW> *>(C + row * a.ldC + 16 * CW * h);
         }
+    };
+    k5_floatx4 acc[LT][4];
 #pragma unroll
-        for (int u = 0; u < UK; ++u)
+    for (int lt = 0; lt < LT; ++lt)
 #pragma unroll
-            for (int lt = 0; lt < LT; ++lt) acc[lt] = __builtin_amdgcn_mfma_f32_16x16x4f32(cv[u][lt], sv[u], acc[lt], 0, 0, 0);
+        for (int x = 0; x < 4; ++x) acc[lt][x] = k5_floatx4{0.f, 0.f, 0.f, 0.f};
+    auto step = [&](const k5_floatx4 &s, const Pack<float, CW> (&v)[CN]) {
+#pragma unroll
+        for (int lt = 0; lt < LT; ++lt)
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+                acc[lt][x] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[lt / CW].v[lt % CW], s[x], acc[lt][x], 0, 0, 0);
+    };
+    const int64_t nfull = (r1 - r0) / (4 * UK);   // batches without a row past the chunk
+    if (nfull > 0) {
+        Batch cur, next;
+        load(cur, r0);
+        for (int64_t b = 0; b < nfull; ++b) {
+            load(next, r0 + min(b + 1, nfull - 1) * (4 * UK));
+            __builtin_amdgcn_sched_barrier(0);   // the compiler would otherwise sink these reads below the products
+#pragma unroll
+            for (int u = 0; u < UK; ++u) step(cur.s[u], cur.v[u]);
+            cur = next;
+        }
     }
-    // acc[lt][r] = partial(l = 16 lt + 4 kk + r, column c)
+    for (int64_t rb = r0 + nfull * (4 * UK); rb < r1; rb += 4) {
+        const int64_t row = min(rb + kk, r1 - 1);   // lanes past the chunk read its last slice and are zeroed
+        const bool ok = rb + kk < r1;
+        k5_floatx4 s = *reinterpret_cast<const k5_floatx4 *>(S + row * a.MN);
+        Pack<float, CW> v[CN];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) s[x] = ok ? s[x] : 0.f;
+#pragma unroll
+        for (int h = 0; h < CN; ++h) {
+            v[h] = *reinterpret_cast<const Pack<float, CW> *>(C + row * a.ldC + 16 * CW * h);
+#pragma unroll
+            for (int i = 0; i < CW; ++i) v[h].v[i] = ok ? v[h].v[i] : 0.f;
+        }
+        step(s, v);
+    }
+    // acc[lt][x][r] = partial(l = 16 CW (lt / CW) + CW (4 kk + r) + lt % CW, column c + x)
     float *P = static_cast<float *>(a.partials) + (int64_t)blockIdx.x * a.L * a.MN + c;
 #pragma unroll
     for (int lt = 0; lt < LT; ++lt)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) P[(int64_t)(lt * 16 + 4 * kk + r) * a.MN] = acc[lt][r];
+        for (int r = 0; r < 4; ++r) {
+            const int l = 16 * CW * (lt / CW) + CW * (4 * kk + r) + lt % CW;
+            *reinterpret_cast<k5_floatx4 *>(P + (int64_t)l * a.MN) = k5_floatx4{acc[lt][0][r], acc[lt][1][r], acc[lt][2][r], acc[lt][3][r]};
+        }
 }
 
 // partial(b, l, (m,n)) = sum_{fibers f in chunk b} C(i_f,l) * D(j_f,m) * t(f,n); thread = (m,n)
@@ -237,25 +276,27 @@ __global__ void __launch_bounds__(NT) linear_all_kernel(K5Args a, const int32_t 
         if (ok[r]) P[((int64_t)blockIdx.y * KB_L + r) * NT + tid] = acc[r];
 }
 
-// A(e) = sum over chunks b of partial(b, e), in an order fixed by the launch: a workgroup owns 64 output
-// elements, its four wavefronts take the chunks round robin and their sums are added in wavefront order.
-// Every output element is written.
-template <typename T>
+// A(e) = sum over chunks b of partial(b, e), in an order fixed by the launch: a workgroup owns EW output
+// elements, its NT / EW groups of lanes take the chunks round robin and their sums are added in group order.
+// Every output element is written.  Small outputs over many chunks (16^3: 4096 elements, 507 chunks) leave 64-element
+// workgroups a chain of 127 reads each and the chip mostly idle; 16 elements keep the reads whole 64-byte segments, four
+// times the workgroups and a quarter of the chain (11 -> 5.5 us).
+template <typename T, int EW>
 __global__ void __launch_bounds__(NT) sum_partials_kernel(const T *__restrict__ partials, int nchunks, int64_t elems, T *__restrict__ out)
 {
     __shared__ T part_s[NT];
-    const int lane = threadIdx.x % 64, part = threadIdx.x / 64;
-    const int64_t e = (int64_t)blockIdx.x * 64 + lane;
+    const int lane = threadIdx.x % EW, part = threadIdx.x / EW;
+    const int64_t e = (int64_t)blockIdx.x * EW + lane;
     T s = T(0);
     if (e < elems) {
-#pragma unroll 4
-        for (int b = part; b < nchunks; b += NT / 64) s += partials[(int64_t)b * elems + e];
+#pragma unroll 8
+        for (int b = part; b < nchunks; b += NT / EW) s += partials[(int64_t)b * elems + e];
     }
     part_s[threadIdx.x] = s;
     __syncthreads();
     if (part == 0 && e < elems) {
         T tot = part_s[lane];
-        for (int w = 1; w < NT / 64; ++w) tot += part_s[w * 64 + lane];
+        for (int w = 1; w < NT / EW; ++w) tot += part_s[w * EW + lane];
         out[e] = tot;
     }
 }
@@ -315,12 +356,13 @@ sc_status run_ttmc_all(const sc_plan *p, const sc_csf_view *sp, const sc_dense_v
         if (p->k5_mfma_reduce) {
             if constexpr (sizeof(T) == 4) {
                 if (MN % 64 != 0) return SC_ERR_SCHED_UNSUPPORTED;
-                const dim3 mgrid((unsigned)p->k5_nchunks, (unsigned)(MN / 64), 1);
+                const int waves = MN % 256 == 0 ? 4 : MN % 128 == 0 ? 2 : 1;   // wavefronts (of 64 columns) per workgroup
+                const dim3 mgrid((unsigned)p->k5_nchunks, (unsigned)(MN / (64 * waves)), 1);
                 ln.begin("ttmc_all_mode0_reduce_mfma");
-                if (L == 16) mode0_reduce_mfma_kernel<1><<<mgrid, NT, 0, stream>>>(a);
-                else if (L == 32) mode0_reduce_mfma_kernel<2><<<mgrid, NT, 0, stream>>>(a);
-                else if (L == 64) mode0_reduce_mfma_kernel<4><<<mgrid, NT, 0, stream>>>(a);
-                else if (L == 128) mode0_reduce_mfma_kernel<8><<<mgrid, NT, 0, stream>>>(a);
+                if (L == 16) mode0_reduce_mfma_kernel<1><<<mgrid, 64 * waves, 0, stream>>>(a);
+                else if (L == 32) mode0_reduce_mfma_kernel<2><<<mgrid, 64 * waves, 0, stream>>>(a);
+                else if (L == 64) mode0_reduce_mfma_kernel<4><<<mgrid, 64 * waves, 0, stream>>>(a);
+                else if (L == 128) mode0_reduce_mfma_kernel<8><<<mgrid, 64 * waves, 0, stream>>>(a);
                 else return SC_ERR_SCHED_UNSUPPORTED;
                 ln.end();
             } else {
@@ -333,8 +375,13 @@ sc_status run_ttmc_all(const sc_plan *p, const sc_csf_view *sp, const sc_dense_v
         }
     }
     ln.begin("ttmc_all_sum_partials");
-    sum_partials_kernel<T><<<(unsigned)((elems + 63) / 64), NT, 0, stream>>>(static_cast<const T *>(a.partials), (int)p->k5_nchunks, elems,
-                                                                               static_cast<T *>(out));
+    // 16 elements per workgroup while 64 would leave compute units without one and there are chunks to share out
+    if (elems <= (int64_t)64 * p->n_cu && p->k5_nchunks >= 64)
+        sum_partials_kernel<T, 16><<<(unsigned)((elems + 15) / 16), NT, 0, stream>>>(static_cast<const T *>(a.partials), (int)p->k5_nchunks,
+                                                                                     elems, static_cast<T *>(out));
+    else
+        sum_partials_kernel<T, 64><<<(unsigned)((elems + 63) / 64), NT, 0, stream>>>(static_cast<const T *>(a.partials), (int)p->k5_nchunks,
+                                                                                     elems, static_cast<T *>(out));
     ln.end();
     return ln.status;
 }
