@@ -2,10 +2,11 @@
 // tensor compiler emits before any split), run as it stands: every stored entry is multiplied
 // with one element of every factor for every combination of the dense output indices, nothing is
 // factored out.  It is the baseline the fused and fissioned nests are compared with
-// (nnz * L * M multiply-adds for the order-3 chain instead of M * (nnz + F * L), Section 1), not
-// a tuned kernel: one workgroup per tile of nonzeros, one thread per dense output element, the
-// partial sum of an output row kept in a register while the tile stays inside one slice and added
-// atomically to the zeroed output when the slice changes.
+// (nnz * L * M multiply-adds for the order-3 chain instead of M * (nnz + F * L), Section 1), and what
+// SC_SCHED_AUTO falls back to for ranks without a factored kernel.  One workgroup per tile of
+// nonzeros; the partial sum of an output row is kept in registers while the walk stays inside one
+// slice.  linear_tiled_kernel takes the expressions of order 3 and 4 at ranks that are multiples of 4;
+// linear_kernel, one thread per dense output element, the other ranks and the SDDMM.
 //
 //   order 3 chain   A(i,l,m)   += B(i,j,k)   * C(j,l) * D(k,m)
 //   MTTKRP          A(i,r)     += B(i,j,k)   * C(j,r) * D(k,r)
@@ -119,6 +120,209 @@ __global__ void __launch_bounds__(NT) linear_kernel(LinArgs a, const TileRec *__
     }
 }
 
+// Ranks that are multiples of 4: a lane owns a 4 x 4 block of the output row (4 elements of the MTTKRP's), a lane group
+// of GS lanes (the smallest power of two that covers the blocks of a row, at most a wavefront: longer rows are
+// walked once per 64 blocks) walks a contiguous chunk of the tile's nonzeros.  What bounds the nest is instructions and
+// gathers per nonzero, not its multiply-adds: one element per thread cost four wavefronts two 4-byte gathers and their 64-bit
+// addresses per nonzero at 12 x 20 (405 us on 1.5 M nonzeros); with blocks two 16-byte gathers serve four nonzeros and 16
+// multiply-adds per lane (75 us).  The pieces of a slice cut by chunk boundaries are parked in LDS and added by the
+// lane group in which the slice ends; one update per tile and slice, atomic only where another tile holds part of the
+// slice: one atomic update per chunk and slice made a skewed tensor's heavy slices queue on their rows (587 us).
+template <typename T, int KIND>
+__global__ void __launch_bounds__(NT) linear_tiled_kernel(LinArgs a, const TileRec *__restrict__ tiles)
+{
+    constexpr int U = 4;                                 // nonzeros per step
+    constexpr int BX = KIND == K_MTTKRP3 ? 1 : 4;        // block rows
+    constexpr int D = KIND == K_TTMC4 ? 4 : 3;
+    struct alignas(16) V4 { T v[4]; };   // the rows of the factors are 16-byte aligned
+    struct alignas(16) Rec { uint32_t o[3]; int32_t i; };   // byte offsets of the factor rows, output row
+    // records of chunks that start a multiple of 16 apart spread over the banks
+    auto at = [](int c) { return c + (c >> 4); };
+    __shared__ Rec rec_s[LIN_TN + LIN_TN / 16];
+    __shared__ T v_s[LIN_TN + LIN_TN / 16];
+    __shared__ T park_s[4 * BX][NT];    // the open sum of every chunk ...
+    __shared__ int32_t began_s[NT];     // ... whether its slice began in that chunk
+    const TileRec t = tiles[blockIdx.x];
+    const int tid = threadIdx.x;
+    const int nchild = t.n1 - t.n0;
+    const T *vals = static_cast<const T *>(a.vals);
+    for (int c = tid; c < nchild; c += NT) {
+        const int32_t z = t.n0 + c;
+        int32_t x = z;
+        Rec r;
+        r.o[2] = 0;
+        r.o[D - 2] = (uint32_t)a.crd[D - 1][z] * (uint32_t)(a.ld[D - 2] * sizeof(T));
+        x = parent_in(a.pos[D - 1], t.a0, t.na, x);
+        r.o[D - 3] = (uint32_t)a.crd[D - 2][x] * (uint32_t)(a.ld[D - 3] * sizeof(T));
+        x = parent_in(a.pos[D - 2], t.b0, t.nb, x);
+        if (D == 4) {
+            r.o[0] = (uint32_t)a.crd[1][x] * (uint32_t)(a.ld[0] * sizeof(T));
+            x = parent_in(a.pos[1], t.c0, t.nc, x);
+        }
+        r.i = a.crd[0][x];
+        rec_s[at(c)] = r;
+        v_s[at(c)] = vals[z];
+    }
+    __syncthreads();
+
+    const int E = a.row_elems, nblk = E / (4 * BX);
+    int gs_log = 0;
+    while ((1 << gs_log) < nblk && gs_log < 6) ++gs_log;
+    const int G = NT >> gs_log, g = tid >> gs_log, li = tid & ((1 << gs_log) - 1);
+    const int q = (nchild + G - 1) / G, c0 = min(g * q, nchild), c1 = min(c0 + q, nchild);
+    const bool some = c0 < c1;
+    // the chunk's first slice began in an earlier chunk / its last slice goes on in the next one
+    const bool cont = some && c0 > 0 && rec_s[at(c0 - 1)].i == rec_s[at(c0)].i;
+    const bool open = some && c1 < nchild && rec_s[at(c1)].i == rec_s[at(c1 - 1)].i;
+    // slices shared with the neighbouring tiles
+    const int32_t i_in = (t.flags & (D == 4 ? 16 : 4)) ? rec_s[at(0)].i : -1, i_out = (t.flags & (D == 4 ? 32 : 8)) ? rec_s[at(nchild - 1)].i : -1;
+    T *A = static_cast<T *>(a.A);
+    const char *F0 = static_cast<const char *>(a.F[0]), *F1 = static_cast<const char *>(a.F[1]), *F2 = static_cast<const char *>(a.F[2]);
+    for (int pass = 0; pass < nblk; pass += 1 << gs_log) {
+        const int blk = min(pass + li, nblk - 1);
+        const bool mine = some && pass + li < nblk;
+        // block -> byte offsets of its pieces in the factor rows, first element and row distance in the output row
+        uint32_t p0 = 0, p1 = 0, p2 = 0;
+        int e0, dist = 0;
+        if (KIND == K_MTTKRP3) {
+            e0 = 4 * blk;
+            p0 = p1 = (uint32_t)(e0 * sizeof(T));
+        } else if (KIND == K_TTMC3) {
+            const int n4 = a.cols[1] / 4, x = blk / n4, y = blk % n4;
+            p0 = (uint32_t)(4 * x * sizeof(T));
+            p1 = (uint32_t)(4 * y * sizeof(T));
+            dist = a.cols[1];
+            e0 = 4 * x * dist + 4 * y;
+        } else {
+            const int m4 = a.cols[1] / 4, n4 = a.cols[2] / 4, l = blk / (m4 * n4), x = blk / n4 % m4, y = blk % n4;
+            p0 = (uint32_t)(l * sizeof(T));
+            p1 = (uint32_t)(4 * x * sizeof(T));
+            p2 = (uint32_t)(4 * y * sizeof(T));
+            dist = a.cols[2];
+            e0 = (l * a.cols[1] + 4 * x) * dist + 4 * y;
+        }
+        T acc[BX][4];
+#pragma unroll
+        for (int x = 0; x < BX; ++x)
+#pragma unroll
+            for (int y = 0; y < 4; ++y) acc[x][y] = T(0);
+        bool first = cont;       // still in the slice that began in an earlier chunk
+        int32_t cur = -1, head_i = -1;
+        T head[BX][4];
+#pragma unroll
+        for (int x = 0; x < BX; ++x)
+#pragma unroll
+            for (int y = 0; y < 4; ++y) head[x][y] = T(0);
+        auto emit = [&](int32_t i, const T (&o)[BX][4]) {
+            T *dst = A + (int64_t)i * E + e0;
+#pragma unroll
+            for (int x = 0; x < BX; ++x) {
+                V4 w;
+#pragma unroll
+                for (int y = 0; y < 4; ++y) w.v[y] = o[x][y];
+                if (i != i_in && i != i_out) {
+                    *reinterpret_cast<V4 *>(dst + x * dist) = w;
+                } else {
+#pragma unroll
+                    for (int y = 0; y < 4; ++y) atomic_add(dst + x * dist + y, w.v[y]);
+                }
+            }
+        };
+        auto end_slice = [&]() {
+            if (first) {
+#pragma unroll
+                for (int x = 0; x < BX; ++x)
+#pragma unroll
+                    for (int y = 0; y < 4; ++y) head[x][y] = acc[x][y];
+                head_i = cur;
+            } else {
+                emit(cur, acc);
+            }
+            first = false;
+#pragma unroll
+            for (int x = 0; x < BX; ++x)
+#pragma unroll
+                for (int y = 0; y < 4; ++y) acc[x][y] = T(0);
+        };
+        if (mine) {
+            cur = rec_s[at(c0)].i;
+            for (int c = c0; c < c1; c += U) {
+                Rec r[U];
+                T v[U], s[U];
+                V4 x[U], y[U];
+    #pragma unroll
+                for (int u = 0; u < U; ++u) {   // steps past the chunk repeat its last nonzero and are not added
+                    r[u] = rec_s[at(min(c + u, c1 - 1))];
+                    v[u] = v_s[at(min(c + u, c1 - 1))];
+                }
+    #pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (KIND == K_TTMC4) {
+                        s[u] = *reinterpret_cast<const T *>(F0 + (r[u].o[0] + p0));
+                        x[u] = *reinterpret_cast<const V4 *>(F1 + (r[u].o[1] + p1));
+                        y[u] = *reinterpret_cast<const V4 *>(F2 + (r[u].o[2] + p2));
+                    } else {
+                        x[u] = *reinterpret_cast<const V4 *>(F0 + (r[u].o[0] + p0));
+                        y[u] = *reinterpret_cast<const V4 *>(F1 + (r[u].o[1] + p1));
+                    }
+                }
+    #pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (c + u < c1) {
+                        if (r[u].i != cur) {
+                            end_slice();
+                            cur = r[u].i;
+                        }
+                        const T vs = KIND == K_TTMC4 ? v[u] * s[u] : v[u];
+                        if (KIND == K_MTTKRP3) {
+    #pragma unroll
+                            for (int k = 0; k < 4; ++k) acc[0][k] += vs * x[u].v[k] * y[u].v[k];
+                        } else {
+    #pragma unroll
+                            for (int k = 0; k < BX; ++k) {
+                                const T vx = vs * x[u].v[k];
+    #pragma unroll
+                                for (int n = 0; n < 4; ++n) acc[k][n] += vx * y[u].v[n];
+                            }
+                        }
+                    }
+            }
+            if (!open) end_slice();
+        }
+        // ---- slices cut by chunk boundaries ----
+        if (pass) __syncthreads();   // the previous pass's pieces have been read
+        if (mine && open) {
+#pragma unroll
+            for (int x = 0; x < BX; ++x)
+#pragma unroll
+                for (int y = 0; y < 4; ++y) park_s[4 * x + y][tid] = acc[x][y];
+        }
+        if (li == 0) began_s[g] = !first;
+        __syncthreads();
+        if (head_i >= 0) {
+            for (int h = g - 1; h >= 0; --h) {
+#pragma unroll
+                for (int x = 0; x < BX; ++x)
+#pragma unroll
+                    for (int y = 0; y < 4; ++y) head[x][y] += park_s[4 * x + y][(h << gs_log) + li];
+                if (began_s[h]) break;   // the slice began in chunk h
+            }
+            emit(head_i, head);
+        }
+    }
+}
+
+template <typename T>
+void launch_linear_nest(const sc_plan *p, const LinArgs &a, int ntiles, hipStream_t stream)
+{
+    const bool by4 = a.cols[1] % 4 == 0 && (p->kind == K_TTMC4 ? a.cols[2] : a.cols[0]) % 4 == 0;
+    // blocks of 4 x 4 wherever the ranks allow: 405 -> 75 us at 12 x 20
+    if (by4 && p->kind == K_TTMC3) linear_tiled_kernel<T, K_TTMC3><<<ntiles, NT, 0, stream>>>(a, p->d_tiles);
+    else if (by4 && p->kind == K_MTTKRP3) linear_tiled_kernel<T, K_MTTKRP3><<<ntiles, NT, 0, stream>>>(a, p->d_tiles);
+    else if (by4 && p->kind == K_TTMC4) linear_tiled_kernel<T, K_TTMC4><<<ntiles, NT, 0, stream>>>(a, p->d_tiles);
+    else linear_kernel<T><<<ntiles, NT, 0, stream>>>(a, p->d_tiles);
+}
+
 }  // namespace
 
 size_t linear_lds_bytes(const sc_plan *p)
@@ -154,9 +358,9 @@ sc_status launch_linear(const sc_plan *p, const sc_csf_view *sp, const sc_dense_
     a.row_elems = (int32_t)p->out_row_elems;
     ln.begin("linear_nest");
     if (p->dtype == SC_F64)
-        linear_kernel<double><<<ntiles, NT, 0, stream>>>(a, p->d_tiles);
+        launch_linear_nest<double>(p, a, ntiles, stream);
     else
-        linear_kernel<float><<<ntiles, NT, 0, stream>>>(a, p->d_tiles);
+        launch_linear_nest<float>(p, a, ntiles, stream);
     ln.end();
     return ln.status;
 }

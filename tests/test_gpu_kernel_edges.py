@@ -1,0 +1,56 @@
+"""GPU parity at the sizes where a kernel's split of the work has edges: remainders of its blocks, chunks and batches, the
+first and last size of a dispatch rule, slices cut by chunk and tile boundaries.  Against the oracle, within the tolerance of
+the other parity tests (1e-5 / 1e-12 times the sum of |partial products|)."""
+import numpy as np
+import pytest
+
+from paper_2311_09549_amd import binding as sc
+from paper_2311_09549_amd import synth
+from paper_2311_09549_amd.driver import Contraction
+
+from helpers import assert_parity
+
+pytestmark = pytest.mark.gpu
+
+
+def _problem(kind, dims, lengths, ranks, dtype="f32", seed=0):
+    """lengths: stored entries per slice; the other coordinates are drawn without repetition inside a slice."""
+    rng = np.random.default_rng(seed)
+    space = int(np.prod(dims[1:]))
+    rows, keys = [], []
+    for i, n in lengths:
+        rows.append(np.full(n, i))
+        keys.append(np.sort(rng.choice(space, size=n, replace=False)))
+    key, cols = np.concatenate(keys), []
+    for n in reversed(dims[1:]):
+        cols.append(key % n)
+        key = key // n
+    coords = [np.concatenate(rows)] + cols[::-1]
+    coords = [np.ascontiguousarray(c, dtype=np.int32) for c in coords]
+    dt = np.float64 if dtype == "f64" else np.float32
+    cfg = dict(kind=kind, dims=tuple(dims), nnz=coords[0].size, ranks=tuple(ranks), dtype=dtype, expr=synth.KINDS[kind][0])
+    factors = [rng.standard_normal(s).astype(dt) for s in synth.factor_shapes(cfg)]
+    return cfg, dict(coords=coords, vals=rng.uniform(-1, 1, coords[0].size).astype(dt), factors=factors)
+
+
+def _check(oracle, cfg, data, which, deterministic=False):
+    print(f"{cfg['kind']} {which} {cfg['dtype']} dims={cfg['dims']} ranks={cfg['ranks']} nnz={cfg['nnz']}", flush=True)
+    con = Contraction(cfg["expr"], data["coords"], data["vals"], cfg["dims"], data["factors"],
+                      sc.schedule(which, deterministic=deterministic), synth.output_shape(cfg))
+    con.run()
+    assert_parity(oracle, cfg, data, con.result())
+    return con
+
+
+# one slice over several tiles, slices that end at a chunk's or a tile's last entry, unit slices
+LENGTHS = [(0, 1), (1, 63), (2, 64), (3, 65), (5, 831), (6, 2300), (7, 1), (8, 1), (9, 700)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("kind,ranks", [("ttmc3", (4, 4)), ("ttmc3", (12, 20)), ("ttmc3", (36, 32)), ("ttmc3", (5, 8)), ("mttkrp3", (4,)),
+                                        ("mttkrp3", (12,)), ("mttkrp3", (260,)), ("ttmc4", (3, 4, 4)), ("ttmc4", (12, 12, 4)), ("ttmc4", (2, 6, 4))])
+def test_unfactored_nest_blocks(oracle, kind, ranks, dtype):
+    """Rows of one block, of a partly filled lane group, of more than a wavefront's blocks; ranks that are no multiple of 4."""
+    dims = (11, 41, 97) if kind != "ttmc4" else (11, 13, 17, 19)
+    cfg, data = _problem(kind, dims, LENGTHS, ranks, dtype)
+    _check(oracle, cfg, data, "linear")
