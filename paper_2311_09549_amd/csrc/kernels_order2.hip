@@ -4,7 +4,8 @@
 //
 // MODE 0 (FUSED): the sampled value t stays a register scalar; one walk over the stored
 //                 entries of S gathers X(i,:), Y(j,:) and Z(j,:), reduces the dot product
-//                 across the lane group and accumulates t * Z(j,:) into the row sum.
+//                 across the lane group and accumulates t * Z(j,:) into the row sum
+//                 (X(i,:) once per tile for tiles inside one row).
 // MODE 1 (FISSIONED, first kernel, SDDMM):  t(z) written to the workspace, one per entry.
 // MODE 2 (FISSIONED, second kernel, SpMM):  A(i,:) += t(z) * Z(j,:) with t read back.
 //
@@ -13,6 +14,8 @@
 // record per entry {X row offset, Y row offset, Z row offset, value} plus a row-end mark, so
 // the walk is a branch-free batch of gathers followed by arithmetic.
 #include "device_common.h"
+
+#include <type_traits>
 
 namespace sck {
 
@@ -38,6 +41,131 @@ template <typename T>
 __host__ __device__ constexpr size_t order2_lds_bytes(int tn, int ta)
 {
     return (size_t)NT * 16 + (size_t)padded(tn + 8) * (sizeof(SdRec<T>) + 4) + (size_t)(3 * ta + 8) * 4 + 2 * NT * 4 + 64;
+}
+
+// One step of a sum over adjacent lanes: p plus the value of the lane that the DPP control names.
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float p)
+{
+    const int b = __builtin_bit_cast(int, p);
+    return p + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(b, b, CTRL, 0xf, 0xf, false));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double p)
+{
+    struct Words { int lo, hi; } b = __builtin_bit_cast(Words, p);
+    b.lo = __builtin_amdgcn_update_dpp(b.lo, b.lo, CTRL, 0xf, 0xf, false);
+    b.hi = __builtin_amdgcn_update_dpp(b.hi, b.hi, CTRL, 0xf, 0xf, false);
+    return p + __builtin_bit_cast(double, b);
+}
+
+// Sum over a lane group, in every lane of it.  Up to 16 lanes on the vector ALU: neighbours, pairs, mirrored halves of
+// eight, mirrored rows of sixteen (once the lanes of a quad agree, a mirrored lane holds the other half's sum).  Shuffles go
+// through the LDS pipe, which the records of the walk already use.
+template <typename T, int LG>
+__device__ __forceinline__ T group_sum(T p)
+{
+    if (LG >= 2) p = dpp_add<0xb1>(p);    // quad_perm 1 0 3 2
+    if (LG >= 4) p = dpp_add<0x4e>(p);    // quad_perm 2 3 0 1
+    if (LG >= 8) p = dpp_add<0x141>(p);   // row_half_mirror
+    if (LG >= 16) p = dpp_add<0x140>(p);  // row_mirror
+    if (LG >= 32) p += __shfl_xor(p, 16, LG);
+    if (LG >= 64) p += __shfl_xor(p, 32, LG);
+    return p;
+}
+
+// A tile that lies inside one row of S: X(i,:) stays in registers (one 16-byte gather through the L1 less of three per
+// entry), there are no row tables and no row ends, and eight entries are in flight per lane group.  Every lane group sums its
+// chunk, the first one adds the groups' sums in their order.  With the sums over lane groups on the
+// vector ALU: 856 -> 806 us (fused, rank 64, 16 M entries over 1 M x 1 M with power-law rows).  What is left is bound by the
+// gathers of Y and Z, 8.2 GB through the L1s.
+template <typename T, int W, int MODE>
+__device__ __forceinline__ void one_row_tile(const Order2Args &a, const TileRec &t, T *slot_s, SdRec<T> *rec_s)
+{
+    constexpr int VEC = VecWidth<T>::value;
+    constexpr int LG = W / VEC;
+    constexpr int G = NT / LG;
+    constexpr int U = 8;
+    using P = Pack<T, VEC>;
+    const int tid = threadIdx.x, g = tid / LG, li = tid % LG;
+    const int nchild = t.n1 - t.n0;
+    const int q = (nchild + G - 1) / G;
+    const int gs = min(g * q, nchild), ge = min(gs + q, nchild);
+    const uint32_t rowY = (uint32_t)(a.ldY * sizeof(T)), rowZ = (uint32_t)(a.ldZ * sizeof(T));
+    const int32_t i = a.crd1[t.a0];
+    P x;
+    if (MODE < 2) x = *reinterpret_cast<const P *>(static_cast<const T *>(a.X) + (int64_t)i * a.ldX + li * VEC);
+    const T *vals = static_cast<const T *>(MODE == 2 ? a.T : a.vals);
+#pragma unroll 4
+    for (int c = tid; c < nchild; c += NT) {
+        const uint32_t j = (uint32_t)a.crd2[t.n0 + c];
+        SdRec<T> rec;
+        rec.xoff = 0;
+        rec.yoff = j * rowY;
+        rec.zoff = j * rowZ;
+        rec.v = vals[t.n0 + c];
+        rec_s[pidx(c)] = rec;
+    }
+    __syncthreads();
+    const char *Yb = static_cast<const char *>(a.Y) + li * 16;
+    const char *Zb = static_cast<const char *>(a.Z) + li * 16;
+    P sum;
+#pragma unroll
+    for (int k = 0; k < VEC; ++k) sum.v[k] = T(0);
+    // FULL: all U entries lie in the chunk; otherwise the ones past it repeat its last and are not added
+    auto batch = [&](int c, auto full) {
+        constexpr bool FULL = decltype(full)::value;
+        SdRec<T> r[U];
+        P y[U], z[U];
+        T sampled = T(0);
+#pragma unroll
+        for (int u = 0; u < U; ++u) r[u] = rec_s[pidx(FULL ? c + u : min(c + u, ge - 1))];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (MODE < 2) y[u] = *reinterpret_cast<const P *>(Yb + r[u].yoff);
+            if (MODE != 1) z[u] = *reinterpret_cast<const P *>(Zb + r[u].zoff);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            T tv = r[u].v;
+            if (MODE < 2) {
+                T p = T(0);
+#pragma unroll
+                for (int k = 0; k < VEC; ++k) p += x.v[k] * y[u].v[k];
+                tv *= group_sum<T, LG>(p);
+            }
+            if (MODE == 1) {
+                if (LG >= U) sampled = li == u ? tv : sampled;
+                else if (li == 0 && (FULL || c + u < ge)) static_cast<T *>(a.T)[t.n0 + c + u] = tv;
+            } else if (FULL || c + u < ge) {
+#pragma unroll
+                for (int k = 0; k < VEC; ++k) sum.v[k] += tv * z[u].v[k];
+            }
+        }
+        if (MODE == 1 && LG >= U && li < U && (FULL || c + li < ge)) static_cast<T *>(a.T)[t.n0 + c + li] = sampled;
+    };
+    int c = gs;
+    for (; c + U <= ge; c += U) batch(c, std::true_type{});
+    if (c < ge) batch(c, std::false_type{});
+    if (MODE == 1) return;
+    reinterpret_cast<P *>(slot_s)[tid] = sum;
+    __syncthreads();
+    if (tid >= LG) return;
+#pragma unroll
+    for (int h = 1; h < G; ++h) {
+        const P o = reinterpret_cast<const P *>(slot_s)[h * LG + tid];
+#pragma unroll
+        for (int k = 0; k < VEC; ++k) sum.v[k] += o.v[k];
+    }
+    T *dst = static_cast<T *>(a.A) + (int64_t)i * W + tid * VEC;
+    if (!(t.flags & 3)) {
+        *reinterpret_cast<P *>(dst) = sum;
+    } else if (a.partials) {   // the tile's one piece, numbered as its first row's if that row began in an earlier tile
+        *reinterpret_cast<P *>(static_cast<T *>(a.partials) + (int64_t)((t.flags & 1) ? t.pad[0] : t.pad[1]) * W + tid * VEC) = sum;
+    } else {
+#pragma unroll
+        for (int k = 0; k < VEC; ++k) atomic_add(dst + k, sum.v[k]);
+    }
 }
 
 template <typename T, int W, int MODE>
@@ -66,6 +194,10 @@ __global__ void __launch_bounds__(NT) sddmm_spmm_kernel(Order2Args a)
     const int tid = threadIdx.x;
     const int nchild = t.n1 - t.n0;
     const int na = t.na;
+    if (na == 1) {
+        one_row_tile<T, W, MODE>(a, t, slot_s, rec_s);
+        return;
+    }
     const int q = max(((nchild + G - 1) / G + U - 1) / U * U, U);   // entries per lane group, multiple of U
     const uint32_t rowX = (uint32_t)(a.ldX * sizeof(T)), rowY = (uint32_t)(a.ldY * sizeof(T)), rowZ = (uint32_t)(a.ldZ * sizeof(T));
 
@@ -200,9 +332,7 @@ __global__ void __launch_bounds__(NT) sddmm_spmm_kernel(Order2Args a)
                     T p = T(0);
 #pragma unroll
                     for (int i = 0; i < VEC; ++i) p += x[u].v[i] * y[u].v[i];
-#pragma unroll
-                    for (int m = LG / 2; m >= 1; m >>= 1) p += __shfl_xor(p, m, LG);
-                    tv *= p;
+                    tv *= group_sum<T, LG>(p);
                 }
                 if (MODE == 1) {
                     if (li == 0 && c + u < nchild) static_cast<T *>(a.T)[t.n0 + c + u] = tv;

@@ -73,3 +73,13 @@ def test_sampled_product_tile_order(oracle, width, dtype):
     for which in ("fused", "fissioned"):
         _check(oracle, cfg, data, which)
         _check(oracle, cfg, data, which, deterministic=True)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("width", [16, 32, 64, 128])
+def test_sampled_product_one_row(oracle, width, dtype):
+    """A tile inside one row: fewer entries than lane groups, partly filled batches, a full tile, one entry in the next tile."""
+    for n in (1, 7, 65, 513, 1023, 1024, 1025):
+        cfg, data = _problem("sddmm_spmm", (5, 3001), [(3, n)], (width, width), dtype)
+        for which in ("fused", "fissioned"):
+            _check(oracle, cfg, data, which)
