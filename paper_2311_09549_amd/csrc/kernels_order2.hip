@@ -77,8 +77,8 @@ __device__ __forceinline__ T group_sum(T p)
 // A tile that lies inside one row of S: X(i,:) stays in registers (one 16-byte gather through the L1 less of three per
 // entry), there are no row tables and no row ends, and eight entries are in flight per lane group.  Every lane group sums its
 // chunk, the first one adds the groups' sums in their order.  With the sums over lane groups on the
-// vector ALU: 856 -> 806 us (fused, rank 64, 16 M entries over 1 M x 1 M with power-law rows).  What is left is bound by the
-// gathers of Y and Z, 8.2 GB through the L1s.
+// vector ALU: 856 -> 806 us (fused, rank 64, 16 M entries over 1 M x 1 M with power-law rows).  What is left is bound by what
+// misses the L2s: 5.5 GB a launch at 7.1 TB/s, mostly the Y and Z rows of short rows of S.
 template <typename T, int W, int MODE>
 __device__ __forceinline__ void one_row_tile(const Order2Args &a, const TileRec &t, T *slot_s, SdRec<T> *rec_s)
 {
