@@ -22,6 +22,8 @@
 // separately and only the final output rows need recombining.
 #include "leaf_walk.h"
 
+#include <type_traits>
+
 namespace sck {
 
 // ------------------------------------------------------------------------------------------
@@ -200,7 +202,10 @@ __global__ void __launch_bounds__(NT) order3_kernel(Order3Args a)
     }
     // Rows of at most NT / 2 elements: NT / (L W) sets of threads deal the tile's slices out among themselves (a slice has one
     // set, its sum one order).  The reads of C are independent of each other; eight are kept in flight, since their
-    // latency is what the loop consists of.  Both took the 8 x 8 chain on 8,000 nonzeros in fp64 from 37 to 13 us.
+    // latency is what the loop consists of.  Both took the 8 x 8 chain on 8,000 nonzeros in fp64 from 37 to 13 us.  What is left of
+    // a slice goes in batches of four, two and one: a clamped batch of eight made slices of one to three fibers pay for
+    // eight reads each (fp64, 120,000 nonzeros in 38,000 slices at 64 x 64: 786 us one read at a time, 1020 us in clamped
+    // batches, 680 us so; 40,000 nonzeros in 25,000 slices: 452, 682, 451 us).
     const int sets = max(1, NT / (L * W)), set = sets > 1 ? tid / (L * W) : 0;
     if (set >= sets) return;
     for (int e = sets > 1 ? tid % (L * W) : tid; e < L * W; e += NT) {
@@ -212,15 +217,27 @@ __global__ void __launch_bounds__(NT) order3_kernel(Order3Args a)
             // update, except that a deterministic schedule still expects the tile's (zero) piece
             if (f0 >= f1 && !(a.partials && (first_shared || last_shared))) continue;
             T acc = T(0);
-            constexpr int UC = 8;
-            for (int fb = f0; fb < f1; fb += UC) {
+            auto batch = [&](auto count, int fb) {
+                constexpr int UC = decltype(count)::value;
                 T cv[UC];
 #pragma unroll
-                for (int u = 0; u < UC; ++u) cv[u] = C[(int64_t)crda_s[min(fb + u, f1 - 1)] * a.ldC + l];
+                for (int u = 0; u < UC; ++u) cv[u] = C[(int64_t)crda_s[fb + u] * a.ldC + l];
 #pragma unroll
-                for (int u = 0; u < UC; ++u)
-                    if (fb + u < f1) acc += cv[u] * row_s[(fb + u) * RS + m];
+                for (int u = 0; u < UC; ++u) acc += cv[u] * row_s[(fb + u) * RS + m];
+            };
+            int fb = f0;
+            if (f1 - f0 > 1) {
+                for (; fb + 8 <= f1; fb += 8) batch(std::integral_constant<int, 8>{}, fb);
+                if (fb + 4 <= f1) {
+                    batch(std::integral_constant<int, 4>{}, fb);
+                    fb += 4;
+                }
+                if (fb + 2 <= f1) {
+                    batch(std::integral_constant<int, 2>{}, fb);
+                    fb += 2;
+                }
             }
+            if (fb < f1) batch(std::integral_constant<int, 1>{}, fb);
             T *dst = A + (int64_t)crdb_s[ls] * L * W + e;
             if (!first_shared && !last_shared) {
                 *dst = acc;

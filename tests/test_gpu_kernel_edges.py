@@ -83,3 +83,19 @@ def test_sampled_product_one_row(oracle, width, dtype):
         cfg, data = _problem("sddmm_spmm", (5, 3001), [(3, n)], (width, width), dtype)
         for which in ("fused", "fissioned"):
             _check(oracle, cfg, data, which)
+
+
+# slices of 1 .. 9 and 15 .. 18 fibers (distinct j, so that a slice has as many fibers as entries), dealt out to up to four sets of threads
+FIBERS = [(i, n) for i, n in enumerate([1, 2, 3, 4, 5, 6, 7, 8, 9, 15, 16, 17, 18, 1, 1, 1, 2, 3, 700, 9, 8])]
+
+
+@pytest.mark.parametrize("dtype,ranks", [("f64", (8, 8)), ("f64", (16, 8)), ("f64", (8, 64)), ("f64", (32, 16)), ("f32", (8, 8)), ("f32", (8, 32))])
+def test_order3_consumer_batches(oracle, dtype, ranks):
+    """Whole and partial batches of fibers per slice in the general order-3 consumer, one set of threads and several."""
+    cfg, data = _problem("ttmc3", (23, 1009, 1), FIBERS, ranks, dtype)
+    data["coords"][2] = np.random.default_rng(1).integers(0, 53, cfg["nnz"]).astype(np.int32)
+    cfg["dims"] = (23, 1009, 53)
+    data["factors"][1] = np.random.default_rng(2).standard_normal((53, ranks[1])).astype(data["vals"].dtype)
+    for which in ("fused", "fissioned"):
+        _check(oracle, cfg, data, which)
+        _check(oracle, cfg, data, which, deterministic=True)
