@@ -14,6 +14,8 @@
 //   SDDMM -> SpMM   A(i,l)     += S(i,j) * X(i,k) * Y(j,k) * Z(j,l)      (loops k and l both inside)
 #include "device_common.h"
 
+#include <type_traits>
+
 namespace sck {
 
 namespace {
@@ -128,7 +130,10 @@ __global__ void __launch_bounds__(NT) linear_kernel(LinArgs a, const TileRec *__
 // multiply-adds per lane (75 us).  The pieces of a slice cut by chunk boundaries are parked in LDS and added by the
 // lane group in which the slice ends; one update per tile and slice, atomic only where another tile holds part of the
 // slice: one atomic update per chunk and slice made a skewed tensor's heavy slices queue on their rows (587 us).
-template <typename T, int KIND>
+// NARROW, rows of at most 8 blocks: up to 256 lane groups, so the pieces of a heavy slice make a long chain.  They are added
+// up inside the wavefronts first: 200 slices of 1,500 nonzeros at 4 x 4 took 61 us, 34 us with one element per
+// thread, 16 us so; the MTTKRP at rank 4 41, 29 and 14 us.  Wider rows gain less than the steps cost (12 x 20: 37.2 -> 38.0 us).
+template <typename T, int KIND, bool NARROW>
 __global__ void __launch_bounds__(NT) linear_tiled_kernel(LinArgs a, const TileRec *__restrict__ tiles)
 {
     constexpr int U = 4;                                 // nonzeros per step
@@ -141,7 +146,7 @@ __global__ void __launch_bounds__(NT) linear_tiled_kernel(LinArgs a, const TileR
     __shared__ Rec rec_s[LIN_TN + LIN_TN / 16];
     __shared__ T v_s[LIN_TN + LIN_TN / 16];
     __shared__ T park_s[4 * BX][NT];    // the open sum of every chunk ...
-    __shared__ int32_t began_s[NT];     // ... whether its slice began in that chunk
+    __shared__ int32_t began_s[NT];     // ... bit 0: the slice began in a chunk that this sum holds, bit 1: summed over the wavefront
     const TileRec t = tiles[blockIdx.x];
     const int tid = threadIdx.x;
     const int nchild = t.n1 - t.n0;
@@ -291,13 +296,40 @@ __global__ void __launch_bounds__(NT) linear_tiled_kernel(LinArgs a, const TileR
         }
         // ---- slices cut by chunk boundaries ----
         if (pass) __syncthreads();   // the previous pass's pieces have been read
+        int began = !first;
+        if constexpr (NARROW) {
+            // four chunks in a row that lie inside one slice: the wavefront's open sums are added up by doubling steps, each
+            // from the chunk where its slice began or, if that is in an earlier wavefront, from the wavefront's first chunk
+            const unsigned long long inside = __ballot(some && first && open);
+            const int gs = 1 << gs_log;
+            if (inside & (inside >> gs) & (inside >> 2 * gs) & (inside >> 3 * gs)) {
+#pragma unroll
+                for (int x = 0; x < BX; ++x)
+#pragma unroll
+                    for (int y = 0; y < 4; ++y) acc[x][y] = mine && open ? acc[x][y] : T(0);
+                const int lane = tid % 64;
+                for (int d = gs; d < 64; d <<= 1) {
+                    const int before = __shfl_up(began, d);
+                    const bool add = lane >= d && !began;
+#pragma unroll
+                    for (int x = 0; x < BX; ++x)
+#pragma unroll
+                        for (int y = 0; y < 4; ++y) {
+                            const T o = __shfl_up(acc[x][y], d);
+                            acc[x][y] += add ? o : T(0);
+                        }
+                    began |= lane >= d && before;
+                }
+                began |= 2;
+            }
+        }
         if (mine && open) {
 #pragma unroll
             for (int x = 0; x < BX; ++x)
 #pragma unroll
                 for (int y = 0; y < 4; ++y) park_s[4 * x + y][tid] = acc[x][y];
         }
-        if (li == 0) began_s[g] = !first;
+        if (li == 0) began_s[g] = began;
         __syncthreads();
         if (head_i >= 0) {
             for (int h = g - 1; h >= 0; --h) {
@@ -305,7 +337,9 @@ __global__ void __launch_bounds__(NT) linear_tiled_kernel(LinArgs a, const TileR
                 for (int x = 0; x < BX; ++x)
 #pragma unroll
                     for (int y = 0; y < 4; ++y) head[x][y] += park_s[4 * x + y][(h << gs_log) + li];
-                if (began_s[h]) break;   // the slice began in chunk h
+                const int b = began_s[h];
+                if (b & 1) break;                                           // the slice began in chunk h ...
+                if (NARROW && b) h = ((h << gs_log) & ~63) >> gs_log;       // ... or the sum reaches back to the wavefront's first chunk
             }
             emit(head_i, head);
         }
@@ -316,10 +350,16 @@ template <typename T>
 void launch_linear_nest(const sc_plan *p, const LinArgs &a, int ntiles, hipStream_t stream)
 {
     const bool by4 = a.cols[1] % 4 == 0 && (p->kind == K_TTMC4 ? a.cols[2] : a.cols[0]) % 4 == 0;
+    const int nblk = a.row_elems / (p->kind == K_MTTKRP3 ? 4 : 16);
+    auto tiled = [&](auto kind) {
+        constexpr int KIND = decltype(kind)::value;
+        if (nblk <= 8) linear_tiled_kernel<T, KIND, true><<<ntiles, NT, 0, stream>>>(a, p->d_tiles);
+        else linear_tiled_kernel<T, KIND, false><<<ntiles, NT, 0, stream>>>(a, p->d_tiles);
+    };
     // blocks of 4 x 4 wherever the ranks allow: 405 -> 75 us at 12 x 20
-    if (by4 && p->kind == K_TTMC3) linear_tiled_kernel<T, K_TTMC3><<<ntiles, NT, 0, stream>>>(a, p->d_tiles);
-    else if (by4 && p->kind == K_MTTKRP3) linear_tiled_kernel<T, K_MTTKRP3><<<ntiles, NT, 0, stream>>>(a, p->d_tiles);
-    else if (by4 && p->kind == K_TTMC4) linear_tiled_kernel<T, K_TTMC4><<<ntiles, NT, 0, stream>>>(a, p->d_tiles);
+    if (by4 && p->kind == K_TTMC3) tiled(std::integral_constant<int, K_TTMC3>{});
+    else if (by4 && p->kind == K_MTTKRP3) tiled(std::integral_constant<int, K_MTTKRP3>{});
+    else if (by4 && p->kind == K_TTMC4) tiled(std::integral_constant<int, K_TTMC4>{});
     else linear_kernel<T><<<ntiles, NT, 0, stream>>>(a, p->d_tiles);
 }
 

@@ -99,3 +99,17 @@ def test_order3_consumer_batches(oracle, dtype, ranks):
     for which in ("fused", "fissioned"):
         _check(oracle, cfg, data, which)
         _check(oracle, cfg, data, which, deterministic=True)
+
+
+# tiles of 1024: slices that take a few chunks of a tile, a whole wavefront's, several wavefronts' and a whole tile
+HEAVY = [(0, 5), (1, 1000), (2, 19), (3, 256), (4, 70), (5, 300), (6, 398), (7, 3), (8, 3000), (9, 69), (10, 1024)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("kind,ranks", [("ttmc3", (4, 4)), ("ttmc3", (8, 4)), ("ttmc3", (16, 16)), ("ttmc3", (16, 32)), ("mttkrp3", (4,)), ("mttkrp3", (8,)),
+                                        ("mttkrp3", (20,)), ("ttmc4", (1, 4, 4)), ("ttmc4", (4, 4, 8))])
+def test_unfactored_nest_heavy_slices(oracle, kind, ranks, dtype):
+    """Sums of slices over many chunks, from one lane per chunk (64 chunks in a wavefront) to a wavefront per chunk."""
+    dims = (11, 41, 97) if kind != "ttmc4" else (11, 13, 17, 19)
+    cfg, data = _problem(kind, dims, HEAVY, ranks, dtype)
+    _check(oracle, cfg, data, "linear")
