@@ -20,7 +20,7 @@ namespace sck {
 
 namespace {
 
-constexpr int LIN_TN = 1024;   // nonzeros per tile at most (LDS: five words per nonzero)
+constexpr int LIN_TN = 1024;   // nonzeros per tile at most (sizes the LDS arrays)
 
 struct LinArgs {
     const int32_t *pos[4];
@@ -122,6 +122,18 @@ __global__ void __launch_bounds__(NT) linear_kernel(LinArgs a, const TileRec *__
     }
 }
 
+// LDS of a workgroup of linear_tiled_kernel.
+template <typename T, int BX>   // BX: rows of a block
+struct LinTiledLds {
+    struct alignas(16) Rec { uint32_t o[3]; int32_t i; };   // byte offsets of the factor rows, output row
+    Rec rec[LIN_TN + LIN_TN / 16];
+    T v[LIN_TN + LIN_TN / 16];
+    T park[4 * BX][NT];    // the open sum of every chunk ...
+    int32_t began[NT];     // ... bit 0: the slice began in a chunk that this sum holds, bit 1: summed over the wavefront
+};
+
+constexpr int lin_block_rows(int kind) { return kind == K_MTTKRP3 ? 1 : 4; }
+
 // Ranks that are multiples of 4: a lane owns a 4 x 4 block of the output row (4 elements of the MTTKRP's), a lane group
 // of GS lanes (the smallest power of two that covers the blocks of a row, at most a wavefront: longer rows are
 // walked once per 64 blocks) walks a contiguous chunk of the tile's nonzeros.  What bounds the nest is instructions and
@@ -137,16 +149,18 @@ template <typename T, int KIND, bool NARROW>
 __global__ void __launch_bounds__(NT) linear_tiled_kernel(LinArgs a, const TileRec *__restrict__ tiles)
 {
     constexpr int U = 4;                                 // nonzeros per step
-    constexpr int BX = KIND == K_MTTKRP3 ? 1 : 4;        // block rows
+    constexpr int BX = lin_block_rows(KIND);
     constexpr int D = KIND == K_TTMC4 ? 4 : 3;
     struct alignas(16) V4 { T v[4]; };   // the rows of the factors are 16-byte aligned
-    struct alignas(16) Rec { uint32_t o[3]; int32_t i; };   // byte offsets of the factor rows, output row
+    using Rec = typename LinTiledLds<T, BX>::Rec;
     // records of chunks that start a multiple of 16 apart spread over the banks
     auto at = [](int c) { return c + (c >> 4); };
-    __shared__ Rec rec_s[LIN_TN + LIN_TN / 16];
-    __shared__ T v_s[LIN_TN + LIN_TN / 16];
-    __shared__ T park_s[4 * BX][NT];    // the open sum of every chunk ...
-    __shared__ int32_t began_s[NT];     // ... bit 0: the slice began in a chunk that this sum holds, bit 1: summed over the wavefront
+    static_assert(sizeof(LinTiledLds<T, BX>) <= 64 * 1024, "LDS of a workgroup");
+    __shared__ LinTiledLds<T, BX> lds;
+    auto &rec_s = lds.rec;
+    auto &v_s = lds.v;
+    auto &park_s = lds.park;
+    auto &began_s = lds.began;
     const TileRec t = tiles[blockIdx.x];
     const int tid = threadIdx.x;
     const int nchild = t.n1 - t.n0;
@@ -346,20 +360,30 @@ __global__ void __launch_bounds__(NT) linear_tiled_kernel(LinArgs a, const TileR
     }
 }
 
+// Chains whose last two ranks, and MTTKRPs whose rank, are multiples of 4 run linear_tiled_kernel: 405 -> 75 us at 12 x 20.
+bool linear_is_tiled(const sc_plan *p)
+{
+    switch (p->kind) {
+    case K_TTMC3:
+    case K_MTTKRP3: return p->fcols[0] % 4 == 0 && p->fcols[1] % 4 == 0;
+    case K_TTMC4: return p->fcols[1] % 4 == 0 && p->fcols[2] % 4 == 0;
+    default: return false;
+    }
+}
+
 template <typename T>
 void launch_linear_nest(const sc_plan *p, const LinArgs &a, int ntiles, hipStream_t stream)
 {
-    const bool by4 = a.cols[1] % 4 == 0 && (p->kind == K_TTMC4 ? a.cols[2] : a.cols[0]) % 4 == 0;
-    const int nblk = a.row_elems / (p->kind == K_MTTKRP3 ? 4 : 16);
+    const int nblk = a.row_elems / (4 * lin_block_rows(p->kind));
     auto tiled = [&](auto kind) {
         constexpr int KIND = decltype(kind)::value;
         if (nblk <= 8) linear_tiled_kernel<T, KIND, true><<<ntiles, NT, 0, stream>>>(a, p->d_tiles);
         else linear_tiled_kernel<T, KIND, false><<<ntiles, NT, 0, stream>>>(a, p->d_tiles);
     };
-    // blocks of 4 x 4 wherever the ranks allow: 405 -> 75 us at 12 x 20
-    if (by4 && p->kind == K_TTMC3) tiled(std::integral_constant<int, K_TTMC3>{});
-    else if (by4 && p->kind == K_MTTKRP3) tiled(std::integral_constant<int, K_MTTKRP3>{});
-    else if (by4 && p->kind == K_TTMC4) tiled(std::integral_constant<int, K_TTMC4>{});
+    const bool blocks = linear_is_tiled(p);
+    if (blocks && p->kind == K_TTMC3) tiled(std::integral_constant<int, K_TTMC3>{});
+    else if (blocks && p->kind == K_MTTKRP3) tiled(std::integral_constant<int, K_MTTKRP3>{});
+    else if (blocks && p->kind == K_TTMC4) tiled(std::integral_constant<int, K_TTMC4>{});
     else linear_kernel<T><<<ntiles, NT, 0, stream>>>(a, p->d_tiles);
 }
 
@@ -368,7 +392,10 @@ void launch_linear_nest(const sc_plan *p, const LinArgs &a, int ntiles, hipStrea
 size_t linear_lds_bytes(const sc_plan *p)
 {
     if (p->caps.tn > LIN_TN) return SIZE_MAX;
-    return (size_t)LIN_TN * (16 + (p->dtype == SC_F64 ? 8 : 4));
+    const bool f64 = p->dtype == SC_F64;
+    if (!linear_is_tiled(p)) return (size_t)LIN_TN * (16 + (f64 ? 8 : 4));   // four coordinates and the value
+    if (lin_block_rows(p->kind) == 1) return f64 ? sizeof(LinTiledLds<double, 1>) : sizeof(LinTiledLds<float, 1>);
+    return f64 ? sizeof(LinTiledLds<double, 4>) : sizeof(LinTiledLds<float, 4>);
 }
 
 sc_status launch_linear(const sc_plan *p, const sc_csf_view *sp, const sc_dense_view *fac, void *out, hipStream_t stream)

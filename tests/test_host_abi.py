@@ -432,6 +432,27 @@ def test_linear_plan_counts_the_unfactored_nest(cid, scale):
     assert sc.plan_model(fused)[0] < want or cfg["dims"][0] < 300
 
 
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("kind,ranks,blocks", [("ttmc3", (24, 20), 16), ("ttmc3", (24, 22), 0), ("mttkrp3", (12,), 4), ("mttkrp3", (6,), 0),
+                                               ("ttmc4", (3, 4, 8), 16), ("ttmc4", (4, 4, 6), 0), ("sddmm_spmm", (24, 24), 0)])
+def test_unfactored_nest_reports_the_lds_of_its_kernel(kind, ranks, blocks, dtype):
+    """The footprint the cost evaluator prints and judges by is that of the kernel that runs.  Blocks of the output row
+    (4 x 4, or 4 elements): 1024 nonzeros, padded by a sixteenth, with a 16-byte record and the value, a parked block per
+    thread and a word per thread.  Otherwise four coordinates and the value of 1024 nonzeros."""
+    dims = {"ttmc3": (9, 8, 7), "mttkrp3": (9, 8, 7), "ttmc4": (6, 5, 4, 3), "sddmm_spmm": (9, 8)}[kind]
+    cfg = dict(kind=kind, dims=dims, nnz=30, ranks=ranks, dtype=dtype, expr=synth.KINDS[kind][0])
+    dt = np.float64 if dtype == "f64" else np.float32
+    flat = np.arange(30) * (int(np.prod(dims)) // 30)
+    csf = sc.coo_to_csf([c.astype(np.int32) for c in np.unravel_index(flat, dims)], np.ones(30, dt), dims)
+    factors = [np.ones(s, dt) for s in synth.factor_shapes(cfg)]
+    text = sc.plan_describe(sc.plan_create(cfg["expr"], csf, factors, sc.schedule("auto")))
+    line = [ln for ln in text.splitlines() if "candidate LINEAR" in ln][0]
+    e = 8 if dtype == "f64" else 4
+    want = 1088 * (16 + e) + 256 * blocks * e + 256 * 4 if blocks else 1024 * (16 + e)
+    per_cu = min(8, 160 * 1024 // (-(-want // 1280) * 1280))
+    assert f" {want} bytes of LDS per workgroup ({per_cu} per compute unit)" in line, line
+
+
 def test_all_mode_ttmc_plans():
     """Kernel 5 of Table 2: classification, the three schedules picked by naming their temporaries, the
     iteration counts of their nests (the same closed forms the counted twins reproduce), refusals."""
