@@ -113,3 +113,19 @@ def test_unfactored_nest_heavy_slices(oracle, kind, ranks, dtype):
     dims = (11, 41, 97) if kind != "ttmc4" else (11, 13, 17, 19)
     cfg, data = _problem(kind, dims, HEAVY, ranks, dtype)
     _check(oracle, cfg, data, "linear")
+
+
+@pytest.mark.parametrize("dtype,ranks,kernel", [
+    ("f32", (64, 80), "mfma"), ("f32", (32, 112), "mfma"), ("f32", (16, 96), "mfma"), ("f32", (128, 64), "mfma"),   # partial last block of 64 columns
+    ("f32", (8, 12), "tiled"), ("f32", (128, 128), "tiled"), ("f64", (64, 128), "tiled"), ("f64", (8, 4), "tiled"),  # up to 64 KB of E in LDS
+    ("f32", (64, 6), "valu"), ("f64", (16, 10), "valu"), ("f64", (128, 128), "valu")])                               # M no multiple of 4, E beyond it
+def test_trailing_product_kernels(oracle, dtype, ranks, kernel):
+    """Each kernel of the trailing product at one row, odd numbers of rows and remainders of its row blocks."""
+    for rows in (1, 17, 64, 333):
+        lengths = [(i, 1 + i % 5) for i in range(0, rows, 2)]
+        cfg, data = _problem("mttkrp_gemm", (rows, 41, 97), lengths, ranks, dtype)
+        con = _check(oracle, cfg, data, "fused")
+        sc.plan_set_profiling(con.plan, True)
+        con.run()
+        torch.cuda.synchronize()
+        assert sc.plan_kernel_times(con.plan)[-1][0] == f"trailing_gemm_{kernel}"
