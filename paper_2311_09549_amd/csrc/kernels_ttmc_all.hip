@@ -19,9 +19,11 @@
 // L x (M N) tile in registers and stores it in its own slot of the workspace; sum_partials adds the
 // slots in chunk order.  The reduction over i is a dense (L x I) * (I x MN) product with I large:
 // 2 L flops per 4-byte element of S read.  In fp32 with L in {16, 32, 64, 128} and M N a multiple of 64 it runs
-// on the matrix cores with all of L per workgroup, so that S is read once whatever L is; the other cases
+// on the matrix cores with all of L per wavefront, so that S is read once whatever L is; the other cases
 // (fp64, other ranks) run on the vector ALUs, a thread per column with 16 values of l in registers.
 #include "device_common.h"
+
+#include <type_traits>
 
 namespace sck {
 
@@ -82,50 +84,53 @@ __global__ void __launch_bounds__(NT) mode0_reduce_kernel(K5Args a)
 }
 
 // The same partial sums on the matrix cores, fp32, L = 16 LT in {16, 32, 64, 128}, M N a multiple of 64: a wavefront takes all of L
-// for 64 columns, so S is read once; four slices per v_mfma_f32_16x16x4_f32 with C^T as operand A (l along the rows) and S
+// for 16 X columns (X = 4 or 1); four slices per v_mfma_f32_16x16x4_f32 with C^T as operand A (l along the rows) and S
 // as operand B, both straight from global memory.  Which l and which column a tile's rows and columns stand for is free, so
-// a lane reads 16 adjacent bytes of a row of S (one column in each of the wavefront's four column tiles) and up to 16 of a row
-// of C (one l in each of four l tiles): three loads per 4 LT MFMAs at L = 128.  With 4-byte loads, nine per LT MFMAs, the L1
-// address path bound the kernel (2606 us = 66 TFLOP/s on 40,000 slices at 128 x 128 x 128, where the fp32 matrix rate of a large
-// library product is 149; 1532 us = 110 now).  The reads of the next UK steps are in flight while this batch is multiplied; the wavefronts
-// of a workgroup read the same rows of C.
+// a lane reads 4 X adjacent bytes of a row of S (one column in each of the wavefront's X column tiles) and up to 16 of a row
+// of C (one l in each of four l tiles): three loads per 4 LT MFMAs at L = 128 and X = 4.  With 4-byte loads, nine per LT MFMAs, 40,000 slices
+// at 128 x 128 x 128 took 2606 us = 66 TFLOP/s, where the fp32 matrix rate of a large library product is 149; 1532 us = 110
+// now.  The reads of the next UK steps are in flight while this batch is multiplied; the wavefronts of a workgroup read
+// the same rows of C.
+// X = 4 reads S and C with the fewest instructions; where it leaves most SIMDs without a wavefront, X = 1 has four
+// times the wavefronts and a quarter of the chain of MFMAs in each.  Whole calls, 100,000 nonzeros in 4,000 slices (63 chunks): 128 x 16 x 16
+// 33.2 us with X = 4, 26.7 with X = 1; 64 x 16 x 16 26.3 and 23.7.
 typedef float k5_floatx4 __attribute__((ext_vector_type(4)));
-template <int LT>
+template <int LT, int X>
 __global__ void __launch_bounds__(NT, 2) mode0_reduce_mfma_kernel(K5Args a)
 {
-    constexpr int UK = LT >= 8 ? 2 : 4;    // steps of four slices per batch of reads
+    constexpr int UK = LT * X >= 32 ? 2 : 4;   // steps of four slices per batch of reads
     constexpr int CW = LT < 4 ? LT : 4;    // adjacent values of l a lane reads at once ...
     constexpr int CN = LT / CW;            // ... in CN pieces, 16 CW values of l apart
     const int tid = threadIdx.x;
     const int wave = tid / 64, lane = tid % 64, kk = lane / 16, col = lane % 16;
-    const int c = ((int)blockIdx.y * ((int)blockDim.x / 64) + wave) * 64 + 4 * col;   // < M N: the launch has M N / 64 wavefronts along y
+    const int c = ((int)blockIdx.y * ((int)blockDim.x / 64) + wave) * 16 * X + X * col;   // < M N: the launch has M N / (16 X) wavefronts along y
     const int64_t r0 = (int64_t)blockIdx.x * a.chunk, r1 = min(r0 + a.chunk, a.rows);
     const float *C = static_cast<const float *>(a.C) + CW * col;
     const float *S = static_cast<const float *>(a.S) + c;
     struct Batch {
-        k5_floatx4 s[UK];
+        Pack<float, X> s[UK];
         Pack<float, CW> v[UK][CN];
     };
     auto load = [&](Batch &b, int64_t rb) {
 #pragma unroll
         for (int u = 0; u < UK; ++u) {
             const int64_t row = rb + 4 * u + kk;
-            b.s[u] = *reinterpret_cast<const k5_floatx4 *>(S + row * a.MN);
+            b.s[u] = *reinterpret_cast<const Pack<float, X> *>(S + row * a.MN);
 #pragma unroll
             for (int h = 0; h < CN; ++h) b.v[u][h] = *reinterpret_cast<const Pack<float, CW> *>(C + row * a.ldC + 16 * CW * h);
         }
     };
-    k5_floatx4 acc[LT][4];
+    k5_floatx4 acc[LT][X];
 #pragma unroll
     for (int lt = 0; lt < LT; ++lt)
 #pragma unroll
-        for (int x = 0; x < 4; ++x) acc[lt][x] = k5_floatx4{0.f, 0.f, 0.f, 0.f};
-    auto step = [&](const k5_floatx4 &s, const Pack<float, CW> (&v)[CN]) {
+        for (int x = 0; x < X; ++x) acc[lt][x] = k5_floatx4{0.f, 0.f, 0.f, 0.f};
+    auto step = [&](const Pack<float, X> &s, const Pack<float, CW> (&v)[CN]) {
 #pragma unroll
         for (int lt = 0; lt < LT; ++lt)
 #pragma unroll
-            for (int x = 0; x < 4; ++x)
-                acc[lt][x] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[lt / CW].v[lt % CW], s[x], acc[lt][x], 0, 0, 0);
+            for (int x = 0; x < X; ++x)
+                acc[lt][x] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[lt / CW].v[lt % CW], s.v[x], acc[lt][x], 0, 0, 0);
     };
     const int64_t nfull = (r1 - r0) / (4 * UK);   // batches without a row past the chunk
     if (nfull > 0) {
@@ -142,10 +147,10 @@ __global__ void __launch_bounds__(NT, 2) mode0_reduce_mfma_kernel(K5Args a)
     for (int64_t rb = r0 + nfull * (4 * UK); rb < r1; rb += 4) {
         const int64_t row = min(rb + kk, r1 - 1);   // lanes past the chunk read its last slice and are zeroed
         const bool ok = rb + kk < r1;
-        k5_floatx4 s = *reinterpret_cast<const k5_floatx4 *>(S + row * a.MN);
+        Pack<float, X> s = *reinterpret_cast<const Pack<float, X> *>(S + row * a.MN);
         Pack<float, CW> v[CN];
 #pragma unroll
-        for (int x = 0; x < 4; ++x) s[x] = ok ? s[x] : 0.f;
+        for (int x = 0; x < X; ++x) s.v[x] = ok ? s.v[x] : 0.f;
 #pragma unroll
         for (int h = 0; h < CN; ++h) {
             v[h] = *reinterpret_cast<const Pack<float, CW> *>(C + row * a.ldC + 16 * CW * h);
@@ -161,7 +166,10 @@ __global__ void __launch_bounds__(NT, 2) mode0_reduce_mfma_kernel(K5Args a)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int l = 16 * CW * (lt / CW) + CW * (4 * kk + r) + lt % CW;
-            *reinterpret_cast<k5_floatx4 *>(P + (int64_t)l * a.MN) = k5_floatx4{acc[lt][0][r], acc[lt][1][r], acc[lt][2][r], acc[lt][3][r]};
+            Pack<float, X> o;
+#pragma unroll
+            for (int x = 0; x < X; ++x) o.v[x] = acc[lt][x][r];
+            *reinterpret_cast<Pack<float, X> *>(P + (int64_t)l * a.MN) = o;
         }
 }
 
@@ -356,13 +364,23 @@ sc_status run_ttmc_all(const sc_plan *p, const sc_csf_view *sp, const sc_dense_v
         if (p->k5_mfma_reduce) {
             if constexpr (sizeof(T) == 4) {
                 if (MN % 64 != 0) return SC_ERR_SCHED_UNSUPPORTED;
-                const int waves = MN % 256 == 0 ? 4 : MN % 128 == 0 ? 2 : 1;   // wavefronts (of 64 columns) per workgroup
-                const dim3 mgrid((unsigned)p->k5_nchunks, (unsigned)(MN / (64 * waves)), 1);
+                // 64 columns per wavefront, 16 up to two wavefronts of 64 per compute unit.  Whole calls at 512 wavefronts of 64: 128 x 32 x
+                // 32 42.2 us with 64 columns, 38.2 with 16; at 628: 44.6 and 42.5 at 128 x 16 x 16, but 32.2 and 33.6 at 32 x 16 x 16; at
+                // 1008 64 columns are equal or ahead at every L (64 x 32 x 32: 36.9 and 38.3).
+                const bool narrow = p->k5_nchunks * (MN / 64) <= (int64_t)2 * p->n_cu;
+                const int cols = narrow ? 16 : 64, strips = (int)(MN / cols);
+                const int waves = strips % 4 == 0 ? 4 : strips % 2 == 0 ? 2 : 1;   // wavefronts per workgroup
+                const dim3 mgrid((unsigned)p->k5_nchunks, (unsigned)(strips / waves), 1);
+                auto reduce = [&](auto lt) {
+                    constexpr int LT = decltype(lt)::value;
+                    if (narrow) mode0_reduce_mfma_kernel<LT, 1><<<mgrid, 64 * waves, 0, stream>>>(a);
+                    else mode0_reduce_mfma_kernel<LT, 4><<<mgrid, 64 * waves, 0, stream>>>(a);
+                };
                 ln.begin("ttmc_all_mode0_reduce_mfma");
-                if (L == 16) mode0_reduce_mfma_kernel<1><<<mgrid, 64 * waves, 0, stream>>>(a);
-                else if (L == 32) mode0_reduce_mfma_kernel<2><<<mgrid, 64 * waves, 0, stream>>>(a);
-                else if (L == 64) mode0_reduce_mfma_kernel<4><<<mgrid, 64 * waves, 0, stream>>>(a);
-                else if (L == 128) mode0_reduce_mfma_kernel<8><<<mgrid, 64 * waves, 0, stream>>>(a);
+                if (L == 16) reduce(std::integral_constant<int, 1>{});
+                else if (L == 32) reduce(std::integral_constant<int, 2>{});
+                else if (L == 64) reduce(std::integral_constant<int, 4>{});
+                else if (L == 128) reduce(std::integral_constant<int, 8>{});
                 else return SC_ERR_SCHED_UNSUPPORTED;
                 ln.end();
             } else {

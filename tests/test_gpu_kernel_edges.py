@@ -129,3 +129,15 @@ def test_trailing_product_kernels(oracle, dtype, ranks, kernel):
         con.run()
         torch.cuda.synchronize()
         assert sc.plan_kernel_times(con.plan)[-1][0] == f"trailing_gemm_{kernel}"
+
+
+@pytest.mark.parametrize("dtype,L,MN,rows", [
+    ("f32", 16, (8, 8), (1, 63, 64, 65)), ("f32", 32, (8, 16), (3, 130)), ("f32", 64, (16, 16), (61, 200)), ("f32", 128, (16, 16), (15, 67, 193)),  # 16 columns per wavefront
+    ("f32", 16, (64, 64), (577, 700)), ("f32", 32, (128, 128), (193,)), ("f32", 64, (64, 64), (583,)), ("f32", 128, (128, 128), (201,)),           # 64
+    ("f32", 16, (16, 16), (8300,)), ("f64", 16, (8, 8), (4099,)), ("f64", 8, (16, 8), (5001,))])                                                   # many chunks, small output
+def test_core_tensor_reduction(oracle, dtype, L, MN, rows):
+    """The reduction over the first mode: chunks that end inside a batch of slices, one wavefront's worth of columns and many, and
+    the sum of the chunks with 16 and with 64 elements per workgroup."""
+    for n in rows:
+        cfg, data = _problem("ttmc_all", (n, 41, 97), [(i, 1 + i % 3) for i in range(0, n, 1 + n // 300)], (L,) + MN, dtype)
+        _check(oracle, cfg, data, "fused")
