@@ -588,7 +588,9 @@ void list_rows_to_zero(sc_plan *p, const HostCsf &h)
 {
     p->zero_rows.clear();
     p->zero_selective = false;
-    if (p->sched == SC_SCHED_LINEAR) return;   // every row is accumulated atomically: the whole output starts at zero
+    // The unfactored nest: the whole output starts at zero.  linear_kernel adds every row atomically; linear_tiled_kernel stores the rows
+    // of slices inside one tile whole, which are thus written twice.
+    if (p->sched == SC_SCHED_LINEAR) return;
     const int64_t rows = p->dims[0];
     std::vector<char> stored((size_t)rows, 0);
     for (int64_t s = 0; s < p->nfib[0]; ++s) stored[(size_t)h.crd[0][s]] = 1;
