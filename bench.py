@@ -8,11 +8,13 @@ default run measures all five benchmark workloads one after the other: the top-l
 `value`, `roofline` and `cpu_baseline` are those of the largest one (the order-4 TTM chain,
 50 M nonzeros), and `per_config` carries the same figures for each of the five.
 
-Prints ONE JSON line.  Per workload: effective GFLOP/s of the schedule (its own flop count,
-multiply and add counted separately, over the measured step time), a `roofline` object for
-the dominant kernel (algorithmic HBM bytes over its HIP-event-timed duration against
-8 TB/s), the FISSIONED schedule with its traversal kernel's achieved bandwidth, the LINEAR
-(unfactored) nest, the two speedups, and the fp64 oracle timed on the host cores.
+Prints ONE JSON line of a few kilobytes.  Per workload: effective GFLOP/s of the schedule (its
+own flop count, multiply and add counted separately, over the measured step time), a
+`roofline` object for the dominant kernel (algorithmic HBM bytes over its HIP-event-timed
+duration against 8 TB/s), the FISSIONED schedule with its traversal kernel's achieved
+bandwidth, the LINEAR (unfactored) nest, the two speedups, and the fp64 oracle timed on the
+host cores.  `--details FILE` writes the whole record: every kernel's time, the statistics over
+the steps, workspace sizes, the evaluator's candidates.
 """
 from __future__ import annotations
 
@@ -30,17 +32,61 @@ HBM_PEAK_GBS = 8000.0
 HEADLINE = 5   # the largest single-GPU workload
 
 WORKLOAD_TEXT = {
-    1: "configs[0]: TTM chain order 3, fp64, 200^3, 8,000 uniform nonzeros, L=M=8",
-    2: "configs[1]: MTTKRP order 3, fp32, 50,000x20,000x10,000, 20M Zipf(1.2) nonzeros, rank 32",
-    3: "configs[2]: TTM chain order 3, fp32, 100,000x50,000x20,000, 30M Zipf(1.1) nonzeros, L=M=16",
-    4: "configs[3]: SDDMM->SpMM, fp32, 1Mx1M, 16M nonzeros (rows Zipf 1.3), K=L=64",
-    5: "configs[4]: TTM chain order 4, fp32, 10,000^4, 50M Zipf(1.1) nonzeros, L=M=N=8",
+    1: "TTM chain order 3, fp64, 200^3, 8,000 uniform nonzeros, L=M=8",
+    2: "MTTKRP order 3, fp32, 50,000x20,000x10,000, 20M Zipf(1.2) nonzeros, rank 32",
+    3: "TTM chain order 3, fp32, 100,000x50,000x20,000, 30M Zipf(1.1) nonzeros, L=M=16",
+    4: "SDDMM->SpMM, fp32, 1Mx1M, 16M nonzeros (rows Zipf 1.3), K=L=64",
+    5: "TTM chain order 4, fp32, 10,000^4, 50M Zipf(1.1) nonzeros, L=M=N=8",
 }
 
 PAPER_CONTEXT = ("context only, other hardware and other baseline: the paper reports its fused schedules running "
                  "orders of magnitude faster than the default TACO schedules on 4x Intel Xeon E5-4650 "
                  "(32 cores, 2.7 GHz, 80 MB LLC, GCC 11.4 -O3 -ffast-math, median of 31 runs); it prints "
                  "no GFLOP/s or GB/s figure for these five workloads")
+
+
+def _pick(rec, *keys):
+    return {k: rec[k] for k in keys if k in rec}
+
+
+def _short(x):
+    """Numbers to six significant digits."""
+    if isinstance(x, dict):
+        return {k: _short(v) for k, v in x.items()}
+    if isinstance(x, list):
+        return [_short(v) for v in x]
+    return float(f"{x:.6g}") if isinstance(x, float) else x
+
+
+def result_line(result):
+    """The line that is printed: the whole record of the headline workload, the figures of the others.  Whoever reads it
+    may keep only the last kilobytes of the output, so it stays within them."""
+    line = {k: v for k, v in result.items() if k not in ("per_config", "next_workloads")}
+    line["per_config"] = []
+    for r in result.get("per_config", []):
+        c = _pick(r, "config_id", "workload", "dtype", "ms_per_step", "gflops", "mfma_busy", "fused_vs_fissioned_speedup",
+                  "fused_vs_linear_speedup")
+        c["roofline"] = _pick(r["roofline"], "kernel", "achieved", "frac", "traffic", "kernel_ms")
+        if "fissioned" in r:
+            c["fissioned"] = _pick(r["fissioned"], "ms_per_step")
+            c["fissioned"].update(_pick(r["fissioned"].get("traversal", {}), "gbs", "frac"))
+        if "linear" in r:
+            c["linear_ms"] = r["linear"]["ms_per_step"]
+        if "cpu_baseline" in r:
+            c["cpu_gflops"] = r["cpu_baseline"]["value"]
+        line["per_config"].append(c)
+    if "next_workloads" in result:
+        line["next_workloads"] = {}
+        for name, r in result["next_workloads"].items():
+            if name.endswith("rank_sweep"):   # [L, M, N, ms]
+                line["next_workloads"][name] = [[p["L"], p["M"], p["N"], p["ms"]] for p in r]
+                continue
+            w = _pick(r, "workload")
+            w["schedules"] = {k: _pick(v, "ms_per_step", "gflops") for k, v in r["schedules"].items()}
+            if "cpu_baseline" in r:
+                w["cpu_gflops"] = r["cpu_baseline"]["value"]
+            line["next_workloads"][name] = w
+    return json.dumps(_short(line), separators=(",", ":"))
 
 
 def main() -> int:
@@ -57,10 +103,10 @@ def main() -> int:
                     help="skip the LINEAR (unfactored) nest, the baseline the paper's speedups are quoted against")
     ap.add_argument("--calibrate-copy", action="store_true",
                     help="also queue and time the library's plain copy kernel (1 GiB), for counter runs")
+    ap.add_argument("--details", default="", help="write the whole record to this file as JSON")
     args = ap.parse_args()
     if args.gpus != 1:
-        print("bench.py: this build runs on ONE GPU; --gpus must be 1 (sharding by top-level slice is "
-              "described in DESIGN.md but not built)", file=sys.stderr)
+        print("bench.py: the library runs on ONE GPU; --gpus must be 1 (sharding by top-level slice is not built)", file=sys.stderr)
         return 2
 
     import numpy as np
@@ -356,10 +402,10 @@ def main() -> int:
             nw["ttmc_all_rank_sweep"] = bench_rank_sweep()
         if args.config in (0, 7):
             R, M = synth.CONFIGS[7]["ranks"]
-            nw["mttkrp_gemm"] = bench_next(7, "MTTKRP then GEMM A(i,m) (Table 2, kernel 8), fp32, the tensor of configs[1], R=32, M=64",
+            nw["mttkrp_gemm"] = bench_next(7, "MTTKRP then GEMM A(i,m) (Table 2, kernel 8), fp32, the tensor of the MTTKRP workload, R=32, M=64",
                                            CLASS_VARIANTS, st, linear_flops=4.0 * R * M * synth.CONFIGS[7]["nnz"])
         if args.config in (0, 8):
-            nw["sddmm_spmm_gemm"] = bench_next(8, "SDDMM->SpMM then GEMM A(i,m) (Table 2, kernel 2), fp32, the matrix of configs[3], K=L=M=64",
+            nw["sddmm_spmm_gemm"] = bench_next(8, "SDDMM->SpMM then GEMM A(i,m) (Table 2, kernel 2), fp32, the matrix of the SDDMM->SpMM workload, K=L=M=64",
                                                CLASS_VARIANTS[:2], st, with_oracle=False)
         if args.config in (0, 9):
             nw["ttmc_all_uniform_case1"] = bench_next(9, "all-mode TTMC, motivating case 1 of Section 3: uniform 1800x800x1000, sparsity 0.008, L,M,N=64,16,32 "
@@ -370,7 +416,10 @@ def main() -> int:
                                                           "(the paper's Figure 2 schedules on 32 Xeon cores: 10.20 s / 8.60 s / 33.51 s)", K5_VARIANTS, 5,
                                                        with_oracle=False)
         result["next_workloads"] = nw
-    print(json.dumps(result))
+    if args.details:
+        with open(args.details, "w") as fh:
+            json.dump(result, fh, indent=1)
+    print(result_line(result))
     return 0
 
 
