@@ -98,6 +98,7 @@ typedef float k5_floatx4 __attribute__((ext_vector_type(4)));
 template <int LT, int X>
 __global__ void __launch_bounds__(NT, 2) mode0_reduce_mfma_kernel(K5Args a)
 {
+    typedef float SVec __attribute__((ext_vector_type(X)));
     constexpr int UK = LT * X >= 32 ? 2 : 4;   // steps of four slices per batch of reads
     constexpr int CW = LT < 4 ? LT : 4;    // adjacent values of l a lane reads at once ...
     constexpr int CN = LT / CW;            // ... in CN pieces, 16 CW values of l apart
@@ -108,14 +109,14 @@ __global__ void __launch_bounds__(NT, 2) mode0_reduce_mfma_kernel(K5Args a)
     const float *C = static_cast<const float *>(a.C) + CW * col;
     const float *S = static_cast<const float *>(a.S) + c;
     struct Batch {
-        Pack<float, X> s[UK];
+        SVec s[UK];
         Pack<float, CW> v[UK][CN];
     };
     auto load = [&](Batch &b, int64_t rb) {
 #pragma unroll
         for (int u = 0; u < UK; ++u) {
             const int64_t row = rb + 4 * u + kk;
-            b.s[u] = *reinterpret_cast<const Pack<float, X> *>(S + row * a.MN);
+            b.s[u] = *reinterpret_cast<const SVec *>(S + row * a.MN);
 #pragma unroll
             for (int h = 0; h < CN; ++h) b.v[u][h] = *reinterpret_cast<const Pack<float, CW> *>(C + row * a.ldC + 16 * CW * h);
         }
@@ -125,12 +126,12 @@ __global__ void __launch_bounds__(NT, 2) mode0_reduce_mfma_kernel(K5Args a)
     for (int lt = 0; lt < LT; ++lt)
 #pragma unroll
         for (int x = 0; x < X; ++x) acc[lt][x] = k5_floatx4{0.f, 0.f, 0.f, 0.f};
-    auto step = [&](const Pack<float, X> &s, const Pack<float, CW> (&v)[CN]) {
+    auto step = [&](const SVec &s, const Pack<float, CW> (&v)[CN]) {
 #pragma unroll
         for (int lt = 0; lt < LT; ++lt)
 #pragma unroll
             for (int x = 0; x < X; ++x)
-                acc[lt][x] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[lt / CW].v[lt % CW], s.v[x], acc[lt][x], 0, 0, 0);
+                acc[lt][x] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[lt / CW].v[lt % CW], s[x], acc[lt][x], 0, 0, 0);
     };
     const int64_t nfull = (r1 - r0) / (4 * UK);   // batches without a row past the chunk
     if (nfull > 0) {
@@ -147,10 +148,10 @@ __global__ void __launch_bounds__(NT, 2) mode0_reduce_mfma_kernel(K5Args a)
     for (int64_t rb = r0 + nfull * (4 * UK); rb < r1; rb += 4) {
         const int64_t row = min(rb + kk, r1 - 1);   // lanes past the chunk read its last slice and are zeroed
         const bool ok = rb + kk < r1;
-        Pack<float, X> s = *reinterpret_cast<const Pack<float, X> *>(S + row * a.MN);
+        SVec s = *reinterpret_cast<const SVec *>(S + row * a.MN);
         Pack<float, CW> v[CN];
 #pragma unroll
-        for (int x = 0; x < X; ++x) s.v[x] = ok ? s.v[x] : 0.f;
+        for (int x = 0; x < X; ++x) s[x] = ok ? s[x] : 0.f;
 #pragma unroll
         for (int h = 0; h < CN; ++h) {
             v[h] = *reinterpret_cast<const Pack<float, CW> *>(C + row * a.ldC + 16 * CW * h);
@@ -166,10 +167,10 @@ __global__ void __launch_bounds__(NT, 2) mode0_reduce_mfma_kernel(K5Args a)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int l = 16 * CW * (lt / CW) + CW * (4 * kk + r) + lt % CW;
-            Pack<float, X> o;
+            SVec o;
 #pragma unroll
-            for (int x = 0; x < X; ++x) o.v[x] = acc[lt][x][r];
-            *reinterpret_cast<Pack<float, X> *>(P + (int64_t)l * a.MN) = o;
+            for (int x = 0; x < X; ++x) o[x] = acc[lt][x][r];
+            *reinterpret_cast<SVec *>(P + (int64_t)l * a.MN) = o;
         }
 }
 
