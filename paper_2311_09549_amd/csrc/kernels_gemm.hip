@@ -7,7 +7,8 @@
 // matrix cores: v_mfma_f32_16x16x4_f32, a wavefront per block of 16 rows of P, all of E's columns in
 // turn.  It moves I * (R + M) elements for 2 I R M flops, so at these ranks it is bound by memory
 // traffic; what the kernel has to get right is 16-byte accesses on both sides.  fp64, and ranks
-// that are not multiples of the MFMA tile, take the vector-ALU kernel.
+// that are not multiples of the MFMA tile, run on the vector ALUs: 2 x 4 outputs per thread with E in
+// LDS, or one output per thread where M is no multiple of 4 or E is beyond 64 KB.
 #include "device_common.h"
 
 namespace sck {
