@@ -122,15 +122,17 @@ __global__ void __launch_bounds__(NT) linear_kernel(LinArgs a, const TileRec *__
     }
 }
 
-// LDS of a workgroup of linear_tiled_kernel.
-template <typename T, int BX>   // BX: rows of a block
-struct LinTiledLds {
-    struct alignas(16) Rec { uint32_t o[3]; int32_t i; };   // byte offsets of the factor rows, output row
-    Rec rec[LIN_TN + LIN_TN / 16];
-    T v[LIN_TN + LIN_TN / 16];
-    T park[4 * BX][NT];    // the open sum of every chunk ...
-    int32_t began[NT];     // ... bit 0: the slice began in a chunk that this sum holds, bit 1: summed over the wavefront
-};
+struct alignas(16) LinRec { uint32_t o[3]; int32_t i; };   // byte offsets of the factor rows, output row
+
+constexpr int LIN_PADDED = LIN_TN + LIN_TN / 16;
+// LDS bytes of a workgroup of linear_tiled_kernel with blocks of BX rows: records, values, a parked block and a word per thread.
+// (As one struct in LDS the arrays cost the fp32 MTTKRP six registers and with them a sixth wavefront per SIMD: 306 -> 327 us on
+// 20 M nonzeros at rank 32.)
+template <typename T, int BX>
+constexpr size_t lin_tiled_lds_bytes()
+{
+    return (size_t)LIN_PADDED * (sizeof(LinRec) + sizeof(T)) + (size_t)NT * (4 * BX * sizeof(T) + 4);
+}
 
 constexpr int lin_block_rows(int kind) { return kind == K_MTTKRP3 ? 1 : 4; }
 
@@ -152,15 +154,15 @@ __global__ void __launch_bounds__(NT) linear_tiled_kernel(LinArgs a, const TileR
     constexpr int BX = lin_block_rows(KIND);
     constexpr int D = KIND == K_TTMC4 ? 4 : 3;
     struct alignas(16) V4 { T v[4]; };   // the rows of the factors are 16-byte aligned
-    using Rec = typename LinTiledLds<T, BX>::Rec;
+    using Rec = LinRec;
     // records of chunks that start a multiple of 16 apart spread over the banks
     auto at = [](int c) { return c + (c >> 4); };
-    static_assert(sizeof(LinTiledLds<T, BX>) <= 64 * 1024, "LDS of a workgroup");
-    __shared__ LinTiledLds<T, BX> lds;
-    auto &rec_s = lds.rec;
-    auto &v_s = lds.v;
-    auto &park_s = lds.park;
-    auto &began_s = lds.began;
+    __shared__ Rec rec_s[LIN_PADDED];
+    __shared__ T v_s[LIN_PADDED];
+    __shared__ T park_s[4 * BX][NT];    // the open sum of every chunk ...
+    __shared__ int32_t began_s[NT];     // ... bit 0: the slice began in a chunk that this sum holds, bit 1: summed over the wavefront
+    static_assert(sizeof(rec_s) + sizeof(v_s) + sizeof(park_s) + sizeof(began_s) == lin_tiled_lds_bytes<T, BX>(), "reported LDS");
+    static_assert(lin_tiled_lds_bytes<T, BX>() <= 64 * 1024, "LDS of a workgroup");
     const TileRec t = tiles[blockIdx.x];
     const int tid = threadIdx.x;
     const int nchild = t.n1 - t.n0;
@@ -394,8 +396,8 @@ size_t linear_lds_bytes(const sc_plan *p)
     if (p->caps.tn > LIN_TN) return SIZE_MAX;
     const bool f64 = p->dtype == SC_F64;
     if (!linear_is_tiled(p)) return (size_t)LIN_TN * (16 + (f64 ? 8 : 4));   // four coordinates and the value
-    if (lin_block_rows(p->kind) == 1) return f64 ? sizeof(LinTiledLds<double, 1>) : sizeof(LinTiledLds<float, 1>);
-    return f64 ? sizeof(LinTiledLds<double, 4>) : sizeof(LinTiledLds<float, 4>);
+    if (lin_block_rows(p->kind) == 1) return f64 ? lin_tiled_lds_bytes<double, 1>() : lin_tiled_lds_bytes<float, 1>();
+    return f64 ? lin_tiled_lds_bytes<double, 4>() : lin_tiled_lds_bytes<float, 4>();
 }
 
 sc_status launch_linear(const sc_plan *p, const sc_csf_view *sp, const sc_dense_view *fac, void *out, hipStream_t stream)
