@@ -314,11 +314,14 @@ __global__ void __launch_bounds__(NT) linear_tiled_kernel(LinArgs a, const TileR
         if (pass) __syncthreads();   // the previous pass's pieces have been read
         int began = !first;
         if constexpr (NARROW) {
-            // four chunks in a row that lie inside one slice: the wavefront's open sums are added up by doubling steps, each
-            // from the chunk where its slice began or, if that is in an earlier wavefront, from the wavefront's first chunk
+            // four chunks in a row (eight of one or two lanes) that lie inside one slice: the wavefront's open sums are added up by doubling
+            // steps, each from the chunk where its slice began or, if that is in an earlier wavefront, from the wavefront's first chunk
             const unsigned long long inside = __ballot(some && first && open);
             const int gs = 1 << gs_log;
-            if (inside & (inside >> gs) & (inside >> 2 * gs) & (inside >> 3 * gs)) {
+            unsigned long long row = inside & (inside >> gs);
+            row &= row >> 2 * gs;
+            if (gs <= 2) row &= row >> 4 * gs;
+            if (row) {
 #pragma unroll
                 for (int x = 0; x < BX; ++x)
 #pragma unroll
