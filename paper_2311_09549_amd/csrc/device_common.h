@@ -211,13 +211,12 @@ WalkShape leaf_traverse_walk_shape(sc_dtype dtype, int W);
 sc_status launch_leaf_producer(const sc_plan *p, Launcher &ln, const void *vals, const sc_dense_view &F, void *Tout, int W, const char *name,
                                void *partials);
 
-// Order-3 TTM chain on matrix cores (fp32, L = M = 16; its own kernel file): the FUSED schedule (T == nullptr)
+// Order-3 TTM chain on matrix cores (fp32, L = M = 16, deterministic; its own kernel file): the FUSED schedule (T == nullptr)
 // or the consumer kernel of the FISSIONED one.
 size_t ttmc3_mfma_lds_bytes(const sc_plan *p);
 WalkShape ttmc3_mfma_walk_shape();
 bool ttmc3_mfma_caps_ok(const sc_plan *p);
-int ttmc3_mfma_run(const sc_plan *p, bool one_tile_per_workgroup);
-// `partials`: deterministic schedules only (else null): slots for the pieces of rows that span tiles.
+// `partials`: slots for the pieces of rows that span tiles (deterministic schedules are what it runs).
 sc_status launch_ttmc3_mfma(const sc_plan *p, Launcher &ln, const sc_csf_view *sp, const sc_dense_view *fac, const void *T, void *out,
                             void *partials);
 
@@ -225,16 +224,13 @@ sc_status launch_ttmc3_mfma(const sc_plan *p, Launcher &ln, const sc_csf_view *s
 // (dst = the output for the top level, the temporary for level a).
 sc_status launch_fixup(const sc_plan *p, Launcher &ln, const FixLevel &lv, void *workspace, void *dst);
 
+// kernels_slice.hip: A(i,:,:) = sum over the children of slice i of C(j,:)^T (x) T(f,:), the rows of T formed from the leaves (T ==
+// nullptr, D = the last mode's factor) or read from the workspace.
+sc_status launch_slice(const sc_plan *p, Launcher &ln, const sc_csf_view *sp, const sc_dense_view &C, const sc_dense_view *D, const void *T,
+                       int64_t W, void *out, const char *name);
+
 // Order-4 TTM chain on matrix cores (fp32, M = N = 8, L <= 16; its own kernel file): mode 0 the FUSED schedule,
 // modes 1 and 2 the second and third kernel of the FISSIONED one.
-// kernels_ttmc3w.hip: order-3 chain on matrix cores for rank pairs that are multiples of 16 (other than 16 x 16), fused and
-// the consumer kernel of the FISSIONED schedule
-bool ttmc3_wide_ranks(int64_t L, int64_t W);
-WalkShape ttmc3_wide_walk_shape(int W);
-size_t ttmc3_wide_lds_bytes(const sc_plan *p);
-int ttmc3_wide_run(const sc_plan *p);
-sc_status launch_ttmc3_wide(const sc_plan *p, Launcher &ln, const sc_csf_view *sp, const sc_dense_view *fac, const void *T, void *out);
-
 size_t ttmc4_mfma_lds_bytes(const sc_plan *p);
 WalkShape ttmc4_mfma_walk_shape();
 bool ttmc4_mfma_caps_ok(const sc_plan *p);

@@ -11,6 +11,8 @@
 #include <stdexcept>
 #include <set>
 #include <string>
+#include <thread>
+#include <type_traits>
 #include <vector>
 
 #include "plan.h"
@@ -567,6 +569,273 @@ sc_status build_walk_tables(sc_plan *p, const sc_csf_view *v, const HostCsf &h, 
     return SC_OK;
 }
 
+// Host side of the tables of a slice product (SliceTables): arrays per range of slices, each made by a thread of its own.
+struct SlicePart {
+    std::vector<SliceChunk> chunks;   // step0 and group0 from the part's first
+    std::vector<uint32_t> leaf, at;
+    std::vector<int32_t> gj, first;
+    int32_t nsteps = 0, ngroups = 0;
+    bool failed = false;              // out of memory
+};
+struct SliceBuild {
+    std::vector<SlicePart> parts;
+    std::vector<SliceRun> runs;
+    std::vector<SliceChunk> chunks;
+    std::vector<int32_t> cut_rows;   // output rows of the slices that a run's end cuts
+};
+
+// Pieces of fibers of one slice on their way into a chunk, by length.
+struct SlicePieces {
+    struct Piece { int32_t z, len, j; } list[256];
+    int32_t n = 0, leaves = 0, longest = 0;
+    int32_t count[kSlicePiece + 1] = {0};
+    // steps of the groups of four they make, longest first
+    int32_t steps() const
+    {
+        int32_t s = 0, at = 0;
+        for (int len = longest; len > 0; --len) {
+            s += len * ((at + count[len] + 3) / 4 - (at + 3) / 4);
+            at += count[len];
+        }
+        return s;
+    }
+    bool fits(int32_t len, int32_t room)
+    {
+        if (n == 256) return false;
+        if (std::max(len, longest) + (leaves + len + 3) / 4 <= room) return true;   // at most the longest and a quarter of all leaves
+        const int32_t was = longest;
+        longest = std::max(longest, len);
+        ++count[len];
+        const bool ok = steps() <= room;
+        --count[len];
+        longest = was;
+        return ok;
+    }
+    void add(int32_t z, int32_t len, int32_t j)
+    {
+        list[n++] = Piece{z, len, j};
+        leaves += len;
+        longest = std::max(longest, len);
+        ++count[len];
+    }
+};
+
+// Lists the steps of the slices [s0, s1), in chunks of at most `cap`.
+void list_steps(SliceSource src, int piece, int cap, const HostCsf &h, int64_t s0, int64_t s1, SlicePart &b)
+{
+    const int32_t *pos1 = h.pos[1];
+    const int64_t children = pos1[s1] - pos1[s0];
+    SliceChunk c = {};
+    int32_t &nsteps = b.nsteps, &ngroups = b.ngroups;
+    auto flush = [&](int32_t next_leaf, int32_t next_slice) {
+        if (c.nsteps) b.chunks.push_back(c);
+        c = SliceChunk{};
+        c.step0 = nsteps;
+        c.leaf0 = next_leaf;
+        c.group0 = ngroups;
+        c.slice0 = next_slice;
+    };
+    c.slice0 = (int32_t)s0;
+    if (src == SLICE_ROWS) {
+        b.first.reserve((size_t)(children / 4 + s1 - s0));
+        for (int64_t s = s0; s < s1; ++s) {
+            for (int32_t f = pos1[s]; f < pos1[s + 1]; f += 4) {
+                if (c.nsteps == cap) flush(0, (int32_t)s);
+                b.first.push_back(f);
+                ++nsteps;
+                ++c.nsteps;
+            }
+            c.send |= 1ull << (c.nsteps - 1);
+            if (c.nsteps == cap) flush(0, (int32_t)s + 1);
+        }
+    } else {
+        const int32_t *pos2 = h.pos[2], *crd1 = h.crd[1], *crd2 = h.crd[2];
+        c.leaf0 = pos2[pos1[s0]];
+        const size_t leaves = (size_t)(pos2[pos1[s1]] - c.leaf0);
+        b.leaf.reserve(leaves * 9 / 8 + 1024);
+        b.at.reserve(leaves * 9 / 32 + 256);
+        b.gj.reserve((size_t)children * 5 / 4 + 1024);
+        SlicePieces::Piece sorted[256];
+        for (int64_t s = s0; s < s1; ++s) {
+            int32_t f = pos1[s];
+            const int32_t fend = pos1[s + 1];
+            int32_t z = pos2[f];
+            // a slice longer than what is left of a chunk starts the next one, unless much is left
+            if (cap - c.nsteps < 8 && (pos2[fend] - z) / 4 >= cap - c.nsteps) flush(z, (int32_t)s);
+            while (f < fend) {
+                SlicePieces w;
+                const int32_t room = cap - c.nsteps;
+                while (f < fend) {
+                    const int32_t len = std::min<int32_t>(pos2[f + 1] - z, piece);
+                    if (!w.fits(len, room)) break;
+                    w.add(z, len, crd1[f]);
+                    z += len;
+                    if (z == pos2[f + 1]) ++f;
+                }
+                int32_t at[kSlicePiece + 2] = {0};   // first place of the pieces of each length, longest first
+                for (int len = kSlicePiece - 1; len > 0; --len) at[len] = at[len + 1] + w.count[len + 1];
+                for (int k = 0; k < w.n; ++k) sorted[at[w.list[k].len]++] = w.list[k];
+                for (int k = 0; k < w.n; k += 4) {
+                    const int have = std::min(4, w.n - k), steps = sorted[k].len;
+                    const size_t o = b.leaf.size();
+                    b.leaf.resize(o + 4 * (size_t)steps);
+                    b.at.resize(b.at.size() + (size_t)steps, 0xffffffffu);
+                    uint8_t *place = reinterpret_cast<uint8_t *>(b.at.data()) + o;
+                    for (int q = 0; q < 4; ++q) {
+                        const SlicePieces::Piece &pc = sorted[k + std::min(q, have - 1)];
+                        const int32_t len = q < have ? pc.len : 0, zl = pc.z + pc.len - 1;
+                        for (int u = 0; u < len; ++u) {
+                            b.leaf[o + 4 * (size_t)u + q] = (uint32_t)crd2[pc.z + u];
+                            place[4 * u + q] = (uint8_t)(pc.z + u - c.leaf0);
+                        }
+                        for (int u = len; u < steps; ++u) b.leaf[o + 4 * (size_t)u + q] = (uint32_t)crd2[zl];   // past the piece: its last row again, no value
+                        b.gj.push_back(pc.j);
+                    }
+                    nsteps += steps;
+                    c.nsteps += steps;
+                    c.gend |= 1ull << (c.nsteps - 1);
+                    ++ngroups;
+                    ++c.ngroups;
+                }
+                c.nleaves += w.leaves;
+                if (f < fend) flush(z, (int32_t)s);
+            }
+            c.send |= 1ull << (c.nsteps - 1);
+            if (c.nsteps == cap) flush(z, (int32_t)s + 1);
+        }
+    }
+    flush(0, 0);
+}
+
+// Lists the steps of a plan's slice products and cuts them into runs of equal work.
+void build_slices(const sc_plan *p, SliceSource src, int piece, const HostCsf &h, SliceBuild &b)
+{
+    const int64_t S = p->nfib[0], children = p->nfib[1];
+    // Steps per chunk: 64, fewer where that would leave wavefront slots without a chunk.
+    int cap = 64;
+    while (cap > 16 && (src == SLICE_ROWS ? children : p->nnz) < (int64_t)4 * cap * 8 * p->n_cu) cap /= 2;
+    // A thread per 256,000 leaves (children), at most eight; ranges of slices with about equal numbers of them.
+    const int32_t *pos1 = h.pos[1], *pos2 = src == SLICE_ROWS ? nullptr : h.pos[2];
+    auto before = [&](int64_t s) { return (int64_t)(pos2 ? pos2[pos1[s]] : pos1[s]); };
+    const int64_t units = before(S);
+    const int64_t most_threads = std::max<int64_t>(1, std::min<int64_t>(8, std::thread::hardware_concurrency()));
+    const int64_t nparts = std::max<int64_t>(1, std::min(units / 256000, most_threads));
+    std::vector<int64_t> from(1, 0);
+    for (int64_t n = 1; n < nparts; ++n) {
+        int64_t lo = from.back(), hi = S;   // first slice that begins at or after the n-th share
+        while (lo < hi) {
+            const int64_t mid = (lo + hi) / 2;
+            if (before(mid) < units * n / nparts) lo = mid + 1; else hi = mid;
+        }
+        if (lo > from.back() && lo < S) from.push_back(lo);
+    }
+    from.push_back(S);
+    b.parts.resize(from.size() - 1);
+    auto work = [&](size_t n) {
+        try {
+            list_steps(src, piece, cap, h, from[n], from[n + 1], b.parts[n]);
+        } catch (...) { b.parts[n].failed = true; }
+    };
+    std::vector<std::thread> threads;
+    threads.reserve(b.parts.size());
+    size_t own = 1;   // parts from here on had no thread to be had
+    try {
+        for (; own < b.parts.size(); ++own) threads.emplace_back(work, own);
+    } catch (...) {
+    }
+    work(0);
+    for (; own < b.parts.size(); ++own) work(own);
+    for (std::thread &t : threads) t.join();
+    int32_t nsteps = 0, ngroups = 0;
+    for (SlicePart &part : b.parts) {
+        if (part.failed) throw std::bad_alloc();
+        for (SliceChunk k : part.chunks) {
+            k.step0 += nsteps;
+            k.group0 += ngroups;
+            b.chunks.push_back(k);
+        }
+        nsteps += part.nsteps;
+        ngroups += part.ngroups;
+    }
+    if (src == SLICE_ROWS) b.parts.back().first.push_back((int32_t)children);
+
+    // Work of a step, a group, a slice and a chunk in vector-ALU issue slots of a wavefront: the gather and its arithmetic; the row of
+    // C and the matrix products (8 slots each); the stores of the row; the staging.
+    const int64_t L = p->fcols[0], W = p->kind == K_TTMC4 ? p->fcols[1] * p->fcols[2] : p->fcols[1];
+    const SliceShape sh = slice_shape(L, W, p->sched == SC_SCHED_LINEAR);
+    const int64_t tiles = (int64_t)sh.lt * sh.mt;
+    const double w_step = 6 + sh.mt, w_group = 6 + 8 * tiles, w_slice = 8 + 4 * tiles, w_chunk = 60;
+    auto cost = [&](const SliceChunk &k) {
+        const int g = src == SLICE_ROWS ? k.nsteps : k.ngroups;
+        return w_step * k.nsteps + w_group * g + w_slice * __builtin_popcountll(k.send) + w_chunk;
+    };
+    double total = 0;
+    for (const SliceChunk &k : b.chunks) total += cost(k);
+    // Runs: enough of them for the wavefront slots of the chip, of 96 steps where there are that many; short ones make the runs of a
+    // heavy slice queue on its row.
+    const int per_run = sh.wl * sh.wm;
+    int64_t nruns = std::min<int64_t>(nsteps / 96, p->n_cu * (src == SLICE_ROWS ? 64 : 32) / per_run);
+    nruns = std::max<int64_t>(nruns, std::min<int64_t>((nsteps + 15) / 16, p->n_cu * 8 / per_run));
+    if (p->tune.per_cu > 0) nruns = std::min<int64_t>((int64_t)p->n_cu * 4 * p->tune.per_cu, (nsteps + 15) / 16);
+    if (p->tune.tn > 0) nruns = std::max<int64_t>(nruns, nsteps / std::max<int64_t>(8, p->tune.tn / 4));
+    // rows of T are addressed with 32-bit offsets from the run's first child
+    const int64_t most = src == SLICE_ROWS ? ((int64_t)1 << 31) / (4 * 4 * W) - 64 : (int64_t)nsteps;
+    double done = 0;
+    int32_t run_step0 = 0;
+    bool open = false;   // the step before was not the last of its slice
+    for (size_t n = 0; n < b.chunks.size(); ++n) {
+        const SliceChunk &k = b.chunks[n];
+        const double per_step = cost(k) / k.nsteps;
+        int32_t slice = k.slice0;
+        for (int32_t s = 0; s < k.nsteps; s += 8) {
+            const int32_t here = std::min(8, k.nsteps - s);
+            if (b.runs.empty() || done >= total * (double)b.runs.size() / (double)nruns || k.step0 + s - run_step0 + here > most) {
+                b.runs.push_back(SliceRun{(int32_t)n, s, open ? 1 : 0, 0});
+                run_step0 = k.step0 + s;
+                const int32_t row = h.crd[0][slice];
+                if (open && (b.cut_rows.empty() || b.cut_rows.back() != row)) b.cut_rows.push_back(row);
+            }
+            const uint32_t ends = (uint32_t)(k.send >> s) & ((1u << here) - 1);
+            slice += __builtin_popcount(ends);
+            open = !(ends >> (here - 1) & 1);
+            done += per_step * here;
+        }
+    }
+    b.runs.push_back(SliceRun{(int32_t)b.chunks.size(), 0, 0, 0});
+    b.chunks.push_back(SliceChunk{});   // the chunk after the last is read, not worked on
+}
+
+sc_status upload_slices(sc_plan *p, const SliceBuild &b)
+{
+    SliceTables &t = p->slice;
+    t.nruns = (int32_t)b.runs.size() - 1;
+    size_t total = 0;
+    auto upload = [&](auto **dev, const auto &v) {
+        const size_t bytes = sizeof(v[0]) * v.size();
+        total += bytes;
+        return hipMalloc((void **)dev, bytes) == hipSuccess && hipMemcpy(*dev, v.data(), bytes, hipMemcpyHostToDevice) == hipSuccess;
+    };
+    auto upload_parts = [&](auto **dev, auto member) {
+        using E = std::remove_reference_t<decltype(**dev)>;
+        size_t n = 0, done = 0;
+        for (const SlicePart &part : b.parts) n += (part.*member).size();
+        if (n == 0) return true;
+        if (hipMalloc((void **)dev, sizeof(E) * n) != hipSuccess) return false;
+        total += sizeof(E) * n;
+        for (const SlicePart &part : b.parts) {
+            const std::vector<E> &v = part.*member;
+            if (!v.empty() && hipMemcpy(*dev + done, v.data(), sizeof(E) * v.size(), hipMemcpyHostToDevice) != hipSuccess) return false;
+            done += v.size();
+        }
+        return true;
+    };
+    if (!upload(&t.d_runs, b.runs) || !upload(&t.d_chunks, b.chunks) || !upload_parts(&t.d_leaf, &SlicePart::leaf) ||
+        !upload_parts(&t.d_at, &SlicePart::at) || !upload_parts(&t.d_gj, &SlicePart::gj) || !upload_parts(&t.d_first, &SlicePart::first))
+        return SC_ERR_DEVICE;
+    appendf(p->text, "slice products: %d runs of %zu chunks, %zu bytes of plan-owned device tables\n", t.nruns, b.chunks.size() - 1, total);
+    return SC_OK;
+}
+
 // Top level of a tile record ("a" for order 2, "b" for order 3, "c" for order 4): whether its
 // first / last slice continues from the previous / into the next tile, first slice, slice count.
 struct TopLevel {
@@ -584,20 +853,22 @@ TopLevel top_level(int order, const TileRec &t)
 // to be zero before they run: rows of empty slices and, unless the schedule is deterministic
 // (then a last kernel writes them), rows whose slice spans several tiles and is accumulated
 // atomically.  Every other row is stored whole by the one tile that holds its slice.
-void list_rows_to_zero(sc_plan *p, const HostCsf &h)
+void list_rows_to_zero(sc_plan *p, const HostCsf &h, const std::vector<int32_t> *cut_rows)
 {
     p->zero_rows.clear();
     p->zero_selective = false;
     // The unfactored nest: the whole output starts at zero.  linear_kernel adds every row atomically; linear_tiled_kernel stores the rows
     // of slices inside one tile whole, which are thus written twice.
-    if (p->sched == SC_SCHED_LINEAR) return;
+    if (p->sched == SC_SCHED_LINEAR && !cut_rows) return;
     const int64_t rows = p->dims[0];
     std::vector<char> stored((size_t)rows, 0);
     for (int64_t s = 0; s < p->nfib[0]; ++s) stored[(size_t)h.crd[0][s]] = 1;
     p->zero_rows.clear();
     for (int64_t r = 0; r < rows; ++r)
         if (!stored[(size_t)r]) p->zero_rows.push_back((int32_t)r);
-    if (!p->deterministic) {
+    if (cut_rows) {   // slice products: the slices that a run's end cuts
+        p->zero_rows.insert(p->zero_rows.end(), cut_rows->begin(), cut_rows->end());
+    } else if (!p->deterministic) {
         // Kernels that take one tile per workgroup add every piece of a spanning slice atomically.  The persistent
         // kernels keep such a slice in registers from tile to tile of a run and add only what crosses a run's end.
         const int run = plan_output_run(p);
@@ -1484,13 +1755,20 @@ static sc_status plan_create_impl(sc_plan **out, const char *expr, const sc_csf_
     if (tu.ta) p->caps.ta = tu.ta;
     if (tu.tb) p->caps.tb = tu.tb;
     if (lds_bytes_needed(p) > 64 * 1024) return SC_ERR_SCHED_UNSUPPORTED;
+    SliceBuild slices;
+    bool sliced = false;
     try {
         build_tiles(sparse, h, p->caps, p->tiles);
         if (p->deterministic) {
             if (!plan_supports_deterministic(p)) return SC_ERR_SCHED_UNSUPPORTED;
             assign_piece_slots(p, h);
         }
-        list_rows_to_zero(p, h);
+        int piece = 1;
+        const SliceSource src = plan_slice_source(p, &piece);
+        int ndev = 0;
+        sliced = src != SLICE_NONE && p->nnz > 0 && hipGetDeviceCount(&ndev) == hipSuccess && ndev > 0;
+        if (sliced) build_slices(p, src, piece, h, slices);
+        list_rows_to_zero(p, h, sliced ? &slices.cut_rows : nullptr);
     } catch (const std::bad_alloc &) { return SC_ERR_ALLOC; }
 
     // ---- workspace, model, text ----
@@ -1620,6 +1898,10 @@ static sc_status plan_create_impl(sc_plan **out, const char *expr, const sc_csf_
             p->walk.shape = plan_walk_shape(p);
             const sc_status ws = build_walk_tables(p, sparse, h, order);
             if (ws != SC_OK) return ws;
+            if (sliced) {
+                const sc_status us = upload_slices(p, slices);
+                if (us != SC_OK) return us;
+            }
         }
         if (p->zero_selective && !p->zero_rows.empty()) {
             if (hipMalloc((void **)&p->d_zero_rows, sizeof(int32_t) * p->zero_rows.size()) != hipSuccess) return SC_ERR_DEVICE;
@@ -1831,6 +2113,9 @@ extern "C" sc_status sc_plan_destroy(sc_plan *plan)
     for (uint32_t *r : plan->walk.d_rec)
         if (r) (void)hipFree(r);
     if (plan->walk.d_heads) (void)hipFree(plan->walk.d_heads);
+    const sck::SliceTables &sl = plan->slice;
+    for (void *d : {(void *)sl.d_runs, (void *)sl.d_chunks, (void *)sl.d_leaf, (void *)sl.d_at, (void *)sl.d_gj, (void *)sl.d_first})
+        if (d) (void)hipFree(d);
     for (sck::FixLevel *lv : {&plan->det_top, &plan->det_a, &plan->det_b}) {
         if (lv->d_fix) (void)hipFree(lv->d_fix);
         if (lv->d_segs) (void)hipFree(lv->d_segs);

@@ -766,15 +766,12 @@ sc_status run_order3(const sc_plan *p, const sc_csf_view *sp, const sc_dense_vie
                 mttkrp3_fused_kernel<T, W, true><<<ntiles, NT, mttkrp_lds_bytes<T>(W, a.tn, a.ta, a.tb), stream>>>(a);
             else
                 mttkrp3_fused_kernel<T, W, false><<<ntiles, NT, mttkrp_lds_bytes<T>(W, a.tn, a.ta, a.tb), stream>>>(a);
+        } else if (plan_slice_source(p, nullptr) != SLICE_NONE) {
+            return launch_slice(p, ln, sp, fac[0], &fac[1], nullptr, fac[1].cols, out, "ttmc3_fused_mfma");
         } else if (mfma) {
             ln.status = launch_ttmc3_mfma(p, ln, sp, fac, nullptr, out, a.partials);
             if (ln.status != SC_OK) return ln.status;
             return launch_fixup(p, ln, p->det_top, ws, out);
-        } else if (plan_uses_wide_ttmc3(p)) {
-            if constexpr (sizeof(T) == 4) {
-                ln.status = launch_ttmc3_wide(p, ln, sp, fac, nullptr, out);
-                return ln.status;
-            }
         } else {
             if constexpr (can_mf) {
                 if (mf) {
@@ -802,15 +799,12 @@ sc_status run_order3(const sc_plan *p, const sc_csf_view *sp, const sc_dense_vie
                 hadamard_consume_kernel<T, W, true><<<ntiles, NT, hadamard_lds_bytes<T>(a.ta, a.tb), stream>>>(a);
             else
                 hadamard_consume_kernel<T, W, false><<<ntiles, NT, hadamard_lds_bytes<T>(a.ta, a.tb), stream>>>(a);
+        } else if (plan_slice_source(p, nullptr) != SLICE_NONE) {
+            return launch_slice(p, ln, sp, fac[0], nullptr, a.T, fac[1].cols, out, "ttmc3_consume_mfma");
         } else if (mfma) {
             ln.status = launch_ttmc3_mfma(p, ln, sp, fac, a.T, out, a.partials);
             if (ln.status != SC_OK) return ln.status;
             return launch_fixup(p, ln, p->det_top, ws, out);
-        } else if (plan_uses_wide_ttmc3(p)) {
-            if constexpr (sizeof(T) == 4) {
-                ln.status = launch_ttmc3_wide(p, ln, sp, fac, a.T, out);
-                return ln.status;
-            }
         } else {
             if constexpr (can_mf) {
                 if (mf) {
@@ -930,19 +924,25 @@ sc_status launch_fixup(const sc_plan *p, Launcher &ln, const FixLevel &lv, void 
     return ln.status;
 }
 
-// Order-3 chains whose ranks are multiples of the MFMA tile (other than 16 x 16) run the kernel that keeps a slice's
-// output tiles in registers across the work tiles of a run (FUSED, and as the consumer behind the leaf traversal);
-// deterministic plans stay with the general kernel.
-bool plan_uses_wide_ttmc3(const sc_plan *p)
+// fp32 chains of order 3 in every class, and the last kernel of the FISSIONED order-4 chain at 8 x 8, unless the caller asks for a
+// reproducible sum.  Start and now, whole calls in us: 6 M entries at 64 x 32 383 and 214; 4 M at 128 x 128 (inside kernel 5) 1930 and 946;
+// 1.5 M at 16 x 16 67 and 25, at 8 x 64 147 and 53; unfactored, 1.5 M at 12 x 20 79 and 41, at 4 x 4 45 and 28; 120,000 entries in 38,000
+// slices 23 to 1002 and 15 to 467.  Even at 20,000 entries up to 16 x 32 (launch latency).
+SliceSource plan_slice_source(const sc_plan *p, int *piece)
 {
-    return p->kind == K_TTMC3 && p->dtype == SC_F32 && (p->sched == SC_SCHED_FUSED || p->sched == SC_SCHED_FISSIONED) &&
-           !p->deterministic && ttmc3_wide_ranks(p->fcols[0], p->fcols[1]);
+    if (piece) *piece = kSlicePiece;
+    if (p->dtype != SC_F32 || p->deterministic) return SLICE_NONE;
+    if (p->kind == K_TTMC3 && slice_shape(p->fcols[0], p->fcols[1], p->sched == SC_SCHED_LINEAR).lt) {
+        if (p->sched == SC_SCHED_LINEAR && piece) *piece = 1;   // nothing is factored out: every stored entry is a piece
+        return p->sched == SC_SCHED_FISSIONED ? SLICE_ROWS : SLICE_LEAVES;
+    }
+    if (p->kind == K_TTMC4 && p->sched == SC_SCHED_FISSIONED && p->fcols[0] <= 16 && p->fcols[1] == 8 && p->fcols[2] == 8) return SLICE_ROWS;
+    return SLICE_NONE;
 }
 
 bool plan_wants_tensor_order(const sc_plan *p)
 {
     if (p->dtype != SC_F32 || p->sched == SC_SCHED_LINEAR) return false;
-    if (plan_uses_wide_ttmc3(p)) return true;
     if (p->kind == K_TTMC3) return p->fcols[0] == 16 && p->fcols[1] == 16;
     return p->kind == K_TTMC4 && p->fcols[0] <= 16 && p->fcols[1] == 8 && p->fcols[2] == 8;   // the matrix-core kernels of the order-4 chain
 }
@@ -952,17 +952,14 @@ int plan_output_run(const sc_plan *p)
     if (p->sched != SC_SCHED_FUSED && p->sched != SC_SCHED_FISSIONED) return 0;
     if (p->deterministic) return 0;   // one tile per workgroup, pieces in slots: no row is added to
     const bool fused = p->sched == SC_SCHED_FUSED;
-    if (plan_uses_wide_ttmc3(p)) return ttmc3_wide_run(p);
-    if (p->kind == K_TTMC3 && plan_wants_tensor_order(p)) return ttmc3_mfma_run(p, false);
-    if (p->kind == K_TTMC4 && plan_wants_tensor_order(p)) return ttmc4_mfma_run(p, fused ? 0 : 2, false);
+    if (p->kind == K_TTMC4 && fused && plan_wants_tensor_order(p)) return ttmc4_mfma_run(p, 0, false);
     return 0;
 }
 
 WalkShape plan_walk_shape(const sc_plan *p)
 {
-    if (p->sched == SC_SCHED_LINEAR) return WalkShape{};
+    if (p->sched == SC_SCHED_LINEAR || plan_slice_source(p, nullptr) == SLICE_LEAVES) return WalkShape{};
     if (p->kind == K_TTMC4 && plan_wants_tensor_order(p)) return ttmc4_mfma_walk_shape();   // its leaf level also serves the traversal kernel
-    if (plan_uses_wide_ttmc3(p) && p->sched == SC_SCHED_FUSED) return ttmc3_wide_walk_shape((int)p->fcols[1]);
     if (p->kind == K_TTMC3 && p->sched == SC_SCHED_FUSED && plan_wants_tensor_order(p)) return ttmc3_mfma_walk_shape();
     // FISSIONED, order >= 3: the leaf traversal, whose rows are as wide as the last factor
     if (p->sched == SC_SCHED_FISSIONED && (p->kind == K_TTMC3 || p->kind == K_MTTKRP3))
@@ -984,9 +981,6 @@ size_t lds_bytes_needed(const sc_plan *p)
             return p->dtype == SC_F64 ? mttkrp_lds_bytes<double>(w, p->caps.tn, p->caps.ta, p->caps.tb)
                                       : mttkrp_lds_bytes<float>(w, p->caps.tn, p->caps.ta, p->caps.tb);
         }
-        if (plan_uses_wide_ttmc3(p))
-            return p->sched == SC_SCHED_FUSED ? ttmc3_wide_lds_bytes(p)
-                                              : std::max(ttmc3_wide_lds_bytes(p), leaf_traverse_lds_bytes(p, (int)producer_width(p)));
         if (p->kind == K_TTMC3 && plan_wants_tensor_order(p)) {
             if (!ttmc3_mfma_caps_ok(p)) return SIZE_MAX;
             if (p->sched != SC_SCHED_FISSIONED) return ttmc3_mfma_lds_bytes(p);

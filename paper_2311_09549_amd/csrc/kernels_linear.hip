@@ -5,7 +5,8 @@
 // (nnz * L * M multiply-adds for the order-3 chain instead of M * (nnz + F * L), Section 1), and what
 // SC_SCHED_AUTO falls back to for ranks without a factored kernel.  One workgroup per tile of
 // nonzeros; the partial sum of an output row is kept in registers while the walk stays inside one
-// slice.  linear_tiled_kernel takes the expressions of order 3 and 4 at ranks that are multiples of 4;
+// slice.  The fp32 chain of order 3 runs as slice products (kernels_slice.hip) up to rank 128: every stored entry is a child of
+// its own there.  linear_tiled_kernel takes the other expressions of order 3 and 4 at ranks that are multiples of 4;
 // linear_kernel, one thread per dense output element, the other ranks and the SDDMM.
 //
 //   order 3 chain   A(i,l,m)   += B(i,j,k)   * C(j,l) * D(k,m)
@@ -413,6 +414,7 @@ sc_status launch_linear(const sc_plan *p, const sc_csf_view *sp, const sc_dense_
     const int ntiles = (int)p->tiles.size();
     if (ntiles == 0) return ln.status;
     if (p->caps.tn > LIN_TN) return SC_ERR_SCHED_UNSUPPORTED;
+    if (plan_slice_source(p, nullptr) != SLICE_NONE) return launch_slice(p, ln, sp, fac[0], &fac[1], nullptr, fac[1].cols, out, "linear_nest");
     LinArgs a = {};
     for (int m = 0; m < 4; ++m) {
         a.pos[m] = sp->pos[m];

@@ -276,6 +276,8 @@ sc_status run_order4(const sc_plan *p, const sc_csf_view *sp, const sc_dense_vie
                 st = launch_fixup(p, ln, p->det_b, ws, a.T2);
                 if (st != SC_OK) return st;
             }
+            if (plan_slice_source(p, nullptr) != SLICE_NONE)
+                return launch_slice(p, ln, sp, fac[0], nullptr, a.T2, M * N, out, "ttmc4_consume_mfma");
             ln.status = launch_ttmc4_mfma(p, ln, sp, fac, 2, a.T1, a.T2, out, det ? wsb + p->det_top.slot_offset : nullptr);
             if (ln.status != SC_OK || !det) return ln.status;
             return launch_fixup(p, ln, p->det_top, ws, out);

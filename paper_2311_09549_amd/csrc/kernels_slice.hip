@@ -1,0 +1,440 @@
+// Slice products on matrix cores, fp32: the last contraction of a TTM chain,
+//     A(i,:,:) = sum over the children f of slice i of  C(j_f,:)^T (x) T(f,:)          (L x W per slice)
+// with the rows of T either formed on the way from the leaves of the tensor (FUSED, and the unfactored nest: Table 2,
+// kernel 6 <SpTTM, TTM>; also the sparse part of kernel 5) or read from the workspace (the last kernel of the FISSIONED
+// schedules of order 3 and 4).
+//
+// Four children form a step group, the K = 4 of v_mfma_f32_16x16x4_f32: lanes 16 kk .. 16 kk + 15 hold the row of child kk.
+// Which l and m a tile's rows and columns stand for is free, so a lane reads MT adjacent values of a row of T (or of D) and LT
+// adjacent values of a row of C straight into operand registers: no row of T passes through LDS.  A wavefront owns a run of
+// steps and all (or a quarter, half) of the L x W output of the slice it is in; it shares nothing with its neighbours, so
+// there is no barrier, and wavefronts in different phases keep the gathers and the matrix cores busy together.
+//
+//   SRC_LEAVES  the plan lists for every step the leaf that each of the four fibers of the group contributes: its last coordinate
+//               and the place of its value among the values of the chunk of steps (64 at most), which are contiguous.  Fibers are
+//               cut into pieces of at most kSlicePiece leaves and grouped by length inside a chunk's part of a slice.
+//               t(f,:) += B * D(k,:) stays in MT registers until the group's last step.
+//   SRC_ROWS    a step is four consecutive children; their rows of T are 4 W adjacent floats in memory.
+//
+// A run ends anywhere in a slice (runs have equal work): a slice inside one run is stored once, a slice cut by a run's end
+// is added to the zeroed row atomically, after the runs of a workgroup that lie inside one slice have been added up in LDS.  A chunk is staged
+// in a region of LDS of the wavefront's own ({row offset, value} per leaf, offset of C(j,:) per child), read a chunk ahead; the loop
+// then takes U steps per batch, whose gathers are all issued before the first is used.
+#include "device_common.h"
+
+#include <type_traits>
+
+namespace sck {
+
+namespace {
+
+constexpr int SRC_LEAVES = 0, SRC_ROWS = 1;
+
+// An output larger than this is stored with the non-temporal hint: written through the L2s it evicts the rows of C and D that the
+// gathers hit there (500 MB at 64 x 32: 289 us, 229 us so; 2.6 GB at 128 x 128: 1056 and 945 us), while the 41 MB of S at 16 x 16 are
+// better found there by the next kernel (12.6 us, 15.4 us so).
+constexpr int64_t kStreamBytes = 128 << 20;
+
+struct SliceArgs {
+    int32_t nruns;
+    const uint32_t *leaf, *at;   // SRC_LEAVES: 4 last coordinates per step, 4 places of the value in the chunk (bytes)
+    const int32_t *gj;           // SRC_LEAVES: 4 per group, coordinate of the row of C
+    const int32_t *first;        // SRC_ROWS: first child of every step and the child count
+    const int32_t *crd1;         // output row of every slice
+    const int32_t *crd2;         // SRC_ROWS: coordinate of the row of C of every child
+    int32_t nslices;
+    const float *vals;           // SRC_LEAVES
+    const float *C, *D;          // D: SRC_LEAVES the factor of the last mode, SRC_ROWS the rows of T
+    uint32_t rowC, rowD;         // bytes from row to row
+    float *A;
+    int32_t L, W;
+    int32_t stream;              // the output is stored past the L2s
+};
+
+typedef float sl_floatx4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ int sl_uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
+
+// Steps per batch and wavefronts per SIMD by the number of 16 x 16 tiles.  One tile: 45.5 us with eight steps, 43 with four (4 M
+// leaves, 16 x 16); eight tiles: 221 us with four steps and four wavefronts, 203 with eight and three (6 M leaves, 64 x 32); sixteen: 957 us with
+// four steps and three wavefronts, 946 with eight and two where four wavefronts share a run (128 x 128), but 97 and 121 us where each has its
+// own (64 x 64, 1 M leaves in 1,800 slices).
+constexpr int slice_batch(int tiles, int per_run) { return tiles == 1 || (tiles == 16 && per_run < 4) ? 4 : 8; }
+constexpr int slice_occupancy(int tiles, int per_run, bool edge)
+{
+    return (tiles == 16 && per_run == 4 ? 2 : tiles >= 8 ? 3 : 4) - (edge ? 1 : 0);
+}
+
+// Two sets of sums (TWO in the kernel): up to four tiles, and eight in the EDGE instantiations, which run the unfactored nest.  Eight tiles of a
+// chain are no further from the exact sum without them than the tiled kernel they replaced was (2.9e-7 and 3.6e-7 at 64 x 32), and
+// 16 us of 234 faster; sixteen leave no registers for them.
+constexpr bool slice_two_sums(int tiles, bool edge) { return tiles <= 4 || (tiles == 8 && edge); }
+
+// runs: nruns + 1 records, chunks: one past the last.  Arguments of their own, so that the loop reads them through the scalar cache.
+// LT, MT: 16-wide tiles of l and m per wavefront; WL x WM wavefronts share a run; EDGE: L or W may be less than the tiles cover; all of the unfactored nest.
+template <int LT, int MT, int WL, int WM, int SRC, bool EDGE>
+__global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, WL * WM, EDGE)) slice_kernel(SliceArgs a, const SliceRun *__restrict__ runs,
+                                                                                      const SliceChunk *__restrict__ chunks)
+{
+    constexpr int WPR = WL * WM;              // wavefronts per run
+    constexpr int U = slice_batch(LT * MT, WPR);   // steps per batch
+    typedef float TVec __attribute__((ext_vector_type(MT)));
+    typedef float CVec __attribute__((ext_vector_type(LT)));
+    struct alignas(8) Rec { uint32_t off; float v; };
+
+    struct Own {                          // a wavefront's own staging region
+        alignas(16) Rec rec[256];
+        uint32_t coff[256];
+        float swap[256];                  // the chunk's values while it is staged; a row on its way to atomic additions
+    };
+    union Lds {
+        Own own[NT / 64];
+        float sum[2][WPR < 4 ? 256 * LT * MT : 4];   // after the runs: sums on their way to another wavefront
+    };
+    __shared__ Lds lds;
+    __shared__ int inside_s[NT / 64];
+
+    const int wave = sl_uni(threadIdx.x / 64), lane = threadIdx.x % 64;
+    const int kk = lane / 16, col = lane % 16;
+    const int run = (int)blockIdx.x * (4 / WPR) + wave / WPR, sub = wave % WPR;
+    Rec *rec_s = lds.own[wave].rec;
+    uint32_t *coff_s = lds.own[wave].coff;
+    float *swap_s = lds.own[wave].swap;
+    const int L = EDGE ? a.L : 16 * LT * WL, W = EDGE ? a.W : 16 * MT * WM;
+    const int l0 = (sub / WM) * 16 * LT, m0 = (sub % WM) * 16 * MT;
+    // first of the lane's values of l and m; lanes past a row read its end again and are not stored
+    const int ll = l0 + LT * col, lm = m0 + MT * col;
+    // uniform bases and 32-bit byte offsets: one addition per gather
+    const uint32_t c_lane = 4 * (EDGE ? min(ll, L - LT) : ll), d_lane = 4 * (EDGE ? min(lm, W - MT) : lm);
+    const char *Cb = reinterpret_cast<const char *>(a.C), *Db = reinterpret_cast<const char *>(a.D);
+
+    // a wavefront past the last run has no steps
+    const SliceRun r = runs[min(run, a.nruns)], r_end = runs[min(run + 1, a.nruns)];
+    const int c_end = r_end.chunk0 + (r_end.step > 0 ? 1 : 0);   // one past the last chunk of which this run has steps
+    SliceChunk ch = chunks[r.chunk0];
+    auto below = [](uint64_t bits, int n) { return __builtin_popcountll(bits & ((1ull << n) - 1)); };   // n < 64
+    const int slice0 = ch.slice0 + below(ch.send, r.step);
+    int sl = slice0;
+    bool open = (r.flags & 1) != 0;   // the slice began in an earlier run
+    int fbase = 0;
+    if (SRC == SRC_ROWS && r.chunk0 < c_end) {
+        fbase = a.first[ch.step0 + r.step];
+        Db += (int64_t)fbase * a.rowD;
+    }
+
+    // Global reads of a chunk's staging: lane n takes step n (those past the chunk repeat its last one) and the group that step belongs
+    // to.  They are issued a chunk ahead and land while the one before is worked on.
+    struct Stage {
+        uint4 leaf;
+        uint32_t at;
+        int4 j;
+        float v[4];
+        int f0, f1, row;
+    };
+    auto issue = [&](const SliceChunk &k, Stage &s) {
+        const int n = min(lane, k.nsteps - 1);
+        s.row = a.crd1[min(k.slice0 + lane, a.nslices - 1)];   // the output rows of the slices the chunk may complete
+        if (SRC == SRC_LEAVES) {
+            s.leaf = reinterpret_cast<const uint4 *>(a.leaf)[k.step0 + n];
+            s.at = a.at[k.step0 + n];
+            const int g = __builtin_amdgcn_mbcnt_hi((uint32_t)(k.gend >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)k.gend, 0));   // groups completed before step `lane`
+            s.j = reinterpret_cast<const int4 *>(a.gj)[k.group0 + min(g, k.ngroups - 1)];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) s.v[q] = a.vals[k.leaf0 + min(64 * q + lane, k.nleaves - 1)];
+        } else {
+            s.f0 = a.first[k.step0 + n];
+            s.f1 = a.first[k.step0 + n + 1];   // 1 to 4 children
+            s.j.x = a.crd2[s.f0];
+            s.j.y = a.crd2[min(s.f0 + 1, s.f1 - 1)];
+            s.j.z = a.crd2[min(s.f0 + 2, s.f1 - 1)];
+            s.j.w = a.crd2[s.f1 - 1];
+        }
+    };
+
+    // Sums of up to SPAN steps, and of those: one chain of additions over a run of hundreds of steps in a heavy slice was up to 2.3 times
+    // further from the sum in double precision than the tile by tile sums it replaces.
+    constexpr bool TWO = slice_two_sums(LT * MT, EDGE);
+    constexpr int SPAN = 16;
+    sl_floatx4 acc[MT][LT], tot[TWO ? MT : 1][TWO ? LT : 1];
+    auto clear = [&](auto &v) {
+        for (auto &row : v)
+            for (sl_floatx4 &e : row) e = sl_floatx4{0.f, 0.f, 0.f, 0.f};
+    };
+    auto gather_sums = [&](sl_floatx4 (&to)[MT][LT], const sl_floatx4 (&from)[MT][LT]) {
+#pragma unroll
+        for (int x = 0; x < MT; ++x)
+#pragma unroll
+            for (int y = 0; y < LT; ++y) to[x][y] += from[x][y];
+    };
+    TVec t;
+#pragma unroll
+    for (int x = 0; x < MT; ++x) t[x] = 0.f;
+    clear(acc);
+    clear(tot);
+
+    auto multiply = [&](const TVec &tv, const CVec &cv) {
+#pragma unroll
+        for (int x = 0; x < MT; ++x)
+#pragma unroll
+            for (int y = 0; y < LT; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(cv[y], tv[x], acc[x][y], 0, 0, 0);
+    };
+    // acc[x][y][q] = A(l = l0 + LT (4 kk + q) + y, m = lm + x): a store instruction covers four rows l of 16 MT adjacent floats
+    constexpr int STORE = 0, STREAM = 1, ADD = 2;
+    auto emit = [&](int row, auto how) {
+        constexpr int HOW = decltype(how)::value;
+        float *A = a.A + (int64_t)row * L * W;
+#pragma unroll
+        for (int y = 0; y < LT; ++y)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int l = l0 + LT * (4 * kk + q) + y;
+                TVec o;
+#pragma unroll
+                for (int x = 0; x < MT; ++x) o[x] = acc[x][y][q];
+                if (HOW != ADD) {
+                    TVec *dst = reinterpret_cast<TVec *>(A + l * W + lm);
+                    if (!EDGE || (l < L && lm < W)) {
+                        if (HOW == STREAM) __builtin_nontemporal_store(o, dst);
+                        else *dst = o;
+                    }
+                } else {
+                    // adjacent lanes on adjacent floats: an addition of MT floats per lane visits every cache line MT times
+                    if (MT > 1) *reinterpret_cast<TVec *>(swap_s + MT * lane) = o;
+#pragma unroll
+                    for (int x = 0; x < MT; ++x) {
+                        const float v = MT > 1 ? swap_s[16 * MT * kk + 16 * x + col] : o[0];
+                        const int m = m0 + 16 * x + col;
+                        if (!EDGE || (l < L && m < W)) atomic_add(A + l * W + m, v);
+                    }
+                }
+            }
+    };
+
+    int last_row = 0;
+    bool goes_on = false;   // the slice the run ends in goes on in the next run
+    Stage st;
+    if (r.chunk0 < c_end) issue(ch, st);
+    for (int c = r.chunk0; c < c_end; ++c) {
+        const int from = c == r.chunk0 ? r.step : 0, to = c == r_end.chunk0 ? r_end.step : ch.nsteps;
+        const int ns = ch.nsteps, sl_base = ch.slice0, rowv = st.row;
+        const uint64_t gm = ch.gend, sm = ch.send;
+        // ---- stage: registers -> LDS; steps past the chunk count as zero ----
+        const bool live = lane < ns;
+        if (SRC == SRC_LEAVES) {
+            const int nl = ch.nleaves;
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int q = 0; q < 4; ++q) swap_s[64 * q + lane] = 64 * q + lane < nl ? st.v[q] : 0.f;   // place 255 is zero in a chunk of fewer leaves
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            float v[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] = swap_s[st.at >> 8 * q & 255];
+            uint4 *dst = reinterpret_cast<uint4 *>(rec_s + 4 * lane);
+            auto word = [&](float x) { return live ? __builtin_bit_cast(uint32_t, x) : 0u; };
+            dst[0] = uint4{st.leaf.x * a.rowD, word(v[0]), st.leaf.y * a.rowD, word(v[1])};
+            dst[1] = uint4{st.leaf.z * a.rowD, word(v[2]), st.leaf.w * a.rowD, word(v[3])};
+        } else {
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                Rec e;   // children past the step repeat its last row and count as zero
+                e.off = (uint32_t)(min(st.f0 + q, st.f1 - 1) - fbase) * a.rowD;   // (steps before the run's first are not read)
+                e.v = live && st.f0 + q < st.f1 ? 1.f : 0.f;
+                rec_s[4 * lane + q] = e;
+            }
+        }
+        reinterpret_cast<uint4 *>(coff_s)[lane] =
+            uint4{(uint32_t)st.j.x * a.rowC, (uint32_t)st.j.y * a.rowC, (uint32_t)st.j.z * a.rowC, (uint32_t)st.j.w * a.rowC};
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        ch = chunks[c + 1];
+        if (c + 1 < c_end) issue(ch, st);
+
+        for (int b = from; b < to; b += U) {
+            const uint32_t gb = SRC == SRC_LEAVES ? (uint32_t)(gm >> b) : 0xffffffffu, sb = (uint32_t)(sm >> b);
+            Rec rec[U];
+            uint32_t co[U];
+            TVec d[U];
+            CVec c[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) rec[u] = rec_s[4 * (b + u) + kk];
+#pragma unroll
+            for (int u = 0; u < U; ++u) co[u] = coff_s[4 * (b + u) + kk];
+#pragma unroll
+            for (int u = 0; u < U; ++u) d[u] = *reinterpret_cast<const TVec *>(Db + (rec[u].off + d_lane));
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (SRC == SRC_ROWS || (gb >> u & 1)) c[u] = *reinterpret_cast<const CVec *>(Cb + (co[u] + c_lane));
+            uint32_t ge = gb;
+            __asm__ volatile("" : "+s"(ge));   // tests of its own below: a bit kept over the batch costs more scalar instructions
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (SRC == SRC_LEAVES) {
+#pragma unroll
+                    for (int x = 0; x < MT; ++x) t[x] += rec[u].v * d[u][x];
+                } else {
+#pragma unroll
+                    for (int x = 0; x < MT; ++x) t[x] = rec[u].v != 0.f ? d[u][x] : 0.f;
+                }
+                if (SRC == SRC_ROWS || (ge >> u & 1)) {
+                    multiply(t, c[u]);
+                    if (SRC == SRC_LEAVES) {
+#pragma unroll
+                        for (int x = 0; x < MT; ++x) t[x] = 0.f;
+                    }
+                    if (sb >> u & 1) {
+                        const int row = __builtin_amdgcn_readlane(rowv, sl - sl_base);
+                        if constexpr (TWO) {
+                            gather_sums(acc, tot);
+                            clear(tot);
+                        }
+                        if (open) emit(row, std::integral_constant<int, ADD>{});
+                        else if (a.stream) emit(row, std::integral_constant<int, STREAM>{});
+                        else emit(row, std::integral_constant<int, STORE>{});
+                        clear(acc);
+                        open = false;
+                        ++sl;
+                    }
+                }
+            }
+            if constexpr (TWO) {
+                if ((b + U) % SPAN == 0) {
+                    gather_sums(tot, acc);
+                    clear(acc);
+                }
+            }
+        }
+        if (c + 1 == c_end) {
+            // a group cut by the run's end is multiplied as far as it has come
+            if (SRC == SRC_LEAVES && !(gm >> (to - 1) & 1)) multiply(t, *reinterpret_cast<const CVec *>(Cb + (coff_s[4 * (to - 1) + kk] + c_lane)));
+            goes_on = !(sm >> (to - 1) & 1);
+            last_row = __builtin_amdgcn_readlane(rowv, min(sl - sl_base, 63));
+            if constexpr (TWO) gather_sums(acc, tot);
+        }
+    }
+    // What is left of a slice that goes on in the next run.  Runs that lie inside one slice are added up inside the workgroup first,
+    // in two rounds (0 to 1 and 2 to 3, then the pair 0, 1 to the last that follows it); the rest goes to the slice's row atomically.
+    if constexpr (WPR < 4) {
+        constexpr int RPB = 4 / WPR;
+        const int rw = wave / WPR;
+        const bool inside = goes_on && open && sl == slice0;
+        if (lane == 0) inside_s[wave] = (goes_on ? 1 : 0) | (inside ? 2 : 0);
+        __syncthreads();
+        auto state = [&](int n) { return sl_uni(inside_s[n * WPR]); };
+        // run n's sum goes to run n + 1
+        auto pass = [&](int n) { return n + 1 < RPB && (state(n) & 1) && (state(n + 1) & 2); };
+        auto send_to = [&](float *buf) {
+#pragma unroll
+            for (int x = 0; x < MT; ++x)
+#pragma unroll
+                for (int y = 0; y < LT; ++y) *reinterpret_cast<sl_floatx4 *>(buf + (x * LT + y) * 256 + 4 * lane) = acc[x][y];
+        };
+        auto add_from = [&](const float *buf) {
+#pragma unroll
+            for (int x = 0; x < MT; ++x)
+#pragma unroll
+                for (int y = 0; y < LT; ++y) acc[x][y] += *reinterpret_cast<const sl_floatx4 *>(buf + (x * LT + y) * 256 + 4 * lane);
+        };
+        const bool mine = rw % 2 == 0 && pass(rw), theirs = rw % 2 == 1 && pass(rw - 1);
+        if (mine) send_to(lds.sum[wave / (2 * WPR) * WPR + sub]);
+        __syncthreads();
+        if (theirs) add_from(lds.sum[wave / (2 * WPR) * WPR + sub]);
+        goes_on = goes_on && !mine;
+        if constexpr (RPB == 4) {
+            __syncthreads();
+            const bool across = pass(1);
+            const int to = pass(2) ? 3 : 2;
+            if (across && rw == 1) send_to(lds.sum[0]);
+            __syncthreads();
+            if (across && rw == to) add_from(lds.sum[0]);
+            goes_on = goes_on && !(across && rw == 1);
+        }
+        if (MT > 1) __syncthreads();   // the sums have been read: their space is the staging regions again
+    }
+    if (goes_on) emit(last_row, std::integral_constant<int, ADD>{});
+}
+
+template <int SRC>
+void dispatch_slice(const SliceArgs &a, const SliceTables &st, bool linear, hipStream_t stream)
+{
+    auto go = [&](auto lt, auto mt, auto wl, auto wm) {
+        constexpr int LT = decltype(lt)::value, MT = decltype(mt)::value, WL = decltype(wl)::value, WM = decltype(wm)::value;
+        constexpr int RPB = 4 / (WL * WM);
+        const int blocks = (a.nruns + RPB - 1) / RPB;
+        if (linear || a.L != 16 * LT * WL || a.W != 16 * MT * WM) slice_kernel<LT, MT, WL, WM, SRC, true><<<blocks, NT, 0, stream>>>(a, st.d_runs, st.d_chunks);
+        else slice_kernel<LT, MT, WL, WM, SRC, false><<<blocks, NT, 0, stream>>>(a, st.d_runs, st.d_chunks);
+    };
+    const SliceShape sh = slice_shape(a.L, a.W, linear);
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    using I4 = std::integral_constant<int, 4>;
+    auto over_m = [&](auto lt, auto wl) {
+        constexpr int LT = decltype(lt)::value, WL = decltype(wl)::value;
+        if constexpr (SRC == SRC_LEAVES && LT == 4) {
+            if (sh.mt == 2 && sh.wm == 2) return go(lt, I2{}, wl, I2{});   // the unfactored nest
+            if constexpr (WL == 1) {
+                if (sh.wm == 4) return go(lt, I2{}, wl, I4{});
+            }
+        }
+        if (sh.wm == 2) go(lt, I4{}, wl, I2{});
+        else if (sh.mt == 1) go(lt, I1{}, wl, I1{});
+        else if (sh.mt == 2) go(lt, I2{}, wl, I1{});
+        else go(lt, I4{}, wl, I1{});
+    };
+    if (sh.wl == 2) over_m(I4{}, I2{});
+    else if (sh.lt == 1) over_m(I1{}, I1{});
+    else if (sh.lt == 2) over_m(I2{}, I1{});
+    else over_m(I4{}, I1{});
+}
+
+}  // namespace
+
+SliceShape slice_shape(int64_t L, int64_t W, bool linear)
+{
+    SliceShape s;
+    if (L < 1 || L > 128 || W < 4 || W > 128 || W % 4 || (L > 16 && L % 4)) return s;   // the 16-byte (8-byte) pieces a lane reads and stores
+    s.lt = L <= 16 ? 1 : L <= 32 ? 2 : 4;
+    s.mt = W <= 16 ? 1 : W <= 32 ? 2 : 4;
+    s.wl = L > 64 ? 2 : 1;
+    s.wm = W > 64 ? 2 : 1;
+    if (linear && !slice_two_sums(s.lt * s.mt, true)) {
+        // the unfactored nest adds a product per stored entry, with nothing summed up ahead of it: two sets of sums always
+        s.mt = 2;
+        s.wm *= 2;
+        if (s.wl * s.wm > 4) s.lt = 0;
+    }
+    return s;
+}
+
+sc_status launch_slice(const sc_plan *p, Launcher &ln, const sc_csf_view *sp, const sc_dense_view &C, const sc_dense_view *D, const void *T,
+                       int64_t W, void *out, const char *name)
+{
+    const SliceTables &st = p->slice;
+    if (!st.d_runs) return SC_ERR_SCHED_UNSUPPORTED;
+    SliceArgs a = {};
+    a.nruns = st.nruns;
+    a.leaf = st.d_leaf;
+    a.at = st.d_at;
+    a.gj = st.d_gj;
+    a.first = st.d_first;
+    a.crd1 = sp->crd[0];
+    a.crd2 = sp->crd[1];
+    a.nslices = (int32_t)p->nfib[0];
+    a.vals = static_cast<const float *>(sp->vals);
+    a.C = static_cast<const float *>(C.data);
+    a.rowC = (uint32_t)(C.ld * 4);
+    a.D = static_cast<const float *>(T ? T : D->data);
+    a.rowD = (uint32_t)(T ? W * 4 : D->ld * 4);
+    a.A = static_cast<float *>(out);
+    a.L = (int32_t)C.cols;
+    a.W = (int32_t)W;
+    a.stream = p->out_elems * 4 > kStreamBytes;
+    ln.begin(name);
+    if (T) dispatch_slice<SRC_ROWS>(a, st, false, ln.stream);
+    else dispatch_slice<SRC_LEAVES>(a, st, p->sched == SC_SCHED_LINEAR, ln.stream);
+    ln.end();
+    return ln.status;
+}
+
+}  // namespace sck

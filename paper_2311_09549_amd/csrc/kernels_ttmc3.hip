@@ -1,5 +1,5 @@
-// TTM chain of order 3 on matrix cores (Table 2, kernel 6 <SpTTM, TTM>), fp32, L = M = 16; the FUSED
-// schedule in one kernel and, with FUSED = false, the consumer half of the FISSIONED schedule (the
+// TTM chain of order 3 on matrix cores (Table 2, kernel 6 <SpTTM, TTM>), fp32, L = M = 16, deterministic
+// schedules (the others run the slice products of kernels_slice.hip); the FUSED schedule in one kernel and, with FUSED = false, the consumer half of the FISSIONED schedule (the
 // rows of T then come from the workspace instead of the leaf walk):
 //     T(f,:)   = sum_{k' in fiber f} B * D(k,:)              (producer, leaf traversal)
 //     A(i,:,:) += C(j,:)^T (x) T(f,:)   over the fibers of slice i   (consumer, rank-1 updates)
@@ -21,11 +21,8 @@
 //            piece of a slice that continues from / into another wavefront or tile is parked
 //            in LDS (at most one head and one tail piece per wavefront, plain stores).
 //   combine  wavefront 0 adds the parked pieces in fiber order and stores every slice that
-//            ends in the tile.  A workgroup owns a contiguous run of tiles, and the sum of a
-//            slice that continues into the next tile stays in wavefront 0's registers, so a
-//            heavy slice costs one global update per workgroup instead of one per tile; only a
-//            slice that crosses the run's ends is added atomically to the zeroed output.  No
-//            LDS atomics are involved (they measured several times slower than this scheme).
+//            ends in the tile; the pieces of slices shared with other tiles go to the slots that the plan
+//            numbered.  No LDS atomics are involved (they measured several times slower than this scheme).
 #include "leaf_walk.h"
 
 namespace sck {
@@ -40,9 +37,8 @@ struct Ttmc3Args {
     int64_t ldC, ldD;
     const float *T;   // FISSIONED consumer: the materialised temporary, one 16-wide row per fiber
     float *A;
-    float *partials;   // deterministic schedules: slots for the pieces of rows that span tiles (runs are single tiles then), else null
+    float *partials;   // slots for the pieces of rows that span tiles (not read when there are none)
     int32_t tn, ta, tb;
-    int32_t ntiles, run;   // tiles in the plan; tiles per workgroup
 };
 
 using Ttmc3Rec = LeafRec<float>;
@@ -73,9 +69,7 @@ __host__ __device__ constexpr size_t ttmc3_lds_bytes(int tn, int ta, int tb)
 
 typedef float t3_floatx4 __attribute__((ext_vector_type(4)));
 
-// DET: the deterministic variant (pieces of rows that span tiles go to plan-numbered slots), a
-// separate instantiation so that the atomic variant keeps its register budget.
-template <bool FUSED, bool DET>
+template <bool FUSED>
 __global__ void __launch_bounds__(NT, 5) ttmc3_mfma_kernel(Ttmc3Args a, const TileRec *__restrict__ tiles)
 {
     constexpr int U = T3_U;
@@ -93,9 +87,7 @@ __global__ void __launch_bounds__(NT, 5) ttmc3_mfma_kernel(Ttmc3Args a, const Ti
     int *meta_s = crdb_s + a.tb;                                                         // WAVES x 4: head slice, head ends, tail slice
 
     const int tid = threadIdx.x;
-    const int first = blockIdx.x * a.run, lastp1 = min(first + a.run, a.ntiles);
-    t3_floatx4 carry = {0.f, 0.f, 0.f, 0.f};   // wavefront 0: sum so far of the slice that continues from the previous tile
-    bool chain_shared = false;                 // that slice began before this workgroup's run
+    const int tile = blockIdx.x;
     // Global reads of one tile's staging, all issued before the first is used.
     constexpr int TR = (NT + T3_G - 1) / T3_G;   // T rows copied per lane group: ta <= TR * G
     struct Stage {
@@ -127,14 +119,11 @@ __global__ void __launch_bounds__(NT, 5) ttmc3_mfma_kernel(Ttmc3Args a, const Ti
         s.ps = a.pos2[t.b0 + min(tid, nb)];
         s.ci = a.crd1[t.b0 + min(tid, nb - 1)];
     };
-    TileRec t = tiles[first];   // a launched workgroup has at least one tile
+    const TileRec t = tiles[tile];
     Stage st;
-    issue(t, first, st);
+    issue(t, tile, st);
 
-    for (int tile = first; tile < lastp1; ++tile) {
-    const TileRec tn = tiles[min(tile + 1, lastp1 - 1)];
     const bool in_f = (t.flags & 4) != 0, out_f = (t.flags & 8) != 0;
-    if (tile == first && in_f) chain_shared = true;
     const int nchild = t.n1 - t.n0;
     const int na = t.na, nb = t.nb;
     const int q = leaf_chunk<U>(nchild, T3_G);   // nonzeros per lane group, multiple of U
@@ -183,11 +172,6 @@ __global__ void __launch_bounds__(NT, 5) ttmc3_mfma_kernel(Ttmc3Args a, const Ti
         if (tid < nb) crdb_s[tid] = ci;
     }
     __syncthreads();
-
-    // ---- consumer kernel: the next tile's reads go out now and land while this tile is worked on
-    // (the fused kernel has no registers to spare for that: it measured slower with spills) ----
-    Stage sn;
-    if (!FUSED && tile + 1 < lastp1) issue(tn, tile + 1, sn);
 
     // ---- walk (leaves -> T rows in LDS), combine ----
     if (FUSED) {
@@ -256,48 +240,31 @@ __global__ void __launch_bounds__(NT, 5) ttmc3_mfma_kernel(Ttmc3Args a, const Ti
 
     // ---- combine ----
     if (wave == 0) {
-        auto emit = [&](const t3_floatx4 &v, int ls, bool atomic) {
-            float *dst = a.A + (int64_t)uni(crdb_s[ls]) * 256 + lane * 4;
-            if (!atomic) {
-                *reinterpret_cast<t3_floatx4 *>(dst) = v;
-            } else if (DET) {
-                // deterministic: this tile's piece of the row goes to its slot (a tile whose only
-                // slice continues on both sides has one piece, numbered as its first)
+        auto emit = [&](const t3_floatx4 &v, int ls, bool shared) {
+            if (!shared) {
+                *reinterpret_cast<t3_floatx4 *>(a.A + (int64_t)uni(crdb_s[ls]) * 256 + lane * 4) = v;
+            } else {
+                // this tile's piece of the row goes to its slot (a tile whose only slice continues on both
+                // sides has one piece, numbered as its first)
                 const int slot = (ls == 0 && in_f) ? t.pad[0] : t.pad[1];
                 *reinterpret_cast<t3_floatx4 *>(a.partials + (int64_t)slot * 256 + lane * 4) = v;
-            } else {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) atomic_add(dst + r, v[r]);
             }
         };
-        t3_floatx4 acc = carry;   // zero unless a slice continues from the previous tile of the run
-        if (!in_f) acc = t3_floatx4{0.f, 0.f, 0.f, 0.f};
+        t3_floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int w = 0; w < T3_WAVES; ++w) {
             const int hl = uni(meta_s[4 * w]), he = uni(meta_s[4 * w + 1]), tl = uni(meta_s[4 * w + 2]);
             if (hl >= 0) {
                 acc += *reinterpret_cast<const t3_floatx4 *>(part_s + (2 * w) * 256 + lane * 4);
                 if (he) {
-                    const bool incoming = hl == 0 && in_f;
-                    emit(acc, hl, incoming && chain_shared);
-                    if (incoming) chain_shared = false;
+                    emit(acc, hl, hl == 0 && in_f);
                     acc = t3_floatx4{0.f, 0.f, 0.f, 0.f};
                 }
             }
             if (tl >= 0) acc = *reinterpret_cast<const t3_floatx4 *>(part_s + (2 * w + 1) * 256 + lane * 4);
         }
-        if (out_f) {
-            if (tile + 1 == lastp1) emit(acc, nb - 1, true);   // continues in another workgroup's run
-            else carry = acc;
-        }
+        if (out_f) emit(acc, nb - 1, true);
     }
-    __syncthreads();
-    if (tile + 1 < lastp1) {
-        if (FUSED) issue(tn, tile + 1, sn);
-        t = tn;
-        st = sn;
-    }
-    }  // tiles of the run
 }
 
 WalkShape ttmc3_mfma_walk_shape()
@@ -314,18 +281,6 @@ size_t ttmc3_mfma_lds_bytes(const sc_plan *p) { return ttmc3_lds_bytes(p->caps.t
 bool ttmc3_mfma_caps_ok(const sc_plan *p)
 {
     return p->caps.tn <= T3_MAXR * NT && p->caps.ta <= NT && p->caps.tb + 1 <= NT && p->caps.tb >= 1;
-}
-
-// Tiles per workgroup: four runs per resident workgroup slot (shorter runs even out the tiles' different costs); a
-// deterministic schedule takes one tile per workgroup, so that the pieces are the ones the plan numbered.
-int ttmc3_mfma_run(const sc_plan *p, bool one_tile_per_workgroup)
-{
-    const int ntiles = (int)p->tiles.size();
-    if (ntiles == 0 || one_tile_per_workgroup) return 1;
-    const int fit = lds_workgroups_per_cu(ttmc3_lds_bytes(p->caps.tn, p->caps.ta, p->caps.tb), p->lds_per_cu);
-    const int per_cu = p->tune.per_cu > 0 ? std::min(p->tune.per_cu, 64) : 4 * fit;
-    const int want = std::min(ntiles, p->n_cu * per_cu);
-    return (ntiles + want - 1) / want;
 }
 
 sc_status launch_ttmc3_mfma(const sc_plan *p, Launcher &ln, const sc_csf_view *sp, const sc_dense_view *fac, const void *T, void *out,
@@ -352,25 +307,11 @@ sc_status launch_ttmc3_mfma(const sc_plan *p, Launcher &ln, const sc_csf_view *s
     a.T = static_cast<const float *>(T);
     a.A = static_cast<float *>(out);
     a.tn = p->caps.tn; a.ta = p->caps.ta; a.tb = p->caps.tb;
-    // persistent launch over contiguous runs of tiles (the tile table of such a plan is in tensor order)
     const size_t lds = ttmc3_lds_bytes(a.tn, a.ta, a.tb);
     a.partials = static_cast<float *>(partials);
-    a.ntiles = ntiles;
-    a.run = ttmc3_mfma_run(p, partials != nullptr);
-    const int blocks = (ntiles + a.run - 1) / a.run;
-    if (T == nullptr) {
-        ln.begin("ttmc3_fused_mfma");
-        if (partials)
-            ttmc3_mfma_kernel<true, true><<<blocks, NT, lds, ln.stream>>>(a, p->d_tiles);
-        else
-            ttmc3_mfma_kernel<true, false><<<blocks, NT, lds, ln.stream>>>(a, p->d_tiles);
-    } else {
-        ln.begin("ttmc3_consume_mfma");
-        if (partials)
-            ttmc3_mfma_kernel<false, true><<<blocks, NT, lds, ln.stream>>>(a, p->d_tiles);
-        else
-            ttmc3_mfma_kernel<false, false><<<blocks, NT, lds, ln.stream>>>(a, p->d_tiles);
-    }
+    ln.begin(T ? "ttmc3_consume_mfma" : "ttmc3_fused_mfma");
+    if (T) ttmc3_mfma_kernel<false><<<ntiles, NT, lds, ln.stream>>>(a, p->d_tiles);
+    else ttmc3_mfma_kernel<true><<<ntiles, NT, lds, ln.stream>>>(a, p->d_tiles);
     ln.end();
     return ln.status;
 }

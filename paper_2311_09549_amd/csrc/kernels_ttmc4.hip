@@ -1,6 +1,7 @@
 // Order-4 TTM chain on matrix cores, fp32, M = N = 8, L <= 16; MODE 0 is the FUSED schedule in one
 // kernel, MODE 1 and 2 are the second and third kernel of the FISSIONED schedule (T1 rows read from
-// the workspace and T2 rows written to it; T2 rows read from the workspace):
+// the workspace and T2 rows written to it; T2 rows read from the workspace, deterministic schedules only: the others run
+// that kernel as a slice product, kernels_slice.hip):
 //     A(i,l,m,n) = sum_{j,k,p} B(i,j,k,p) * C(j,l) * D(k,m) * E(p,n)
 // under the two-level nest obtained by applying the split-and-fuse step of Section 4.2 twice
 // (the shape of the second schedule of Table 2, kernel 5):
@@ -454,7 +455,7 @@ bool ttmc4_mfma_caps_ok(const sc_plan *p)
 
 // Tiles per workgroup.  Several runs per resident workgroup slot: shorter runs even out the tiles' different costs,
 // longer ones save row updates; six per slot measured best for the fused kernel (24 per compute unit), 32 per compute
-// unit for the two kernels of the FISSIONED schedule.  A deterministic schedule takes one tile per workgroup, so that
+// unit for the second kernel of the FISSIONED schedule.  A deterministic schedule takes one tile per workgroup, so that
 // the pieces are the ones the plan numbered.
 int ttmc4_mfma_run(const sc_plan *p, int mode, bool one_tile_per_workgroup)
 {
@@ -497,6 +498,7 @@ sc_status launch_ttmc4_mfma(const sc_plan *p, Launcher &ln, const sc_csf_view *s
     a.partials = static_cast<float *>(partials);
     a.slot_b = p->d_slot_b;
     if (partials && mode == 1 && !p->d_slot_b) return SC_ERR_SCHED_UNSUPPORTED;
+    if (!partials && mode == 2) return SC_ERR_SCHED_UNSUPPORTED;   // the slice products of kernels_slice.hip run it
     a.ntiles = ntiles;
     a.run = ttmc4_mfma_run(p, mode, partials != nullptr);
     const int blocks = (ntiles + a.run - 1) / a.run;
@@ -514,10 +516,7 @@ sc_status launch_ttmc4_mfma(const sc_plan *p, Launcher &ln, const sc_csf_view *s
             ttmc4_mfma_kernel<1, false><<<blocks, NT, lds, ln.stream>>>(a, p->d_tiles);
     } else {
         ln.begin("ttmc4_consume_mfma");
-        if (partials)
-            ttmc4_mfma_kernel<2, true><<<blocks, NT, lds, ln.stream>>>(a, p->d_tiles);
-        else
-            ttmc4_mfma_kernel<2, false><<<blocks, NT, lds, ln.stream>>>(a, p->d_tiles);
+        ttmc4_mfma_kernel<2, true><<<blocks, NT, lds, ln.stream>>>(a, p->d_tiles);
     }
     ln.end();
     return ln.status;

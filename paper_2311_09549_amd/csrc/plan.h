@@ -115,6 +115,41 @@ __host__ __device__ inline int walk_chunk(int n, int groups, int u)
     return q > u ? q : u;
 }
 
+// Tables of the slice products (kernels_slice.hip): the children of every slice in groups of four, a group's work in steps, the
+// steps in chunks of at most 64 that hold whole groups, the chunks cut into runs of equal work, one run per wavefront (or pair, or
+// four of them).
+constexpr int kSlicePiece = 16;   // leaves per piece of a fiber at most
+
+struct SliceChunk {
+    int32_t step0, nsteps;     // its steps
+    int32_t leaf0, nleaves;    // from the leaves: the (contiguous) leaves they hold
+    int32_t group0, ngroups;   // from the leaves: their groups
+    int32_t slice0, pad;       // slice of the first step
+    uint64_t gend, send;       // bit n: step n is the last of its group / of its slice
+};
+static_assert(sizeof(SliceChunk) == 48, "SliceChunk layout");
+
+struct SliceRun {
+    int32_t chunk0, step;   // first chunk, and the run's first step in it (a multiple of 8)
+    int32_t flags;          // bit 0: the slice of that step began in an earlier run
+    int32_t pad;
+};
+
+// 16-wide tiles of l and m per wavefront, wavefronts over l and over m (lt = 0: ranks the kernel does not take)
+struct SliceShape {
+    int32_t lt = 0, mt = 0, wl = 1, wm = 1;
+};
+
+struct SliceTables {
+    int32_t nruns = 0;
+    SliceRun *d_runs = nullptr;       // nruns + 1
+    SliceChunk *d_chunks = nullptr;
+    uint32_t *d_leaf = nullptr;       // from the leaves: 4 per step, last coordinate of the leaf of each child of the group
+    uint32_t *d_at = nullptr;         // ... a byte for each of these: the leaf's place in the chunk (255: none, unless the chunk has 256)
+    int32_t *d_gj = nullptr;          // ... 4 per group: coordinate of the child
+    int32_t *d_first = nullptr;       // from rows of T: first child of every step and the child count
+};
+
 struct Intermediate {
     std::string name;   // e.g. "T(i,j,m)"
     size_t offset = 0;  // byte offset inside the workspace (FISSIONED only)
@@ -164,6 +199,7 @@ struct sc_plan {
     std::vector<int32_t> slot_b;
     int32_t *d_slot_b = nullptr;   // plan-owned device copy, in the order of the device tile table
     sck::WalkTables walk;          // plan-owned device tables of the segmented walks (kernels that use them)
+    sck::SliceTables slice;        // plan-owned device tables of the slice products
     double model_flops = 0, model_bytes = 0;
     std::string text;  // description
 
@@ -223,8 +259,11 @@ bool plan_wants_tensor_order(const sc_plan *plan);
 // atomically, so only those rows have to start from zero.  The launchers use the same number.
 int plan_output_run(const sc_plan *plan);
 
-// True for the FUSED order-3 chains that run the matrix-core kernel for rank pairs beyond 16 x 16 (kernels_ttmc3w.hip).
-bool plan_uses_wide_ttmc3(const sc_plan *plan);
+// What the plan's slice products (kernels_slice.hip) start from: nothing (the plan has none), the leaves (leaves per piece
+// of a fiber at most), or rows of T.
+enum SliceSource { SLICE_NONE, SLICE_LEAVES, SLICE_ROWS };
+SliceSource plan_slice_source(const sc_plan *plan, int *piece);
+SliceShape slice_shape(int64_t L, int64_t W, bool linear);
 
 // True when the kernels of the plan can run without floating-point atomics (FUSED schedules of
 // the kernels that emit one piece per tile and shared row).

@@ -141,3 +141,49 @@ def test_core_tensor_reduction(oracle, dtype, L, MN, rows):
     for n in rows:
         cfg, data = _problem("ttmc_all", (n, 41, 97), [(i, 1 + i % 3) for i in range(0, n, 1 + n // 300)], (L,) + MN, dtype)
         _check(oracle, cfg, data, "fused")
+
+
+# ---- slice products: steps, chunks of 64 steps, runs, sums over the runs of a workgroup ----
+def _fibers(shape, seed=0):
+    """shape: per slice a list of fiber lengths; every fiber's entries start at a drawn place of the last mode."""
+    rng = np.random.default_rng(seed)
+    J, K = max(len(f) for f in shape) + 3, max(max(f) for f in shape if f) + 5
+    i, j, k = [], [], []
+    for s, lens in enumerate(shape):
+        for f, n in zip(np.sort(rng.choice(J, size=len(lens), replace=False)), lens):
+            i.append(np.full(n, s)), j.append(np.full(n, f)), k.append(np.arange(n) + rng.integers(0, K - n + 1))
+    coords = [np.concatenate(x).astype(np.int32) for x in (i, j, k)]
+    return (len(shape) + 1, J, K), coords, rng
+
+
+SHAPES = {
+    "whole_chunks": [[16] * 64, [16] * 16, [16] * 15, [1] * 256, [4] * 64],   # 256 leaves in a chunk: no place is free for "none"
+    "short": [[1]] * 70 + [[1, 1]] * 5 + [[], [3, 1, 1, 2, 1]] + [[1] * 5] * 9,
+    "long_fibers": [[700, 1, 33, 17], [15, 16, 17], [2048]],
+    "heavy": [[2, 1], [1, 2, 3, 1] * 1500, [1]],   # one slice through many runs and workgroups
+}
+
+
+@pytest.mark.parametrize("shape", sorted(SHAPES))
+@pytest.mark.parametrize("ranks,classes", [((16, 16), "ful"), ((8, 8), "fu"), ((64, 32), "fu"), ((16, 128), "fu"), ((128, 16), "u"), ((64, 64), "fu"), ((128, 64), "u"),
+                                           ((128, 128), "fu"), ((4, 4), "l"), ((20, 36), "l"), ((72, 12), "l"), ((3, 100), "l"), ((100, 124), "l")])
+def test_slice_products(oracle, shape, ranks, classes):
+    dims, coords, rng = _fibers(SHAPES[shape])
+    cfg = dict(kind="ttmc3", dims=dims, nnz=coords[0].size, ranks=ranks, dtype="f32", expr=synth.KINDS["ttmc3"][0])
+    factors = [rng.standard_normal(s).astype(np.float32) for s in synth.factor_shapes(cfg)]
+    data = dict(coords=coords, vals=rng.uniform(-1, 1, coords[0].size).astype(np.float32), factors=factors)
+    for which in ("fused", "fissioned", "linear"):
+        if {"fused": "f", "fissioned": "u", "linear": "l"}[which] not in classes:
+            continue
+        for leaves in (0, 32):   # the built-in runs, and runs of eight steps
+            sc.tuning_set("tile_leaves", leaves)
+            try:
+                _check(oracle, cfg, data, which)
+            finally:
+                sc.tuning_set("tile_leaves", 0)
+
+
+def test_slice_products_stored_past_the_caches(oracle):
+    """An output above the size from which rows are stored with the non-temporal hint."""
+    cfg, data = _problem("ttmc3", (9000, 41, 97), [(i, 1 + i % 7) for i in range(0, 9000, 5)], (64, 64))
+    _check(oracle, cfg, data, "fused")
