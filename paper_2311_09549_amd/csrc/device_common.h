@@ -33,6 +33,25 @@ __device__ __forceinline__ void atomic_add(T *p, T v)
     atomicAdd(p, v);
 }
 
+// Adds a row held by a group of LG lanes, VEC adjacent elements per lane (lane `li` of the group those from li * VEC), to `row`.  Each
+// instruction adds LG adjacent elements: with a lane's own elements in turn every cache line of the row is visited VEC
+// times, and the visits of the tiles of a heavy slice queue on it one after the other.
+template <typename T, int VEC, int LG>
+__device__ __forceinline__ void group_atomic_add(T *row, const T (&v)[VEC], int li)
+{
+#pragma unroll
+    for (int x = 0; x < VEC; ++x) {
+        const int e = x * LG + li;   // held by lane e / VEC of the group
+        T o = T(0);
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) {
+            const T w = __shfl(v[i], e / VEC, LG);
+            o = e % VEC == i ? w : o;
+        }
+        atomic_add(row + e, o);
+    }
+}
+
 // Largest lp in [0, np) with bnd[lp] <= x  (bnd[0] <= x < bnd[np] assumed).
 __device__ __forceinline__ int find_segment(const int *bnd, int np, int x)
 {

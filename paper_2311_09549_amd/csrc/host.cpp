@@ -1751,6 +1751,7 @@ static sc_status plan_create_impl(sc_plan **out, const char *expr, const sc_csf_
                      : default_caps(p->kind, p->dtype, p->sched, p->fcols);
     if (p->caps.tn <= 0) return SC_ERR_SCHED_UNSUPPORTED;  // no kernel instantiated for these ranks
     const Tuning &tu = p->tune;
+    if (!linear) p->caps.tn = plan_tile_leaves(p);
     if (tu.tn) p->caps.tn = tu.tn;
     if (tu.ta) p->caps.ta = tu.ta;
     if (tu.tb) p->caps.tb = tu.tb;

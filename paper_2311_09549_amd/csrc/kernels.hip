@@ -892,6 +892,21 @@ TileCaps default_caps(Kind kind, sc_dtype dtype, sc_sched_kind sched, const int6
     return c;
 }
 
+int32_t plan_tile_leaves(const sc_plan *p)
+{
+    const int e = p->dtype == SC_F64 ? 8 : 4;
+    // Few entries: tiles small enough for three per compute unit, where the kernels' time falls with the tile's (fp64 sampled product at
+    // rank 64, 20,000 entries: 50 us in tiles of 1024, 16 in tiles of 64; fp64 MTTKRP at rank 64, 100,000 entries: 25 and 16; fp64 chain at
+    // 16 x 16, 5,000 entries: 23 and 15).  Deterministic plans add the pieces of rows that span tiles in two more launches: small tiles
+    // make such rows where large ones had none, so the smallest plans and the FISSIONED ones stay with the large tiles.
+    const bool fused = p->sched == SC_SCHED_FUSED;
+    const bool takes = p->kind == K_SDDMM_SPMM ? !p->deterministic || p->nnz >= 32768
+                       : p->kind == K_MTTKRP3  ? fused && (!p->deterministic || (p->nnz >= 32768 && p->fcols[0] * e >= 128))
+                                               : p->kind == K_TTMC3 && p->dtype == SC_F64 && fused && p->out_row_elems * e <= 2048;
+    const int64_t few = std::max<int64_t>(64, (p->nnz / (3 * p->n_cu) + 63) / 64 * 64);
+    return takes && 2 * few <= p->caps.tn ? (int32_t)few : p->caps.tn;
+}
+
 bool plan_supports_deterministic(const sc_plan *p)
 {
     if (p->kind == K_SDDMM_SPMM) return true;   // both schedules: the sampled values have one writer each

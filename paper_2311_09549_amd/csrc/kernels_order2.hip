@@ -163,8 +163,7 @@ __device__ __forceinline__ void one_row_tile(const Order2Args &a, const TileRec 
     } else if (a.partials) {   // the tile's one piece, numbered as its first row's if that row began in an earlier tile
         *reinterpret_cast<P *>(static_cast<T *>(a.partials) + (int64_t)((t.flags & 1) ? t.pad[0] : t.pad[1]) * W + tid * VEC) = sum;
     } else {
-#pragma unroll
-        for (int k = 0; k < VEC; ++k) atomic_add(dst + k, sum.v[k]);
+        group_atomic_add<T, VEC, LG>(static_cast<T *>(a.A) + (int64_t)i * W, sum.v, tid);
     }
 }
 
@@ -277,8 +276,7 @@ __global__ void __launch_bounds__(NT) sddmm_spmm_kernel(Order2Args a)
             const int slot = (lr == 0 && (t.flags & 1)) ? t.pad[0] : t.pad[1];
             *reinterpret_cast<P *>(static_cast<T *>(a.partials) + (int64_t)slot * W + li * VEC) = row;
         } else {
-#pragma unroll
-            for (int i = 0; i < VEC; ++i) atomic_add(dst + i, row.v[i]);
+            group_atomic_add<T, VEC, LG>(A + (int64_t)crda_s[lr] * W, row.v, li);
         }
     };
 

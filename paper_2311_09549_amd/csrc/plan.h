@@ -249,6 +249,9 @@ inline int lds_workgroups_per_cu(size_t lds, int64_t lds_per_cu = 160 * 1024)
 // Built-in tile caps for a contraction (host side; the kernels size their LDS from them).
 TileCaps default_caps(Kind kind, sc_dtype dtype, sc_sched_kind sched, const int64_t *fcols);
 
+// Leaves per tile of a plan whose caps are the built-in ones: fewer for small problems.
+int32_t plan_tile_leaves(const sc_plan *plan);
+
 // True when the plan's kernels walk contiguous runs of tiles and therefore want the device tile
 // table in tensor order rather than interleaved.
 bool plan_wants_tensor_order(const sc_plan *plan);

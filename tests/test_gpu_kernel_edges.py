@@ -187,3 +187,20 @@ def test_slice_products_stored_past_the_caches(oracle):
     """An output above the size from which rows are stored with the non-temporal hint."""
     cfg, data = _problem("ttmc3", (9000, 41, 97), [(i, 1 + i % 7) for i in range(0, 9000, 5)], (64, 64))
     _check(oracle, cfg, data, "fused")
+
+
+# ---- tiles of few leaves: small problems and wide gathered rows; rows shared by several tiles ----
+@pytest.mark.parametrize("deterministic", [False, True])
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("kind,dims,ranks,most", [("sddmm_spmm", (11, 4000), (16, 16), 64), ("sddmm_spmm", (11, 4000), (32, 32), 64), ("sddmm_spmm", (11, 4000), (64, 64), 64),
+                                                  ("sddmm_spmm", (11, 4000), (128, 128), 64), ("mttkrp3", (11, 41, 97), (8,), 64), ("mttkrp3", (11, 41, 97), (128,), 64),
+                                                  ("ttmc3", (11, 41, 97), (16, 16), 64), ("sddmm_spmm", (40, 40000), (64, 64), 192)])
+def test_small_tiles(oracle, kind, dims, ranks, most, dtype, deterministic):
+    lengths = LENGTHS if dims[0] == 11 else [(i, 30000 if i == 3 else 3000) for i in range(39)]
+    cfg, data = _problem(kind, dims, lengths, ranks, dtype)
+    con = _check(oracle, cfg, data, "fused", deterministic)
+    first = sc.plan_tile(con.plan, 0)
+    if not deterministic and not (kind == "ttmc3" and dtype == "f32"):   # the fp32 chain runs as slice products
+        assert first[1] - first[0] <= most
+    if kind == "sddmm_spmm":
+        _check(oracle, cfg, data, "fissioned", deterministic)
