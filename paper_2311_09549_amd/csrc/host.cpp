@@ -762,7 +762,7 @@ void build_slices(const sc_plan *p, SliceSource src, int piece, const HostCsf &h
     // Work of a step, a group, a slice and a chunk in vector-ALU issue slots of a wavefront: the gather and its arithmetic; the row of
     // C and the matrix products (8 slots each); the stores of the row; the staging.
     const int64_t L = p->fcols[0], W = p->kind == K_TTMC4 ? p->fcols[1] * p->fcols[2] : p->fcols[1];
-    const SliceShape sh = slice_shape(L, W, p->sched == SC_SCHED_LINEAR);
+    const SliceShape sh = slice_shape(L, W);
     const int64_t tiles = (int64_t)sh.lt * sh.mt;
     const double w_step = 6 + sh.mt, w_group = 6 + 8 * tiles, w_slice = 8 + 4 * tiles, w_chunk = 60;
     auto cost = [&](const SliceChunk &k) {

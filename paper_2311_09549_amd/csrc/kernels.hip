@@ -940,14 +940,14 @@ sc_status launch_fixup(const sc_plan *p, Launcher &ln, const FixLevel &lv, void 
 }
 
 // fp32 chains of order 3 in every class, and the last kernel of the FISSIONED order-4 chain at 8 x 8, unless the caller asks for a
-// reproducible sum.  Start and now, whole calls in us: 6 M entries at 64 x 32 383 and 214; 4 M at 128 x 128 (inside kernel 5) 1930 and 946;
+// reproducible sum.  Start and now, whole calls in us: 6 M entries at 64 x 32 383 and 234; 4 M at 128 x 128 (inside kernel 5) 1930 and 1060;
 // 1.5 M at 16 x 16 67 and 25, at 8 x 64 147 and 53; unfactored, 1.5 M at 12 x 20 79 and 41, at 4 x 4 45 and 28; 120,000 entries in 38,000
 // slices 23 to 1002 and 15 to 467.  Even at 20,000 entries up to 16 x 32 (launch latency).
 SliceSource plan_slice_source(const sc_plan *p, int *piece)
 {
     if (piece) *piece = kSlicePiece;
     if (p->dtype != SC_F32 || p->deterministic) return SLICE_NONE;
-    if (p->kind == K_TTMC3 && slice_shape(p->fcols[0], p->fcols[1], p->sched == SC_SCHED_LINEAR).lt) {
+    if (p->kind == K_TTMC3 && slice_shape(p->fcols[0], p->fcols[1]).lt) {
         if (p->sched == SC_SCHED_LINEAR && piece) *piece = 1;   // nothing is factored out: every stored entry is a piece
         return p->sched == SC_SCHED_FISSIONED ? SLICE_ROWS : SLICE_LEAVES;
     }

@@ -56,28 +56,21 @@ typedef float sl_floatx4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ int sl_uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
 // Steps per batch and wavefronts per SIMD by the number of 16 x 16 tiles.  One tile: 45.5 us with eight steps, 43 with four (4 M
-// leaves, 16 x 16); eight tiles: 221 us with four steps and four wavefronts, 203 with eight and three (6 M leaves, 64 x 32); sixteen: 957 us with
-// four steps and three wavefronts, 946 with eight and two where four wavefronts share a run (128 x 128), but 97 and 121 us where each has its
-// own (64 x 64, 1 M leaves in 1,800 slices).
-constexpr int slice_batch(int tiles, int per_run) { return tiles == 1 || (tiles == 16 && per_run < 4) ? 4 : 8; }
-constexpr int slice_occupancy(int tiles, int per_run, bool edge)
-{
-    return (tiles == 16 && per_run == 4 ? 2 : tiles >= 8 ? 3 : 4) - (edge ? 1 : 0);
-}
-
-// Two sets of sums (TWO in the kernel): up to four tiles, and eight in the EDGE instantiations, which run the unfactored nest.  Eight tiles of a
-// chain are no further from the exact sum without them than the tiled kernel they replaced was (2.9e-7 and 3.6e-7 at 64 x 32), and
-// 16 us of 234 faster; sixteen leave no registers for them.
-constexpr bool slice_two_sums(int tiles, bool edge) { return tiles <= 4 || (tiles == 8 && edge); }
+// leaves, 16 x 16); eight tiles: 234 us with eight steps and three wavefronts, 239 to 245 with four steps or two or four wavefronts (6 M
+// leaves, 64 x 32); sixteen: what two wavefronts have registers for.
+constexpr int slice_batch(int tiles) { return tiles == 1 || tiles == 16 ? 4 : 8; }
+constexpr int slice_occupancy(int tiles, bool edge) { return tiles == 16 ? 2 : (tiles == 8 ? 3 : 4) - (edge ? 1 : 0); }
 
 // runs: nruns + 1 records, chunks: one past the last.  Arguments of their own, so that the loop reads them through the scalar cache.
-// LT, MT: 16-wide tiles of l and m per wavefront; WL x WM wavefronts share a run; EDGE: L or W may be less than the tiles cover; all of the unfactored nest.
+// LT, MT: 16-wide tiles of l and m per wavefront; WL x WM wavefronts share a run; EDGE: L or W may be less than the tiles cover.
 template <int LT, int MT, int WL, int WM, int SRC, bool EDGE>
-__global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, WL * WM, EDGE)) slice_kernel(SliceArgs a, const SliceRun *__restrict__ runs,
+__global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, EDGE)) slice_kernel(SliceArgs a, const SliceRun *__restrict__ runs,
                                                                                       const SliceChunk *__restrict__ chunks)
 {
     constexpr int WPR = WL * WM;              // wavefronts per run
-    constexpr int U = slice_batch(LT * MT, WPR);   // steps per batch
+    constexpr int WAVES = NT / 64;
+    constexpr int RPB = WAVES / WPR;          // runs per workgroup
+    constexpr int U = slice_batch(LT * MT);   // steps per batch
     typedef float TVec __attribute__((ext_vector_type(MT)));
     typedef float CVec __attribute__((ext_vector_type(LT)));
     struct alignas(8) Rec { uint32_t off; float v; };
@@ -88,15 +81,15 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, WL * WM, EDGE)) s
         float swap[256];                  // the chunk's values while it is staged; a row on its way to atomic additions
     };
     union Lds {
-        Own own[NT / 64];
-        float sum[2][WPR < 4 ? 256 * LT * MT : 4];   // after the runs: sums on their way to another wavefront
+        Own own[WAVES];
+        float sum[2][RPB > 1 ? 256 * LT * MT : 4];   // after the runs: sums on their way to another wavefront
     };
     __shared__ Lds lds;
-    __shared__ int inside_s[NT / 64];
+    __shared__ int inside_s[WAVES];
 
     const int wave = sl_uni(threadIdx.x / 64), lane = threadIdx.x % 64;
     const int kk = lane / 16, col = lane % 16;
-    const int run = (int)blockIdx.x * (4 / WPR) + wave / WPR, sub = wave % WPR;
+    const int run = (int)blockIdx.x * RPB + wave / WPR, sub = wave % WPR;
     Rec *rec_s = lds.own[wave].rec;
     uint32_t *coff_s = lds.own[wave].coff;
     float *swap_s = lds.own[wave].swap;
@@ -151,11 +144,11 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, WL * WM, EDGE)) s
         }
     };
 
-    // Sums of up to SPAN steps, and of those: one chain of additions over a run of hundreds of steps in a heavy slice was up to 2.3 times
-    // further from the sum in double precision than the tile by tile sums it replaces.
-    constexpr bool TWO = slice_two_sums(LT * MT, EDGE);
+    // Sums of up to SPAN steps, and sums of those.  One chain of additions over a run, hundreds of steps long in a heavy slice, was up to 2.3
+    // times further from the sum in double precision than the tile by tile sums it replaces; so 64 x 64 values are
+    // shared by two wavefronts, though one would hold them once (64 x 32: 234 us, 218 with one set of sums).
     constexpr int SPAN = 16;
-    sl_floatx4 acc[MT][LT], tot[TWO ? MT : 1][TWO ? LT : 1];
+    sl_floatx4 acc[MT][LT], tot[MT][LT];
     auto clear = [&](auto &v) {
         for (auto &row : v)
             for (sl_floatx4 &e : row) e = sl_floatx4{0.f, 0.f, 0.f, 0.f};
@@ -285,10 +278,8 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, WL * WM, EDGE)) s
                     }
                     if (sb >> u & 1) {
                         const int row = __builtin_amdgcn_readlane(rowv, sl - sl_base);
-                        if constexpr (TWO) {
-                            gather_sums(acc, tot);
-                            clear(tot);
-                        }
+                        gather_sums(acc, tot);
+                        clear(tot);
                         if (open) emit(row, std::integral_constant<int, ADD>{});
                         else if (a.stream) emit(row, std::integral_constant<int, STREAM>{});
                         else emit(row, std::integral_constant<int, STORE>{});
@@ -298,11 +289,9 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, WL * WM, EDGE)) s
                     }
                 }
             }
-            if constexpr (TWO) {
-                if ((b + U) % SPAN == 0) {
-                    gather_sums(tot, acc);
-                    clear(acc);
-                }
+            if ((b + U) % SPAN == 0) {
+                gather_sums(tot, acc);
+                clear(acc);
             }
         }
         if (c + 1 == c_end) {
@@ -310,13 +299,12 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, WL * WM, EDGE)) s
             if (SRC == SRC_LEAVES && !(gm >> (to - 1) & 1)) multiply(t, *reinterpret_cast<const CVec *>(Cb + (coff_s[4 * (to - 1) + kk] + c_lane)));
             goes_on = !(sm >> (to - 1) & 1);
             last_row = __builtin_amdgcn_readlane(rowv, min(sl - sl_base, 63));
-            if constexpr (TWO) gather_sums(acc, tot);
+            gather_sums(acc, tot);
         }
     }
     // What is left of a slice that goes on in the next run.  Runs that lie inside one slice are added up inside the workgroup first,
     // in two rounds (0 to 1 and 2 to 3, then the pair 0, 1 to the last that follows it); the rest goes to the slice's row atomically.
-    if constexpr (WPR < 4) {
-        constexpr int RPB = 4 / WPR;
+    if constexpr (RPB > 1) {
         const int rw = wave / WPR;
         const bool inside = goes_on && open && sl == slice0;
         if (lane == 0) inside_s[wave] = (goes_on ? 1 : 0) | (inside ? 2 : 0);
@@ -356,54 +344,49 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, WL * WM, EDGE)) s
 }
 
 template <int SRC>
-void dispatch_slice(const SliceArgs &a, const SliceTables &st, bool linear, hipStream_t stream)
+void dispatch_slice(const SliceArgs &a, const SliceTables &st, hipStream_t stream)
 {
     auto go = [&](auto lt, auto mt, auto wl, auto wm) {
         constexpr int LT = decltype(lt)::value, MT = decltype(mt)::value, WL = decltype(wl)::value, WM = decltype(wm)::value;
-        constexpr int RPB = 4 / (WL * WM);
+        constexpr int RPB = NT / 64 / (WL * WM);
         const int blocks = (a.nruns + RPB - 1) / RPB;
-        if (linear || a.L != 16 * LT * WL || a.W != 16 * MT * WM) slice_kernel<LT, MT, WL, WM, SRC, true><<<blocks, NT, 0, stream>>>(a, st.d_runs, st.d_chunks);
+        if (a.L != 16 * LT * WL || a.W != 16 * MT * WM) slice_kernel<LT, MT, WL, WM, SRC, true><<<blocks, NT, 0, stream>>>(a, st.d_runs, st.d_chunks);
         else slice_kernel<LT, MT, WL, WM, SRC, false><<<blocks, NT, 0, stream>>>(a, st.d_runs, st.d_chunks);
     };
-    const SliceShape sh = slice_shape(a.L, a.W, linear);
+    const SliceShape sh = slice_shape(a.L, a.W);
     using I1 = std::integral_constant<int, 1>;
     using I2 = std::integral_constant<int, 2>;
     using I4 = std::integral_constant<int, 4>;
     auto over_m = [&](auto lt, auto wl) {
-        constexpr int LT = decltype(lt)::value, WL = decltype(wl)::value;
-        if constexpr (SRC == SRC_LEAVES && LT == 4) {
-            if (sh.mt == 2 && sh.wm == 2) return go(lt, I2{}, wl, I2{});   // the unfactored nest
-            if constexpr (WL == 1) {
-                if (sh.wm == 4) return go(lt, I2{}, wl, I4{});
-            }
+        if (sh.mt == 1) go(lt, I1{}, wl, I1{});
+        else if constexpr (decltype(lt)::value == 4) {
+            if (sh.wm == 1) go(lt, I2{}, wl, I1{});
+            else if (sh.mt == 2 && sh.wm == 2) go(lt, I2{}, wl, I2{});
+            else if constexpr (decltype(wl)::value == 1) go(lt, I2{}, wl, I4{});
+            else go(lt, I4{}, wl, I2{});
+        } else {
+            if (sh.mt == 2) go(lt, I2{}, wl, I1{});
+            else if (sh.wm == 1) go(lt, I4{}, wl, I1{});
+            else go(lt, I4{}, wl, I2{});
         }
-        if (sh.wm == 2) go(lt, I4{}, wl, I2{});
-        else if (sh.mt == 1) go(lt, I1{}, wl, I1{});
-        else if (sh.mt == 2) go(lt, I2{}, wl, I1{});
-        else go(lt, I4{}, wl, I1{});
     };
-    if (sh.wl == 2) over_m(I4{}, I2{});
-    else if (sh.lt == 1) over_m(I1{}, I1{});
+    if (sh.lt == 1) over_m(I1{}, I1{});
     else if (sh.lt == 2) over_m(I2{}, I1{});
-    else over_m(I4{}, I1{});
+    else if (sh.wl == 1) over_m(I4{}, I1{});
+    else over_m(I4{}, I2{});
 }
 
 }  // namespace
 
-SliceShape slice_shape(int64_t L, int64_t W, bool linear)
+SliceShape slice_shape(int64_t L, int64_t W)
 {
     SliceShape s;
     if (L < 1 || L > 128 || W < 4 || W > 128 || W % 4 || (L > 16 && L % 4)) return s;   // the 16-byte (8-byte) pieces a lane reads and stores
     s.lt = L <= 16 ? 1 : L <= 32 ? 2 : 4;
-    s.mt = W <= 16 ? 1 : W <= 32 ? 2 : 4;
+    s.mt = W <= 16 ? 1 : W <= 32 || s.lt == 4 ? 2 : 4;   // eight tiles per wavefront at most
     s.wl = L > 64 ? 2 : 1;
-    s.wm = W > 64 ? 2 : 1;
-    if (linear && !slice_two_sums(s.lt * s.mt, true)) {
-        // the unfactored nest adds a product per stored entry, with nothing summed up ahead of it: two sets of sums always
-        s.mt = 2;
-        s.wm *= 2;
-        if (s.wl * s.wm > 4) s.lt = 0;
-    }
+    if (L > 64 && W > 64) s.mt = 4;   // sixteen, since four wavefronts make a workgroup (in workgroups of eight 128 x 128 took 1390 us for 1060)
+    s.wm = W <= 16 * s.mt ? 1 : W <= 32 * s.mt ? 2 : 4;
     return s;
 }
 
@@ -431,8 +414,8 @@ sc_status launch_slice(const sc_plan *p, Launcher &ln, const sc_csf_view *sp, co
     a.W = (int32_t)W;
     a.stream = p->out_elems * 4 > kStreamBytes;
     ln.begin(name);
-    if (T) dispatch_slice<SRC_ROWS>(a, st, false, ln.stream);
-    else dispatch_slice<SRC_LEAVES>(a, st, p->sched == SC_SCHED_LINEAR, ln.stream);
+    if (T) dispatch_slice<SRC_ROWS>(a, st, ln.stream);
+    else dispatch_slice<SRC_LEAVES>(a, st, ln.stream);
     ln.end();
     return ln.status;
 }

@@ -116,8 +116,8 @@ __host__ __device__ inline int walk_chunk(int n, int groups, int u)
 }
 
 // Tables of the slice products (kernels_slice.hip): the children of every slice in groups of four, a group's work in steps, the
-// steps in chunks of at most 64 that hold whole groups, the chunks cut into runs of equal work, one run per wavefront (or pair, or
-// four of them).
+// steps in chunks of at most 64 that hold whole groups, the chunks cut into runs of equal work, one run per wavefront (or per two
+// or four of them).
 constexpr int kSlicePiece = 16;   // leaves per piece of a fiber at most
 
 struct SliceChunk {
@@ -266,7 +266,7 @@ int plan_output_run(const sc_plan *plan);
 // of a fiber at most), or rows of T.
 enum SliceSource { SLICE_NONE, SLICE_LEAVES, SLICE_ROWS };
 SliceSource plan_slice_source(const sc_plan *plan, int *piece);
-SliceShape slice_shape(int64_t L, int64_t W, bool linear);
+SliceShape slice_shape(int64_t L, int64_t W);
 
 // True when the kernels of the plan can run without floating-point atomics (FUSED schedules of
 // the kernels that emit one piece per tile and shared row).
