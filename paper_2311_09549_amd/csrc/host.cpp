@@ -888,7 +888,7 @@ void list_rows_to_zero(sc_plan *p, const HostCsf &h, const std::vector<int32_t> 
             last_listed = row;
         }
     }
-    p->zero_selective = (int64_t)p->zero_rows.size() * 2 <= rows;
+    p->zero_selective = (int64_t)p->zero_rows.size() * 4 <= rows * 3;
     if (!p->zero_selective) {
         p->zero_rows.clear();
         p->zero_rows.shrink_to_fit();
