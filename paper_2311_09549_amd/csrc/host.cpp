@@ -849,6 +849,7 @@ TopLevel top_level(int order, const TileRec &t)
     return {(t.flags & in_bit) != 0, (t.flags & out_bit) != 0, o4 ? t.c0 : o2 ? t.a0 : t.b0, o4 ? t.nc : o2 ? t.na : t.nb};
 }
 
+// `cut_rows`: slice products only, the output rows of the slices that a run's end cuts.
 // Lists the output rows that the kernels do not overwrite completely and that therefore have
 // to be zero before they run: rows of empty slices and, unless the schedule is deterministic
 // (then a last kernel writes them), rows whose slice spans several tiles and is accumulated
@@ -857,7 +858,7 @@ void list_rows_to_zero(sc_plan *p, const HostCsf &h, const std::vector<int32_t> 
 {
     p->zero_rows.clear();
     p->zero_selective = false;
-    // The unfactored nest: the whole output starts at zero.  linear_kernel adds every row atomically; linear_tiled_kernel stores the rows
+    // The unfactored nest outside slice products: the whole output starts at zero.  linear_kernel adds every row atomically; linear_tiled_kernel stores the rows
     // of slices inside one tile whole, which are thus written twice.
     if (p->sched == SC_SCHED_LINEAR && !cut_rows) return;
     const int64_t rows = p->dims[0];

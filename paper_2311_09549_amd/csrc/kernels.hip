@@ -30,9 +30,9 @@ namespace sck {
 // Order-3 kernels:  T(f, x) = sum_{k' in fiber f} B * D(k, x)   then
 //   hadamard:  A(i, r)    += C(j, r) * T(f, r)                      (MTTKRP)
 //   outer:     A(i, l, m) += C(j, l) * T(f, m)                      (kernel 6 of Table 2)
-// The MTTKRP and the fp32 16 x 16 outer product have kernels of their own (below and in
-// kernels_ttmc3.hip); order3_kernel is the general outer-product kernel for every other rank
-// and for fp64:
+// The MTTKRP has kernels of its own (below), the fp32 outer product runs as slice products
+// (kernels_slice.hip) and, under a deterministic schedule at 16 x 16, in kernels_ttmc3.hip;
+// order3_kernel is the general outer-product kernel for fp64 and the other deterministic ranks:
 //   MODE 0: fused (T lives in LDS for the tile)      -- FUSED schedule
 //   MODE 2: consumer only, T read back from HBM      -- FISSIONED, second kernel (the first is
 //           the leaf traversal of kernels_traverse.hip)
@@ -62,8 +62,8 @@ __host__ __device__ constexpr size_t order3_lds_bytes(int W, int tn, int ta, int
     return leaf_walk_lds_bytes<T>(W, tn, ta, NT) + (size_t)(3 * ta + 8) * 4 + 64 + (crow_l ? (size_t)ta * (crow_l + 4) * 4 + 16 : 0);
 }
 
-// fp32 outer products whose ranks are multiples of the 16 x 16 MFMA tile (other than the 16 x 16 case, which has a
-// kernel of its own) run the consumer of order3_kernel on the matrix cores.
+// Deterministic fp32 outer products whose ranks are multiples of the 16 x 16 MFMA tile (other than the 16 x 16 case, which
+// has a kernel of its own) run the consumer of order3_kernel on the matrix cores.
 __host__ __device__ constexpr bool order3_mfma_ranks(int L, int W)
 {
     return W % 16 == 0 && (L == 16 || L == 32 || L == 64 || L == 128) && !(L == 16 && W == 16);
@@ -866,8 +866,7 @@ TileCaps default_caps(Kind kind, sc_dtype dtype, sc_sched_kind sched, const int6
             c.ta = (int32_t)std::max<int64_t>(32, std::min<int64_t>(512, (16 * 1024) / (w * e)));
             c.tb = c.ta;
             if (dtype == SC_F32 && order3_mfma_ranks((int)fcols[0], (int)w)) {
-                // matrix-core consumers (the kernel for rank pairs beyond 16 x 16, and the general kernel under a
-                // deterministic schedule): T rows and C rows of a tile share about 26 KB; 768 nonzeros and 112 fibers
+                // matrix-core consumer (the general kernel under a deterministic schedule): T rows and C rows of a tile share about 26 KB; 768 nonzeros and 112 fibers
                 // measured best on the uniform 11.5 M-nonzero case at 16 x 32
                 c.tn = 768;
                 c.ta = (int32_t)std::max<int64_t>(16, std::min<int64_t>(256, (26 * 1024) / ((w + 4 + fcols[0] + 4) * 4)));

@@ -7,7 +7,7 @@
 // Four children form a step group, the K = 4 of v_mfma_f32_16x16x4_f32: lanes 16 kk .. 16 kk + 15 hold the row of child kk.
 // Which l and m a tile's rows and columns stand for is free, so a lane reads MT adjacent values of a row of T (or of D) and LT
 // adjacent values of a row of C straight into operand registers: no row of T passes through LDS.  A wavefront owns a run of
-// steps and all (or a quarter, half) of the L x W output of the slice it is in; it shares nothing with its neighbours, so
+// steps and all (or a half, quarter) of the L x W output of the slice it is in; it shares nothing with its neighbours, so
 // there is no barrier, and wavefronts in different phases keep the gathers and the matrix cores busy together.
 //
 //   SRC_LEAVES  the plan lists for every step the leaf that each of the four fibers of the group contributes: its last coordinate

@@ -257,7 +257,7 @@ int32_t plan_tile_leaves(const sc_plan *plan);
 bool plan_wants_tensor_order(const sc_plan *plan);
 
 // Tiles per workgroup of the kernel that writes the plan's output rows when that kernel is persistent over contiguous
-// runs of tiles (the matrix-core kernels); 0 for the kernels that take one tile per workgroup.  Within a run a slice that
+// runs of tiles (the fused order-4 matrix-core kernel); 0 for the kernels that take one tile per workgroup.  Within a run a slice that
 // continues from tile to tile stays in registers and is stored once; only a slice that crosses a run's end is added
 // atomically, so only those rows have to start from zero.  The launchers use the same number.
 int plan_output_run(const sc_plan *plan);
