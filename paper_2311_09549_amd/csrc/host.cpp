@@ -678,18 +678,17 @@ void list_steps(SliceSource src, int piece, int cap, const HostCsf &h, int64_t s
                 for (int k = 0; k < w.n; k += 4) {
                     const int have = std::min(4, w.n - k), steps = sorted[k].len;
                     const size_t o = b.leaf.size();
-                    b.leaf.resize(o + 4 * (size_t)steps);
+                    b.leaf.resize(o + 4 * (size_t)steps, 0xffffffffu);
                     b.at.resize(b.at.size() + (size_t)steps, 0xffffffffu);
                     uint8_t *place = reinterpret_cast<uint8_t *>(b.at.data()) + o;
                     for (int q = 0; q < 4; ++q) {
                         const SlicePieces::Piece &pc = sorted[k + std::min(q, have - 1)];
-                        const int32_t len = q < have ? pc.len : 0, zl = pc.z + pc.len - 1;
+                        const int32_t len = q < have ? pc.len : 0;
                         for (int u = 0; u < len; ++u) {
                             b.leaf[o + 4 * (size_t)u + q] = (uint32_t)crd2[pc.z + u];
                             place[4 * u + q] = (uint8_t)(pc.z + u - c.leaf0);
                         }
-                        for (int u = len; u < steps; ++u) b.leaf[o + 4 * (size_t)u + q] = (uint32_t)crd2[zl];   // past the piece: its last row again, no value
-                        b.gj.push_back(pc.j);
+                        b.gj.push_back(q < have ? pc.j : -1);   // (and the leaves past a piece: no row)
                     }
                     nsteps += steps;
                     c.nsteps += steps;

@@ -46,6 +46,7 @@ struct SliceArgs {
     const float *vals;           // SRC_LEAVES
     const float *C, *D;          // D: SRC_LEAVES the factor of the last mode, SRC_ROWS the rows of T
     uint32_t rowC, rowD;         // bytes from row to row
+    uint32_t bytesC, bytesD;     // size of C; of D (SRC_ROWS: reach of the 32-bit offsets from a run's first child)
     float *A;
     int32_t L, W;
     int32_t stream;              // the output is stored past the L2s
@@ -54,6 +55,27 @@ struct SliceArgs {
 typedef float sl_floatx4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ int sl_uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
+
+// Rows are gathered through buffer descriptors: a read past the descriptor's end returns zero and touches no memory.  A place of a step that
+// no child takes has the coordinate kNoRow, whose byte offset lies past the end of every matrix (they are smaller than 2 GiB; the offset
+// is 2^32 less one row, and the lane's part of the row does not carry it over).  So it counts as 0 * 0: with some row that exists and
+// a zero factor, an infinity or a NaN in that row would reach outputs that do not refer to it.
+constexpr int kNoRow = -1;
+constexpr uint32_t kMostBytes = 0x80000000u;
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t sl_rows(const void *base, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);   // untyped, 32-bit
+}
+
+template <int N>
+__device__ __forceinline__ auto sl_gather(__amdgpu_buffer_rsrc_t rows, uint32_t off)
+{
+    typedef float Vec __attribute__((ext_vector_type(N)));
+    if constexpr (N == 1) return __builtin_bit_cast(Vec, __builtin_amdgcn_raw_buffer_load_b32(rows, off, 0, 0));
+    else if constexpr (N == 2) return __builtin_bit_cast(Vec, __builtin_amdgcn_raw_buffer_load_b64(rows, off, 0, 0));
+    else return __builtin_bit_cast(Vec, __builtin_amdgcn_raw_buffer_load_b128(rows, off, 0, 0));
+}
 
 // Steps per batch and wavefronts per SIMD by the number of 16 x 16 tiles.  One tile: 45.5 us with eight steps, 43 with four (4 M
 // leaves, 16 x 16); eight tiles: 234 us with eight steps and three wavefronts, 239 to 245 with four steps or two or four wavefronts (6 M
@@ -97,9 +119,9 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, EDGE)) slice_kern
     const int l0 = (sub / WM) * 16 * LT, m0 = (sub % WM) * 16 * MT;
     // first of the lane's values of l and m; lanes past a row read its end again and are not stored
     const int ll = l0 + LT * col, lm = m0 + MT * col;
-    // uniform bases and 32-bit byte offsets: one addition per gather
+    // 32-bit byte offsets: one addition per gather
     const uint32_t c_lane = 4 * (EDGE ? min(ll, L - LT) : ll), d_lane = 4 * (EDGE ? min(lm, W - MT) : lm);
-    const char *Cb = reinterpret_cast<const char *>(a.C), *Db = reinterpret_cast<const char *>(a.D);
+    const char *Db = reinterpret_cast<const char *>(a.D);
 
     // a wavefront past the last run has no steps
     const SliceRun r = runs[min(run, a.nruns)], r_end = runs[min(run + 1, a.nruns)];
@@ -111,9 +133,10 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, EDGE)) slice_kern
     bool open = (r.flags & 1) != 0;   // the slice began in an earlier run
     int fbase = 0;
     if (SRC == SRC_ROWS && r.chunk0 < c_end) {
-        fbase = a.first[ch.step0 + r.step];
+        fbase = sl_uni(a.first[ch.step0 + r.step]);
         Db += (int64_t)fbase * a.rowD;
     }
+    const __amdgpu_buffer_rsrc_t rowsC = sl_rows(a.C, a.bytesC), rowsD = sl_rows(Db, a.bytesD);
 
     // Global reads of a chunk's staging: lane n takes step n (those past the chunk repeat its last one) and the group that step belongs
     // to.  They are issued a chunk ahead and land while the one before is worked on.
@@ -140,7 +163,7 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, EDGE)) slice_kern
             s.j.x = a.crd2[s.f0];
             s.j.y = a.crd2[min(s.f0 + 1, s.f1 - 1)];
             s.j.z = a.crd2[min(s.f0 + 2, s.f1 - 1)];
-            s.j.w = a.crd2[s.f1 - 1];
+            s.j.w = a.crd2[min(s.f0 + 3, s.f1 - 1)];
         }
     };
 
@@ -211,8 +234,9 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, EDGE)) slice_kern
         const int from = c == r.chunk0 ? r.step : 0, to = c == r_end.chunk0 ? r_end.step : ch.nsteps;
         const int ns = ch.nsteps, sl_base = ch.slice0, rowv = st.row;
         const uint64_t gm = ch.gend, sm = ch.send;
-        // ---- stage: registers -> LDS; steps past the chunk count as zero ----
+        // ---- stage: registers -> LDS; steps past the chunk have no child ----
         const bool live = lane < ns;
+        auto row_at = [&](int x, uint32_t row) { return (uint32_t)(live ? x : kNoRow) * row; };
         if (SRC == SRC_LEAVES) {
             const int nl = ch.nleaves;
             __builtin_amdgcn_wave_barrier();
@@ -225,20 +249,19 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, EDGE)) slice_kern
             for (int q = 0; q < 4; ++q) v[q] = swap_s[st.at >> 8 * q & 255];
             uint4 *dst = reinterpret_cast<uint4 *>(rec_s + 4 * lane);
             auto word = [&](float x) { return live ? __builtin_bit_cast(uint32_t, x) : 0u; };
-            dst[0] = uint4{st.leaf.x * a.rowD, word(v[0]), st.leaf.y * a.rowD, word(v[1])};
-            dst[1] = uint4{st.leaf.z * a.rowD, word(v[2]), st.leaf.w * a.rowD, word(v[3])};
+            dst[0] = uint4{row_at(st.leaf.x, a.rowD), word(v[0]), row_at(st.leaf.y, a.rowD), word(v[1])};
+            dst[1] = uint4{row_at(st.leaf.z, a.rowD), word(v[2]), row_at(st.leaf.w, a.rowD), word(v[3])};
         } else {
             __builtin_amdgcn_wave_barrier();
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                Rec e;   // children past the step repeat its last row and count as zero
-                e.off = (uint32_t)(min(st.f0 + q, st.f1 - 1) - fbase) * a.rowD;   // (steps before the run's first are not read)
-                e.v = live && st.f0 + q < st.f1 ? 1.f : 0.f;
-                rec_s[4 * lane + q] = e;
-            }
+            for (int q = 0; q < 4; ++q)   // (steps before the run's first are not read)
+                rec_s[4 * lane + q].off = row_at(st.f0 + q < st.f1 ? st.f0 + q - fbase : kNoRow, a.rowD);
+            if (st.f0 + 1 >= st.f1) st.j.y = kNoRow;
+            if (st.f0 + 2 >= st.f1) st.j.z = kNoRow;
+            if (st.f0 + 3 >= st.f1) st.j.w = kNoRow;
         }
         reinterpret_cast<uint4 *>(coff_s)[lane] =
-            uint4{(uint32_t)st.j.x * a.rowC, (uint32_t)st.j.y * a.rowC, (uint32_t)st.j.z * a.rowC, (uint32_t)st.j.w * a.rowC};
+            uint4{row_at(st.j.x, a.rowC), row_at(st.j.y, a.rowC), row_at(st.j.z, a.rowC), row_at(st.j.w, a.rowC)};
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
         ch = chunks[c + 1];
@@ -255,10 +278,10 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, EDGE)) slice_kern
 #pragma unroll
             for (int u = 0; u < U; ++u) co[u] = coff_s[4 * (b + u) + kk];
 #pragma unroll
-            for (int u = 0; u < U; ++u) d[u] = *reinterpret_cast<const TVec *>(Db + (rec[u].off + d_lane));
+            for (int u = 0; u < U; ++u) d[u] = sl_gather<MT>(rowsD, rec[u].off + d_lane);
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                if (SRC == SRC_ROWS || (gb >> u & 1)) c[u] = *reinterpret_cast<const CVec *>(Cb + (co[u] + c_lane));
+                if (SRC == SRC_ROWS || (gb >> u & 1)) c[u] = sl_gather<LT>(rowsC, co[u] + c_lane);
             uint32_t ge = gb;
             __asm__ volatile("" : "+s"(ge));   // tests of its own below: a bit kept over the batch costs more scalar instructions
 #pragma unroll
@@ -267,8 +290,7 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, EDGE)) slice_kern
 #pragma unroll
                     for (int x = 0; x < MT; ++x) t[x] += rec[u].v * d[u][x];
                 } else {
-#pragma unroll
-                    for (int x = 0; x < MT; ++x) t[x] = rec[u].v != 0.f ? d[u][x] : 0.f;
+                    t = d[u];
                 }
                 if (SRC == SRC_ROWS || (ge >> u & 1)) {
                     multiply(t, c[u]);
@@ -296,7 +318,7 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, EDGE)) slice_kern
         }
         if (c + 1 == c_end) {
             // a group cut by the run's end is multiplied as far as it has come
-            if (SRC == SRC_LEAVES && !(gm >> (to - 1) & 1)) multiply(t, *reinterpret_cast<const CVec *>(Cb + (coff_s[4 * (to - 1) + kk] + c_lane)));
+            if (SRC == SRC_LEAVES && !(gm >> (to - 1) & 1)) multiply(t, sl_gather<LT>(rowsC, coff_s[4 * (to - 1) + kk] + c_lane));
             goes_on = !(sm >> (to - 1) & 1);
             last_row = __builtin_amdgcn_readlane(rowv, min(sl - sl_base, 63));
             gather_sums(acc, tot);
@@ -409,6 +431,8 @@ sc_status launch_slice(const sc_plan *p, Launcher &ln, const sc_csf_view *sp, co
     a.rowC = (uint32_t)(C.ld * 4);
     a.D = static_cast<const float *>(T ? T : D->data);
     a.rowD = (uint32_t)(T ? W * 4 : D->ld * 4);
+    a.bytesC = (uint32_t)C.rows * a.rowC;   // (below 2 GiB: checked before anything is launched)
+    a.bytesD = T ? kMostBytes : (uint32_t)D->rows * a.rowD;
     a.A = static_cast<float *>(out);
     a.L = (int32_t)C.cols;
     a.W = (int32_t)W;

@@ -144,9 +144,9 @@ struct SliceTables {
     int32_t nruns = 0;
     SliceRun *d_runs = nullptr;       // nruns + 1
     SliceChunk *d_chunks = nullptr;
-    uint32_t *d_leaf = nullptr;       // from the leaves: 4 per step, last coordinate of the leaf of each child of the group
+    uint32_t *d_leaf = nullptr;       // from the leaves: 4 per step, last coordinate of the leaf of each child of the group (-1: none)
     uint32_t *d_at = nullptr;         // ... a byte for each of these: the leaf's place in the chunk (255: none, unless the chunk has 256)
-    int32_t *d_gj = nullptr;          // ... 4 per group: coordinate of the child
+    int32_t *d_gj = nullptr;          // ... 4 per group: coordinate of the child (-1: none)
     int32_t *d_first = nullptr;       // from rows of T: first child of every step and the child count
 };
 

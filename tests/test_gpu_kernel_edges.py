@@ -34,7 +34,7 @@ def _problem(kind, dims, lengths, ranks, dtype="f32", seed=0):
     return cfg, dict(coords=coords, vals=rng.uniform(-1, 1, coords[0].size).astype(dt), factors=factors)
 
 
-def _check(oracle, cfg, data, which, deterministic=False):
+def _run(cfg, data, which, deterministic=False):
     print(f"{cfg['kind']} {which} {cfg['dtype']} dims={cfg['dims']} ranks={cfg['ranks']} nnz={cfg['nnz']}", flush=True)
     con = Contraction(cfg["expr"], data["coords"], data["vals"], cfg["dims"], data["factors"],
                       sc.schedule(which, deterministic=deterministic), synth.output_shape(cfg))
@@ -43,6 +43,11 @@ def _check(oracle, cfg, data, which, deterministic=False):
         if f.shape[1] % step:
             con.factors[n] = torch.nn.functional.pad(f, (0, -f.shape[1] % step), value=float("nan"))[:, : f.shape[1]]
     con.run()
+    return con
+
+
+def _check(oracle, cfg, data, which, deterministic=False):
+    con = _run(cfg, data, which, deterministic)
     assert_parity(oracle, cfg, data, con.result())
     return con
 
@@ -181,6 +186,61 @@ def test_slice_products(oracle, shape, ranks, classes):
                 _check(oracle, cfg, data, which)
             finally:
                 sc.tuning_set("tile_leaves", 0)
+
+
+def _poisoned(oracle, cfg, data, which):
+    """Every output element of the reference that is finite is finite here, and right; the others are not finite here, nor (in one kernel) another value."""
+    got = _run(cfg, data, which).result()
+    clean = [np.nan_to_num(f, nan=0.0, posinf=0.0, neginf=0.0) for f in data["factors"]]   # a zero in the place adds nothing to the bound of the others
+    with np.errstate(invalid="ignore"):
+        ref = oracle.contract(cfg["kind"], data["coords"], data["vals"], cfg["dims"], data["factors"])
+    bound = oracle.abs_bound(cfg["kind"], data["coords"], data["vals"], cfg["dims"], clean)
+    fine = np.isfinite(ref)
+    assert fine.any() and not fine.all()
+    np.testing.assert_array_equal(np.isfinite(got), fine)
+    assert np.all(np.abs(got[fine].astype(np.float64) - ref[fine]) <= 1e-5 * bound[fine])
+    if which != "fissioned":   # (its first kernel, the leaf traversal, multiplies by masked zeros)
+        np.testing.assert_array_equal(got[~fine], ref[~fine].astype(np.float32))
+
+
+@pytest.mark.parametrize("at", [0, 1])
+@pytest.mark.parametrize("ranks,classes", [((16, 16), "ful"), ((8, 8), "ful"), ((32, 16), "fu"), ((16, 32), "fu"), ((64, 32), "fu"), ((16, 128), "fu"), ((64, 64), "fu"),
+                                           ((128, 16), "f"), ((128, 128), "fu"), ((3, 20), "l"), ((72, 12), "l"), ((100, 124), "l")])
+def test_slice_products_with_infinities(oracle, ranks, classes, at):
+    """An infinity or a NaN in every row of C or of D, a column of its own in each: only the outputs that refer to it are not finite.  Chunks end
+    off the batch and runs inside a slice, so places that no child takes stand beside every kind of row."""
+    for name in ("short", "heavy", "whole_chunks"):
+        dims, coords, rng = _fibers(SHAPES[name])
+        cfg = dict(kind="ttmc3", dims=dims, nnz=coords[0].size, ranks=ranks, dtype="f32", expr=synth.KINDS["ttmc3"][0])
+        factors = [rng.uniform(0.5, 1.5, s).astype(np.float32) for s in synth.factor_shapes(cfg)]   # one sign: infinities stay infinities in any order
+        if name == "short" or factors[at].shape[0] > 64:   # every row but, where that would leave no finite element, a few
+            rows = np.arange(factors[at].shape[0]) if name == "short" else rng.choice(factors[at].shape[0], 3, replace=False)
+        else:
+            rows = np.arange(3)
+        for n in rows:
+            factors[at][n, n % factors[at].shape[1]] = [np.inf, np.inf, np.nan][n % 3]
+        data = dict(coords=coords, vals=rng.uniform(0.5, 1, coords[0].size).astype(np.float32), factors=factors)
+        for which in ("fused", "fissioned", "linear"):
+            if {"fused": "f", "fissioned": "u", "linear": "l"}[which] in classes:
+                _poisoned(oracle, cfg, data, which)
+
+
+def test_slice_products_with_infinities_at_a_thread_s_end(oracle):
+    """From rows of T only the last chunk of a planner thread's share is short: two shares, and a row of C that only the last child of the first one has."""
+    counts = np.array(([1] * 7 + [2] * 5 + [5] * 9 + [2] * 3) * 4350 + [4] * 73950)   # 295,800 children in each half, not the same work: no run ends between them
+    starts = np.concatenate([[0], np.cumsum(counts)])
+    s = int(np.searchsorted(starts, starts[-1] // 2))
+    rng = np.random.default_rng(0)
+    i = np.repeat(np.arange(len(counts)), counts).astype(np.int32)
+    j = (np.arange(starts[-1]) - starts[i]).astype(np.int32)
+    j[starts[s] - 1] = 6
+    coords = [i, j, rng.integers(0, 9, i.size).astype(np.int32)]
+    cfg = dict(kind="ttmc3", dims=(len(counts), 7, 9), nnz=i.size, ranks=(8, 8), dtype="f32", expr=synth.KINDS["ttmc3"][0])
+    factors = [rng.uniform(0.5, 1.5, x).astype(np.float32) for x in synth.factor_shapes(cfg)]
+    factors[0][6, :] = np.inf
+    data = dict(coords=coords, vals=rng.uniform(0.5, 1, i.size).astype(np.float32), factors=factors)
+    assert ((counts[:s] + 3) // 4).sum() % 4 != 0   # the share's last batch of steps is not full
+    _poisoned(oracle, cfg, data, "fissioned")
 
 
 def test_slice_products_stored_past_the_caches(oracle):
