@@ -194,6 +194,11 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, EDGE)) slice_kern
 #pragma unroll
             for (int y = 0; y < LT; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(cv[y], tv[x], acc[x][y], 0, 0, 0);
     };
+    // what the lanes of the wavefront wrote to LDS is there for its other lanes, and what they read may be overwritten
+    auto lanes_meet = [] {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
     // acc[x][y][q] = A(l = l0 + LT (4 kk + q) + y, m = lm + x): a store instruction covers four rows l of 16 MT adjacent floats
     constexpr int STORE = 0, STREAM = 1, ADD = 2;
     auto emit = [&](int row, auto how) {
@@ -215,7 +220,11 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, EDGE)) slice_kern
                     }
                 } else {
                     // adjacent lanes on adjacent floats: an addition of MT floats per lane visits every cache line MT times
-                    if (MT > 1) *reinterpret_cast<TVec *>(swap_s + MT * lane) = o;
+                    if (MT > 1) {
+                        lanes_meet();
+                        *reinterpret_cast<TVec *>(swap_s + MT * lane) = o;
+                        lanes_meet();
+                    }
 #pragma unroll
                     for (int x = 0; x < MT; ++x) {
                         const float v = MT > 1 ? swap_s[16 * MT * kk + 16 * x + col] : o[0];
@@ -239,11 +248,10 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, EDGE)) slice_kern
         auto row_at = [&](int x, uint32_t row) { return (uint32_t)(live ? x : kNoRow) * row; };
         if (SRC == SRC_LEAVES) {
             const int nl = ch.nleaves;
-            __builtin_amdgcn_wave_barrier();
+            lanes_meet();
 #pragma unroll
             for (int q = 0; q < 4; ++q) swap_s[64 * q + lane] = 64 * q + lane < nl ? st.v[q] : 0.f;   // place 255 is zero in a chunk of fewer leaves
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
+            lanes_meet();
             float v[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) v[q] = swap_s[st.at >> 8 * q & 255];
@@ -252,7 +260,7 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, EDGE)) slice_kern
             dst[0] = uint4{row_at(st.leaf.x, a.rowD), word(v[0]), row_at(st.leaf.y, a.rowD), word(v[1])};
             dst[1] = uint4{row_at(st.leaf.z, a.rowD), word(v[2]), row_at(st.leaf.w, a.rowD), word(v[3])};
         } else {
-            __builtin_amdgcn_wave_barrier();
+            lanes_meet();
 #pragma unroll
             for (int q = 0; q < 4; ++q)   // (steps before the run's first are not read)
                 rec_s[4 * lane + q].off = row_at(st.f0 + q < st.f1 ? st.f0 + q - fbase : kNoRow, a.rowD);
@@ -262,8 +270,7 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, EDGE)) slice_kern
         }
         reinterpret_cast<uint4 *>(coff_s)[lane] =
             uint4{row_at(st.j.x, a.rowC), row_at(st.j.y, a.rowC), row_at(st.j.z, a.rowC), row_at(st.j.w, a.rowC)};
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+        lanes_meet();
         ch = chunks[c + 1];
         if (c + 1 < c_end) issue(ch, st);
 
