@@ -1277,8 +1277,9 @@ static size_t pick_candidate(const std::vector<Candidate> &cands)
     return best;
 }
 
+// `whole`: false for an inner plan of which at most the leaf traversal is launched (no tables for the kernel that writes its output).
 static sc_status plan_create_impl(sc_plan **out, const char *expr, const sc_csf_view *sparse, const sc_dense_view *factors,
-                                  int32_t nfactors, const sc_schedule *sched);
+                                  int32_t nfactors, const sc_schedule *sched, bool whole = true);
 
 // Kernel 5 of Table 2 (all-mode TTMC).  The caller picks one of the three schedules Table 2 lists by naming
 // its temporaries: {T(i,j,n)} = schedule 1, {T1(i,j,n), T2(i,m,n)} or nothing = schedule 2, {T(i,m,n)} = schedule 3.
@@ -1376,7 +1377,7 @@ static sc_status plan_ttmc_all(sc_plan *p, const char *expr, const Term &lhs, co
     sc_schedule is = {};
     is.kind = (variant == 3 || variant == 0) ? SC_SCHED_LINEAR : variant == 1 ? SC_SCHED_FISSIONED : sched->kind;
     is.deterministic = (variant == 3 || variant == 0) ? 0 : sched->deterministic;
-    sc_status st = plan_create_impl(&p->inner, inner_expr.c_str(), sparse, inner_fac, 2, &is);
+    sc_status st = plan_create_impl(&p->inner, inner_expr.c_str(), sparse, inner_fac, 2, &is, variant >= 2);
     if (st != SC_OK) return st;
     const sc_plan *in = p->inner;
     p->has_device = in->has_device;
@@ -1582,7 +1583,7 @@ static sc_status plan_trailing_gemm(sc_plan *p, const char *expr, const Term &lh
 }
 
 static sc_status plan_create_impl(sc_plan **out, const char *expr, const sc_csf_view *sparse,
-                                  const sc_dense_view *factors, int32_t nfactors, const sc_schedule *sched)
+                                  const sc_dense_view *factors, int32_t nfactors, const sc_schedule *sched, bool whole)
 {
     if (!out) return SC_ERR_NULL;
     *out = nullptr;
@@ -1767,7 +1768,7 @@ static sc_status plan_create_impl(sc_plan **out, const char *expr, const sc_csf_
         int piece = 1;
         const SliceSource src = plan_slice_source(p, &piece);
         int ndev = 0;
-        sliced = src != SLICE_NONE && p->nnz > 0 && hipGetDeviceCount(&ndev) == hipSuccess && ndev > 0;
+        sliced = whole && src != SLICE_NONE && p->nnz > 0 && hipGetDeviceCount(&ndev) == hipSuccess && ndev > 0;
         if (sliced) build_slices(p, src, piece, h, slices);
         list_rows_to_zero(p, h, sliced ? &slices.cut_rows : nullptr);
     } catch (const std::bad_alloc &) { return SC_ERR_ALLOC; }

@@ -45,6 +45,15 @@ def test_parity_three_schedules(oracle, dtype, ranks, scale, which, names):
     assert_parity(oracle, cfg, data, con.result())
 
 
+@pytest.mark.parametrize("which,names", VARIANTS, ids=IDS)
+def test_step_tables_only_where_they_are_read(which, names):
+    """Schedule 1 launches the inner plan's leaf traversal alone, the unfactored form nothing of it: no step tables are made for them."""
+    cfg, data = _cfg(0.002)
+    con = _contraction(cfg, data, which, names)
+    runs_chain = (which, names) not in (VARIANTS[2], VARIANTS[4])
+    assert ("slice products:" in sc.plan_describe(con.plan)) == runs_chain
+
+
 @pytest.mark.parametrize("which,names", VARIANTS[:3], ids=IDS[:3])
 def test_deterministic_is_bit_reproducible(oracle, which, names):
     cfg, data = _cfg(0.02)
