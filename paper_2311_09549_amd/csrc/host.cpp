@@ -662,6 +662,33 @@ void list_steps(SliceSource src, int piece, int cap, const HostCsf &h, int64_t s
             int32_t z = pos2[f];
             // a slice longer than what is left of a chunk starts the next one, unless much is left
             if (cap - c.nsteps < 8 && (pos2[fend] - z) / 4 >= cap - c.nsteps) flush(z, (int32_t)s);
+            if (piece == 1) {   // every leaf a child of its own: four leaves in a row per step, a step per group
+                const int32_t zend = pos2[fend];
+                while (z < zend) {
+                    const int32_t n = std::min(zend - z, 4 * (cap - c.nsteps)), steps = (n + 3) / 4;
+                    const size_t o = b.leaf.size();
+                    b.leaf.resize(o + 4 * (size_t)steps, 0xffffffffu);
+                    b.gj.resize(o + 4 * (size_t)steps, -1);
+                    b.at.resize(o / 4 + (size_t)steps, 0xffffffffu);
+                    memcpy(b.leaf.data() + o, crd2 + z, sizeof(uint32_t) * (size_t)n);
+                    uint8_t *place = reinterpret_cast<uint8_t *>(b.at.data()) + o;
+                    for (int32_t k = 0; k < n; ++k) place[k] = (uint8_t)(z - c.leaf0 + k);
+                    for (int32_t k = 0; k < n;) {
+                        const int32_t here = std::min(n, pos2[f + 1] - z);
+                        std::fill(b.gj.begin() + (ptrdiff_t)o + k, b.gj.begin() + (ptrdiff_t)o + here, crd1[f]);
+                        k = here;
+                        if (z + k == pos2[f + 1]) ++f;
+                    }
+                    c.gend |= (steps == 64 ? ~0ull : (1ull << steps) - 1) << c.nsteps;
+                    nsteps += steps;
+                    c.nsteps += steps;
+                    ngroups += steps;
+                    c.ngroups += steps;
+                    c.nleaves += n;
+                    z += n;
+                    if (z < zend) flush(z, (int32_t)s);
+                }
+            }
             while (f < fend) {
                 SlicePieces w;
                 const int32_t room = cap - c.nsteps;
@@ -1759,17 +1786,43 @@ static sc_status plan_create_impl(sc_plan **out, const char *expr, const sc_csf_
     if (lds_bytes_needed(p) > 64 * 1024) return SC_ERR_SCHED_UNSUPPORTED;
     SliceBuild slices;
     bool sliced = false;
+    int piece = 1;
+    const SliceSource src = plan_slice_source(p, &piece);
+    {
+        int ndev = 0;
+        sliced = whole && src != SLICE_NONE && p->nnz > 0 && hipGetDeviceCount(&ndev) == hipSuccess && ndev > 0;
+    }
+    {
+        // The steps are listed beside the tiles where there is enough of both for a thread (plan of 6 M entries at 64 x 32: 28.4 ms one after
+        // the other, 22.5 beside each other).
+        bool listed = false, failed = false;
+        auto list = [&] {
+            try {
+                build_slices(p, src, piece, h, slices);
+            } catch (...) { failed = true; }
+        };
+        std::thread beside;
+        if (sliced && p->nnz >= 256000) {
+            try {
+                beside = std::thread(list);
+                listed = true;
+            } catch (...) {   // no thread to be had
+            }
+        }
+        try {
+            build_tiles(sparse, h, p->caps, p->tiles);
+        } catch (...) { failed = true; }
+        if (listed) beside.join();
+        else if (sliced) list();
+        if (failed) return SC_ERR_ALLOC;
+    }
+    // what the device reads of the tiles: nothing where slice products from the leaves are all that runs
+    const bool tiles_read = !(sliced && src == SLICE_LEAVES);
     try {
-        build_tiles(sparse, h, p->caps, p->tiles);
         if (p->deterministic) {
             if (!plan_supports_deterministic(p)) return SC_ERR_SCHED_UNSUPPORTED;
             assign_piece_slots(p, h);
         }
-        int piece = 1;
-        const SliceSource src = plan_slice_source(p, &piece);
-        int ndev = 0;
-        sliced = whole && src != SLICE_NONE && p->nnz > 0 && hipGetDeviceCount(&ndev) == hipSuccess && ndev > 0;
-        if (sliced) build_slices(p, src, piece, h, slices);
         list_rows_to_zero(p, h, sliced ? &slices.cut_rows : nullptr);
     } catch (const std::bad_alloc &) { return SC_ERR_ALLOC; }
 
@@ -1876,7 +1929,7 @@ static sc_status plan_create_impl(sc_plan **out, const char *expr, const sc_csf_
     // ---- device tables ----
     int ndev = 0;
     if (hipGetDeviceCount(&ndev) == hipSuccess && ndev > 0) {
-        if (!p->tiles.empty()) {
+        if (!p->tiles.empty() && tiles_read) {
             if (hipMalloc((void **)&p->d_tiles, sizeof(TileRec) * p->tiles.size()) != hipSuccess) return SC_ERR_DEVICE;
             const size_t nt = p->tiles.size();
             std::vector<uint32_t> at;   // tile number per position of the device table
@@ -1900,10 +1953,10 @@ static sc_status plan_create_impl(sc_plan **out, const char *expr, const sc_csf_
             p->walk.shape = plan_walk_shape(p);
             const sc_status ws = build_walk_tables(p, sparse, h, order);
             if (ws != SC_OK) return ws;
-            if (sliced) {
-                const sc_status us = upload_slices(p, slices);
-                if (us != SC_OK) return us;
-            }
+        }
+        if (sliced) {
+            const sc_status us = upload_slices(p, slices);
+            if (us != SC_OK) return us;
         }
         if (p->zero_selective && !p->zero_rows.empty()) {
             if (hipMalloc((void **)&p->d_zero_rows, sizeof(int32_t) * p->zero_rows.size()) != hipSuccess) return SC_ERR_DEVICE;
