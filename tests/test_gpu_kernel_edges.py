@@ -1,6 +1,8 @@
 """GPU parity at the sizes where a kernel's split of the work has edges: remainders of its blocks, chunks and batches, the
 first and last size of a dispatch rule, slices cut by chunk and tile boundaries.  Against the oracle, within the tolerance of
 the other parity tests (1e-5 / 1e-12 times the sum of |partial products|)."""
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -148,7 +150,7 @@ def test_core_tensor_reduction(oracle, dtype, L, MN, rows):
         _check(oracle, cfg, data, "fused")
 
 
-# ---- slice products: steps, chunks of 64 steps, runs, sums over the runs of a workgroup ----
+# ---- slice products: steps, chunks (of 16 steps at these sizes, of 32 and 64 below), runs, sums over the runs of a workgroup ----
 def _fibers(shape, seed=0):
     """shape: per slice a list of fiber lengths; every fiber's entries start at a drawn place of the last mode."""
     rng = np.random.default_rng(seed)
@@ -162,7 +164,7 @@ def _fibers(shape, seed=0):
 
 
 SHAPES = {
-    "whole_chunks": [[16] * 64, [16] * 16, [16] * 15, [1] * 256, [4] * 64],   # 256 leaves in a chunk: no place is free for "none"
+    "whole_chunks": [[16] * 64, [16] * 16, [16] * 15, [1] * 256, [4] * 64],   # every place of a chunk taken
     "short": [[1]] * 70 + [[1, 1]] * 5 + [[], [3, 1, 1, 2, 1]] + [[1] * 5] * 9,
     "long_fibers": [[700, 1, 33, 17], [15, 16, 17], [2048]],
     "heavy": [[2, 1], [1, 2, 3, 1] * 1500, [1]],   # one slice through many runs and workgroups
@@ -241,6 +243,27 @@ def test_slice_products_with_infinities_at_a_thread_s_end(oracle):
     data = dict(coords=coords, vals=rng.uniform(0.5, 1, i.size).astype(np.float32), factors=factors)
     assert ((counts[:s] + 3) // 4).sum() % 4 != 0   # the share's last batch of steps is not full
     _poisoned(oracle, cfg, data, "fissioned")
+
+
+@pytest.mark.parametrize("least,cap", [(300_000, 32), (560_000, 64)])
+@pytest.mark.parametrize("ranks,which", [((16, 16), "fused"), ((32, 32), "fused"), ((8, 8), "fissioned"), ((16, 16), "linear")])
+def test_slice_products_longer_chunks(oracle, ranks, which, least, cap):
+    """Chunks of 32 and 64 steps (with as many slices, and with 256 leaves in 64 steps), which take so many entries; above 512,000 the steps
+    are listed by several threads, each from a first chunk of its own."""
+    wide = ranks[0] * ranks[1] > 256
+    for name, shape in SHAPES.items():
+        once = sum(len(f) if which == "fissioned" else sum(f) for f in shape)
+        if wide and name == "short" or which == "fissioned" and once * 4 < sum(map(sum, shape)):
+            continue   # (400,000 slices of 4 KB; few fibers of many entries)
+        dims, coords, rng = _fibers(shape * -(-least // once))
+        cfg = dict(kind="ttmc3", dims=dims, nnz=coords[0].size, ranks=ranks, dtype="f32", expr=synth.KINDS["ttmc3"][0])
+        factors = [rng.standard_normal(s).astype(np.float32) for s in synth.factor_shapes(cfg)]
+        con = _check(oracle, cfg, dict(coords=coords, vals=rng.uniform(-1, 1, coords[0].size).astype(np.float32), factors=factors), which)
+        slots = (least if which == "fissioned" else coords[0].size) / 4
+        chunks = int(re.search(r"runs of (\d+) chunks", sc.plan_describe(con.plan)).group(1))
+        if name == "whole_chunks" and which != "fissioned" or which == "linear" and name == "heavy":   # nearly every place is taken
+            assert slots / cap <= chunks <= 1.25 * slots / cap + 8
+        assert chunks >= slots / cap / 2
 
 
 def test_slice_products_stored_past_the_caches(oracle):
