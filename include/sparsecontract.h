@@ -275,8 +275,11 @@ sc_status sc_plan_tile(const sc_plan *plan, int64_t index, int32_t rec[9]);
  * level-b nodes of one work tile; 0 restores the built-in choice), "tile_interleave"
  * (stride of the order in which tiles are handed to workgroups; 1 = tensor order),
  * "persistent_per_cu" (workgroups per compute unit launched by the kernels that loop over
- * tiles; 0 = as many as fit).  Unknown names give
- * SC_ERR_EXPR_PARSE; sc_plan_create rejects caps whose on-chip buffers do not fit. */
+ * tiles; 0 = as many as fit).  Plans whose kernel works through runs of steps instead (fp32 chains of
+ * order 3 that need not be reproducible) have no work tiles: sc_plan_tile gives the tiles the caps
+ * would make, "tile_leaves" bounds the length of a run (a quarter of it in steps, at least eight) and
+ * "persistent_per_cu" the number of runs (four per workgroup).  Unknown names give
+ * SC_ERR_EXPR_PARSE; sc_plan_create rejects caps whose on-chip buffers would not fit a kernel over tiles. */
 sc_status sc_tuning_set(const char *name, int64_t value);
 
 /* Measurement aid, not part of the contraction path: queues a plain streaming copy of

@@ -1266,8 +1266,8 @@ static void probe_class(const sc_plan *p, sc_sched_kind kind, bool deterministic
     c.kind = kind;
     c.variant = 0;
     c.available = q.caps.tn > 0 && !(deterministic && (kind == SC_SCHED_LINEAR || !plan_supports_deterministic(&q)));
-    c.lds = c.available ? lds_bytes_needed(&q) : 0;
-    if (c.lds > 64 * 1024) c.available = false;
+    if (c.available && lds_bytes_needed(&q) > 64 * 1024) c.available = false;
+    c.lds = c.available ? lds_bytes_used(&q) : 0;
     c.wg_per_cu = c.available ? lds_workgroups_per_cu(c.lds, p->lds_per_cu) : 0;
     c.admissible = c.available && c.wg_per_cu >= 2;
 }

@@ -1021,6 +1021,14 @@ size_t lds_bytes_needed(const sc_plan *p)
     }
 }
 
+size_t lds_bytes_used(const sc_plan *p)
+{
+    const SliceSource src = plan_slice_source(p, nullptr);
+    if (src == SLICE_LEAVES) return kSliceLdsBytes;
+    if (src == SLICE_ROWS && p->kind == K_TTMC3) return std::max(kSliceLdsBytes, leaf_traverse_lds_bytes(p, (int)p->fcols[1]));
+    return lds_bytes_needed(p);   // (the order-4 chain: its first two kernels need more than the slice product)
+}
+
 sc_status launch_plan(const sc_plan *p, const sc_csf_view *sp, const sc_dense_view *fac, void *out, void *ws, hipStream_t stream)
 {
     if (p->prof && p->prof->on) p->prof->n_launch = 0;

@@ -395,7 +395,6 @@ void launch_linear_nest(const sc_plan *p, const LinArgs &a, int ntiles, hipStrea
 
 }  // namespace
 
-// (Slice products take less LDS than the tiled kernel.)
 size_t linear_lds_bytes(const sc_plan *p)
 {
     if (p->caps.tn > LIN_TN) return SIZE_MAX;

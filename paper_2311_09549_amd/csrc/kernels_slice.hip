@@ -108,6 +108,7 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, EDGE)) slice_kern
     };
     __shared__ Lds lds;
     __shared__ int inside_s[WAVES];
+    static_assert(sizeof(Lds) + sizeof(inside_s) <= kSliceLdsBytes, "LDS the plan reports");
 
     const int wave = sl_uni(threadIdx.x / 64), lane = threadIdx.x % 64;
     const int kk = lane / 16, col = lane % 16;

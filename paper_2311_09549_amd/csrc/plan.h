@@ -267,6 +267,7 @@ int plan_output_run(const sc_plan *plan);
 enum SliceSource { SLICE_NONE, SLICE_LEAVES, SLICE_ROWS };
 SliceSource plan_slice_source(const sc_plan *plan, int *piece);
 SliceShape slice_shape(int64_t L, int64_t W);
+constexpr size_t kSliceLdsBytes = 16400;   // LDS of a workgroup, at every shape
 
 // True when the kernels of the plan can run without floating-point atomics (FUSED schedules of
 // the kernels that emit one piece per tile and shared row).
@@ -275,8 +276,12 @@ bool plan_supports_deterministic(const sc_plan *plan);
 // Lane-group layout of the walks of the kernels the plan dispatches to (levels = 0: no walk tables).
 WalkShape plan_walk_shape(const sc_plan *plan);
 
-// Dynamic LDS bytes the fused / fissioned kernels of a plan need (used for validation).
+// LDS bytes that the kernels which work tile by tile need under the plan's caps (caps that do not fit are refused, also where slice
+// products run and the tiles are only what sc_plan_tile tells).
 size_t lds_bytes_needed(const sc_plan *plan);
+
+// LDS bytes of the kernels that the plan launches.
+size_t lds_bytes_used(const sc_plan *plan);
 
 // Argument checks of an execution followed by launch_plan (shared by the execute entry points).
 sc_status execute_checked(const sc_plan *plan, const sc_csf_view *sparse, const sc_dense_view *factors, int32_t nfactors, void *out,

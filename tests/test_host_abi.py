@@ -438,7 +438,8 @@ def test_linear_plan_counts_the_unfactored_nest(cid, scale):
 def test_unfactored_nest_reports_the_lds_of_its_kernel(kind, ranks, blocks, dtype):
     """The footprint the cost evaluator prints and judges by is that of the kernel that runs.  Blocks of the output row
     (4 x 4, or 4 elements): 1024 nonzeros, padded by a sixteenth, with a 16-byte record and the value, a parked block per
-    thread and a word per thread.  Otherwise four coordinates and the value of 1024 nonzeros."""
+    thread and a word per thread.  Otherwise four coordinates and the value of 1024 nonzeros.  The fp32 chain of order 3 with a last
+    rank that is a multiple of 4 runs as slice products: four wavefronts with 256 offsets and values, 256 offsets, 256 values each, and a word."""
     dims = {"ttmc3": (9, 8, 7), "mttkrp3": (9, 8, 7), "ttmc4": (6, 5, 4, 3), "sddmm_spmm": (9, 8)}[kind]
     cfg = dict(kind=kind, dims=dims, nnz=30, ranks=ranks, dtype=dtype, expr=synth.KINDS[kind][0])
     dt = np.float64 if dtype == "f64" else np.float32
@@ -449,8 +450,21 @@ def test_unfactored_nest_reports_the_lds_of_its_kernel(kind, ranks, blocks, dtyp
     line = [ln for ln in text.splitlines() if "candidate LINEAR" in ln][0]
     e = 8 if dtype == "f64" else 4
     want = 1088 * (16 + e) + 256 * blocks * e + 256 * 4 if blocks else 1024 * (16 + e)
+    if kind == "ttmc3" and dtype == "f32" and blocks:
+        want = 4 * (256 * 8 + 256 * 4 + 256 * 4 + 4)
     per_cu = min(8, 160 * 1024 // (-(-want // 1280) * 1280))
     assert f" {want} bytes of LDS per workgroup ({per_cu} per compute unit)" in line, line
+
+
+@pytest.mark.parametrize("deterministic", [False, True])
+@pytest.mark.parametrize("ranks", [(16, 16), (64, 32), (8, 8)])
+def test_factored_chain_reports_the_lds_of_its_kernel(ranks, deterministic):
+    """The fused fp32 chain runs as slice products, whose footprint does not depend on the ranks; its reproducible form in kernels over tiles."""
+    cfg, data, csf = _small(3, 0.003)
+    factors = [np.ones((f.shape[0], r), np.float32) for f, r in zip(data["factors"], ranks)]
+    text = sc.plan_describe(sc.plan_create(cfg["expr"], csf, factors, sc.schedule("auto", deterministic=deterministic)))
+    line = [ln for ln in text.splitlines() if "candidate FUSED" in ln][0]
+    assert (" 16400 bytes of LDS per workgroup (8 per compute unit)" in line) != deterministic, line
 
 
 def test_all_mode_ttmc_plans():
