@@ -30,10 +30,28 @@ namespace {
 
 constexpr int SRC_LEAVES = 0, SRC_ROWS = 1;
 
-// An output larger than this is stored with the non-temporal hint: written through the L2s it evicts the rows of C and D that the
-// gathers hit there (500 MB at 64 x 32: 289 us, 229 us so; 2.6 GB at 128 x 128: 1056 and 945 us), while the 41 MB of S at 16 x 16 are
-// better found there by the next kernel (12.6 us, 15.4 us so).
-constexpr int64_t kStreamBytes = 128 << 20;
+// Whether the rows of the output are stored with the non-temporal hint.  Written through the L2s they evict the rows of C and D that the
+// gathers hit there, which costs most where a slice gathers much for what it stores; but stores with the hint are slow in pieces of
+// less than half a cache line, and they do not stay in the memory-side cache (256 MB) for whoever reads or writes the output next.  Whole
+// calls on uniform tensors, us without the hint and with it:
+//     entries per slice     3                 9                 20
+//     16 x 32    140 MB     32 and 35         34 and 37         54 and 52 (160 MB)
+//     64 x 64    256 MB     53 and 62         62 and 65         79 and 72
+//                400 MB     93 and 93         98 and 96         129 and 108
+//     16 x 16    256 MB     58 and 88         78 and 74         128 and 89
+//     64 x 16    256 MB     52 and 82         56 and 85         74 and 75
+//                400 MB     90 and 135        98 and 125        132 and 109
+//     24 x 100   400 MB     122 and 203       165 and 232       185 and 225
+// From rows of T, which are read once and evict as well: 16 x 16 at 400 MB 189 and 173, 280 and 252; 64 x 64 at 256 MB 73 and 78, 98 and 96.
+bool stores_past_caches(int64_t bytes, int64_t slices, int64_t children, int64_t L, int64_t W, bool rows)
+{
+    constexpr int64_t MB = 1 << 20;
+    const double per_slice = (double)children / (double)std::max<int64_t>(slices, 1);
+    if (W % 16 != 0) return false;
+    if (bytes > 128 * MB && per_slice >= 16) return true;
+    if (bytes > 256 * MB && per_slice >= 8 && L <= 16) return true;
+    return rows ? bytes > 320 * MB : bytes > 384 * MB && W % 32 == 0;
+}
 
 struct SliceArgs {
     int32_t nruns;
@@ -206,9 +224,9 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, EDGE)) slice_kern
         constexpr int HOW = decltype(how)::value;
         float *A = a.A + (int64_t)row * L * W;
 #pragma unroll
-        for (int y = 0; y < LT; ++y)
+        for (int q = 0; q < 4; ++q)   // (y inside: adjacent rows right after each other, 64 x 8 at 140 MB 135 us the other way and 73 so)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
+            for (int y = 0; y < LT; ++y) {
                 const int l = l0 + LT * (4 * kk + q) + y;
                 TVec o;
 #pragma unroll
@@ -444,7 +462,7 @@ sc_status launch_slice(const sc_plan *p, Launcher &ln, const sc_csf_view *sp, co
     a.A = static_cast<float *>(out);
     a.L = (int32_t)C.cols;
     a.W = (int32_t)W;
-    a.stream = p->out_elems * 4 > kStreamBytes;
+    a.stream = stores_past_caches(p->out_elems * 4, p->nfib[0], T ? p->nfib[1] : p->nnz, a.L, W, T != nullptr);
     ln.begin(name);
     if (T) dispatch_slice<SRC_ROWS>(a, st, ln.stream);
     else dispatch_slice<SRC_LEAVES>(a, st, ln.stream);

@@ -266,10 +266,16 @@ def test_slice_products_longer_chunks(oracle, ranks, which, least, cap):
         assert chunks >= slots / cap / 2
 
 
-def test_slice_products_stored_past_the_caches(oracle):
-    """An output above the size from which rows are stored with the non-temporal hint."""
-    cfg, data = _problem("ttmc3", (9000, 41, 97), [(i, 1 + i % 7) for i in range(0, 9000, 5)], (64, 64))
-    _check(oracle, cfg, data, "fused")
+@pytest.mark.parametrize("which,dims,lengths,ranks", [
+    ("fused", (9000, 41, 97), [(i, 17 + i % 7) for i in range(0, 9000, 5)], (64, 64)),       # 147 MB, slices of some length
+    ("fused", (280_000, 41, 97), [(i, 9 + i % 2) for i in range(0, 280_000, 11)], (16, 16)),  # 287 MB
+    ("fused", (26_000, 41, 97), [(i, 1 + i % 7) for i in range(0, 26_000, 5)], (64, 64)),     # 426 MB, short slices
+    ("fissioned", (88_000, 41, 97), [(i, 1 + i % 7) for i in range(0, 88_000, 9)], (64, 16)),  # 360 MB
+    ("fused", (88_000, 41, 97), [(i, 1 + i % 7) for i in range(0, 88_000, 9)], (64, 16))])     # the same through the caches
+def test_slice_products_stored_past_the_caches(oracle, which, dims, lengths, ranks):
+    """Outputs on the sides of the rule by which rows are stored with the non-temporal hint."""
+    cfg, data = _problem("ttmc3", dims, lengths, ranks)
+    _check(oracle, cfg, data, which)
 
 
 # ---- tiles of few leaves: small problems and wide gathered rows; rows shared by several tiles ----
