@@ -32,25 +32,27 @@ constexpr int SRC_LEAVES = 0, SRC_ROWS = 1;
 
 // Whether the rows of the output are stored with the non-temporal hint.  Written through the L2s they evict the rows of C and D that the
 // gathers hit there, which costs most where a slice gathers much for what it stores; but stores with the hint are slow in pieces of
-// less than half a cache line, and they do not stay in the memory-side cache (256 MB) for whoever reads or writes the output next.  Whole
+// less than a cache line, and they do not stay in the memory-side cache (256 MB) for whoever reads or writes the output next.  Whole
 // calls on uniform tensors, us without the hint and with it:
 //     entries per slice     3                 9                 20
 //     16 x 32    140 MB     32 and 35         34 and 37         54 and 52 (160 MB)
 //     64 x 64    256 MB     53 and 62         62 and 65         79 and 72
 //                400 MB     93 and 93         98 and 96         129 and 108
-//     16 x 16    256 MB     58 and 88         78 and 74         128 and 89
+//     16 x 16    256 MB     53 and 60         74 and 70         124 and 90
+//                400 MB     97 and 93         129 and 97
 //     64 x 16    256 MB     52 and 82         56 and 85         74 and 75
 //                400 MB     90 and 135        98 and 125        132 and 109
 //     24 x 100   400 MB     122 and 203       165 and 232       185 and 225
-// From rows of T, which are read once and evict as well: 16 x 16 at 400 MB 189 and 173, 280 and 252; 64 x 64 at 256 MB 73 and 78, 98 and 96.
+// From rows of T, which are read once and evict as well: 16 x 16 at 400 MB 168 and 156, 248 and 221; 64 x 64 at 256 MB 73 and 78, 98 and 96.
 bool stores_past_caches(int64_t bytes, int64_t slices, int64_t children, int64_t L, int64_t W, bool rows)
 {
     constexpr int64_t MB = 1 << 20;
     const double per_slice = (double)children / (double)std::max<int64_t>(slices, 1);
-    if (W % 16 != 0) return false;
+    const bool one_tile = L <= 16 && W <= 16;   // a slice is one piece
+    if (W % 16 != 0 && !one_tile) return false;
     if (bytes > 128 * MB && per_slice >= 16) return true;
     if (bytes > 256 * MB && per_slice >= 8 && L <= 16) return true;
-    return rows ? bytes > 320 * MB : bytes > 384 * MB && W % 32 == 0;
+    return rows ? bytes > 320 * MB : bytes > 384 * MB && (W % 32 == 0 || one_tile);
 }
 
 struct SliceArgs {
@@ -111,6 +113,7 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, EDGE)) slice_kern
     constexpr int WAVES = NT / 64;
     constexpr int RPB = WAVES / WPR;          // runs per workgroup
     constexpr int U = slice_batch(LT * MT);   // steps per batch
+    constexpr bool TURNED = LT * MT == 1;     // which of l and m runs over the registers of an accumulator
     typedef float TVec __attribute__((ext_vector_type(MT)));
     typedef float CVec __attribute__((ext_vector_type(LT)));
     struct alignas(8) Rec { uint32_t off; float v; };
@@ -211,18 +214,44 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, EDGE)) slice_kern
 #pragma unroll
         for (int x = 0; x < MT; ++x)
 #pragma unroll
-            for (int y = 0; y < LT; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(cv[y], tv[x], acc[x][y], 0, 0, 0);
+            for (int y = 0; y < LT; ++y)
+                acc[x][y] = TURNED ? __builtin_amdgcn_mfma_f32_16x16x4f32(tv[x], cv[y], acc[x][y], 0, 0, 0)
+                                   : __builtin_amdgcn_mfma_f32_16x16x4f32(cv[y], tv[x], acc[x][y], 0, 0, 0);
     };
     // what the lanes of the wavefront wrote to LDS is there for its other lanes, and what they read may be overwritten
     auto lanes_meet = [] {
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
     };
-    // acc[x][y][q] = A(l = l0 + LT (4 kk + q) + y, m = lm + x): a store instruction covers four rows l of 16 MT adjacent floats
+    // acc[x][y][q] = A(l = l0 + LT (4 kk + q) + y, m = lm + x): a store instruction covers four rows l of 16 MT adjacent floats.
+    // One tile: acc[0][0][q] = A(l = col, m = 4 kk + q), one store instruction for the slice (from rows of T at 16 x 16, 150,000 entries in
+    // 55,000 slices: 24.5 us the other way and 21 so; at 64 x 16, 400 MB, two to four rows apart in the same layout 98 and 104).
     constexpr int STORE = 0, STREAM = 1, ADD = 2;
     auto emit = [&](int row, auto how) {
         constexpr int HOW = decltype(how)::value;
         float *A = a.A + (int64_t)row * L * W;
+        if constexpr (TURNED) {
+            if (HOW != ADD) {
+                sl_floatx4 *dst = reinterpret_cast<sl_floatx4 *>(A + col * W + 4 * kk);
+                if (HOW == STREAM) __asm__ volatile("" : "+v"(dst));   // kept apart from the plain store: merged into one, the hint is lost
+                if (!EDGE || (col < L && 4 * kk < W)) {
+                    if (HOW == STREAM) __builtin_nontemporal_store(acc[0][0], dst);
+                    else *dst = acc[0][0];
+                }
+            } else {
+                // adjacent lanes on adjacent floats: the four of a lane one after the other visit every cache line four times
+                lanes_meet();
+                *reinterpret_cast<sl_floatx4 *>(swap_s + 16 * col + 4 * kk) = acc[0][0];
+                lanes_meet();
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int l = 4 * q + kk;
+                    const float v = swap_s[64 * q + lane];
+                    if (!EDGE || (l < L && col < W)) atomic_add(A + l * W + col, v);
+                }
+            }
+            return;
+        }
 #pragma unroll
         for (int q = 0; q < 4; ++q)   // (y inside: adjacent rows right after each other, 64 x 8 at 140 MB 135 us the other way and 73 so)
 #pragma unroll
@@ -386,7 +415,7 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, EDGE)) slice_kern
             if (across && rw == to) add_from(lds.sum[0]);
             goes_on = goes_on && !(across && rw == 1);
         }
-        if (MT > 1) __syncthreads();   // the sums have been read: their space is the staging regions again
+        if (MT > 1 || TURNED) __syncthreads();   // the sums have been read: their space is the staging regions again
     }
     if (goes_on) emit(last_row, std::integral_constant<int, ADD>{});
 }
