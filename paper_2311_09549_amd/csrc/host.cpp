@@ -798,13 +798,15 @@ void build_slices(const sc_plan *p, SliceSource src, int piece, const HostCsf &h
     double total = 0;
     for (const SliceChunk &k : b.chunks) total += cost(k);
     // Runs: enough of them for the wavefront slots of the chip, of 96 steps where there are that many; short ones make the runs of a
-    // heavy slice queue on its row.  Fewer steps than that: a run for each of four wavefronts per SIMD, of sixteen steps at least, up to
-    // two tiles, for two wavefronts beyond, whose sums cost more at a run's end.  Whole calls with two and with four, us: 16 x 16,
-    // 700,000 entries 28.0 and 23.3 (from rows of T 59.8 and 49.7), 8 x 8 from rows, 400,000 40.3 and 32.7, unfactored 4 x 4, 700,000 26.5
-    // and 20.4, 12 x 20, 150,000 23.2 and 22.2; 64 x 16, 60,000 41.8 and 43.1.
+    // heavy slice queue on its row.  Fewer steps than that: a run of sixteen steps at least for each of four wavefronts per SIMD at one
+    // tile, whose sums cost little at a run's end, of two beyond; at two tiles of three, where the runs keep 32 steps.  Whole calls with
+    // two, three and four wavefronts per SIMD, us: 16 x 16, 700,000 entries 22.0, 18.8 and 17.9 (from rows of T 47.9, 38.8 and 36.2), 8 x 8
+    // from rows, 400,000 40.0, 32.6 and 31.6, unfactored 4 x 4, 700,000 20.2, 17.3 and 15.7; two tiles: unfactored 12 x 20, 150,000 17.1, 17.7 and
+    // 17.6, 400,000 21.7, 21.6 and 22.6, 700,000 28.8, 26.8 and 29.0, 16 x 32, 700,000 24.9, 23.0 and 23.8; four: 20 x 20, 700,000 39.7, 37.6 and 45.1.
     const int per_run = sh.wl * sh.wm;
     int64_t nruns = std::min<int64_t>(nsteps / 96, p->n_cu * (src == SLICE_ROWS ? 64 : 32) / per_run);
-    nruns = std::max<int64_t>(nruns, std::min<int64_t>((nsteps + 15) / 16, p->n_cu * (tiles <= 2 ? 16 : 8) / per_run));
+    nruns = std::max<int64_t>(nruns, std::min<int64_t>((nsteps + 15) / 16, p->n_cu * (tiles == 1 ? 16 : 8) / per_run));
+    if (tiles == 2) nruns = std::max<int64_t>(nruns, std::min<int64_t>(nsteps / 32, p->n_cu * 12 / per_run));
     if (p->tune.per_cu > 0) nruns = std::min<int64_t>((int64_t)p->n_cu * 4 * p->tune.per_cu, (nsteps + 15) / 16);
     if (p->tune.tn > 0) nruns = std::max<int64_t>(nruns, nsteps / std::max<int64_t>(8, p->tune.tn / 4));
     // rows of T are addressed with 32-bit offsets from the run's first child
