@@ -31,29 +31,29 @@ namespace {
 constexpr int SRC_LEAVES = 0, SRC_ROWS = 1;
 
 // Whether the rows of the output are stored with the non-temporal hint.  Written through the L2s they evict the rows of C and D that the
-// gathers hit there, which costs most where a slice gathers much for what it stores; but stores with the hint are slow in pieces of
-// less than a cache line, and they do not stay in the memory-side cache (256 MB) for whoever reads or writes the output next.  Whole
-// calls on uniform tensors, us without the hint and with it:
-//     entries per slice     3                 9                 20
-//     16 x 32    140 MB     32 and 35         34 and 37         54 and 52 (160 MB)
-//     64 x 64    256 MB     53 and 62         62 and 65         79 and 72
-//                400 MB     93 and 93         98 and 96         129 and 108
-//     16 x 16    256 MB     53 and 60         74 and 70         124 and 90
-//                400 MB     97 and 93         129 and 97
-//     64 x 16    256 MB     52 and 82         56 and 85         74 and 75
-//                400 MB     90 and 135        98 and 125        132 and 109
-//     24 x 100   400 MB     122 and 203       165 and 232       185 and 225
-// From rows of T, which are read once and evict as well: 16 x 16 at 400 MB 168 and 156, 248 and 221; 64 x 64 at 256 MB 73 and 78, 98 and 96.
-// `bytes`: what the slices store, without the rows of empty ones (64 x 32, 20,000 entries in 7,100 of 60,000 rows: call of 129 us with the hint, 117 without).
-bool stores_past_caches(int64_t bytes, int64_t slices, int64_t children, int64_t L, int64_t W, bool rows)
+// gathers hit there, which costs most where a slice gathers much for what it stores, and an output beyond the memory-side cache (256 MB)
+// evicts the rows that the launch before has zeroed there; but stores with the hint are slow in pieces of less than a cache line, and they
+// do not stay in that cache for whoever reads or writes the output next.  Repeated calls on uniform tensors from leaves, us without the hint and
+// with it, at 64 x 64, 16 x 16 and 64 x 16:
+//     entries per slice             1 or 2                    3                         8                         14 to 18
+//     150 to 180 MB                 36,41  35,39  27,31       40,47  38,43  33,48       45,47  41,48  40,51       51,50  61,54  44,44
+//     300 MB, a third stored        64,61  61,60  55,65
+//             all stored                                      69,71  69,69  69,98       70,74  86,77  71,99       79,80  112,81  87,87
+//     400 MB, a third stored        92,70  97,74  92,85
+//             all stored                                      92,92  93,92  88,135      98,95  116,96  102,128    128,122  174,105  139,113
+//     400 MB, more than three quarters of the rows empty, so that the whole output is zeroed first, five entries: 110,121  97,109
+// From rows of T, which are read once and evict as well: 300 MB, 3 per slice, 16 x 16 125 and 118, 64 x 16 101 and 93, 128 x 16 85 and 95; 8 per
+// slice, 128 x 16 126 and 115; 16 x 16 at 180 MB, 14 per slice, 154 and 130.
+bool stores_past_caches(int64_t bytes, bool all_zeroed, int64_t stored, double per_slice, int64_t L, int64_t W, bool rows)
 {
     constexpr int64_t MB = 1 << 20;
-    const double per_slice = (double)children / (double)std::max<int64_t>(slices, 1);
     const bool one_tile = L <= 16 && W <= 16;   // a slice is one piece
     if (W % 16 != 0 && !one_tile) return false;
-    if (bytes > 128 * MB && per_slice >= 16) return true;
-    if (bytes > 256 * MB && per_slice >= 8 && L <= 16) return true;
-    return rows ? bytes > 320 * MB : bytes > 384 * MB && (W % 32 == 0 || one_tile);
+    if (stored > 128 * MB && per_slice >= (one_tile || (rows && L <= 16) ? 12 : 16)) return true;
+    if (bytes <= 256 * MB || all_zeroed) return false;
+    if (rows) return L <= 64 || W > 16 || per_slice >= 8;
+    if (W % 32 != 0 && !one_tile) return false;
+    return bytes > 384 * MB || bytes - stored > bytes / 8 || one_tile || (L <= 16 && per_slice >= 8);
 }
 
 struct SliceArgs {
@@ -98,9 +98,9 @@ __device__ __forceinline__ auto sl_gather(__amdgpu_buffer_rsrc_t rows, uint32_t 
     else return __builtin_bit_cast(Vec, __builtin_amdgcn_raw_buffer_load_b128(rows, off, 0, 0));
 }
 
-// Steps per batch and wavefronts per SIMD by the number of 16 x 16 tiles.  One tile: 45.5 us with eight steps, 43 with four (4 M
-// leaves, 16 x 16); eight tiles: 234 us with eight steps and three wavefronts, 239 to 245 with four steps or two or four wavefronts (6 M
-// leaves, 64 x 32); sixteen: what two wavefronts have registers for.
+// Steps per batch and wavefronts per SIMD by the number of 16 x 16 tiles.  Repeated calls: one tile, 4 M leaves, 46.5 us with eight steps,
+// 43.7 with four; eight tiles, 6 M leaves at 64 x 32, 227 us with eight steps and three wavefronts, 239 with four steps, 240 with two
+// wavefronts, 410 with four, whose registers spill; sixteen: what two wavefronts have registers for.
 constexpr int slice_batch(int tiles) { return tiles == 1 || tiles == 16 ? 4 : 8; }
 constexpr int slice_occupancy(int tiles, bool edge) { return tiles == 16 ? 2 : (tiles == 8 ? 3 : 4) - (edge ? 1 : 0); }
 
@@ -192,7 +192,7 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, EDGE)) slice_kern
 
     // Sums of up to SPAN steps, and sums of those.  One chain of additions over a run, hundreds of steps long in a heavy slice, was up to 2.3
     // times further from the sum in double precision than the tile by tile sums it replaces; so 64 x 64 values are
-    // shared by two wavefronts, though one would hold them once (64 x 32: 234 us, 218 with one set of sums).
+    // shared by two wavefronts, though one would hold them once (64 x 32, 6 M leaves: call of 227 us, 219 with one set of sums).
     constexpr int SPAN = 16;
     sl_floatx4 acc[MT][LT], tot[MT][LT];
     auto clear = [&](auto &v) {
@@ -492,7 +492,8 @@ sc_status launch_slice(const sc_plan *p, Launcher &ln, const sc_csf_view *sp, co
     a.A = static_cast<float *>(out);
     a.L = (int32_t)C.cols;
     a.W = (int32_t)W;
-    a.stream = stores_past_caches(p->nfib[0] * a.L * W * 4, p->nfib[0], T ? p->nfib[1] : p->nnz, a.L, W, T != nullptr);
+    const int64_t children = T ? p->nfib[1] : p->nnz;
+    a.stream = stores_past_caches(p->out_elems * 4, !p->zero_selective, p->nfib[0] * a.L * W * 4, (double)children / (double)std::max<int64_t>(p->nfib[0], 1), a.L, W, T != nullptr);
     ln.begin(name);
     if (T) dispatch_slice<SRC_ROWS>(a, st, ln.stream);
     else dispatch_slice<SRC_LEAVES>(a, st, ln.stream);

@@ -267,11 +267,13 @@ def test_slice_products_longer_chunks(oracle, ranks, which, least, cap):
 
 
 @pytest.mark.parametrize("which,dims,lengths,ranks", [
-    ("fused", (9000, 41, 97), [(i, 17 + i % 7) for i in range(0, 9000, 5)], (64, 64)),       # 147 MB, slices of some length
-    ("fused", (280_000, 41, 97), [(i, 9 + i % 2) for i in range(0, 280_000, 11)], (16, 16)),  # 287 MB
-    ("fused", (26_000, 41, 97), [(i, 1 + i % 7) for i in range(0, 26_000, 5)], (64, 64)),     # 426 MB, short slices
-    ("fissioned", (88_000, 41, 97), [(i, 1 + i % 7) for i in range(0, 88_000, 9)], (64, 16)),  # 360 MB
-    ("fused", (88_000, 41, 97), [(i, 1 + i % 7) for i in range(0, 88_000, 9)], (64, 16))])     # the same through the caches
+    ("fused", (9000, 41, 97), [(i, 17 + i % 7) for i in range(9000)], (64, 64)),               # 147 MB, slices of some length
+    ("fused", (280_000, 41, 97), [(i, 1 + i % 3) for i in range(0, 280_000, 2)], (16, 16)),    # 287 MB, half of it zeroed
+    ("linear", (500_000, 41, 97), [(i, 1 + i % 3) for i in range(0, 500_000, 2)], (12, 12)),   # the same at the edge of a tile
+    ("fused", (26_000, 41, 97), [(i, 1 + i % 7) for i in range(0, 26_000, 2)], (64, 64)),      # 426 MB, short slices
+    ("fused", (26_000, 41, 97), [(i, 1 + i % 7) for i in range(0, 26_000, 5)], (64, 64)),      # all of it zeroed: through the caches
+    ("fissioned", (88_000, 41, 97), [(i, 1 + i % 7) for i in range(0, 88_000, 2)], (64, 16)),  # 360 MB
+    ("fused", (88_000, 41, 97), [(i, 1 + i % 7) for i in range(0, 88_000, 2)], (64, 16))])     # the same through the caches
 def test_slice_products_stored_past_the_caches(oracle, which, dims, lengths, ranks):
     """Outputs on the sides of the rule by which rows are stored with the non-temporal hint."""
     cfg, data = _problem("ttmc3", dims, lengths, ranks)
