@@ -894,15 +894,23 @@ TileCaps default_caps(Kind kind, sc_dtype dtype, sc_sched_kind sched, const int6
 int32_t plan_tile_leaves(const sc_plan *p)
 {
     const int e = p->dtype == SC_F64 ? 8 : 4;
-    // Few entries: tiles small enough for three per compute unit, where the kernels' time falls with the tile's (fp64 sampled product at
-    // rank 64, 20,000 entries: 50 us in tiles of 1024, 16 in tiles of 64; fp64 MTTKRP at rank 64, 100,000 entries: 25 and 16; fp64 chain at
-    // 16 x 16, 5,000 entries: 23 and 15).  Deterministic plans add the pieces of rows that span tiles in two more launches: small tiles
-    // make such rows where large ones had none, so the smallest plans and the FISSIONED ones stay with the large tiles.
+    // Few entries: tiles small enough for three per compute unit, where the kernels' time falls with the tile's.  Calls in large tiles and in
+    // these, us: fp64 sampled product at rank 64, 20,000 entries 42 and 14; fp64 MTTKRP at rank 64, 100,000 25 and 14; fp64 chain, rows of 2 KB, at
+    // 16 x 16 5,000 entries 30 and 20, at 32 x 8 50,000 40 and 25, with W = 16 from 50,000 on even (20 to 28, either ahead by up to a tenth); rows
+    // beyond 2 KB even as well (32 x 32, 20,000 to 100,000: 43 and 43, 60 and 63, 54 and 56).  Deterministic plans add the pieces of rows that span
+    // tiles in two more launches: small tiles make such rows where large ones had none (16 us a call without, 20 with them), so the smallest
+    // plans, MTTKRPs with rows below 128 bytes (100,000 entries in fp32 at rank 16: 23 and 20, and 16 where no row spans) and FISSIONED ones stay with the large tiles.
+    // fp32 at ranks 16 and 32: not below 384 entries.  Smaller tiles are no faster (sampled product 14.5 us in either, MTTKRP at rank 16, 100,000
+    // entries 15.3 in tiles of 192, 14.1 of 384; at rank 8 the MTTKRP needs the small ones, 14 and 20) and add more pieces to a heavy row one after
+    // the other: error against double precision in tiles of 1024, of three per compute unit and of 384, sampled product at rank 16, 20,000
+    // entries 1.31e-7, 1.68e-7 and 1.42e-7, at rank 32 1.35, 1.54 and 1.26, MTTKRP at rank 16, 100,000 1.20, 1.28 and 1.19.  At rank 64 the
+    // small tiles' is the smaller one (1.56 and 1.41, 1.18 and 1.07).
     const bool fused = p->sched == SC_SCHED_FUSED;
     const bool takes = p->kind == K_SDDMM_SPMM ? !p->deterministic || p->nnz >= 32768
                        : p->kind == K_MTTKRP3  ? fused && (!p->deterministic || (p->nnz >= 32768 && p->fcols[0] * e >= 128))
                                                : p->kind == K_TTMC3 && p->dtype == SC_F64 && fused && p->out_row_elems * e <= 2048;
-    const int64_t few = std::max<int64_t>(64, (p->nnz / (3 * p->n_cu) + 63) / 64 * 64);
+    const int64_t least = p->dtype == SC_F32 && (p->fcols[0] == 16 || p->fcols[0] == 32) ? 384 : 64;
+    const int64_t few = std::max<int64_t>(least, (p->nnz / (3 * p->n_cu) + 63) / 64 * 64);
     return takes && 2 * few <= p->caps.tn ? (int32_t)few : p->caps.tn;
 }
 
@@ -939,9 +947,9 @@ sc_status launch_fixup(const sc_plan *p, Launcher &ln, const FixLevel &lv, void 
 }
 
 // fp32 chains of order 3 in every class, and the last kernel of the FISSIONED order-4 chain at 8 x 8, unless the caller asks for a
-// reproducible sum.  Start and now, whole calls in us: 6 M entries at 64 x 32 383 and 234; 4 M at 128 x 128 (inside kernel 5) 1930 and 1060;
-// 1.5 M at 16 x 16 67 and 25, at 8 x 64 147 and 53; unfactored, 1.5 M at 12 x 20 79 and 41, at 4 x 4 45 and 28; 120,000 entries in 38,000
-// slices 23 to 1002 and 15 to 467.  Even at 20,000 entries up to 16 x 32 (launch latency).
+// reproducible sum.  Repeated calls with the kernels over tiles that ran before, and now, us: 6 M entries at 64 x 32 384 and 227; kernel 5 on 4 M
+// entries at 128 x 128 x 128 3411 and 2470; 1.5 M at 16 x 16 54 and 25, at 8 x 64 139 and 49; unfactored, 1.5 M at 12 x 20 78 and 39, at 4 x 4 46
+// and 23; 120,000 entries in 38,000 slices at 16 x 16 25 and 15, at 128 x 128 1083 and 509; 20,000 in 12,600 at 16 x 16 20 and 13, at 64 x 64 79 and 65.
 SliceSource plan_slice_source(const sc_plan *p, int *piece)
 {
     if (piece) *piece = kSlicePiece;
