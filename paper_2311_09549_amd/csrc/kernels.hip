@@ -900,17 +900,16 @@ int32_t plan_tile_leaves(const sc_plan *p)
     // beyond 2 KB even as well (32 x 32, 20,000 to 100,000: 43 and 43, 60 and 63, 54 and 56).  Deterministic plans add the pieces of rows that span
     // tiles in two more launches: small tiles make such rows where large ones had none (16 us a call without, 20 with them), so the smallest
     // plans, MTTKRPs with rows below 128 bytes (100,000 entries in fp32 at rank 16: 23 and 20, and 16 where no row spans) and FISSIONED ones stay with the large tiles.
-    // fp32 at ranks 16 and 32: not below 384 entries.  Smaller tiles are no faster (sampled product 14.5 us in either, MTTKRP at rank 16, 100,000
-    // entries 15.3 in tiles of 192, 14.1 of 384; at rank 8 the MTTKRP needs the small ones, 14 and 20) and add more pieces to a heavy row one after
-    // the other: error against double precision in tiles of 1024, of three per compute unit and of 384, sampled product at rank 16, 20,000
-    // entries 1.31e-7, 1.68e-7 and 1.42e-7, at rank 32 1.35, 1.54 and 1.26, MTTKRP at rank 16, 100,000 1.20, 1.28 and 1.19.  At rank 64 the
-    // small tiles' is the smaller one (1.56 and 1.41, 1.18 and 1.07).
+    // Small tiles add more pieces to a heavy row one after the other, which shows in fp32 at ranks 16 and 32: error against double precision in
+    // tiles of 1024, these and 384, sampled product at rank 16, 20,000 entries, Zipf 1.3, 1.31e-7, 1.68e-7 and 1.42e-7, at rank 32 1.35, 1.54 and
+    // 1.26, MTTKRP at rank 16, 100,000 1.20, 1.28 and 1.19; at rank 64 the small tiles' is the smaller one (1.56 and 1.41, 1.18 and 1.07).  Tiles
+    // of 384 are as fast where the rows are in the caches (14.5 us), but the fewer of them the longer the chains of reads that miss: sampled
+    // product at rank 32, 15,000 entries of 850,000 x 400,000, 32.3 us and 38.9.
     const bool fused = p->sched == SC_SCHED_FUSED;
     const bool takes = p->kind == K_SDDMM_SPMM ? !p->deterministic || p->nnz >= 32768
                        : p->kind == K_MTTKRP3  ? fused && (!p->deterministic || (p->nnz >= 32768 && p->fcols[0] * e >= 128))
                                                : p->kind == K_TTMC3 && p->dtype == SC_F64 && fused && p->out_row_elems * e <= 2048;
-    const int64_t least = p->dtype == SC_F32 && (p->fcols[0] == 16 || p->fcols[0] == 32) ? 384 : 64;
-    const int64_t few = std::max<int64_t>(least, (p->nnz / (3 * p->n_cu) + 63) / 64 * 64);
+    const int64_t few = std::max<int64_t>(64, (p->nnz / (3 * p->n_cu) + 63) / 64 * 64);
     return takes && 2 * few <= p->caps.tn ? (int32_t)few : p->caps.tn;
 }
 
