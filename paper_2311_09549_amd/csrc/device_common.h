@@ -248,12 +248,14 @@ sc_status launch_fixup(const sc_plan *p, Launcher &ln, const FixLevel &lv, void 
 sc_status launch_slice(const sc_plan *p, Launcher &ln, const sc_csf_view *sp, const sc_dense_view &C, const sc_dense_view *D, const void *T,
                        int64_t W, void *out, const char *name);
 
+// Order-4 TTM chain at 8 x 8, fp32, FUSED, from the leaves in one pass over steps (kernels_chain4.hip).
+sc_status launch_chain4(const sc_plan *p, Launcher &ln, const sc_csf_view *sp, const sc_dense_view *fac, void *out);
+
 // Order-4 TTM chain on matrix cores (fp32, M = N = 8, L <= 16; its own kernel file): mode 0 the FUSED schedule,
 // modes 1 and 2 the second and third kernel of the FISSIONED one.
 size_t ttmc4_mfma_lds_bytes(const sc_plan *p);
 WalkShape ttmc4_mfma_walk_shape();
 bool ttmc4_mfma_caps_ok(const sc_plan *p);
-int ttmc4_mfma_run(const sc_plan *p, int mode, bool one_tile_per_workgroup);
 sc_status launch_ttmc4_mfma(const sc_plan *p, Launcher &ln, const sc_csf_view *sp, const sc_dense_view *fac, int mode, const void *T1,
                             void *T2, void *out, void *partials);
 

@@ -573,14 +573,16 @@ sc_status build_walk_tables(sc_plan *p, const sc_csf_view *v, const HostCsf &h, 
 struct SlicePart {
     std::vector<SliceChunk> chunks;   // step0 and group0 from the part's first
     std::vector<uint32_t> leaf, at;
-    std::vector<int32_t> gj, first;
-    int32_t nsteps = 0, ngroups = 0;
+    std::vector<int32_t> gj, first, gk;
+    std::vector<ChainChunk> kids;     // kid0 from the part's first
+    int32_t nsteps = 0, ngroups = 0, nkids = 0;
     bool failed = false;              // out of memory
 };
 struct SliceBuild {
     std::vector<SlicePart> parts;
     std::vector<SliceRun> runs;
     std::vector<SliceChunk> chunks;
+    std::vector<ChainChunk> kids;
     std::vector<int32_t> cut_rows;   // output rows of the slices that a run's end cuts
 };
 
@@ -733,6 +735,171 @@ void list_steps(SliceSource src, int piece, int cap, const HostCsf &h, int64_t s
     flush(0, 0);
 }
 
+// Pieces of (i,j) fibers of one slice on their way into a chunk of a chain of order 4.
+struct ChainPieces {
+    struct Kid { int32_t z, len, k; };
+    struct Piece { uint64_t key; int32_t first, stride, n, j; };   // children kids[first], kids[first + stride] ...
+    Kid kids[256];
+    Piece pieces[256];
+    int32_t nkids, npieces;
+    // where the leaves that were taken end: leaf, (i,j,k) fiber, (i,j) fiber
+    int32_t z, f3, f2;
+
+    // Takes the leaves [z, z1) of one slice, z in the (i,j,k) fiber f3 of the (i,j) fiber f2.
+    void take(const HostCsf &h, int32_t z1)
+    {
+        const int32_t *pos2 = h.pos[2], *pos3 = h.pos[3], *crd1 = h.crd[1], *crd2 = h.crd[2];
+        nkids = npieces = 0;
+        while (z < z1) {
+            const int32_t first = nkids;
+            int32_t count[kSlicePiece + 2] = {0};
+            while (z < z1 && f3 < pos2[f2 + 1]) {
+                const int32_t len = std::min(std::min(pos3[f3 + 1], z1) - z, kSlicePiece);
+                kids[nkids++] = Kid{z, len, crd2[f3]};
+                ++count[len];
+                z += len;
+                if (z == pos3[f3 + 1]) ++f3;
+            }
+            const int32_t n = nkids - first;
+            if (count[1] < n) {   // longest first
+                Kid was[256];
+                std::copy(kids + first, kids + nkids, was);
+                int32_t at[kSlicePiece + 2] = {0};
+                for (int len = kSlicePiece - 1; len > 0; --len) at[len] = at[len + 1] + count[len + 1];
+                for (int32_t i = 0; i < n; ++i) kids[first + at[was[i].len]++] = was[i];
+            }
+            const int32_t np = (n + kChainPiece - 1) / kChainPiece;   // dealt out in turn
+            for (int32_t i = 0; i < np; ++i) {
+                Piece &pc = pieces[npieces++];
+                pc = Piece{0, first + i, np, (n - i + np - 1) / np, crd1[f2]};
+                // by the number of children, then by their lengths
+                pc.key = (uint64_t)pc.n << 60;
+                for (int32_t u = 0; u < pc.n; ++u) pc.key |= (uint64_t)(kids[pc.first + u * np].len - 1) << (56 - 4 * u);
+            }
+            if (f3 == pos2[f2 + 1]) ++f2;
+        }
+        std::sort(pieces, pieces + npieces, [](const Piece &a, const Piece &b) { return a.key != b.key ? a.key > b.key : a.first < b.first; });
+    }
+    int32_t longest(int32_t g, int32_t u) const   // leaves of the u-th children of the group that starts at piece g
+    {
+        int32_t most = 0;
+        for (int32_t q = g; q < std::min(g + 4, npieces) && u < pieces[q].n; ++q) most = std::max(most, kids[pieces[q].first + u * pieces[q].stride].len);
+        return most;
+    }
+    int32_t steps(int32_t from) const   // ... of a chunk, after `from` others
+    {
+        int32_t s = from;
+        for (int32_t g = 0; g < npieces; g += 4)
+            for (int32_t u = 0; u < pieces[g].n; ++u) {
+                const int32_t most = longest(g, u);
+                s = most > 1 ? (s + 1) / 2 * 2 + (most + 1) / 2 * 2 : s + 1;
+            }
+        return s;
+    }
+};
+
+// Lists the steps of the slices [s0, s1) of a chain of order 4, in chunks of at most `cap`.
+void list_chain(int cap, const HostCsf &h, int64_t s0, int64_t s1, SlicePart &b)
+{
+    const int32_t *pos1 = h.pos[1], *pos2 = h.pos[2], *pos3 = h.pos[3], *crd3 = h.crd[3];
+    SliceChunk c = {};
+    ChainChunk k = {};
+    // Steps without leaves so far; together: of children of several leaves, which end in the last of them.
+    auto add_steps = [&](int32_t n, bool together = false) {
+        b.leaf.resize(b.leaf.size() + 4 * (size_t)n, 0xffffffffu);
+        b.at.resize(b.at.size() + (size_t)n, 0xffffffffu);
+        if (c.nsteps % 2 == 0) {   // a pair that ends, or several of which the last does
+            b.gk.resize(b.gk.size() + 8, -1);
+            ++b.nkids;
+            ++k.nkids;
+            k.kend |= 2ull << (c.nsteps + (together ? n - 2 : 0));
+        }
+        b.nsteps += n;
+        c.nsteps += n;
+    };
+    auto flush = [&](int32_t next_leaf, int32_t next_slice) {
+        if (c.nsteps) {
+            if (c.nsteps % kChainBatch) {   // whole batches: the last group (and slice) ends with the chunk
+                const uint64_t last = 1ull << (c.nsteps - 1);
+                const bool group = c.gend & last, slice = c.send & last;
+                if (c.nsteps % 2) add_steps(1);
+                if (c.nsteps % kChainBatch) add_steps(kChainBatch - c.nsteps % kChainBatch, true);
+                const uint64_t end = 1ull << (c.nsteps - 1);
+                if (group) c.gend ^= last | end;
+                if (slice) c.send ^= last | end;
+            }
+            b.chunks.push_back(c);
+            b.kids.push_back(k);
+        }
+        c = SliceChunk{};
+        k = ChainChunk{};
+        c.step0 = b.nsteps;
+        c.leaf0 = next_leaf;
+        c.group0 = b.ngroups;
+        c.slice0 = next_slice;
+        k.kid0 = b.nkids;
+    };
+    c.slice0 = (int32_t)s0;
+    c.leaf0 = pos3[pos2[pos1[s0]]];
+    const size_t leaves = (size_t)(pos3[pos2[pos1[s1]]] - c.leaf0), kids = (size_t)(pos2[pos1[s1]] - pos2[pos1[s0]]);
+    b.leaf.reserve(leaves * 5 / 4 + 1024);
+    b.at.reserve(leaves * 5 / 16 + 256);
+    b.gk.reserve(kids * 5 / 4 + 1024);
+    b.gj.reserve((size_t)(pos1[s1] - pos1[s0]) * 5 / 4 + kids / 8 + 1024);
+    ChainPieces w, next;
+    next.z = c.leaf0;
+    next.f3 = pos2[pos1[s0]];
+    next.f2 = pos1[s0];
+    for (int64_t s = s0; s < s1; ++s) {
+        const int32_t zend = pos3[pos2[pos1[s + 1]]];
+        // a slice longer than what is left of a chunk starts the next one, unless much is left
+        if (cap - c.nsteps < 8 && (zend - next.z) / 4 >= cap - c.nsteps) flush(next.z, (int32_t)s);
+        while (next.z < zend) {
+            // as many leaves as make steps for what is left of the chunk
+            const int32_t room = cap - c.nsteps;
+            int32_t n = std::min(zend - next.z, 4 * room), steps;
+            for (;;) {
+                w.z = next.z, w.f3 = next.f3, w.f2 = next.f2;
+                w.take(h, next.z + n);
+                steps = w.steps(c.nsteps) - c.nsteps;
+                if (steps <= room) break;
+                n = std::max(1, std::min(n - 1, (int32_t)((int64_t)n * room / steps)));
+            }
+            for (int32_t g = 0; g < w.npieces; g += 4) {
+                for (int32_t u = 0; u < w.pieces[g].n; ++u) {
+                    const int32_t most = w.longest(g, u);
+                    if (most > 1 && c.nsteps % 2) add_steps(1);
+                    const size_t o = b.leaf.size();
+                    add_steps(most > 1 ? (most + 1) / 2 * 2 : 1, most > 1);
+                    uint8_t *place = reinterpret_cast<uint8_t *>(b.at.data()) + o;
+                    int32_t *gk = b.gk.data() + b.gk.size() - 8 + (most > 1 ? 0 : 4 * ((c.nsteps + 1) % 2));
+                    for (int32_t q = 0; q < 4 && g + q < w.npieces; ++q) {
+                        const ChainPieces::Piece &pc = w.pieces[g + q];
+                        if (u >= pc.n) continue;
+                        const ChainPieces::Kid &kid = w.kids[pc.first + u * pc.stride];
+                        gk[q] = kid.k;
+                        if (kid.len > 1) gk[4 + q] = kid.k;   // (no leaf in a second step: no row, whose infinities would meet a zero)
+                        for (int32_t x = 0; x < kid.len; ++x) {
+                            b.leaf[o + 4 * (size_t)x + q] = (uint32_t)crd3[kid.z + x];
+                            place[4 * x + q] = (uint8_t)(kid.z + x - c.leaf0);
+                        }
+                    }
+                }
+                for (int32_t q = 0; q < 4; ++q) b.gj.push_back(g + q < w.npieces ? w.pieces[g + q].j : -1);
+                ++b.ngroups;
+                ++c.ngroups;
+                c.gend |= 1ull << (c.nsteps - 1);
+            }
+            c.nleaves += n;
+            next.z = w.z, next.f3 = w.f3, next.f2 = w.f2;
+            if (next.z < zend) flush(next.z, (int32_t)s);
+        }
+        c.send |= 1ull << (c.nsteps - 1);
+        if (c.nsteps == cap) flush(next.z, (int32_t)s + 1);
+    }
+    flush(0, 0);
+}
+
 // Lists the steps of a plan's slice products and cuts them into runs of equal work.
 void build_slices(const sc_plan *p, SliceSource src, int piece, const HostCsf &h, SliceBuild &b)
 {
@@ -741,8 +908,8 @@ void build_slices(const sc_plan *p, SliceSource src, int piece, const HostCsf &h
     int cap = 64;
     while (cap > 16 && (src == SLICE_ROWS ? children : p->nnz) < (int64_t)4 * cap * 8 * p->n_cu) cap /= 2;
     // A thread per 256,000 leaves (children), at most eight; ranges of slices with about equal numbers of them.
-    const int32_t *pos1 = h.pos[1], *pos2 = src == SLICE_ROWS ? nullptr : h.pos[2];
-    auto before = [&](int64_t s) { return (int64_t)(pos2 ? pos2[pos1[s]] : pos1[s]); };
+    const int32_t *pos1 = h.pos[1], *pos2 = src == SLICE_ROWS ? nullptr : h.pos[2], *pos3 = src == SLICE_CHAIN ? h.pos[3] : nullptr;
+    auto before = [&](int64_t s) { return (int64_t)(pos3 ? pos3[pos2[pos1[s]]] : pos2 ? pos2[pos1[s]] : pos1[s]); };
     const int64_t units = before(S);
     const int64_t most_threads = std::max<int64_t>(1, std::min<int64_t>(8, std::thread::hardware_concurrency()));
     const int64_t nparts = std::max<int64_t>(1, std::min(units / 256000, most_threads));
@@ -759,7 +926,8 @@ void build_slices(const sc_plan *p, SliceSource src, int piece, const HostCsf &h
     b.parts.resize(from.size() - 1);
     auto work = [&](size_t n) {
         try {
-            list_steps(src, piece, cap, h, from[n], from[n + 1], b.parts[n]);
+            if (src == SLICE_CHAIN) list_chain(cap, h, from[n], from[n + 1], b.parts[n]);
+            else list_steps(src, piece, cap, h, from[n], from[n + 1], b.parts[n]);
         } catch (...) { b.parts[n].failed = true; }
     };
     std::vector<std::thread> threads;
@@ -772,7 +940,7 @@ void build_slices(const sc_plan *p, SliceSource src, int piece, const HostCsf &h
     work(0);
     for (; own < b.parts.size(); ++own) work(own);
     for (std::thread &t : threads) t.join();
-    int32_t nsteps = 0, ngroups = 0;
+    int32_t nsteps = 0, ngroups = 0, nkids = 0;
     for (SlicePart &part : b.parts) {
         if (part.failed) throw std::bad_alloc();
         for (SliceChunk k : part.chunks) {
@@ -780,8 +948,13 @@ void build_slices(const sc_plan *p, SliceSource src, int piece, const HostCsf &h
             k.group0 += ngroups;
             b.chunks.push_back(k);
         }
+        for (ChainChunk k : part.kids) {
+            k.kid0 += nkids;
+            b.kids.push_back(k);
+        }
         nsteps += part.nsteps;
         ngroups += part.ngroups;
+        nkids += part.nkids;
     }
     if (src == SLICE_ROWS) b.parts.back().first.push_back((int32_t)children);
 
@@ -790,7 +963,7 @@ void build_slices(const sc_plan *p, SliceSource src, int piece, const HostCsf &h
     const int64_t L = p->fcols[0], W = p->kind == K_TTMC4 ? p->fcols[1] * p->fcols[2] : p->fcols[1];
     const SliceShape sh = slice_shape(L, W);
     const int64_t tiles = (int64_t)sh.lt * sh.mt;
-    const double w_step = 6 + sh.mt, w_group = 6 + 8 * tiles, w_slice = 8 + 4 * tiles, w_chunk = 60;
+    const double w_step = src == SLICE_CHAIN ? 9 : 6 + sh.mt, w_group = 6 + 8 * tiles, w_slice = 8 + 4 * tiles, w_chunk = 60;   // (of a chain: half of the steps end children)
     auto cost = [&](const SliceChunk &k) {
         const int g = src == SLICE_ROWS ? k.nsteps : k.ngroups;
         return w_step * k.nsteps + w_group * g + w_slice * __builtin_popcountll(k.send) + w_chunk;
@@ -811,6 +984,7 @@ void build_slices(const sc_plan *p, SliceSource src, int piece, const HostCsf &h
     if (p->tune.tn > 0) nruns = std::max<int64_t>(nruns, nsteps / std::max<int64_t>(8, p->tune.tn / 4));
     // rows of T are addressed with 32-bit offsets from the run's first child
     const int64_t most = src == SLICE_ROWS ? ((int64_t)1 << 31) / (4 * 4 * W) - 64 : (int64_t)nsteps;
+    const int32_t grain = src == SLICE_CHAIN ? kChainBatch : 8;   // steps between the places where a run may begin: a batch
     double done = 0;
     int32_t run_step0 = 0;
     bool open = false;   // the step before was not the last of its slice
@@ -818,8 +992,8 @@ void build_slices(const sc_plan *p, SliceSource src, int piece, const HostCsf &h
         const SliceChunk &k = b.chunks[n];
         const double per_step = cost(k) / k.nsteps;
         int32_t slice = k.slice0;
-        for (int32_t s = 0; s < k.nsteps; s += 8) {
-            const int32_t here = std::min(8, k.nsteps - s);
+        for (int32_t s = 0; s < k.nsteps; s += grain) {
+            const int32_t here = std::min(grain, k.nsteps - s);
             if (b.runs.empty() || done >= total * (double)b.runs.size() / (double)nruns || k.step0 + s - run_step0 + here > most) {
                 b.runs.push_back(SliceRun{(int32_t)n, s, open ? 1 : 0, 0});
                 run_step0 = k.step0 + s;
@@ -834,6 +1008,7 @@ void build_slices(const sc_plan *p, SliceSource src, int piece, const HostCsf &h
     }
     b.runs.push_back(SliceRun{(int32_t)b.chunks.size(), 0, 0, 0});
     b.chunks.push_back(SliceChunk{});   // the chunk after the last is read, not worked on
+    if (src == SLICE_CHAIN) b.kids.push_back(ChainChunk{});
 }
 
 sc_status upload_slices(sc_plan *p, const SliceBuild &b)
@@ -861,7 +1036,8 @@ sc_status upload_slices(sc_plan *p, const SliceBuild &b)
         return true;
     };
     if (!upload(&t.d_runs, b.runs) || !upload(&t.d_chunks, b.chunks) || !upload_parts(&t.d_leaf, &SlicePart::leaf) ||
-        !upload_parts(&t.d_at, &SlicePart::at) || !upload_parts(&t.d_gj, &SlicePart::gj) || !upload_parts(&t.d_first, &SlicePart::first))
+        !upload_parts(&t.d_at, &SlicePart::at) || !upload_parts(&t.d_gj, &SlicePart::gj) || !upload_parts(&t.d_first, &SlicePart::first) ||
+        !upload_parts(&t.d_gk, &SlicePart::gk) || (!b.kids.empty() && !upload(&t.d_kids, b.kids)))
         return SC_ERR_DEVICE;
     appendf(p->text, "slice products: %d runs of %zu chunks, %zu bytes of plan-owned device tables\n", t.nruns, b.chunks.size() - 1, total);
     return SC_OK;
@@ -901,23 +1077,11 @@ void list_rows_to_zero(sc_plan *p, const HostCsf &h, const std::vector<int32_t> 
     if (cut_rows) {   // slice products: the slices that a run's end cuts
         p->zero_rows.insert(p->zero_rows.end(), cut_rows->begin(), cut_rows->end());
     } else if (!p->deterministic) {
-        // Kernels that take one tile per workgroup add every piece of a spanning slice atomically.  The persistent
-        // kernels keep such a slice in registers from tile to tile of a run and add only what crosses a run's end.
-        const int run = plan_output_run(p);
-        int32_t last_listed = -1;
-        for (size_t n = 0; n < p->tiles.size(); ++n) {
-            const TileRec &t = p->tiles[n];
+        // every piece of a spanning slice is added atomically
+        for (const TileRec &t : p->tiles) {
             const TopLevel tl = top_level(p->order, t);
-            if (!tl.out) continue;
-            const int32_t row = h.crd[0][tl.top0 + tl.ntop - 1];
-            if (run > 0) {
-                if ((n + 1) % (size_t)run != 0) continue;        // continues inside the run
-                if (row == last_listed) continue;                // a slice crossing several runs' ends is listed once
-            } else if (tl.in && tl.ntop == 1) {
-                continue;                                        // listed where the slice starts
-            }
-            p->zero_rows.push_back(row);
-            last_listed = row;
+            if (!tl.out || (tl.in && tl.ntop == 1)) continue;   // (listed where the slice starts)
+            p->zero_rows.push_back(h.crd[0][tl.top0 + tl.ntop - 1]);
         }
     }
     p->zero_selective = (int64_t)p->zero_rows.size() * 4 <= rows * 3;
@@ -1822,7 +1986,7 @@ static sc_status plan_create_impl(sc_plan **out, const char *expr, const sc_csf_
         if (failed) return SC_ERR_ALLOC;
     }
     // what the device reads of the tiles: nothing where slice products from the leaves are all that runs
-    const bool tiles_read = !(sliced && src == SLICE_LEAVES);
+    const bool tiles_read = !(sliced && (src == SLICE_LEAVES || src == SLICE_CHAIN));
     try {
         if (p->deterministic) {
             if (!plan_supports_deterministic(p)) return SC_ERR_SCHED_UNSUPPORTED;
@@ -1905,7 +2069,7 @@ static sc_status plan_create_impl(sc_plan **out, const char *expr, const sc_csf_
     case K_TTMC4:
         appendf(tx, "nest: two-level where: %s from leaves, %s from %s, output from %s (%s)\n", p->inter[0].name.c_str(),
                 p->inter[1].name.c_str(), p->inter[0].name.c_str(), p->inter[1].name.c_str(),
-                p->sched == SC_SCHED_FUSED ? "both per tile in LDS" : "both in the workspace");
+                p->sched == SC_SCHED_FISSIONED ? "both in the workspace" : src == SLICE_CHAIN ? "both in registers" : "both per tile in LDS");
         break;
     case K_TTMC_ALL:
     case K_MTTKRP_GEMM:
@@ -2174,7 +2338,7 @@ extern "C" sc_status sc_plan_destroy(sc_plan *plan)
         if (r) (void)hipFree(r);
     if (plan->walk.d_heads) (void)hipFree(plan->walk.d_heads);
     const sck::SliceTables &sl = plan->slice;
-    for (void *d : {(void *)sl.d_runs, (void *)sl.d_chunks, (void *)sl.d_leaf, (void *)sl.d_at, (void *)sl.d_gj, (void *)sl.d_first})
+    for (void *d : {(void *)sl.d_runs, (void *)sl.d_chunks, (void *)sl.d_leaf, (void *)sl.d_at, (void *)sl.d_gj, (void *)sl.d_first, (void *)sl.d_kids, (void *)sl.d_gk})
         if (d) (void)hipFree(d);
     for (sck::FixLevel *lv : {&plan->det_top, &plan->det_a, &plan->det_b}) {
         if (lv->d_fix) (void)hipFree(lv->d_fix);

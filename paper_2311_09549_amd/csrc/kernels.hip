@@ -957,7 +957,8 @@ SliceSource plan_slice_source(const sc_plan *p, int *piece)
         if (p->sched == SC_SCHED_LINEAR && piece) *piece = 1;   // nothing is factored out: every stored entry is a piece
         return p->sched == SC_SCHED_FISSIONED ? SLICE_ROWS : SLICE_LEAVES;
     }
-    if (p->kind == K_TTMC4 && p->sched == SC_SCHED_FISSIONED && p->fcols[0] <= 16 && p->fcols[1] == 8 && p->fcols[2] == 8) return SLICE_ROWS;
+    if (p->kind == K_TTMC4 && p->sched != SC_SCHED_LINEAR && p->fcols[0] <= 16 && p->fcols[1] == 8 && p->fcols[2] == 8)
+        return p->sched == SC_SCHED_FISSIONED ? SLICE_ROWS : SLICE_CHAIN;
     return SLICE_NONE;
 }
 
@@ -968,18 +969,10 @@ bool plan_wants_tensor_order(const sc_plan *p)
     return p->kind == K_TTMC4 && p->fcols[0] <= 16 && p->fcols[1] == 8 && p->fcols[2] == 8;   // the matrix-core kernels of the order-4 chain
 }
 
-int plan_output_run(const sc_plan *p)
-{
-    if (p->sched != SC_SCHED_FUSED && p->sched != SC_SCHED_FISSIONED) return 0;
-    if (p->deterministic) return 0;   // one tile per workgroup, pieces in slots: no row is added to
-    const bool fused = p->sched == SC_SCHED_FUSED;
-    if (p->kind == K_TTMC4 && fused && plan_wants_tensor_order(p)) return ttmc4_mfma_run(p, 0, false);
-    return 0;
-}
-
 WalkShape plan_walk_shape(const sc_plan *p)
 {
-    if (p->sched == SC_SCHED_LINEAR || plan_slice_source(p, nullptr) == SLICE_LEAVES) return WalkShape{};
+    const SliceSource src = plan_slice_source(p, nullptr);
+    if (p->sched == SC_SCHED_LINEAR || src == SLICE_LEAVES || src == SLICE_CHAIN) return WalkShape{};
     if (p->kind == K_TTMC4 && plan_wants_tensor_order(p)) return ttmc4_mfma_walk_shape();   // its leaf level also serves the traversal kernel
     if (p->kind == K_TTMC3 && p->sched == SC_SCHED_FUSED && plan_wants_tensor_order(p)) return ttmc3_mfma_walk_shape();
     // FISSIONED, order >= 3: the leaf traversal, whose rows are as wide as the last factor
@@ -1032,6 +1025,7 @@ size_t lds_bytes_used(const sc_plan *p)
 {
     const SliceSource src = plan_slice_source(p, nullptr);
     if (src == SLICE_LEAVES) return kSliceLdsBytes;
+    if (src == SLICE_CHAIN) return kChainLdsBytes;
     if (src == SLICE_ROWS && p->kind == K_TTMC3) return std::max(kSliceLdsBytes, leaf_traverse_lds_bytes(p, (int)p->fcols[1]));
     return lds_bytes_needed(p);   // (the order-4 chain: its first two kernels need more than the slice product)
 }

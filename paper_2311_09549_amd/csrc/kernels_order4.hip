@@ -243,7 +243,9 @@ sc_status run_order4(const sc_plan *p, const sc_csf_view *sp, const sc_dense_vie
     const size_t lds = order4_lds_bytes<T>(N, M * N, a.L, a.tn, a.ta, a.tb);
     const bool mfma = sizeof(T) == 4 && a.L <= 16 && M == 8 && N == 8;   // the matrix-core kernel (fp32, M = N = 8)
     if (p->sched == SC_SCHED_FUSED) {
-        if (mfma) {
+        if (plan_slice_source(p, nullptr) == SLICE_CHAIN) {
+            return launch_chain4(p, ln, sp, fac, out);
+        } else if (mfma) {
             void *partials = p->deterministic && ws ? static_cast<char *>(ws) + p->det_top.slot_offset : nullptr;
             ln.status = launch_ttmc4_mfma(p, ln, sp, fac, 0, nullptr, nullptr, out, partials);   // dedicated matrix-core kernel
             if (ln.status != SC_OK) return ln.status;

@@ -20,7 +20,7 @@
 // is added to the zeroed row atomically, after the runs of a workgroup that lie inside one slice have been added up in LDS.  A chunk is staged
 // in a region of LDS of the wavefront's own ({row offset, value} per leaf, offset of C(j,:) per child), read a chunk ahead; the loop
 // then takes U steps per batch, whose gathers are all issued before the first is used.
-#include "device_common.h"
+#include "slice_common.h"
 
 #include <type_traits>
 
@@ -73,31 +73,6 @@ struct SliceArgs {
     int32_t stream;              // the output is stored past the L2s
 };
 
-typedef float sl_floatx4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ int sl_uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
-
-// Rows are gathered through buffer descriptors: a read past the descriptor's end returns zero and touches no memory.  A place of a step that
-// no child takes has the coordinate kNoRow, whose byte offset lies past the end of every matrix (they are smaller than 2 GiB; the offset
-// is 2^32 less one row, and the lane's part of the row does not carry it over).  So it counts as 0 * 0: with some row that exists and
-// a zero factor, an infinity or a NaN in that row would reach outputs that do not refer to it.
-constexpr int kNoRow = -1;
-constexpr uint32_t kMostBytes = 0x80000000u;
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t sl_rows(const void *base, uint32_t bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);   // untyped, 32-bit
-}
-
-template <int N>
-__device__ __forceinline__ auto sl_gather(__amdgpu_buffer_rsrc_t rows, uint32_t off)
-{
-    typedef float Vec __attribute__((ext_vector_type(N)));
-    if constexpr (N == 1) return __builtin_bit_cast(Vec, __builtin_amdgcn_raw_buffer_load_b32(rows, off, 0, 0));
-    else if constexpr (N == 2) return __builtin_bit_cast(Vec, __builtin_amdgcn_raw_buffer_load_b64(rows, off, 0, 0));
-    else return __builtin_bit_cast(Vec, __builtin_amdgcn_raw_buffer_load_b128(rows, off, 0, 0));
-}
-
 // Steps per batch and wavefronts per SIMD by the number of 16 x 16 tiles.  Repeated calls: one tile, 4 M leaves, 46.5 us with eight steps,
 // 43.7 with four; eight tiles, 6 M leaves at 64 x 32, 227 us with eight steps and three wavefronts, 239 with four steps, 240 with two
 // wavefronts, 410 with four, whose registers spill; sixteen: what two wavefronts have registers for.
@@ -129,8 +104,8 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, EDGE)) slice_kern
         float sum[2][RPB > 1 ? 256 * LT * MT : 4];   // after the runs: sums on their way to another wavefront
     };
     __shared__ Lds lds;
-    __shared__ int inside_s[WAVES];
-    static_assert(sizeof(Lds) + sizeof(inside_s) <= kSliceLdsBytes, "LDS the plan reports");
+    __shared__ int state_s[WAVES];
+    static_assert(sizeof(Lds) + sizeof(state_s) <= kSliceLdsBytes, "LDS the plan reports");
 
     const int wave = sl_uni(threadIdx.x / 64), lane = threadIdx.x % 64;
     const int kk = lane / 16, col = lane % 16;
@@ -219,11 +194,6 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, EDGE)) slice_kern
                 acc[x][y] = TURNED ? __builtin_amdgcn_mfma_f32_16x16x4f32(tv[x], cv[y], acc[x][y], 0, 0, 0)
                                    : __builtin_amdgcn_mfma_f32_16x16x4f32(cv[y], tv[x], acc[x][y], 0, 0, 0);
     };
-    // what the lanes of the wavefront wrote to LDS is there for its other lanes, and what they read may be overwritten
-    auto lanes_meet = [] {
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-    };
     // acc[x][y][q] = A(l = l0 + LT (4 kk + q) + y, m = lm + x): a store instruction covers four rows l of 16 MT adjacent floats.
     // One tile: acc[0][0][q] = A(l = col, m = 4 kk + q), one store instruction for the slice (from rows of T at 16 x 16, 150,000 entries in
     // 55,000 slices: 24.5 us the other way and 21 so; at 64 x 16, 400 MB, two to four rows apart in the same layout 98 and 104).
@@ -241,9 +211,9 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, EDGE)) slice_kern
                 }
             } else {
                 // adjacent lanes on adjacent floats: the four of a lane one after the other visit every cache line four times
-                lanes_meet();
+                sl_lanes_meet();
                 *reinterpret_cast<sl_floatx4 *>(swap_s + 16 * col + 4 * kk) = acc[0][0];
-                lanes_meet();
+                sl_lanes_meet();
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int l = 4 * q + kk;
@@ -270,9 +240,9 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, EDGE)) slice_kern
                 } else {
                     // adjacent lanes on adjacent floats: an addition of MT floats per lane visits every cache line MT times
                     if (MT > 1) {
-                        lanes_meet();
+                        sl_lanes_meet();
                         *reinterpret_cast<TVec *>(swap_s + MT * lane) = o;
-                        lanes_meet();
+                        sl_lanes_meet();
                     }
 #pragma unroll
                     for (int x = 0; x < MT; ++x) {
@@ -297,10 +267,10 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, EDGE)) slice_kern
         auto row_at = [&](int x, uint32_t row) { return (uint32_t)(live ? x : kNoRow) * row; };
         if (SRC == SRC_LEAVES) {
             const int nl = ch.nleaves;
-            lanes_meet();
+            sl_lanes_meet();
 #pragma unroll
             for (int q = 0; q < 4; ++q) swap_s[64 * q + lane] = 64 * q + lane < nl ? st.v[q] : 0.f;   // place 255 is zero in a chunk of fewer leaves
-            lanes_meet();
+            sl_lanes_meet();
             float v[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) v[q] = swap_s[st.at >> 8 * q & 255];
@@ -309,7 +279,7 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, EDGE)) slice_kern
             dst[0] = uint4{row_at(st.leaf.x, a.rowD), word(v[0]), row_at(st.leaf.y, a.rowD), word(v[1])};
             dst[1] = uint4{row_at(st.leaf.z, a.rowD), word(v[2]), row_at(st.leaf.w, a.rowD), word(v[3])};
         } else {
-            lanes_meet();
+            sl_lanes_meet();
 #pragma unroll
             for (int q = 0; q < 4; ++q)   // (steps before the run's first are not read)
                 rec_s[4 * lane + q].off = row_at(st.f0 + q < st.f1 ? st.f0 + q - fbase : kNoRow, a.rowD);
@@ -319,7 +289,7 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, EDGE)) slice_kern
         }
         reinterpret_cast<uint4 *>(coff_s)[lane] =
             uint4{row_at(st.j.x, a.rowC), row_at(st.j.y, a.rowC), row_at(st.j.z, a.rowC), row_at(st.j.w, a.rowC)};
-        lanes_meet();
+        sl_lanes_meet();
         ch = chunks[c + 1];
         if (c + 1 < c_end) issue(ch, st);
 
@@ -380,42 +350,8 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, EDGE)) slice_kern
             gather_sums(acc, tot);
         }
     }
-    // What is left of a slice that goes on in the next run.  Runs that lie inside one slice are added up inside the workgroup first,
-    // in two rounds (0 to 1 and 2 to 3, then the pair 0, 1 to the last that follows it); the rest goes to the slice's row atomically.
     if constexpr (RPB > 1) {
-        const int rw = wave / WPR;
-        const bool inside = goes_on && open && sl == slice0;
-        if (lane == 0) inside_s[wave] = (goes_on ? 1 : 0) | (inside ? 2 : 0);
-        __syncthreads();
-        auto state = [&](int n) { return sl_uni(inside_s[n * WPR]); };
-        // run n's sum goes to run n + 1
-        auto pass = [&](int n) { return n + 1 < RPB && (state(n) & 1) && (state(n + 1) & 2); };
-        auto send_to = [&](float *buf) {
-#pragma unroll
-            for (int x = 0; x < MT; ++x)
-#pragma unroll
-                for (int y = 0; y < LT; ++y) *reinterpret_cast<sl_floatx4 *>(buf + (x * LT + y) * 256 + 4 * lane) = acc[x][y];
-        };
-        auto add_from = [&](const float *buf) {
-#pragma unroll
-            for (int x = 0; x < MT; ++x)
-#pragma unroll
-                for (int y = 0; y < LT; ++y) acc[x][y] += *reinterpret_cast<const sl_floatx4 *>(buf + (x * LT + y) * 256 + 4 * lane);
-        };
-        const bool mine = rw % 2 == 0 && pass(rw), theirs = rw % 2 == 1 && pass(rw - 1);
-        if (mine) send_to(lds.sum[wave / (2 * WPR) * WPR + sub]);
-        __syncthreads();
-        if (theirs) add_from(lds.sum[wave / (2 * WPR) * WPR + sub]);
-        goes_on = goes_on && !mine;
-        if constexpr (RPB == 4) {
-            __syncthreads();
-            const bool across = pass(1);
-            const int to = pass(2) ? 3 : 2;
-            if (across && rw == 1) send_to(lds.sum[0]);
-            __syncthreads();
-            if (across && rw == to) add_from(lds.sum[0]);
-            goes_on = goes_on && !(across && rw == 1);
-        }
+        sl_sum_runs<RPB, WPR, MT * LT>(reinterpret_cast<sl_floatx4 (&)[MT * LT]>(acc), goes_on, open && sl == slice0, lds.sum, state_s, wave, lane);
         if (MT > 1 || TURNED) __syncthreads();   // the sums have been read: their space is the staging regions again
     }
     if (goes_on) emit(last_row, std::integral_constant<int, ADD>{});

@@ -1,7 +1,7 @@
 // Order-4 TTM chain on matrix cores, fp32, M = N = 8, L <= 16; MODE 0 is the FUSED schedule in one
 // kernel, MODE 1 and 2 are the second and third kernel of the FISSIONED schedule (T1 rows read from
-// the workspace and T2 rows written to it; T2 rows read from the workspace, deterministic schedules only: the others run
-// that kernel as a slice product, kernels_slice.hip):
+// the workspace and T2 rows written to it; T2 rows read from the workspace).  MODE 0 and 2 run under deterministic schedules only: the others
+// run MODE 0 over steps (kernels_chain4.hip) and MODE 2 as a slice product (kernels_slice.hip):
 //     A(i,l,m,n) = sum_{j,k,p} B(i,j,k,p) * C(j,l) * D(k,m) * E(p,n)
 // under the two-level nest obtained by applying the split-and-fuse step of Section 4.2 twice
 // (the shape of the second schedule of Table 2, kernel 5):
@@ -22,10 +22,6 @@
 //            mn = 16 w .. 16 w + 15 for every slice of the tile (four f2 fibers per
 //            v_mfma_f32_16x16x4_f32, l padded to 16), so no sums cross wavefronts; a lane ends
 //            up with four consecutive mn of one l, i.e. one 16-byte store
-//   carry    a workgroup owns a contiguous run of tiles; the sum of a slice that continues
-//            into the next tile stays in registers, so a heavy slice costs one global update
-//            per workgroup; only a slice that crosses the run's ends is added atomically to
-//            the zeroed output
 #include <type_traits>
 
 #include "leaf_walk.h"
@@ -43,7 +39,7 @@ struct Ttmc4Args {
     const float *T1;   // MODE 1: materialised T1, one 8-wide row per f3 fiber
     float *T2;         // MODE 1 writes, MODE 2 reads: one 64-wide row per f2 fiber
     float *A;
-    float *partials;   // deterministic schedules: slots for the pieces of rows that span tiles (runs are single tiles then), else null
+    float *partials;   // deterministic schedules: slots for the pieces of rows that span tiles (null where none does), else null
     const int32_t *slot_b;   // deterministic MODE 1: first slot of each tile's pieces of T2 rows
     int32_t L;
     int32_t tn, ta, tb;
@@ -88,11 +84,12 @@ __host__ __device__ constexpr size_t ttmc4_lds_bytes(int tn, int ta, int tb, int
 
 typedef float t4_floatx4 __attribute__((ext_vector_type(4)));
 
-// DET: the deterministic variants (pieces of rows that span tiles go to plan-numbered slots: rows of A in
-// MODE 0 and 2, rows of T2 in MODE 1).
+// DET: deterministic schedules (pieces of rows that span tiles go to plan-numbered slots: rows of A in
+// MODE 0 and 2, which run under no other, rows of T2 in MODE 1).
 template <int MODE, bool DET>
 __global__ void __launch_bounds__(NT) ttmc4_mfma_kernel(Ttmc4Args a, const TileRec *__restrict__ tiles)
 {
+    static_assert(DET || MODE == 1, "the other kernels of a schedule that is not deterministic run elsewhere");
     using P = Pack<float, 4>;
     using Rec = LeafRec<float>;
     constexpr int U1 = T4_U1, U2 = T4_U2;
@@ -122,8 +119,6 @@ __global__ void __launch_bounds__(NT) ttmc4_mfma_kernel(Ttmc4Args a, const TileR
     auto uni = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
     const int wave = uni(tid / 64), lane = tid % 64;
     const int kk = lane / 16, col = lane % 16;
-    t4_floatx4 carry = {0.f, 0.f, 0.f, 0.f};   // this wavefront's columns of the slice continuing from the previous tile
-    bool chain_shared = false;                 // that slice began before this workgroup's run
 
     // Global reads of one tile's staging, held in registers: they are issued while the previous
     // tile of the run is still being worked on.
@@ -178,7 +173,6 @@ __global__ void __launch_bounds__(NT) ttmc4_mfma_kernel(Ttmc4Args a, const TileR
     for (int tile = first; tile < lastp1; ++tile) {
         const TileRec tn = tiles[min(tile + 1, lastp1 - 1)];
         const bool in_f = (t.flags & 16) != 0, out_f = (t.flags & 32) != 0;
-        if (tile == first && in_f) chain_shared = true;
         const int nchild = t.n1 - t.n0;
         const int na = t.na, nb = t.nb, nc = t.nc;
         const int q1 = leaf_chunk<U1>(nchild, T4_G1);
@@ -360,21 +354,17 @@ __global__ void __launch_bounds__(NT) ttmc4_mfma_kernel(Ttmc4Args a, const TileR
         if (MODE != 1) {
             const bool lval = col < L;
             const char *Cb = reinterpret_cast<const char *>(a.C) + min(col, L - 1) * 4;
-            const bool last_tile = tile + 1 == lastp1;
-            auto emit = [&](const t4_floatx4 &v, int ls, bool atomic) {
+            auto emit = [&](const t4_floatx4 &v, int ls, bool shared) {
                 // v[r] = A(l = col, mn = 16 wave + 4 kk + r)
                 if (!lval) return;
                 float *dst = a.A + (int64_t)uni(crdc_s[ls]) * rowA + col * T4_W2 + wave * 16 + 4 * kk;
-                if (!atomic) {
+                if (!shared) {
                     *reinterpret_cast<t4_floatx4 *>(dst) = v;
-                } else if (DET) {
-                    // deterministic: this tile's piece of the row goes to its slot (a tile whose only
+                } else {
+                    // this tile's piece of the row goes to its slot (a tile whose only
                     // slice continues on both sides has one piece, numbered as its first)
                     const int slot = (ls == 0 && in_f) ? t.pad[0] : t.pad[1];
                     *reinterpret_cast<t4_floatx4 *>(a.partials + (int64_t)slot * rowA + col * T4_W2 + wave * 16 + 4 * kk) = v;
-                } else {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) atomic_add(dst + r, v[r]);
                 }
             };
             // the loop is compiled once per source of the C rows: with a run-time choice inside it the two reads
@@ -414,15 +404,7 @@ __global__ void __launch_bounds__(NT) ttmc4_mfma_kernel(Ttmc4Args a, const TileR
                         for (int ub = 0; ub < UB; ++ub)
                             if (fb + 4 * ub < f1) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(tv[ub], cv[ub], acc, 0, 0, 0);
                     }
-                    const bool incoming = ls == 0 && in_f, outgoing = ls == nc - 1 && out_f;
-                    if (incoming) acc += carry;
-                    if (outgoing) {
-                        if (last_tile) emit(acc, ls, true);   // continues in another workgroup's run
-                        else carry = acc;
-                    } else {
-                        emit(acc, ls, incoming && chain_shared);
-                        if (incoming) chain_shared = false;
-                    }
+                    emit(acc, ls, (ls == 0 && in_f) || (ls == nc - 1 && out_f));
                 }
             };
             if (MODE == 0 && c_in_lds) slices(std::true_type{});
@@ -453,16 +435,13 @@ bool ttmc4_mfma_caps_ok(const sc_plan *p)
            p->caps.tb >= 1;
 }
 
-// Tiles per workgroup.  Several runs per resident workgroup slot: shorter runs even out the tiles' different costs,
-// longer ones save row updates; six per slot measured best for the fused kernel (24 per compute unit), 32 per compute
-// unit for the second kernel of the FISSIONED schedule.  A deterministic schedule takes one tile per workgroup, so that
-// the pieces are the ones the plan numbered.
-int ttmc4_mfma_run(const sc_plan *p, int mode, bool one_tile_per_workgroup)
+// Tiles per workgroup: 32 runs per compute unit for the second kernel of the FISSIONED schedule (shorter ones even out the tiles' different
+// costs).  A deterministic schedule takes one tile per workgroup, so that the pieces are the ones the plan numbered.
+static int ttmc4_mfma_run(const sc_plan *p)
 {
     const int ntiles = (int)p->tiles.size();
-    if (ntiles == 0 || one_tile_per_workgroup) return 1;
-    const int fit = lds_workgroups_per_cu(ttmc4_lds_bytes(p->caps.tn, p->caps.ta, p->caps.tb, mode), p->lds_per_cu);
-    const int per_cu = p->tune.per_cu > 0 ? std::min(p->tune.per_cu, 64) : (mode == 0 ? 6 * fit : 32);
+    if (ntiles == 0 || p->deterministic) return 1;
+    const int per_cu = p->tune.per_cu > 0 ? std::min(p->tune.per_cu, 64) : 32;
     const int want = std::min(ntiles, p->n_cu * per_cu);
     return (ntiles + want - 1) / want;
 }
@@ -497,20 +476,17 @@ sc_status launch_ttmc4_mfma(const sc_plan *p, Launcher &ln, const sc_csf_view *s
     const size_t lds = ttmc4_lds_bytes(a.tn, a.ta, a.tb, mode);
     a.partials = static_cast<float *>(partials);
     a.slot_b = p->d_slot_b;
-    if (partials && mode == 1 && !p->d_slot_b) return SC_ERR_SCHED_UNSUPPORTED;
-    if (!partials && mode == 2) return SC_ERR_SCHED_UNSUPPORTED;   // the slice products of kernels_slice.hip run it
+    if (p->deterministic && mode == 1 && !p->d_slot_b) return SC_ERR_SCHED_UNSUPPORTED;
+    if (!p->deterministic && mode != 1) return SC_ERR_SCHED_UNSUPPORTED;   // kernels_chain4.hip and kernels_slice.hip run them
     a.ntiles = ntiles;
-    a.run = ttmc4_mfma_run(p, mode, partials != nullptr);
+    a.run = ttmc4_mfma_run(p);
     const int blocks = (ntiles + a.run - 1) / a.run;
     if (mode == 0) {
         ln.begin("ttmc4_fused_mfma");
-        if (partials)
-            ttmc4_mfma_kernel<0, true><<<blocks, NT, lds, ln.stream>>>(a, p->d_tiles);
-        else
-            ttmc4_mfma_kernel<0, false><<<blocks, NT, lds, ln.stream>>>(a, p->d_tiles);
+        ttmc4_mfma_kernel<0, true><<<blocks, NT, lds, ln.stream>>>(a, p->d_tiles);
     } else if (mode == 1) {
         ln.begin("ttmc4_middle");
-        if (partials)
+        if (p->deterministic)
             ttmc4_mfma_kernel<1, true><<<blocks, NT, lds, ln.stream>>>(a, p->d_tiles);
         else
             ttmc4_mfma_kernel<1, false><<<blocks, NT, lds, ln.stream>>>(a, p->d_tiles);

@@ -129,6 +129,19 @@ struct SliceChunk {
 };
 static_assert(sizeof(SliceChunk) == 48, "SliceChunk layout");
 
+// Chains of order 4 from the leaves (kernels_chain4.hip): a group's four children are pieces of (i,j) fibers.  Of a piece's own children,
+// (i,j,k) fibers, those of one leaf take a step each, the others whole pairs of steps, in all four pieces at once.
+// Repeated calls, 50 M entries at 8 x 8 x 8, pieces of 4, 5, 6, 8 and 12 fibers: 559, 543, 547, 562 and 574 us (shorter ones make more
+// groups, longer ones differ more in length; they are 4 bits each in a key: at most 15); batches of 8, 16 and 32 steps: 617, 547 and 605.
+constexpr int kChainPiece = 5;    // (i,j,k) fibers per piece of an (i,j) fiber at most
+constexpr int kChainBatch = 16;   // steps per batch; chunks are whole batches and runs begin with one
+
+struct ChainChunk {
+    uint64_t kend;           // bit n, n odd: children end in the pair of steps n - 1, n
+    int32_t kid0, nkids;     // pairs in which children end
+};
+static_assert(sizeof(ChainChunk) == 16, "ChainChunk layout");
+
 struct SliceRun {
     int32_t chunk0, step;   // first chunk, and the run's first step in it (a multiple of 8)
     int32_t flags;          // bit 0: the slice of that step began in an earlier run
@@ -148,6 +161,8 @@ struct SliceTables {
     uint32_t *d_at = nullptr;         // ... a byte for each of these: the leaf's place in the chunk (255: none, unless the chunk has 256)
     int32_t *d_gj = nullptr;          // ... 4 per group: coordinate of the child (-1: none)
     int32_t *d_first = nullptr;       // from rows of T: first child of every step and the child count
+    ChainChunk *d_kids = nullptr;     // chains of order 4: beside d_chunks
+    int32_t *d_gk = nullptr;          // ... 8 for every pair of steps in which children end, 4 per step: coordinate of the (i,j,k) fiber (-1: none)
 };
 
 struct Intermediate {
@@ -256,18 +271,13 @@ int32_t plan_tile_leaves(const sc_plan *plan);
 // table in tensor order rather than interleaved.
 bool plan_wants_tensor_order(const sc_plan *plan);
 
-// Tiles per workgroup of the kernel that writes the plan's output rows when that kernel is persistent over contiguous
-// runs of tiles (the fused order-4 matrix-core kernel); 0 for the kernels that take one tile per workgroup.  Within a run a slice that
-// continues from tile to tile stays in registers and is stored once; only a slice that crosses a run's end is added
-// atomically, so only those rows have to start from zero.  The launchers use the same number.
-int plan_output_run(const sc_plan *plan);
-
 // What the plan's slice products (kernels_slice.hip) start from: nothing (the plan has none), the leaves (leaves per piece
-// of a fiber at most), or rows of T.
-enum SliceSource { SLICE_NONE, SLICE_LEAVES, SLICE_ROWS };
+// of a fiber at most), the leaves of a chain of order 4, or rows of T.
+enum SliceSource { SLICE_NONE, SLICE_LEAVES, SLICE_CHAIN, SLICE_ROWS };
 SliceSource plan_slice_source(const sc_plan *plan, int *piece);
 SliceShape slice_shape(int64_t L, int64_t W);
 constexpr size_t kSliceLdsBytes = 16400;   // LDS of a workgroup, at every shape
+constexpr size_t kChainLdsBytes = 20496;   // of a chain of order 4
 
 // True when the kernels of the plan can run without floating-point atomics (FUSED schedules of
 // the kernels that emit one piece per tile and shared row).

@@ -190,8 +190,8 @@ def test_slice_products(oracle, shape, ranks, classes):
                 sc.tuning_set("tile_leaves", 0)
 
 
-def _poisoned(oracle, cfg, data, which):
-    """Every output element of the reference that is finite is finite here, and right; the others are not finite here, nor (in one kernel) another value."""
+def _poisoned(oracle, cfg, data, which, same=True):
+    """Every output element of the reference that is finite is finite here, and right; the others are not finite here, nor (`same`, in one kernel) another value."""
     got = _run(cfg, data, which).result()
     clean = [np.nan_to_num(f, nan=0.0, posinf=0.0, neginf=0.0) for f in data["factors"]]   # a zero in the place adds nothing to the bound of the others
     with np.errstate(invalid="ignore"):
@@ -201,7 +201,7 @@ def _poisoned(oracle, cfg, data, which):
     assert fine.any() and not fine.all()
     np.testing.assert_array_equal(np.isfinite(got), fine)
     assert np.all(np.abs(got[fine].astype(np.float64) - ref[fine]) <= 1e-5 * bound[fine])
-    if which != "fissioned":   # (its first kernel, the leaf traversal, multiplies by masked zeros)
+    if same and which != "fissioned":   # (its first kernel, the leaf traversal, multiplies by masked zeros)
         np.testing.assert_array_equal(got[~fine], ref[~fine].astype(np.float32))
 
 
@@ -264,6 +264,73 @@ def test_slice_products_longer_chunks(oracle, ranks, which, least, cap):
         if name == "whole_chunks" and which != "fissioned" or which == "linear" and name == "heavy":   # nearly every place is taken
             assert slots / cap <= chunks <= 1.25 * slots / cap + 8
         assert chunks >= slots / cap / 2
+
+
+# ---- chains of order 4 from the leaves: pairs of steps, pieces of (i,j) fibers, chunks, runs ----
+def _chain(shape, seed=0):
+    """shape: per slice a list of (i,j) fibers, each a list of (i,j,k) fiber lengths; coordinates are drawn."""
+    rng = np.random.default_rng(seed)
+    fibers = [f for s in shape for f in s]
+    J, K, P = max(map(len, shape)) + 3, max(map(len, fibers)) + 2, max(max(f) for f in fibers) + 5
+    cols = ([], [], [], [])
+    for i, sl in enumerate(shape):
+        for j, f in zip(np.sort(rng.choice(J, size=len(sl), replace=False)), sl):
+            for k, n in zip(np.sort(rng.choice(K, size=len(f), replace=False)), f):
+                for c, x in zip(cols, (np.full(n, i), np.full(n, j), np.full(n, k), np.sort(rng.choice(P, size=n, replace=False)))):
+                    c.append(x)
+    return (len(shape) + 1, J, K, P), [np.concatenate(c).astype(np.int32) for c in cols], rng
+
+
+CHAINS = {
+    "singles": [[[1]] * n for n in (1, 2, 3, 4, 5, 8, 63, 64, 65, 255, 256, 257, 1)] + [[[1]]] * 80,   # odd steps at chunks' and slices' ends
+    "children": [[[1] * n] for n in range(1, 13)] + [[[1] * 4] * 64, [[1] * 5, [1] * 6, [1]] * 9, [[1] * 300]],   # pieces of (i,j) fibers
+    "lengths": [[[n] for n in range(1, 20)], [[3, 1, 1, 2, 1, 17, 4]] * 5, [[2], [1], [1], [1], [1], [5, 1]], [[16] * 4] * 4, [[40, 1]], [[700]], [[1, 15, 16, 17, 33]] * 3],
+    "heavy": [[[1]], [[1, 3, 1], [1], [2], [1, 1]] * 900, [[1]]],   # one slice through many runs and workgroups
+}
+
+
+@pytest.mark.parametrize("name", sorted(CHAINS))
+@pytest.mark.parametrize("L", [1, 4, 8, 13, 16])
+def test_chain_of_order_4(oracle, name, L):
+    dims, coords, rng = _chain(CHAINS[name])
+    cfg = dict(kind="ttmc4", dims=dims, nnz=coords[0].size, ranks=(L, 8, 8), dtype="f32", expr=synth.KINDS["ttmc4"][0])
+    factors = [rng.standard_normal(s).astype(np.float32) for s in synth.factor_shapes(cfg)]
+    data = dict(coords=coords, vals=rng.uniform(-1, 1, coords[0].size).astype(np.float32), factors=factors)
+    for leaves in (0, 32):   # the built-in runs, and runs of a batch
+        sc.tuning_set("tile_leaves", leaves)
+        try:
+            con = _check(oracle, cfg, data, "fused")
+        finally:
+            sc.tuning_set("tile_leaves", 0)
+    for n, f in enumerate(con.factors):   # rows too far apart for offsets by products of 24 bits
+        con.factors[n] = torch.nn.functional.pad(f, (0, 128 - f.shape[1]), value=float("nan"))[:, : f.shape[1]]
+    con.out.fill_(float("nan"))
+    con.run()
+    assert_parity(oracle, cfg, data, con.result())
+
+
+@pytest.mark.parametrize("least,cap", [(300_000, 32), (560_000, 64)])
+def test_chain_of_order_4_longer_chunks(oracle, least, cap):
+    """Chunks of 32 and 64 steps; above 512,000 entries the steps are listed by several threads."""
+    for name, shape in CHAINS.items():
+        dims, coords, rng = _chain(shape * -(-least // sum(sum(map(sum, s)) for s in shape)))
+        cfg = dict(kind="ttmc4", dims=dims, nnz=coords[0].size, ranks=(8, 8, 8), dtype="f32", expr=synth.KINDS["ttmc4"][0])
+        factors = [rng.standard_normal(s).astype(np.float32) for s in synth.factor_shapes(cfg)]
+        con = _check(oracle, cfg, dict(coords=coords, vals=rng.uniform(-1, 1, coords[0].size).astype(np.float32), factors=factors), "fused")
+        assert int(re.search(r"runs of (\d+) chunks", sc.plan_describe(con.plan)).group(1)) >= coords[0].size / 4 / cap
+
+
+@pytest.mark.parametrize("at", [0, 1, 2])
+def test_chain_of_order_4_with_infinities(oracle, at):
+    """Only the outputs that refer to a row with an infinity or a NaN are not finite."""
+    for name in ("singles", "children", "lengths"):
+        dims, coords, rng = _chain(CHAINS[name])
+        cfg = dict(kind="ttmc4", dims=dims, nnz=coords[0].size, ranks=(8, 8, 8), dtype="f32", expr=synth.KINDS["ttmc4"][0])
+        factors = [rng.uniform(0.5, 1.5, s).astype(np.float32) for s in synth.factor_shapes(cfg)]   # one sign: infinities stay infinities in any order
+        for n in range(min(3, factors[at].shape[0])):
+            factors[at][n, n] = [np.inf, np.inf, np.nan][n]
+        _poisoned(oracle, cfg, dict(coords=coords, vals=rng.uniform(0.5, 1, coords[0].size).astype(np.float32), factors=factors), "fused",
+                  same=name != "lengths")   # a run's end inside an (i,j,k) fiber: zero times the row in the run that has no leaf of it
 
 
 @pytest.mark.parametrize("which,dims,lengths,ranks", [
