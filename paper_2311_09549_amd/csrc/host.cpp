@@ -1594,11 +1594,23 @@ static sc_status plan_ttmc_all(sc_plan *p, const char *expr, const Term &lhs, co
     // wavefronts per compute unit: fewer chunks keep the slots small when the output is large.
     const int64_t mn = p->fcols[1] * p->fcols[2];
     p->k5_mfma_reduce = variant >= 2 && p->dtype == SC_F32 && (p->fcols[0] == 16 || p->fcols[0] == 32 || p->fcols[0] == 64 || p->fcols[0] == 128) && mn % 64 == 0;
+    // At L = 64 and 128 from 4e9 operations on its products are of 16 bits (kernels_ttmc_all.hip): whole calls without and with them, us: 128 x 128 x 128,
+    // 40,000 slices 2486 and 1912, 4,000 slices 265 and 206; 64 x 64 x 64, 40,000 553 and 517; 64 x 32 x 32, 40,000 (5.2e9) 178 and 168; below, the
+    // launch that splits C takes what is gained: 128 x 16 x 16, 40,000 (2.6e9) 100 and 95, 128 x 32 x 32, 4,000 (1.0e9) 43.0 and 41.7, 300 (0.08e9) 25.4
+    // and 28.0; 64 x 16 x 16, 4,000 (0.13e9) 26.7 and 28.6.  L = 32 reads S at the memory's rate either way: 32 x 128 x 128, 40,000 (42e9) 1599 and 1593.
+    // At L = 128 six additions to a sum for 32 slices take the place of eight; with as long chains of them the error would be 3 to 5 % larger
+    // (1.37e-6 for 1.31e-6 in chunks of 5,000 slices, 0.93e-6 in chunks of 2,500), so chunks stop at sixteen wavefronts per compute unit where they keep
+    // 600 slices; in shorter ones it is the smaller one (3.8e-7 for 4.3e-7 in 500 slices) and more of them take longer (238 us for 206).
+    // (S takes 62 MB and more there, so no plan outgrows the fixed scratch array by the parts of C.)
+    const bool split = p->k5_mfma_reduce && p->fcols[0] >= 64 && 2.0 * L * M * N * (double)units >= 4e9;
     if (p->k5_mfma_reduce) {
-        const int64_t per_chunk = mn / 64, want = (int64_t)p->n_cu * 8;
+        const int64_t per_chunk = mn / 64;
+        int64_t want = (int64_t)p->n_cu * 8;
+        if (split && p->fcols[0] == 128 && units / 600 * per_chunk >= 2 * want) want *= 2;
         p->k5_nchunks = std::max<int64_t>(1, std::min<int64_t>(p->k5_nchunks, (want + per_chunk - 1) / per_chunk));
     }
     p->k5_chunk = std::max<int64_t>(1, (units + p->k5_nchunks - 1) / p->k5_nchunks);
+    if (split) p->k5_chunk = (p->k5_chunk + 31) / 32 * 32;   // whole steps of that kernel
     p->k5_nchunks = std::max<int64_t>(1, (units + p->k5_chunk - 1) / p->k5_chunk);
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -1609,6 +1621,7 @@ static sc_status plan_ttmc_all(sc_plan *p, const char *expr, const Term &lhs, co
     p->k5_s_offset = variant <= 1 ? 0 : take((size_t)p->dims[0] * (size_t)(p->fcols[1] * p->fcols[2]) * esize(p->dtype));
     p->k5_inner_ws_offset = take(variant == 0 ? 0 : in->ws_bytes);
     p->k5_partials_offset = take((size_t)p->k5_nchunks * (size_t)p->out_elems * esize(p->dtype));
+    if (split) p->k5_split_offset = take((size_t)((units + 31) / 32 * 32) * (size_t)p->fcols[0] * 6);
     p->ws_bytes = off;
 
     // temporaries as the caller can read them back after a FISSIONED execution: t rows (one per fiber) and

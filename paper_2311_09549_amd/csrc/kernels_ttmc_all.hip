@@ -174,6 +174,128 @@ __global__ void __launch_bounds__(NT, 2) mode0_reduce_mfma_kernel(K5Args a)
         }
 }
 
+// The same partial sums from products of 16 bits: a value of 24 bits is the exact sum of three of 8, x = h + m + l, each of them a
+// bf16 (h is x without its low 16 bits, m the rest without its own, l what is left), and a product of two of them is exact in fp32.  Of the nine
+// products of parts the three below 2^-24 of the whole, m l, l m and l l, are left out; the other six are added in fp32, the small ones
+// first, by v_mfma_f32_16x16x32_bf16, which takes 32 slices at 16 times the fp32 rate.
+// C is split once by a launch of its own into rows of eight slices (k5_split_kernel), so that a lane reads operand A, eight slices of one l, with
+// one 16-byte load per part; S is read as it is, eight slices of four columns per lane, and split in registers: it passes once.
+// Infinities become NaN on the way (h = x, m = x - h), and a value below 2^-109 loses its last bits, which bf16 cannot hold.
+// Repeated calls, the reduction alone, 40,000 slices: 128 x 128 x 128 1396 us in fp32 (110 TFLOP/s of the 120 it reaches) and 758 (221; S alone takes 450),
+// 128 x 64 x 64 366 and 225, 64 x 64 x 64 200 and 158.  Error against double precision 1.31e-6 and 0.93e-6, 6.4e-7 and 4.9e-7, 6.4e-7 and 2.9e-7:
+// at L = 64 the six products of a step are added up apart from the sum they go to, which takes no longer there; at L = 128, whose registers are
+// full, it does (942 us), and shorter chunks serve instead (plan_ttmc_all).
+constexpr int K5_K = 32;   // slices per step
+typedef __bf16 k5_bf16 __attribute__((ext_vector_type(8)));
+
+// high halves of two words: the truncated bf16 of b (low) and a
+__device__ __forceinline__ uint32_t k5_pack(float a, float b)
+{
+    return __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), 0x07060302);
+}
+
+// the three parts of eight values
+__device__ __forceinline__ void k5_parts(const float (&x)[8], uint4 (&part)[3])
+{
+    float r[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) r[j] = x[j];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        part[p] = uint4{k5_pack(r[1], r[0]), k5_pack(r[3], r[2]), k5_pack(r[5], r[4]), k5_pack(r[7], r[6])};
+        if (p < 2)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) r[j] -= __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, r[j]) & 0xffff0000u);
+    }
+}
+
+// C3[part][slices / 8][l][8], slices up to a multiple of 32; slices past the last are zero
+__global__ void __launch_bounds__(NT) k5_split_kernel(const float *__restrict__ C, int64_t ldC, int64_t rows, int L, int64_t groups, uint4 *__restrict__ C3)
+{
+    const int64_t n = (int64_t)blockIdx.x * NT + threadIdx.x;
+    if (n >= groups * L) return;
+    const int64_t g = n / L;
+    const int l = (int)(n % L);
+    float x[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = 8 * g + j < rows ? C[(8 * g + j) * ldC + l] : 0.f;
+    uint4 part[3];
+    k5_parts(x, part);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) C3[(int64_t)p * groups * L + n] = part[p];
+}
+
+template <int LT>   // L = 16 LT, an even number of tiles
+__global__ void __launch_bounds__(NT, 2) mode0_reduce_split_kernel(K5Args a, const uint4 *__restrict__ C3, int64_t groups)
+{
+    constexpr bool APART = LT <= 4;   // a step's products are added up before they are added to the sum
+    const int tid = threadIdx.x;
+    const int wave = tid / 64, lane = tid % 64, kk = lane / 16, col = lane % 16;
+    const int c = ((int)blockIdx.y * ((int)blockDim.x / 64) + wave) * 64 + 4 * col;
+    const int64_t r0 = (int64_t)blockIdx.x * a.chunk, r1 = min(r0 + a.chunk, a.rows);   // chunks are whole steps
+    const float *S = static_cast<const float *>(a.S) + c;
+    const uint4 *Cl = C3 + kk * a.L + col;   // part p, step of slices [r, r + 32), l = 16 lt + col: Cl[p * groups * L + r / 8 * L + 16 * lt]
+    const int64_t part = groups * a.L;
+    k5_floatx4 acc[LT][4];
+#pragma unroll
+    for (int lt = 0; lt < LT; ++lt)
+#pragma unroll
+        for (int x = 0; x < 4; ++x) acc[lt][x] = k5_floatx4{0.f, 0.f, 0.f, 0.f};
+    k5_floatx4 raw[8];
+    auto load_s = [&](int64_t r) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) raw[j] = *reinterpret_cast<const k5_floatx4 *>(S + min(r + 8 * kk + j, a.rows - 1) * a.MN);
+    };
+    uint4 cv[2][3];
+    auto load_c = [&](uint4 (&v)[3], int64_t r, int lt) {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) v[p] = Cl[p * part + r / 8 * a.L + 16 * lt];
+    };
+    load_s(r0);
+    load_c(cv[0], r0, 0);
+    for (int64_t r = r0; r < r1; r += K5_K) {
+        uint4 s[4][3];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            float v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = r + 8 * kk + j < a.rows ? raw[j][x] : 0.f;   // (slices past the last: zero times zero)
+            k5_parts(v, s[x]);
+        }
+        const int64_t rn = min(r + K5_K, r1 - 1) / K5_K * K5_K;   // the next step, or this one again
+        load_s(rn);
+#pragma unroll
+        for (int lt = 0; lt < LT; ++lt) {
+            if (lt + 1 < LT) load_c(cv[(lt + 1) % 2], r, lt + 1);
+            else load_c(cv[0], rn, 0);
+            __builtin_amdgcn_sched_barrier(0);   // the compiler would otherwise sink these reads below the products
+            k5_floatx4 sum[4];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) sum[x] = APART ? k5_floatx4{0.f, 0.f, 0.f, 0.f} : acc[lt][x];
+            auto add = [&](int pc, int ps) {
+#pragma unroll
+                for (int x = 0; x < 4; ++x)
+                    sum[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(k5_bf16, cv[lt % 2][pc]), __builtin_bit_cast(k5_bf16, s[x][ps]), sum[x], 0, 0, 0);
+            };
+            add(2, 0);
+            add(0, 2);
+            add(1, 1);
+            add(1, 0);
+            add(0, 1);
+            add(0, 0);
+#pragma unroll
+            for (int x = 0; x < 4; ++x) acc[lt][x] = APART ? acc[lt][x] + sum[x] : sum[x];
+        }
+    }
+    // acc[lt][x][q] = partial(l = 16 lt + 4 kk + q, column c + x)
+    float *P = static_cast<float *>(a.partials) + (int64_t)blockIdx.x * a.L * a.MN + c;
+#pragma unroll
+    for (int lt = 0; lt < LT; ++lt)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            *reinterpret_cast<k5_floatx4 *>(P + (int64_t)(16 * lt + 4 * kk + q) * a.MN) = k5_floatx4{acc[lt][0][q], acc[lt][1][q], acc[lt][2][q], acc[lt][3][q]};
+}
+
 // partial(b, l, (m,n)) = sum_{fibers f in chunk b} C(i_f,l) * D(j_f,m) * t(f,n); thread = (m,n)
 template <typename T>
 __global__ void __launch_bounds__(NT) fiber_reduce_kernel(K5Args a)
@@ -365,6 +487,21 @@ sc_status run_ttmc_all(const sc_plan *p, const sc_csf_view *sp, const sc_dense_v
         if (p->k5_mfma_reduce) {
             if constexpr (sizeof(T) == 4) {
                 if (MN % 64 != 0) return SC_ERR_SCHED_UNSUPPORTED;
+                if (p->k5_split_offset != SIZE_MAX) {
+                    const int64_t groups = (a.rows + K5_K - 1) / K5_K * (K5_K / 8);
+                    uint4 *C3 = reinterpret_cast<uint4 *>(wsb + p->k5_split_offset);
+                    ln.begin("ttmc_all_split");
+                    k5_split_kernel<<<(unsigned)((groups * L + NT - 1) / NT), NT, 0, stream>>>(static_cast<const float *>(a.C), a.ldC, a.rows, L, groups, C3);
+                    ln.end();
+                    const int strips = MN / 64, waves = strips % 4 == 0 ? 4 : strips % 2 == 0 ? 2 : 1;   // wavefronts per workgroup
+                    const dim3 sgrid((unsigned)p->k5_nchunks, (unsigned)(strips / waves), 1);
+                    ln.begin("ttmc_all_mode0_reduce_split");
+                    auto reduce = [&](auto lt) { mode0_reduce_split_kernel<decltype(lt)::value><<<sgrid, 64 * waves, 0, stream>>>(a, C3, groups); };
+                    if (L == 64) reduce(std::integral_constant<int, 4>{});
+                    else if (L == 128) reduce(std::integral_constant<int, 8>{});
+                    else return SC_ERR_SCHED_UNSUPPORTED;
+                    ln.end();
+                } else {
                 // 64 columns per wavefront, 16 up to two wavefronts of 64 per compute unit.  Whole calls at 512 wavefronts of 64: 128 x 32 x
                 // 32 42.2 us with 64 columns, 38.2 with 16; at 628: 44.6 and 42.5 at 128 x 16 x 16, but 32.2 and 33.6 at 32 x 16 x 16; at
                 // 1008 64 columns are equal or ahead at every L (64 x 32 x 32: 36.9 and 38.3).
@@ -384,6 +521,7 @@ sc_status run_ttmc_all(const sc_plan *p, const sc_csf_view *sp, const sc_dense_v
                 else if (L == 128) reduce(std::integral_constant<int, 8>{});
                 else return SC_ERR_SCHED_UNSUPPORTED;
                 ln.end();
+                }
             } else {
                 return SC_ERR_SCHED_UNSUPPORTED;
             }

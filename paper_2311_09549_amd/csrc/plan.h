@@ -227,6 +227,7 @@ struct sc_plan {
     size_t k5_inner_ws_offset = 0;     // workspace of the inner plan
     size_t k5_partials_offset = 0;     // k5_nchunks x L x (M N)
     int64_t k5_nchunks = 0, k5_chunk = 0;
+    size_t k5_split_offset = SIZE_MAX;  // C in parts of 16 bits, where that reduction runs on them
     bool k5_mfma_reduce = false;       // the contraction over the first mode runs on the matrix cores (fp32, L in {16, 32, 64, 128}, M N a multiple of 64)
 
     // Trailing dense product (kernels 8 and 2 of Table 2): the sparse part runs as an inner plan (MTTKRP, or kernel 1)

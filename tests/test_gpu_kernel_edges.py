@@ -150,6 +150,24 @@ def test_core_tensor_reduction(oracle, dtype, L, MN, rows):
         _check(oracle, cfg, data, "fused")
 
 
+@pytest.mark.parametrize("ranks,rows", [((64, 64, 64), (7633, 7680)), ((64, 32, 32), (30_529,)), ((128, 64, 64), (3815, 4001)), ((128, 128, 128), (993, 9633)), ((128, 16, 32), (30_529,))])
+def test_core_tensor_reduction_in_parts(oracle, ranks, rows):
+    """Products of 16 bits: slices that do not fill the last step, both forms of the sum, longer and shorter chunks; and an infinity in C, which
+    reaches the outputs of its l and no others."""
+    for n in rows:
+        cfg, data = _problem("ttmc_all", (n, 41, 97), [(i, 1 + i % 3) for i in range(0, n, 1 + n // 150)], ranks, "f32")
+        con = _check(oracle, cfg, data, "fused")
+        sc.plan_set_profiling(con.plan, True)
+        con.run()
+        torch.cuda.synchronize()
+        assert any(name == "ttmc_all_mode0_reduce_split" for name, _ in sc.plan_kernel_times(con.plan))
+        con.factors[0][int(data["coords"][0][-1]), 5] = float("inf")
+        con.run()
+        bad = np.zeros(ranks[0], dtype=bool)
+        bad[5] = True
+        np.testing.assert_array_equal(~np.isfinite(con.result()).all(axis=(1, 2)), bad)
+
+
 # ---- slice products: steps, chunks (of 16 steps at these sizes, of 32 and 64 below), runs, sums over the runs of a workgroup ----
 def _fibers(shape, seed=0):
     """shape: per slice a list of fiber lengths; every fiber's entries start at a drawn place of the last mode."""
