@@ -248,6 +248,9 @@ sc_status launch_fixup(const sc_plan *p, Launcher &ln, const FixLevel &lv, void 
 sc_status launch_slice(const sc_plan *p, Launcher &ln, const sc_csf_view *sp, const sc_dense_view &C, const sc_dense_view *D, const void *T,
                        int64_t W, void *out, const char *name);
 
+// Fused MTTKRP over steps (kernels_mttkrp.hip).
+sc_status launch_mttkrp_steps(const sc_plan *p, Launcher &ln, const sc_csf_view *sp, const sc_dense_view *fac, void *out);
+
 // Order-4 TTM chain at 8 x 8, fp32, FUSED, from the leaves in one pass over steps (kernels_chain4.hip).
 sc_status launch_chain4(const sc_plan *p, Launcher &ln, const sc_csf_view *sp, const sc_dense_view *fac, void *out);
 

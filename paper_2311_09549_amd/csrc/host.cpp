@@ -591,12 +591,14 @@ struct SlicePieces {
     struct Piece { int32_t z, len, j; } list[256];
     int32_t n = 0, leaves = 0, longest = 0;
     int32_t count[kSlicePiece + 1] = {0};
-    // steps of the groups of four they make, longest first
+    const int32_t wide;   // pieces per group
+    explicit SlicePieces(int32_t wide) : wide(wide) {}
+    // steps of the groups they make, longest first
     int32_t steps() const
     {
         int32_t s = 0, at = 0;
         for (int len = longest; len > 0; --len) {
-            s += len * ((at + count[len] + 3) / 4 - (at + 3) / 4);
+            s += len * ((at + count[len] + wide - 1) / wide - (at + wide - 1) / wide);
             at += count[len];
         }
         return s;
@@ -604,7 +606,7 @@ struct SlicePieces {
     bool fits(int32_t len, int32_t room)
     {
         if (n == 256) return false;
-        if (std::max(len, longest) + (leaves + len + 3) / 4 <= room) return true;   // at most the longest and a quarter of all leaves
+        if (std::max(len, longest) + (leaves + len + wide - 1) / wide <= room) return true;   // at most the longest and a share of all leaves
         const int32_t was = longest;
         longest = std::max(longest, len);
         ++count[len];
@@ -622,8 +624,8 @@ struct SlicePieces {
     }
 };
 
-// Lists the steps of the slices [s0, s1), in chunks of at most `cap`.
-void list_steps(SliceSource src, int piece, int cap, const HostCsf &h, int64_t s0, int64_t s1, SlicePart &b)
+// Lists the steps of the slices [s0, s1), `wide` leaves each (a multiple of four), in chunks of at most `cap`.
+void list_steps(SliceSource src, int piece, int wide, int cap, const HostCsf &h, int64_t s0, int64_t s1, SlicePart &b)
 {
     const int32_t *pos1 = h.pos[1];
     const int64_t children = pos1[s1] - pos1[s0];
@@ -663,7 +665,7 @@ void list_steps(SliceSource src, int piece, int cap, const HostCsf &h, int64_t s
             const int32_t fend = pos1[s + 1];
             int32_t z = pos2[f];
             // a slice longer than what is left of a chunk starts the next one, unless much is left
-            if (cap - c.nsteps < 8 && (pos2[fend] - z) / 4 >= cap - c.nsteps) flush(z, (int32_t)s);
+            if (cap - c.nsteps < 8 && cap > 8 && (pos2[fend] - z) / wide >= cap - c.nsteps) flush(z, (int32_t)s);
             if (piece == 1) {   // every leaf a child of its own: four leaves in a row per step, a step per group
                 const int32_t zend = pos2[fend];
                 while (z < zend) {
@@ -692,7 +694,7 @@ void list_steps(SliceSource src, int piece, int cap, const HostCsf &h, int64_t s
                 }
             }
             while (f < fend) {
-                SlicePieces w;
+                SlicePieces w(wide);
                 const int32_t room = cap - c.nsteps;
                 while (f < fend) {
                     const int32_t len = std::min<int32_t>(pos2[f + 1] - z, piece);
@@ -704,18 +706,18 @@ void list_steps(SliceSource src, int piece, int cap, const HostCsf &h, int64_t s
                 int32_t at[kSlicePiece + 2] = {0};   // first place of the pieces of each length, longest first
                 for (int len = kSlicePiece - 1; len > 0; --len) at[len] = at[len + 1] + w.count[len + 1];
                 for (int k = 0; k < w.n; ++k) sorted[at[w.list[k].len]++] = w.list[k];
-                for (int k = 0; k < w.n; k += 4) {
-                    const int have = std::min(4, w.n - k), steps = sorted[k].len;
+                for (int k = 0; k < w.n; k += wide) {
+                    const int have = std::min(wide, w.n - k), steps = sorted[k].len;
                     const size_t o = b.leaf.size();
-                    b.leaf.resize(o + 4 * (size_t)steps, 0xffffffffu);
-                    b.at.resize(b.at.size() + (size_t)steps, 0xffffffffu);
+                    b.leaf.resize(o + wide * (size_t)steps, 0xffffffffu);
+                    b.at.resize(b.leaf.size() / 4, 0xffffffffu);
                     uint8_t *place = reinterpret_cast<uint8_t *>(b.at.data()) + o;
-                    for (int q = 0; q < 4; ++q) {
+                    for (int q = 0; q < wide; ++q) {
                         const SlicePieces::Piece &pc = sorted[k + std::min(q, have - 1)];
                         const int32_t len = q < have ? pc.len : 0;
                         for (int u = 0; u < len; ++u) {
-                            b.leaf[o + 4 * (size_t)u + q] = (uint32_t)crd2[pc.z + u];
-                            place[4 * u + q] = (uint8_t)(pc.z + u - c.leaf0);
+                            b.leaf[o + wide * (size_t)u + q] = (uint32_t)crd2[pc.z + u];
+                            place[wide * u + q] = (uint8_t)(pc.z + u - c.leaf0);
                         }
                         b.gj.push_back(q < have ? pc.j : -1);   // (and the leaves past a piece: no row)
                     }
@@ -905,8 +907,9 @@ void build_slices(const sc_plan *p, SliceSource src, int piece, const HostCsf &h
 {
     const int64_t S = p->nfib[0], children = p->nfib[1];
     // Steps per chunk: 64, fewer where that would leave wavefront slots without a chunk.
-    int cap = 64;
-    while (cap > 16 && (src == SLICE_ROWS ? children : p->nnz) < (int64_t)4 * cap * 8 * p->n_cu) cap /= 2;
+    const int wide = src == SLICE_MTTKRP ? kMttkrpPlaces : 4;   // leaves (children) per step
+    int cap = std::min(64, 256 / wide);
+    while (cap > 64 / wide && (src == SLICE_ROWS ? children : p->nnz) < (int64_t)wide * cap * 8 * p->n_cu) cap /= 2;
     // A thread per 256,000 leaves (children), at most eight; ranges of slices with about equal numbers of them.
     const int32_t *pos1 = h.pos[1], *pos2 = src == SLICE_ROWS ? nullptr : h.pos[2], *pos3 = src == SLICE_CHAIN ? h.pos[3] : nullptr;
     auto before = [&](int64_t s) { return (int64_t)(pos3 ? pos3[pos2[pos1[s]]] : pos2 ? pos2[pos1[s]] : pos1[s]); };
@@ -927,7 +930,7 @@ void build_slices(const sc_plan *p, SliceSource src, int piece, const HostCsf &h
     auto work = [&](size_t n) {
         try {
             if (src == SLICE_CHAIN) list_chain(cap, h, from[n], from[n + 1], b.parts[n]);
-            else list_steps(src, piece, cap, h, from[n], from[n + 1], b.parts[n]);
+            else list_steps(src, piece, wide, cap, h, from[n], from[n + 1], b.parts[n]);
         } catch (...) { b.parts[n].failed = true; }
     };
     std::vector<std::thread> threads;
@@ -961,7 +964,7 @@ void build_slices(const sc_plan *p, SliceSource src, int piece, const HostCsf &h
     // Work of a step, a group, a slice and a chunk in vector-ALU issue slots of a wavefront: the gather and its arithmetic; the row of
     // C and the matrix products (8 slots each); the stores of the row; the staging.
     const int64_t L = p->fcols[0], W = p->kind == K_TTMC4 ? p->fcols[1] * p->fcols[2] : p->fcols[1];
-    const SliceShape sh = slice_shape(L, W);
+    const SliceShape sh = src == SLICE_MTTKRP ? SliceShape{1, 1, 1, 1} : slice_shape(L, W);
     const int64_t tiles = (int64_t)sh.lt * sh.mt;
     const double w_step = src == SLICE_CHAIN ? 9 : 6 + sh.mt, w_group = 6 + 8 * tiles, w_slice = 8 + 4 * tiles, w_chunk = 60;   // (of a chain: half of the steps end children)
     auto cost = [&](const SliceChunk &k) {
@@ -1999,7 +2002,7 @@ static sc_status plan_create_impl(sc_plan **out, const char *expr, const sc_csf_
         if (failed) return SC_ERR_ALLOC;
     }
     // what the device reads of the tiles: nothing where slice products from the leaves are all that runs
-    const bool tiles_read = !(sliced && (src == SLICE_LEAVES || src == SLICE_CHAIN));
+    const bool tiles_read = !(sliced && (src == SLICE_LEAVES || src == SLICE_CHAIN || src == SLICE_MTTKRP));
     try {
         if (p->deterministic) {
             if (!plan_supports_deterministic(p)) return SC_ERR_SCHED_UNSUPPORTED;

@@ -760,7 +760,9 @@ sc_status run_order3(const sc_plan *p, const sc_csf_view *sp, const sc_dense_vie
     const bool mf = can_mf && !had && !mfma && order3_mfma_ranks(a.L, W);
     const size_t lds = order3_lds_bytes<T>(W, a.tn, a.ta, mf ? a.L : 0);
     if (p->sched == SC_SCHED_FUSED) {
-        if (had) {
+        if (had && plan_slice_source(p, nullptr) == SLICE_MTTKRP) {
+            return launch_mttkrp_steps(p, ln, sp, fac, out);
+        } else if (had) {
             ln.begin("mttkrp3_fused");
             if (a.partials)
                 mttkrp3_fused_kernel<T, W, true><<<ntiles, NT, mttkrp_lds_bytes<T>(W, a.tn, a.ta, a.tb), stream>>>(a);
@@ -945,6 +947,15 @@ sc_status launch_fixup(const sc_plan *p, Launcher &ln, const FixLevel &lv, void 
     return ln.status;
 }
 
+// MTTKRPs with rows of 128 bytes (fp32 at rank 32, fp64 at 16) whose slices hold 160 entries and more on average run over steps: shorter slices leave
+// lane groups without a fiber.  Calls in the kernel over tiles and over steps, us, by entries per slice: uniform, 3 M entries 300 55.1 and 46.5 (fp64 60.3 and
+// 50.0), 96 52.2 and 57.0, 48 51.3 and 60.1, 12 53.7 and 78.8; 20 M 222 484 and 475; power laws, 20 M 400 182 and 157, 1 M 200 21.4 and 17.0 (fp64 21.0 and 18.0),
+// 5 M 100 63.1 and 57.9, 1 M 12 28.7 and 26.3 (fp64 27.9 and 28.6).  Rows of 256 bytes gained nothing (6 M at rank 64 116 and 113, at 128 207 and 218).
+static bool mttkrp_over_steps(const sc_plan *p)
+{
+    return p->kind == K_MTTKRP3 && p->sched == SC_SCHED_FUSED && p->fcols[0] * (p->dtype == SC_F64 ? 8 : 4) == 128 && p->nnz >= 160 * p->nfib[0];
+}
+
 // fp32 chains of order 3 in every class, and the last kernel of the FISSIONED order-4 chain at 8 x 8, unless the caller asks for a
 // reproducible sum.  Repeated calls with the kernels over tiles that ran before, and now, us: 6 M entries at 64 x 32 384 and 227; kernel 5 on 4 M
 // entries at 128 x 128 x 128 3411 and 2470; 1.5 M at 16 x 16 54 and 25, at 8 x 64 139 and 49; unfactored, 1.5 M at 12 x 20 78 and 39, at 4 x 4 46
@@ -952,7 +963,12 @@ sc_status launch_fixup(const sc_plan *p, Launcher &ln, const FixLevel &lv, void 
 SliceSource plan_slice_source(const sc_plan *p, int *piece)
 {
     if (piece) *piece = kSlicePiece;
-    if (p->dtype != SC_F32 || p->deterministic) return SLICE_NONE;
+    if (p->deterministic) return SLICE_NONE;
+    if (mttkrp_over_steps(p)) {
+        if (piece) *piece = kMttkrpPiece;
+        return SLICE_MTTKRP;
+    }
+    if (p->dtype != SC_F32) return SLICE_NONE;
     if (p->kind == K_TTMC3 && slice_shape(p->fcols[0], p->fcols[1]).lt) {
         if (p->sched == SC_SCHED_LINEAR && piece) *piece = 1;   // nothing is factored out: every stored entry is a piece
         return p->sched == SC_SCHED_FISSIONED ? SLICE_ROWS : SLICE_LEAVES;
@@ -972,7 +988,7 @@ bool plan_wants_tensor_order(const sc_plan *p)
 WalkShape plan_walk_shape(const sc_plan *p)
 {
     const SliceSource src = plan_slice_source(p, nullptr);
-    if (p->sched == SC_SCHED_LINEAR || src == SLICE_LEAVES || src == SLICE_CHAIN) return WalkShape{};
+    if (p->sched == SC_SCHED_LINEAR || src == SLICE_LEAVES || src == SLICE_CHAIN || src == SLICE_MTTKRP) return WalkShape{};
     if (p->kind == K_TTMC4 && plan_wants_tensor_order(p)) return ttmc4_mfma_walk_shape();   // its leaf level also serves the traversal kernel
     if (p->kind == K_TTMC3 && p->sched == SC_SCHED_FUSED && plan_wants_tensor_order(p)) return ttmc3_mfma_walk_shape();
     // FISSIONED, order >= 3: the leaf traversal, whose rows are as wide as the last factor
@@ -1026,6 +1042,7 @@ size_t lds_bytes_used(const sc_plan *p)
     const SliceSource src = plan_slice_source(p, nullptr);
     if (src == SLICE_LEAVES) return kSliceLdsBytes;
     if (src == SLICE_CHAIN) return kChainLdsBytes;
+    if (src == SLICE_MTTKRP) return mttkrp_steps_lds_bytes(p->dtype == SC_F64 ? 8 : 4);
     if (src == SLICE_ROWS && p->kind == K_TTMC3) return std::max(kSliceLdsBytes, leaf_traverse_lds_bytes(p, (int)p->fcols[1]));
     return lds_bytes_needed(p);   // (the order-4 chain: its first two kernels need more than the slice product)
 }

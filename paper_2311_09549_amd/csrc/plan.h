@@ -273,12 +273,15 @@ int32_t plan_tile_leaves(const sc_plan *plan);
 bool plan_wants_tensor_order(const sc_plan *plan);
 
 // What the plan's slice products (kernels_slice.hip) start from: nothing (the plan has none), the leaves (leaves per piece
-// of a fiber at most), the leaves of a chain of order 4, or rows of T.
-enum SliceSource { SLICE_NONE, SLICE_LEAVES, SLICE_CHAIN, SLICE_ROWS };
+// of a fiber at most), the leaves of a chain of order 4, those of an MTTKRP (kernels_mttkrp.hip), or rows of T.
+enum SliceSource { SLICE_NONE, SLICE_LEAVES, SLICE_CHAIN, SLICE_MTTKRP, SLICE_ROWS };
 SliceSource plan_slice_source(const sc_plan *plan, int *piece);
 SliceShape slice_shape(int64_t L, int64_t W);
 constexpr size_t kSliceLdsBytes = 16400;   // LDS of a workgroup, at every shape
 constexpr size_t kChainLdsBytes = 20496;   // of a chain of order 4
+constexpr size_t mttkrp_steps_lds_bytes(size_t e) { return 4 * 256 * (2 * e + 4 + e); }
+constexpr int kMttkrpPlaces = 8;   // leaves per step of an MTTKRP
+constexpr int kMttkrpPiece = 6;    // leaves per piece of its fibers at most: 16, 8 and 6 183, 168 and 165 us (20 M entries at rank 32; long pieces differ more in length)
 
 // True when the kernels of the plan can run without floating-point atomics (FUSED schedules of
 // the kernels that emit one piece per tile and shared row).

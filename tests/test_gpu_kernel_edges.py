@@ -284,6 +284,44 @@ def test_slice_products_longer_chunks(oracle, ranks, which, least, cap):
         assert chunks >= slots / cap / 2
 
 
+MTTKRPS = {   # 160 entries per slice and more
+    "units": [[1] * n for n in (160, 200, 255, 256, 257, 700, 1, 9)],
+    "lengths": [[1, 2, 3, 5, 6, 7, 12, 13, 40] * 4, [700, 1, 33], [6] * 64, [2] * 300, [1]],
+    "heavy": [[1, 2, 3, 1] * 1500, [1], [2, 1] * 100],   # one slice through many runs
+}
+
+
+@pytest.mark.parametrize("dtype,R", [("f32", 32), ("f64", 16)])
+@pytest.mark.parametrize("name", sorted(MTTKRPS))
+def test_mttkrp_over_steps(oracle, name, dtype, R):
+    """Pieces of fibers in eights, chunks, runs inside slices; and an infinity in a row of C or D, which reaches the outputs that refer to it only."""
+    dims, coords, rng = _fibers(MTTKRPS[name])
+    cfg = dict(kind="mttkrp3", dims=dims, nnz=coords[0].size, ranks=(R,), dtype=dtype, expr=synth.KINDS["mttkrp3"][0])
+    dt = np.float64 if dtype == "f64" else np.float32
+    factors = [rng.standard_normal(s).astype(dt) for s in synth.factor_shapes(cfg)]
+    data = dict(coords=coords, vals=rng.uniform(-1, 1, coords[0].size).astype(dt), factors=factors)
+    for leaves in (0, 32):   # the built-in runs, and runs of eight steps
+        sc.tuning_set("tile_leaves", leaves)
+        try:
+            con = _check(oracle, cfg, data, "fused")
+        finally:
+            sc.tuning_set("tile_leaves", 0)
+    assert "slice products" in sc.plan_describe(con.plan)
+    if dtype == "f32":
+        for at in (0, 1):
+            bad = [f.copy() for f in factors]
+            bad[at][coords[at + 1][-1], 3] = np.inf
+            _poisoned(oracle, cfg, dict(data, factors=bad), "fused", same=False)
+
+
+@pytest.mark.parametrize("least,slices", [(300_000, 1800), (1_100_000, 400)])
+def test_mttkrp_over_steps_longer_chunks(oracle, least, slices):
+    """Chunks of 16 and 32 steps, listed by one thread and by several."""
+    cfg, data = _problem("mttkrp3", (slices + 3, 89, 97), [(i, least // slices + i % 7) for i in range(slices)], (32,))
+    con = _check(oracle, cfg, data, "fused")
+    assert "slice products" in sc.plan_describe(con.plan)
+
+
 # ---- chains of order 4 from the leaves: pairs of steps, pieces of (i,j) fibers, chunks, runs ----
 def _chain(shape, seed=0):
     """shape: per slice a list of (i,j) fibers, each a list of (i,j,k) fiber lengths; coordinates are drawn."""
