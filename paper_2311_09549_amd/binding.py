@@ -13,6 +13,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 
 import numpy as np
 
@@ -56,6 +57,14 @@ class DenseView(ctypes.Structure):
                 ("ld", ctypes.c_int64), ("dtype", ctypes.c_int)]
 
 
+# The same records packed by one call each: an execution fills one CsfView and a DenseView per factor, and field by field that took longer than
+# a small contraction (host side of a call on 8,000 entries: 14 us, FILLME so).
+_pack_csf = struct.Struct("@i4qqi4q4P4PPi0q").pack
+_pack_dense = [struct.Struct("@" + "Pqqqi" * n + "0q").pack for n in range(5)]
+assert len(_pack_csf(*[0] * 21)) == ctypes.sizeof(CsfView)
+assert all(len(pack(*[0] * (5 * n))) == n * ctypes.sizeof(DenseView) for n, pack in enumerate(_pack_dense))
+
+
 class Schedule(ctypes.Structure):
     _fields_ = [("kind", ctypes.c_int), ("n_intermediates", ctypes.c_int32),
                 ("intermediate", ctypes.c_char_p * 2), ("fuse_depth", ctypes.c_int32 * 2),
@@ -70,11 +79,12 @@ class ScError(RuntimeError):
 
 
 _lib = None
+_sc_execute = None   # sc_execute with declared argument types
 
 
 def lib():
     """The loaded shared library (raises if it has not been built)."""
-    global _lib
+    global _lib, _sc_execute
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise ImportError(
@@ -90,6 +100,10 @@ def lib():
         for name in EXPORTS:
             if name != "sc_status_string":
                 getattr(_lib, name).restype = ctypes.c_int
+        ptr = ctypes.c_void_p
+        _sc_execute = _lib["sc_execute"]
+        _sc_execute.restype = ctypes.c_int
+        _sc_execute.argtypes = [ptr, ptr, ptr, ctypes.c_int32, ptr, ptr, ctypes.c_size_t, ptr]
     return _lib
 
 
@@ -120,6 +134,8 @@ def _dtype_code(dt) -> int:
 
 def _addr(x) -> int:
     """Raw address of a numpy array, a torch tensor, an int or None."""
+    if hasattr(x, "data_ptr"):
+        return x.data_ptr()
     if x is None:
         return 0
     if isinstance(x, int):
@@ -165,6 +181,13 @@ class Csf:
         v.on_device = int(self.on_device)
         return v
 
+    def packed(self):
+        """The bytes of view()."""
+        n = self.order
+        none = (0,) * (4 - n)
+        return _pack_csf(n, *self.dims[:n], *none, self.nnz, self.dtype_code, *self.nfib[:n], *none, 0, *map(_addr, self.pos[1:n]), *none,
+                         *map(_addr, self.crd[:n]), *none, _addr(self.vals), self.on_device)
+
     def to_device(self, device="cuda"):
         import torch
         pos = [None] + [torch.from_numpy(p).to(device) for p in self.pos[1:]]
@@ -196,6 +219,16 @@ def coo_to_csf(coords, vals, dims) -> Csf:
     cv = coo_view(coords, vals, dims)
     _check(lib().sc_coo_to_csf(ctypes.byref(cv), ctypes.byref(out)), "sc_coo_to_csf")
     return Csf(order, dims, out.nnz, out.dtype, [out.nfib[m] for m in range(order)], pos, crd, vals, False)
+
+
+def _dense_fields(x):
+    """The fields of dense_view(x) for an array, a tensor or a DenseView."""
+    if isinstance(x, (DenseView, np.ndarray)):
+        v = x if isinstance(x, DenseView) else dense_view(x)
+        return v.data or 0, v.rows, v.cols, v.ld, v.dtype
+    shape, stride = x.shape, x.stride()
+    assert stride[1] == 1
+    return x.data_ptr(), shape[0], shape[1], stride[0], SC_F64 if x.element_size() == 8 else SC_F32
 
 
 def dense_view(x, dtype=None, rows=None, cols=None, ld=None) -> DenseView:
@@ -317,12 +350,17 @@ def stream_copy(dst, src, nbytes: int, stream=0):
 
 def execute(plan: Plan, csf: Csf, factors, out, workspace=None, workspace_bytes=0, stream=0):
     """Queues the contraction on `stream` (a raw hipStream_t address, 0 = default stream)."""
-    fv = (DenseView * len(factors))(*[f if isinstance(f, DenseView) else dense_view(f) for f in factors])
-    view = csf.view()
-    st = lib().sc_execute(plan.handle, ctypes.byref(view), fv, ctypes.c_int32(len(factors)),
-                          ctypes.c_void_p(_addr(out)), ctypes.c_void_p(_addr(workspace)),
-                          ctypes.c_size_t(int(workspace_bytes)), ctypes.c_void_p(int(stream)))
-    _check(st, "sc_execute")
+    if _sc_execute is None:
+        lib()
+    n = len(factors)
+    if type(csf) is Csf and n < len(_pack_dense):
+        fields = []
+        for f in factors:
+            fields += _dense_fields(f)
+        view, fv = csf.packed(), _pack_dense[n](*fields)
+    else:
+        view, fv = ctypes.byref(csf.view()), (DenseView * n)(*[f if isinstance(f, DenseView) else dense_view(f) for f in factors])
+    _check(_sc_execute(plan.handle, view, fv, n, _addr(out), _addr(workspace), int(workspace_bytes), int(stream)), "sc_execute")
 
 
 STATIC_WORKSPACE_BYTES = 32 << 20   # SC_STATIC_WORKSPACE_BYTES of the header

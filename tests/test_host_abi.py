@@ -540,3 +540,20 @@ def test_cost_evaluator_picks_a_schedule():
     plan = sc.plan_create(cfg["expr"], csf, odd, sc.schedule("auto"))
     assert sc.plan_chosen(plan) == ("fused", 3)
     assert _status(sc.plan_create, cfg["expr"], csf, odd, sc.schedule("auto", deterministic=True)) == "SC_ERR_SCHED_UNSUPPORTED"
+
+
+@pytest.mark.parametrize("order", [2, 3, 4])
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+def test_packed_views(order, dtype):
+    """What an execution hands over by one call of pack is what the ctypes records hold: arrays, tensors, longer rows, a record."""
+    import torch
+    dims = (5, 7, 6, 4)[:order]
+    key = np.arange(0, int(np.prod(dims)), 3)
+    coords = [np.ascontiguousarray(c, dtype=np.int32) for c in np.unravel_index(key, dims)]
+    csf = sc.coo_to_csf(coords, np.ones(len(key), dtype), dims)
+    for c in (csf, csf.to_device("cpu")):
+        assert c.packed() == bytes(c.view())
+    t = torch.from_numpy(np.ones((9, 24), dtype))
+    for x in (np.ones((5, 8), dtype), t, t[:, :20], sc.dense_view(np.ones((3, 4), dtype)), sc.dense_view(None, "f32", 3, 4, 8)):
+        v = x if isinstance(x, sc.DenseView) else sc.dense_view(x)
+        assert sc._pack_dense[2](*sc._dense_fields(x) * 2) == bytes(v) * 2
