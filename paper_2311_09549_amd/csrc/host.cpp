@@ -917,9 +917,9 @@ void build_slices(const sc_plan *p, SliceSource src, int piece, const HostCsf &h
 {
     const int64_t S = p->nfib[0], children = p->nfib[1];
     // Steps per chunk: 64, fewer where that would leave wavefront slots without a chunk.
-    const int wide = src == SLICE_MTTKRP ? kMttkrpPlaces : 4;   // leaves (children) per step
+    const int wide = src == SLICE_MTTKRP ? (int)(1024 / (p->fcols[0] * (int64_t)esize(p->dtype))) : 4;   // leaves (children) per step
     int cap = std::min(64, 256 / wide);
-    while (cap > 64 / wide && (src == SLICE_ROWS ? children : p->nnz) < (int64_t)wide * cap * 8 * p->n_cu) cap /= 2;
+    while (cap > std::max(8, 64 / wide) && (src == SLICE_ROWS ? children : p->nnz) < (int64_t)wide * cap * 8 * p->n_cu) cap /= 2;
     // A thread per 256,000 leaves (children), at most eight; ranges of slices with about equal numbers of them.
     const int32_t *pos1 = h.pos[1], *pos2 = src == SLICE_ROWS ? nullptr : h.pos[2], *pos3 = src == SLICE_CHAIN ? h.pos[3] : nullptr;
     auto before = [&](int64_t s) { return (int64_t)(pos3 ? pos3[pos2[pos1[s]]] : pos2 ? pos2[pos1[s]] : pos1[s]); };
@@ -1442,6 +1442,7 @@ static void probe_class(const sc_plan *p, sc_sched_kind kind, bool deterministic
     for (int m = 0; m < 4; ++m) { q.dims[m] = p->dims[m]; q.nfib[m] = p->nfib[m]; }
     for (int s = 0; s < 3; ++s) { q.frows[s] = p->frows[s]; q.fcols[s] = p->fcols[s]; }
     q.out_elems = p->out_elems; q.out_row_elems = p->out_row_elems;
+    q.nnz_long = p->nnz_long;
     q.sched = kind;
     q.deterministic = deterministic;
     q.caps = kind == SC_SCHED_LINEAR ? TileCaps{1024, 1024, 1024} : default_caps(q.kind, q.dtype, kind, q.fcols);
@@ -1909,6 +1910,12 @@ static sc_status plan_create_impl(sc_plan **out, const char *expr, const sc_csf_
         *out = p;
         return SC_OK;
     }
+
+    if (p->kind == K_MTTKRP3)
+        for (int64_t n = 0; n < p->nfib[0]; ++n) {
+            const int64_t entries = h.pos[2][h.pos[1][n + 1]] - h.pos[2][h.pos[1][n]];
+            if (entries >= kLongSlice) p->nnz_long += entries;
+        }
 
     // ---- schedule ----
     if (sched->deterministic != 0 && sched->deterministic != 1) return SC_ERR_SCHED_UNSUPPORTED;

@@ -947,13 +947,18 @@ sc_status launch_fixup(const sc_plan *p, Launcher &ln, const FixLevel &lv, void 
     return ln.status;
 }
 
-// MTTKRPs with rows of 128 bytes (fp32 at rank 32, fp64 at 16) whose slices hold 160 entries and more on average run over steps: shorter slices leave
-// lane groups without a fiber.  Calls in the kernel over tiles and over steps, us, by entries per slice: uniform, 3 M entries 300 55.1 and 46.5 (fp64 60.3 and
-// 50.0), 96 52.2 and 57.0, 48 51.3 and 60.1, 12 53.7 and 78.8; 20 M 222 484 and 475; power laws, 20 M 400 182 and 157, 1 M 200 21.4 and 17.0 (fp64 21.0 and 18.0),
-// 5 M 100 63.1 and 57.9, 1 M 12 28.7 and 26.3 (fp64 27.9 and 28.6).  Rows of 256 bytes gained nothing (6 M at rank 64 116 and 113, at 128 207 and 218).
+// MTTKRPs with rows of 64 bytes in fp32 and of 128 run over steps where at least half of 32,768 entries and more lie in slices of 160 and more, in fp64
+// seven tenths: short slices leave lane groups without a fiber, and few entries leave the lists longer than the walk.  Device time of a call in the
+// kernel over tiles and over steps, us, at ranks 16 and 32 in fp32: power laws with a share in long slices of 0.43 (300,000 entries in 48,000 slices)
+// 16.6,16.0 and 15.0,16.0; 0.52 (40,000 in 2,000) 11.1,9.2 and 11.3,8.3; 0.57 (100,000 in 4,750) 14.8,9.6 and 12.2,9.4; 0.62 (300,000 in 9,800) 17.1,10.7 and
+// 14.0,10.9; 0.65 (1 M in 62,000) 24.1,24.1 and 25.6,24.2; 0.81 (5 M in 50,000) 60.0,51.1 and 57.8,53.6; 20 M in 50,000 174,134 and 170,144; uniform,
+// 300 per slice 46.8,34.2 and 50.6,43.6, 96 (none long) 52.2,57.0 at 32, 48 51.3,60.1, 12 53.7,78.8; 20,000 entries 8.8,9.8 and 8.9,9.2.  In fp64 at rank 16: share 0.57
+// 10.5,10.1, 0.62 12.5,12.3, 0.65 27.9,28.6, 0.81 72.6,64.1.  Rows of 256 bytes gained nothing (6 M at rank 64 116 and 113, at 128 207 and 218).
 static bool mttkrp_over_steps(const sc_plan *p)
 {
-    return p->kind == K_MTTKRP3 && p->sched == SC_SCHED_FUSED && p->fcols[0] * (p->dtype == SC_F64 ? 8 : 4) == 128 && p->nnz >= 160 * p->nfib[0];
+    if (p->kind != K_MTTKRP3 || p->sched != SC_SCHED_FUSED || p->nnz < 32768) return false;
+    if (p->dtype == SC_F64) return p->fcols[0] == 16 && 10 * p->nnz_long >= 7 * p->nnz;
+    return (p->fcols[0] == 16 || p->fcols[0] == 32) && 2 * p->nnz_long >= p->nnz;
 }
 
 // fp32 chains of order 3 in every class, and the last kernel of the FISSIONED order-4 chain at 8 x 8, unless the caller asks for a

@@ -62,7 +62,7 @@ __global__ void __launch_bounds__(NT, 4) chain4_kernel(ChainArgs a, const SliceR
     };
     union Lds {
         Own own[WAVES];
-        float sum[2][4 * 256];   // after the runs: sums on their way to another wavefront
+        sl_floatx4 sum[2][4 * 64];   // after the runs: sums on their way to another wavefront
     };
     __shared__ Lds lds;
     __shared__ int state_s[WAVES];

@@ -1,12 +1,13 @@
 // Fused MTTKRP over steps: A(i,:) = sum over the fibers f of slice i of C(j_f,:) * t(f,:), t(f,:) = sum over the leaves of f of B * D(k,:),
-// the Hadamard counterpart of the slice products (kernels_slice.hip), for rows of 128 bytes.  Eight lanes hold a row, 16 bytes each; the eight lane groups of a wavefront take
-// pieces of eight fibers of a slice at a time, grouped by length, so that all of them end in the same step: a row of C is gathered once per group of
+// the Hadamard counterpart of the slice products (kernels_slice.hip), for rows of 64 and 128 bytes.  LG lanes hold a row, 16 bytes each; the G = 64 / LG lane groups of a wavefront take
+// pieces of G fibers of a slice at a time, grouped by length, so that all of them end in the same step: a row of C is gathered once per group of
 // pieces, with every lane in use, where a walk of each lane group for itself gathers under the mask of the fibers that end at every step.  A
 // gather of 16 bytes per lane takes the L1 address path 16 cycles whatever its mask, and that path is what bounds these kernels.
 // 20 M entries at rank 32: 182 us in the kernel over tiles and 157 so; the path is 0.93 busy, at 21 cycles per gather where the rows that come
 // from the L2 (2 cycles a line) are counted in.
 // A wavefront owns a run of steps; there is no barrier.  The sum over a slice stays in registers, is added up over the lane groups where the
-// slice ends, and stored; a slice cut by a run's end is added to the zeroed row atomically.
+// slice ends, and stored; a slice cut by a run's end is added to the zeroed row atomically,
+// after the runs of a workgroup that lie inside one slice have been added up in LDS.
 #include "slice_common.h"
 
 #include <type_traits>
@@ -25,12 +26,12 @@ struct MttkrpArgs {
     void *A;
 };
 
-template <typename T>
+template <typename T, int LG>
 __global__ void __launch_bounds__(NT, 4) mttkrp3_steps_kernel(MttkrpArgs a, const SliceRun *__restrict__ runs, const SliceChunk *__restrict__ chunks)
 {
-    constexpr int VEC = 16 / (int)sizeof(T), LG = 8, G = 64 / LG, R = LG * VEC, WAVES = NT / 64;
+    constexpr int VEC = 16 / (int)sizeof(T), G = 64 / LG, R = LG * VEC, WAVES = NT / 64;
     constexpr int U = sizeof(T) == 4 ? 8 : 4;   // steps per batch: 3 M entries in fp64 52.7 us with eight, 40.6 with four; 20 M in fp32 168 and 176
-    static_assert(G == kMttkrpPlaces, "leaves per step");
+    static_assert(G >= 4, "four places of a lane belong to one step");
     typedef T Vec __attribute__((ext_vector_type(VEC)));
     struct alignas(2 * sizeof(T)) Rec { uint32_t off; T v; };
     struct Own {                       // a wavefront's own staging region
@@ -38,8 +39,14 @@ __global__ void __launch_bounds__(NT, 4) mttkrp3_steps_kernel(MttkrpArgs a, cons
         uint32_t coff[256];
         T swap[256];                   // the chunk's values while it is staged
     };
-    __shared__ Own own[WAVES];
-    static_assert(sizeof(own) <= mttkrp_steps_lds_bytes(sizeof(T)), "LDS the plan reports");
+    union Lds {
+        Own own[WAVES];
+        Vec sum[2][64];                // after the runs: sums on their way to another wavefront
+    };
+    __shared__ Lds lds;
+    __shared__ int state_s[WAVES];
+    Own(&own)[WAVES] = lds.own;
+    static_assert(sizeof(lds) + sizeof(state_s) <= mttkrp_steps_lds_bytes(sizeof(T)), "LDS the plan reports");
 
     const int wave = sl_uni(threadIdx.x / 64), lane = threadIdx.x % 64;
     const int g = lane / LG;
@@ -56,7 +63,8 @@ __global__ void __launch_bounds__(NT, 4) mttkrp3_steps_kernel(MttkrpArgs a, cons
     const SliceRun r = runs[min(run, a.nruns)], r_end = runs[min(run + 1, a.nruns)];
     const int c_end = r_end.chunk0 + (r_end.step > 0 ? 1 : 0);   // one past the last chunk of which this run has steps
     SliceChunk ch = chunks[r.chunk0];
-    int sl = ch.slice0 + __builtin_popcountll(ch.send & ((1ull << r.step) - 1));
+    const int slice0 = ch.slice0 + __builtin_popcountll(ch.send & ((1ull << r.step) - 1));
+    int sl = slice0;
     bool open = (r.flags & 1) != 0;   // the slice began in an earlier run
 
     // Global reads of a chunk's staging, issued a chunk ahead: a lane takes four places, 4 lane .. 4 lane + 3 (places past the chunk repeat its last ones).
@@ -169,6 +177,10 @@ __global__ void __launch_bounds__(NT, 4) mttkrp3_steps_kernel(MttkrpArgs a, cons
             last_row = __builtin_amdgcn_readlane(rowv, min(sl - sl_base, 63));
         }
     }
+    acc += tot;
+    tot = Vec{};
+    sl_sum_runs<WAVES, 1, 1>(reinterpret_cast<Vec (&)[1]>(acc), goes_on, open && sl == slice0, lds.sum, state_s, wave, lane);
+    __syncthreads();   // the sums have been read: their space is the staging regions again
     if (goes_on) emit(last_row, true);
 }
 
@@ -196,8 +208,9 @@ sc_status launch_mttkrp_steps(const sc_plan *p, Launcher &ln, const sc_csf_view 
     a.A = out;
     const int blocks = (a.nruns + NT / 64 - 1) / (NT / 64);
     ln.begin("mttkrp3_fused");
-    if (p->dtype == SC_F64) mttkrp3_steps_kernel<double><<<blocks, NT, 0, ln.stream>>>(a, st.d_runs, st.d_chunks);
-    else mttkrp3_steps_kernel<float><<<blocks, NT, 0, ln.stream>>>(a, st.d_runs, st.d_chunks);
+    if (p->dtype == SC_F64) mttkrp3_steps_kernel<double, 8><<<blocks, NT, 0, ln.stream>>>(a, st.d_runs, st.d_chunks);
+    else if (p->fcols[0] == 32) mttkrp3_steps_kernel<float, 8><<<blocks, NT, 0, ln.stream>>>(a, st.d_runs, st.d_chunks);
+    else mttkrp3_steps_kernel<float, 4><<<blocks, NT, 0, ln.stream>>>(a, st.d_runs, st.d_chunks);
     ln.end();
     return ln.status;
 }

@@ -101,7 +101,7 @@ __global__ void __launch_bounds__(NT, slice_occupancy(LT * MT, EDGE)) slice_kern
     };
     union Lds {
         Own own[WAVES];
-        float sum[2][RPB > 1 ? 256 * LT * MT : 4];   // after the runs: sums on their way to another wavefront
+        sl_floatx4 sum[2][RPB > 1 ? 64 * LT * MT : 1];   // after the runs: sums on their way to another wavefront
     };
     __shared__ Lds lds;
     __shared__ int state_s[WAVES];

@@ -215,6 +215,7 @@ struct sc_plan {
     int32_t *d_slot_b = nullptr;   // plan-owned device copy, in the order of the device tile table
     sck::WalkTables walk;          // plan-owned device tables of the segmented walks (kernels that use them)
     sck::SliceTables slice;        // plan-owned device tables of the slice products
+    int64_t nnz_long = 0;          // entries in slices of kLongSlice entries and more (MTTKRP)
     double model_flops = 0, model_bytes = 0;
     std::string text;  // description
 
@@ -279,8 +280,8 @@ SliceSource plan_slice_source(const sc_plan *plan, int *piece);
 SliceShape slice_shape(int64_t L, int64_t W);
 constexpr size_t kSliceLdsBytes = 16400;   // LDS of a workgroup, at every shape
 constexpr size_t kChainLdsBytes = 20496;   // of a chain of order 4
-constexpr size_t mttkrp_steps_lds_bytes(size_t e) { return 4 * 256 * (2 * e + 4 + e); }
-constexpr int kMttkrpPlaces = 8;   // leaves per step of an MTTKRP
+constexpr size_t mttkrp_steps_lds_bytes(size_t e) { return 4 * 256 * (2 * e + 4 + e) + 16; }
+constexpr int64_t kLongSlice = 160;   // entries of what the choice of an MTTKRP's kernel takes for a long slice
 constexpr int kMttkrpPiece = 6;    // leaves per piece of its fibers at most: 16, 8 and 6 183, 168 and 165 us (20 M entries at rank 32; long pieces differ more in length)
 
 // True when the kernels of the plan can run without floating-point atomics (FUSED schedules of

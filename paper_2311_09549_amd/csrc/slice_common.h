@@ -40,25 +40,24 @@ __device__ __forceinline__ void sl_lanes_meet()
 
 // What is left of a slice that goes on in the next run.  Runs that lie inside one slice are added up inside the workgroup first,
 // in two rounds (0 to 1 and 2 to 3, then the pair 0, 1 to the last that follows it); what is left of `goes_on` afterwards goes to the slice's row atomically.
-// RPB runs of WPR wavefronts per workgroup, N accumulators of a lane; `same`: the run ends in the slice it began in, which an earlier run began.
+// RPB runs of WPR wavefronts per workgroup, N accumulators (of 16 bytes) of a lane; `same`: the run ends in the slice it began in, which an earlier run began.
 // The staging regions are free once the first barrier is passed, and sums may lie in them until the next one after this.
-template <int RPB, int WPR, int N, int ROWS>
-__device__ __forceinline__ void sl_sum_runs(sl_floatx4 (&acc)[N], bool &goes_on, bool same, float (&sum)[2][ROWS], int *state_s, int wave, int lane)
+template <int RPB, int WPR, int N, typename V>
+__device__ __forceinline__ void sl_sum_runs(V (&acc)[N], bool &goes_on, bool same, V (*sum)[64 * N], int *state_s, int wave, int lane)
 {
-    static_assert(ROWS >= 256 * N, "a wavefront's accumulators");
     const int rw = wave / WPR, sub = wave % WPR;
     if (lane == 0) state_s[wave] = (goes_on ? 1 : 0) | (goes_on && same ? 2 : 0);
     __syncthreads();
     auto state = [&](int n) { return sl_uni(state_s[n * WPR]); };
     // run n's sum goes to run n + 1
     auto pass = [&](int n) { return n + 1 < RPB && (state(n) & 1) && (state(n + 1) & 2); };
-    auto send_to = [&](float *buf) {
+    auto send_to = [&](V *buf) {
 #pragma unroll
-        for (int x = 0; x < N; ++x) *reinterpret_cast<sl_floatx4 *>(buf + x * 256 + 4 * lane) = acc[x];
+        for (int x = 0; x < N; ++x) buf[x * 64 + lane] = acc[x];
     };
-    auto add_from = [&](const float *buf) {
+    auto add_from = [&](const V *buf) {
 #pragma unroll
-        for (int x = 0; x < N; ++x) acc[x] += *reinterpret_cast<const sl_floatx4 *>(buf + x * 256 + 4 * lane);
+        for (int x = 0; x < N; ++x) acc[x] += buf[x * 64 + lane];
     };
     const bool mine = rw % 2 == 0 && pass(rw), theirs = rw % 2 == 1 && pass(rw - 1);
     if (mine) send_to(sum[wave / (2 * WPR) * WPR + sub]);

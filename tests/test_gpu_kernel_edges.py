@@ -284,17 +284,17 @@ def test_slice_products_longer_chunks(oracle, ranks, which, least, cap):
         assert chunks >= slots / cap / 2
 
 
-MTTKRPS = {   # 160 entries per slice and more
-    "units": [[1] * n for n in (160, 200, 255, 256, 257, 700, 1, 9)],
-    "lengths": [[1, 2, 3, 5, 6, 7, 12, 13, 40] * 4, [700, 1, 33], [6] * 64, [2] * 300, [1]],
-    "heavy": [[1, 2, 3, 1] * 1500, [1], [2, 1] * 100],   # one slice through many runs
+MTTKRPS = {   # 32,768 entries and more, most of them in slices of 160 and more
+    "units": [[1] * n for n in (160, 200, 255, 256, 257, 700, 1, 9)] * 19,
+    "lengths": [[1, 2, 3, 5, 6, 7, 12, 13, 40] * 4, [700, 1, 33], [6] * 64, [2] * 300, [1]] * 16,
+    "heavy": [[1], [1, 2, 3, 1] * 4700, [1], [2, 1] * 100],   # one slice through many runs and workgroups
 }
 
 
-@pytest.mark.parametrize("dtype,R", [("f32", 32), ("f64", 16)])
+@pytest.mark.parametrize("dtype,R", [("f32", 16), ("f32", 32), ("f64", 16)])
 @pytest.mark.parametrize("name", sorted(MTTKRPS))
 def test_mttkrp_over_steps(oracle, name, dtype, R):
-    """Pieces of fibers in eights, chunks, runs inside slices; and an infinity in a row of C or D, which reaches the outputs that refer to it only."""
+    """Pieces of fibers in eights and sixteens, chunks, runs inside slices; and an infinity in a row of C or D, which reaches the outputs that refer to it only."""
     dims, coords, rng = _fibers(MTTKRPS[name])
     cfg = dict(kind="mttkrp3", dims=dims, nnz=coords[0].size, ranks=(R,), dtype=dtype, expr=synth.KINDS["mttkrp3"][0])
     dt = np.float64 if dtype == "f64" else np.float32
