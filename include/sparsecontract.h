@@ -34,8 +34,9 @@
  *   - sc_execute allocates nothing, never synchronises and launches only on the stream
  *     it is given.  sc_plan_create allocates the plan-owned device tables: tile records and,
  *     for the kernels that use them, walk tables (4 bytes per stored nonzero and per node of
- *     the level above) or step tables (about 5.4 bytes per stored nonzero and 4.5 per node of
- *     the level above, at most 20 and 16), see sc_plan_create.
+ *     the level above) or step tables (order-3 chains about 5.4 bytes per stored nonzero and 4.5 per
+ *     node of the level above, at most 20 and 16; 11 per nonzero of a 50 M order-4 chain, 7 to 8 of a
+ *     20 M MTTKRP, at most 52 and 80 where slices are short), see sc_plan_create.
  */
 #ifndef SPARSECONTRACT_H
 #define SPARSECONTRACT_H
@@ -133,7 +134,7 @@ typedef struct {
  *   fuse_depth[t]    how many leading sparse loops producer and consumer share (the fused prefix of
  *                    Section 4.2).  FISSIONED and AUTO: must be 0.  FUSED: 0 = the depth the library's
  *                    kernel for this expression is built at, or that depth itself (order-3 and order-4
- *                    TTM chains 1: the temporaries of a chunk of a slice in LDS; MTTKRP and the
+ *                    TTM chains 1: the temporaries of a chunk of a slice in LDS or registers; MTTKRP and the
  *                    SDDMM -> SpMM pair 2: the temporary of one fiber / one stored entry in
  *                    registers); any other value returns SC_ERR_SCHED_UNSUPPORTED rather than being
  *                    ignored.  sc_plan_describe reports the on-chip granularity.

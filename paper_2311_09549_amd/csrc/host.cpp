@@ -1612,11 +1612,12 @@ static sc_status plan_ttmc_all(sc_plan *p, const char *expr, const Term &lhs, co
     // 40,000 slices 2486 and 1912, 4,000 slices 265 and 206; 64 x 64 x 64, 40,000 553 and 517; 64 x 32 x 32, 40,000 (5.2e9) 178 and 168; below, the
     // launch that splits C takes what is gained: 128 x 16 x 16, 40,000 (2.6e9) 100 and 95, 128 x 32 x 32, 4,000 (1.0e9) 43.0 and 41.7, 300 (0.08e9) 25.4
     // and 28.0; 64 x 16 x 16, 4,000 (0.13e9) 26.7 and 28.6.  L = 32 reads S at the memory's rate either way: 32 x 128 x 128, 40,000 (42e9) 1599 and 1593.
-    // At L = 128 six additions to a sum for 32 slices take the place of eight; with as long chains of them the error would be 3 to 5 % larger
-    // (1.37e-6 for 1.31e-6 in chunks of 5,000 slices, 0.93e-6 in chunks of 2,500), so chunks stop at sixteen wavefronts per compute unit where they keep
-    // 600 slices; in shorter ones it is the smaller one (3.8e-7 for 4.3e-7 in 500 slices) and more of them take longer (238 us for 206).
+    // At L = 128 a chunk's sum is one chain: chunks stop at sixteen wavefronts per compute unit where they keep 600 slices; more of shorter ones
+    // take longer (4,000 slices 238 us for 206).  There it needs five sixths of the slices stored, as otherwise its error may be the larger one: of
+    // 99,000 slices, fp32 and this form, 128 x 16 x 32 with 0.85 stored 3.62e-7 and 3.46e-7, with 0.75 even, with 30,000 entries in all 2.07e-7 and
+    // 2.64e-7; 128 x 32 x 32 with 0.85 stored 4.75e-7 and 4.40e-7 (349 and 288 us).
     // (S takes 62 MB and more there, so no plan outgrows the fixed scratch array by the parts of C.)
-    const bool split = p->k5_mfma_reduce && p->fcols[0] >= 64 && 2.0 * L * M * N * (double)units >= 4e9;
+    const bool split = p->k5_mfma_reduce && (p->fcols[0] == 64 || (p->fcols[0] == 128 && 6 * p->nfib[0] >= 5 * units)) && 2.0 * L * M * N * (double)units >= 4e9;
     if (p->k5_mfma_reduce) {
         const int64_t per_chunk = mn / 64;
         int64_t want = (int64_t)p->n_cu * 8;

@@ -970,7 +970,7 @@ SliceSource plan_slice_source(const sc_plan *p, int *piece)
     if (piece) *piece = kSlicePiece;
     if (p->deterministic) return SLICE_NONE;
     if (mttkrp_over_steps(p)) {
-        if (piece) *piece = kMttkrpPiece;
+        if (piece) *piece = p->nnz >= 12 * p->nfib[1] ? kSlicePiece : kMttkrpPiece;   // (long fibers: a row of C for every piece)
         return SLICE_MTTKRP;
     }
     if (p->dtype != SC_F32) return SLICE_NONE;

@@ -175,23 +175,26 @@ __global__ void __launch_bounds__(NT, 2) mode0_reduce_mfma_kernel(K5Args a)
 }
 
 // The same partial sums from products of 16 bits: a value of 24 bits is the exact sum of three of 8, x = h + m + l, each of them a
-// bf16 (h is x without its low 16 bits, m the rest without its own, l what is left), and a product of two of them is exact in fp32.  Of the nine
-// products of parts the three below 2^-24 of the whole, m l, l m and l l, are left out; the other six are added in fp32, the small ones
+// bf16 (h the nearest to x, m to x - h, l what is left), and a product of two of them is exact in fp32.  Of the nine
+// products of parts the three below 2^-26 of the whole, m l, l m and l l, are left out; the other six are added in fp32, the small ones
 // first, by v_mfma_f32_16x16x32_bf16, which takes 32 slices at 16 times the fp32 rate.
 // C is split once by a launch of its own into rows of eight slices (k5_split_kernel), so that a lane reads operand A, eight slices of one l, with
 // one 16-byte load per part; S is read as it is, eight slices of four columns per lane, and split in registers: it passes once.
-// Infinities become NaN on the way (h = x, m = x - h), and a value below 2^-109 loses its last bits, which bf16 cannot hold.
-// Repeated calls, the reduction alone, 40,000 slices: 128 x 128 x 128 1396 us in fp32 (110 TFLOP/s of the 120 it reaches) and 758 (221; S alone takes 450),
-// 128 x 64 x 64 366 and 225, 64 x 64 x 64 200 and 158.  Error against double precision 1.31e-6 and 0.93e-6, 6.4e-7 and 4.9e-7, 6.4e-7 and 2.9e-7:
-// at L = 64 the six products of a step are added up apart from the sum they go to, which takes no longer there; at L = 128, whose registers are
-// full, it does (942 us), and shorter chunks serve instead (plan_ttmc_all).
+// Infinities become NaN on the way (h = x, m = x - h), as do values past the largest bf16 (3.39e38), and a value below 2^-109 loses its last bits,
+// which bf16 cannot hold.
+// Repeated calls, the reduction alone, 40,000 slices, fp32 and this form: 128 x 128 x 128 1398 and 810 us (S alone takes 450), 128 x 64 x 64 366 and 228,
+// 64 x 64 x 64 198 and 155.  Error against double precision 1.31e-6 and 0.74e-6, 6.3e-7 and 4.1e-7, 6.4e-7 and 2.0e-7.
+// At L = 64 the six products of a step are added up apart from the sum they go to; at L = 128, whose registers are
+// full, that took longer (942 us for 765), and shorter chunks serve instead (plan_ttmc_all).
 constexpr int K5_K = 32;   // slices per step
 typedef __bf16 k5_bf16 __attribute__((ext_vector_type(8)));
 
-// high halves of two words: the truncated bf16 of b (low) and a
+// the nearest bf16 of a (low half) and b
 __device__ __forceinline__ uint32_t k5_pack(float a, float b)
 {
-    return __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), 0x07060302);
+    typedef float F2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 B2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(F2{a, b}, B2));
 }
 
 // the three parts of eight values
@@ -202,10 +205,16 @@ __device__ __forceinline__ void k5_parts(const float (&x)[8], uint4 (&part)[3])
     for (int j = 0; j < 8; ++j) r[j] = x[j];
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
-        part[p] = uint4{k5_pack(r[1], r[0]), k5_pack(r[3], r[2]), k5_pack(r[5], r[4]), k5_pack(r[7], r[6])};
+        uint32_t w[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) w[j] = k5_pack(r[2 * j], r[2 * j + 1]);
+        part[p] = uint4{w[0], w[1], w[2], w[3]};
         if (p < 2)
 #pragma unroll
-            for (int j = 0; j < 8; ++j) r[j] -= __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, r[j]) & 0xffff0000u);
+            for (int j = 0; j < 4; ++j) {
+                r[2 * j] -= __builtin_bit_cast(float, w[j] << 16);
+                r[2 * j + 1] -= __builtin_bit_cast(float, w[j] & 0xffff0000u);
+            }
     }
 }
 
@@ -229,6 +238,9 @@ template <int LT>   // L = 16 LT, an even number of tiles
 __global__ void __launch_bounds__(NT, 2) mode0_reduce_split_kernel(K5Args a, const uint4 *__restrict__ C3, int64_t groups)
 {
     constexpr bool APART = LT <= 4;   // a step's products are added up before they are added to the sum
+    // The instruction's own sums are cut off, not rounded, and always to the same side, which adds up over the steps.  So S is taken with the other
+    // sign every TURN steps, and the sum turned with it (64 x 32 x 32, 99,000 slices, one in three stored: 3.9e-7 without, 1.7e-7 so; fp32 2.1e-7).
+    constexpr int TURN = APART ? 1 : 4;
     const int tid = threadIdx.x;
     const int wave = tid / 64, lane = tid % 64, kk = lane / 16, col = lane % 16;
     const int c = ((int)blockIdx.y * ((int)blockDim.x / 64) + wave) * 64 + 4 * col;
@@ -253,13 +265,15 @@ __global__ void __launch_bounds__(NT, 2) mode0_reduce_split_kernel(K5Args a, con
     };
     load_s(r0);
     load_c(cv[0], r0, 0);
+    float sign = 1.f;
+    int to_turn = TURN;
     for (int64_t r = r0; r < r1; r += K5_K) {
         uint4 s[4][3];
 #pragma unroll
         for (int x = 0; x < 4; ++x) {
             float v[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = r + 8 * kk + j < a.rows ? raw[j][x] : 0.f;   // (slices past the last: zero times zero)
+            for (int j = 0; j < 8; ++j) v[j] = r + 8 * kk + j < a.rows ? sign * raw[j][x] : 0.f;   // (slices past the last: zero times zero)
             k5_parts(v, s[x]);
         }
         const int64_t rn = min(r + K5_K, r1 - 1) / K5_K * K5_K;   // the next step, or this one again
@@ -284,9 +298,23 @@ __global__ void __launch_bounds__(NT, 2) mode0_reduce_split_kernel(K5Args a, con
             add(0, 1);
             add(0, 0);
 #pragma unroll
-            for (int x = 0; x < 4; ++x) acc[lt][x] = APART ? acc[lt][x] + sum[x] : sum[x];
+            for (int x = 0; x < 4; ++x) acc[lt][x] = APART ? acc[lt][x] + sign * sum[x] : sum[x];
+        }
+        if (--to_turn == 0 && (APART || r + K5_K < r1)) {
+            to_turn = TURN;
+            sign = -sign;
+            if (!APART)
+#pragma unroll
+                for (int lt = 0; lt < LT; ++lt)
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) acc[lt][x] = -acc[lt][x];
         }
     }
+    if (!APART)
+#pragma unroll
+        for (int lt = 0; lt < LT; ++lt)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) acc[lt][x] *= sign;
     // acc[lt][x][q] = partial(l = 16 lt + 4 kk + q, column c + x)
     float *P = static_cast<float *>(a.partials) + (int64_t)blockIdx.x * a.L * a.MN + c;
 #pragma unroll
