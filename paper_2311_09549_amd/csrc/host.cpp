@@ -461,14 +461,9 @@ void tile_order(const sc_plan *p, const HostCsf &h, std::vector<uint32_t> &at)
 }
 
 // Builds the tile table: leaves are cut into runs of at most caps.tn, shortened so that no
-// tile touches more than caps.ta level-a nodes (and caps.tb level-b nodes for order 4).  `whole`: a slice that does not end in a tile starts the
-// next one, unless it starts the tile, so that only slices longer than a tile are shared.
-void build_tiles(const sc_csf_view *v, const HostCsf &h, const TileCaps &caps, bool whole, std::vector<TileRec> &tiles)
+// tile touches more than caps.ta level-a nodes (and caps.tb level-b nodes for order 4).
+void build_tiles(const sc_csf_view *v, const HostCsf &h, const TileCaps &caps, std::vector<TileRec> &tiles)
 {
-    const auto first_leaf = [&](int64_t slice) {
-        for (int m = 1; m < v->order; ++m) slice = h.pos[m][slice];
-        return slice;
-    };
     const int d = v->order;
     const int64_t nnz = v->nnz;
     tiles.clear();
@@ -488,11 +483,6 @@ void build_tiles(const sc_csf_view *v, const HostCsf &h, const TileCaps &caps, b
                 n1 = std::min<int64_t>(n1, h.pos[la + 1][h.pos[lb + 1][b0 + caps.tb]]);
         }
         if (lc >= 0) c0 = parent_of(h.pos[lc + 1], v->nfib[lc], b0);
-        if (whole && n1 < nnz) {
-            int32_t slice = parent_of(h.pos[la + 1], v->nfib[la], (int32_t)n1);   // of the first leaf past the tile
-            for (int m = la; m > 0; --m) slice = parent_of(h.pos[m], v->nfib[m - 1], slice);
-            if (first_leaf(slice) > n0) n1 = first_leaf(slice);
-        }
         const int32_t a1 = parent_of(h.pos[la + 1], v->nfib[la], (int32_t)(n1 - 1));
         t.n0 = (int32_t)n0; t.n1 = (int32_t)n1;
         t.a0 = a0; t.na = a1 - a0 + 1;
@@ -1982,23 +1972,11 @@ static sc_status plan_create_impl(sc_plan **out, const char *expr, const sc_csf_
                      : default_caps(p->kind, p->dtype, p->sched, p->fcols);
     if (p->caps.tn <= 0) return SC_ERR_SCHED_UNSUPPORTED;  // no kernel instantiated for these ranks
     const Tuning &tu = p->tune;
-    const int32_t most_leaves = p->caps.tn;
     if (!linear) p->caps.tn = plan_tile_leaves(p);
-    // Tiles of few leaves hold whole slices where every slice fits one: then no row is added to, none has to be zero before (but those of empty
-    // slices), nor fixed up under a deterministic plan, and a call is a launch or three fewer.  Calls with and without, us: 8,000 entries of 200 x 200 x 200 in
-    // fp64 9.5 and 6.3 (device 7.3 and 5.3); MTTKRP of 50,000 entries in 2,000 slices 12.2 and 8.2, deterministic 15.2 and 8.5; sampled product of 200,000
-    // in 20,000 rows 12.5 and 10.0, deterministic 15.2 and 10.0.  With longer slices among them shared rows remain: 14.7 and 14.8 (100,000 entries at rank 16, Zipf 1.1).
-    bool whole_slices = p->caps.tn < most_leaves;
     if (tu.tn) p->caps.tn = tu.tn;
     if (tu.ta) p->caps.ta = tu.ta;
     if (tu.tb) p->caps.tb = tu.tb;
     if (lds_bytes_needed(p) > 64 * 1024) return SC_ERR_SCHED_UNSUPPORTED;
-    for (int64_t n = 0, z = 0; whole_slices && n < p->nfib[0]; ++n) {
-        int64_t end = n + 1;
-        for (int m = 1; m < p->order; ++m) end = h.pos[m][end];
-        whole_slices = end - z <= p->caps.tn;
-        z = end;
-    }
     SliceBuild slices;
     bool sliced = false;
     int piece = 1;
@@ -2025,7 +2003,7 @@ static sc_status plan_create_impl(sc_plan **out, const char *expr, const sc_csf_
             }
         }
         try {
-            build_tiles(sparse, h, p->caps, whole_slices, p->tiles);
+            build_tiles(sparse, h, p->caps, p->tiles);
         } catch (...) { failed = true; }
         if (listed) beside.join();
         else if (sliced) list();

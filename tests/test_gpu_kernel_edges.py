@@ -419,17 +419,3 @@ def test_small_tiles(oracle, kind, dims, ranks, most, dtype, deterministic):
         assert first[1] - first[0] <= most
     if kind == "sddmm_spmm":
         _check(oracle, cfg, data, "fissioned", deterministic)
-
-
-@pytest.mark.parametrize("deterministic", [False, True])
-@pytest.mark.parametrize("kind,ranks,dtype", [("sddmm_spmm", (32, 32), "f32"), ("mttkrp3", (32,), "f32"), ("mttkrp3", (64,), "f64"), ("ttmc3", (8, 8), "f64")])
-def test_whole_slices_per_tile(oracle, kind, ranks, dtype, deterministic):
-    """Slices that all fit a tile of 64 leaves share none, an empty one among them or not; one more entry, and they do."""
-    dims = (1300, 4000) if kind == "sddmm_spmm" else (1300, 41, 97)
-    full = [(i, 64 if i % 5 == 0 else 1 + i % 40) for i in range(1300)]
-    for lengths in (full, [(0, 65)] + full[1:], full[:250] + full[251:]):
-        cfg, data = _problem(kind, dims, lengths, ranks, dtype)
-        con = _check(oracle, cfg, data, "fused", deterministic)
-        tiles = [sc.plan_tile(con.plan, n) for n in range(sc.plan_tile_count(con.plan))]
-        assert any(t[8] & (1 if kind == "sddmm_spmm" else 4) for t in tiles) == (lengths[0][1] == 65)
-        assert max(t[1] - t[0] for t in tiles) == 64
