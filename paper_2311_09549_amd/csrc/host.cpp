@@ -627,6 +627,7 @@ struct SlicePieces {
 // Lists the steps of the slices [s0, s1), `wide` leaves each (a multiple of four), in chunks of at most `cap`.
 void list_steps(SliceSource src, int piece, int wide, int cap, const HostCsf &h, int64_t s0, int64_t s1, SlicePart &b)
 {
+    piece = std::min(piece, cap);   // an empty chunk holds any piece, so that the next one is always taken
     const int32_t *pos1 = h.pos[1];
     const int64_t children = pos1[s1] - pos1[s0];
     SliceChunk c = {};

@@ -315,6 +315,20 @@ def test_mttkrp_over_steps(oracle, name, dtype, R):
             _poisoned(oracle, cfg, dict(data, factors=bad), "fused", same=False)
 
 
+@pytest.mark.parametrize("dtype,R", [("f32", 16), ("f32", 32), ("f64", 16)])
+@pytest.mark.parametrize("least", [33_000, 200_000, 500_000, 600_000])
+def test_mttkrp_over_steps_long_fibers(oracle, dtype, R, least):
+    """Pieces of sixteen leaves, in chunks of 8 steps (whose pieces are of 8) and longer ones."""
+    lengths = np.random.default_rng(1).integers(9, 41, size=least // 24)
+    dims, coords, rng = _fibers([list(s) for s in np.array_split(lengths, least // 500)])
+    assert coords[0].size >= 12 * lengths.size
+    cfg = dict(kind="mttkrp3", dims=dims, nnz=coords[0].size, ranks=(R,), dtype=dtype, expr=synth.KINDS["mttkrp3"][0])
+    dt = np.float64 if dtype == "f64" else np.float32
+    factors = [rng.standard_normal(s).astype(dt) for s in synth.factor_shapes(cfg)]
+    con = _check(oracle, cfg, dict(coords=coords, vals=rng.uniform(-1, 1, coords[0].size).astype(dt), factors=factors), "fused")
+    assert "slice products" in sc.plan_describe(con.plan)
+
+
 @pytest.mark.parametrize("least,slices", [(300_000, 1800), (1_100_000, 400)])
 def test_mttkrp_over_steps_longer_chunks(oracle, least, slices):
     """Chunks of 16 and 32 steps, listed by one thread and by several."""
