@@ -576,6 +576,7 @@ struct SlicePart {
     std::vector<uint32_t> leaf, at;
     std::vector<int32_t> gj, first, gk;
     std::vector<ChainChunk> kids;     // kid0 from the part's first
+    std::vector<uint64_t> empty;      // beside kids: steps without a leaf in which a group begins
     int32_t nsteps = 0, ngroups = 0, nkids = 0;
     bool failed = false;              // out of memory
 };
@@ -584,6 +585,7 @@ struct SliceBuild {
     std::vector<SliceRun> runs;
     std::vector<SliceChunk> chunks;
     std::vector<ChainChunk> kids;
+    std::vector<uint64_t> empty;
     std::vector<int32_t> cut_rows;   // output rows of the slices that a run's end cuts
 };
 
@@ -817,6 +819,7 @@ void list_chain(int cap, const HostCsf &h, int64_t s0, int64_t s1, SlicePart &b)
     const int32_t *pos1 = h.pos[1], *pos2 = h.pos[2], *pos3 = h.pos[3], *crd3 = h.crd[3];
     SliceChunk c = {};
     ChainChunk k = {};
+    uint64_t empty = 0;
     // Places for the steps of a chunk are there before it is begun, and grow by many chunks at a time.
     auto make_room = [&] {
         const size_t steps = (size_t)b.nsteps + 64, kids = (size_t)b.nkids + 32;
@@ -849,9 +852,11 @@ void list_chain(int cap, const HostCsf &h, int64_t s0, int64_t s1, SlicePart &b)
             }
             b.chunks.push_back(c);
             b.kids.push_back(k);
+            b.empty.push_back(empty);
         }
         c = SliceChunk{};
         k = ChainChunk{};
+        empty = 0;
         c.step0 = b.nsteps;
         c.leaf0 = next_leaf;
         c.group0 = b.ngroups;
@@ -890,7 +895,10 @@ void list_chain(int cap, const HostCsf &h, int64_t s0, int64_t s1, SlicePart &b)
                 const int32_t have = std::min(4, w.npieces - g);
                 for (int32_t u = 0; u < w.piece(g).n; ++u) {
                     const int32_t most = w.longest(g, u);
-                    if (most > 1 && c.nsteps % 2) add_steps(1);
+                    if (most > 1 && c.nsteps % 2) {
+                        if (u == 0) empty |= 1ull << c.nsteps;
+                        add_steps(1);
+                    }
                     uint32_t *leaf = b.leaf.data() + 4 * (size_t)b.nsteps;
                     uint8_t *place = reinterpret_cast<uint8_t *>(b.at.data() + b.nsteps);
                     add_steps(most > 1 ? (most + 1) / 2 * 2 : 1, most > 1);
@@ -982,6 +990,7 @@ void build_slices(const sc_plan *p, SliceSource src, int piece, const HostCsf &h
             k.kid0 += nkids;
             b.kids.push_back(k);
         }
+        b.empty.insert(b.empty.end(), part.empty.begin(), part.empty.end());
         nsteps += part.nsteps;
         ngroups += part.ngroups;
         nkids += part.nkids;
@@ -1024,7 +1033,9 @@ void build_slices(const sc_plan *p, SliceSource src, int piece, const HostCsf &h
         int32_t slice = k.slice0;
         for (int32_t s = 0; s < k.nsteps; s += grain) {
             const int32_t here = std::min(grain, k.nsteps - s);
-            if (b.runs.empty() || done >= total * (double)b.runs.size() / (double)nruns || k.step0 + s - run_step0 + here > most) {
+            // (a run does not end where a group's leaves are still to come: zero times its rows of C, if they hold an infinity, is no number)
+            const bool may = !(src == SLICE_CHAIN && s > 0 && b.empty[n] >> (s - 1) & 1);
+            if (b.runs.empty() || (may && done >= total * (double)b.runs.size() / (double)nruns) || k.step0 + s - run_step0 + here > most) {
                 b.runs.push_back(SliceRun{(int32_t)n, s, open ? 1 : 0, 0});
                 run_step0 = k.step0 + s;
                 const int32_t row = h.crd[0][slice];

@@ -182,6 +182,23 @@ __global__ void __launch_bounds__(NT, 4) chain4_kernel(ChainArgs a, const SliceR
         co[4] = row_at(st.j.z, a.rowC);
         co[6] = row_at(st.j.w, a.rowC);
         sl_lanes_meet();
+        // Where a run's end cuts a group, a child without a leaf (a piece without a child) in the one run has no row in it: its sum there is zero, and zero
+        // times a row with an infinity is no number.
+        if (from > 0 && !(gm >> (from - 1) & 1)) {
+            // The run begins inside a group: a child whose leaves (a piece whose children) all lie in the run before has no row in this one (its sum
+            // here is zero, and zero times a row with an infinity is no number).
+            int ln = lane, none = kNoRow;
+            __asm__ volatile("" : "+v"(ln), "+s"(none));   // worked out here: kept over the loop it costs registers
+            const int kk = ln / 16, col = ln % 16, last = min(from + __builtin_ctzll(gm >> from), to - 1);
+            const uint32_t no_leaf = row_at(none, a.rowE);
+            bool any = false;
+#pragma clang loop unroll(disable)
+            for (int s = from + col; s <= last; s += 16) any |= rec_s[4 * s + kk].off != no_leaf;
+            if (!(__ballot(any) >> 16 * kk & 0xffff)) coff_s[8 * (last / 2) + 2 * kk + last % 2] = row_at(none, a.rowC);
+            if (!(km >> (from - 1) & 1) && col < 2 && rec_s[4 * (from + col) + kk].off == no_leaf)
+                doff_s[4 * (min(from + __builtin_ctzll(km >> from) - 1, to - 2) + col) + kk] = row_at(none, a.rowD);   // (in the pair where they end)
+            sl_lanes_meet();
+        }
         ch = chunks[c + 1];
         kc = kids[c + 1];
         if (c + 1 < c_end) issue(ch, kc, st);

@@ -135,6 +135,15 @@ __global__ void __launch_bounds__(NT, 4) mttkrp3_steps_kernel(MttkrpArgs a, cons
         }
         reinterpret_cast<uint4 *>(coff_s)[lane] = uint4{(uint32_t)st.j.x * a.rowC, (uint32_t)st.j.y * a.rowC, (uint32_t)st.j.z * a.rowC, (uint32_t)st.j.w * a.rowC};
         sl_lanes_meet();
+        if (from > 0 && !(gm >> (from - 1) & 1)) {
+            // The run begins inside a group: a piece whose leaves all lie in the run before has no row in this one (its sum here is zero, and
+            // zero times a row with an infinity is no number).
+            int ln = lane, none = kNoRow;
+            __asm__ volatile("" : "+v"(ln), "+s"(none));   // worked out here: kept over the loop it costs registers
+            const int end = from + __builtin_ctzll(gm >> from), g = ln / LG;
+            if (rec_s[G * from + g].off == none * a.rowD) coff_s[G * end + g] = coff_s[G * min(end, to - 1) + g] = none * a.rowC;
+            sl_lanes_meet();
+        }
         ch = chunks[c + 1];
         if (c + 1 < c_end) issue(ch, st);
 

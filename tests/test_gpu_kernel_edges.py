@@ -209,8 +209,8 @@ def test_slice_products(oracle, shape, ranks, classes):
                 sc.tuning_set("tile_leaves", 0)
 
 
-def _poisoned(oracle, cfg, data, which, same=True):
-    """Every output element of the reference that is finite is finite here, and right; the others are not finite here, nor (`same`, in one kernel) another value."""
+def _poisoned(oracle, cfg, data, which):
+    """Every output element of the reference that is finite is finite here, and right; the others are not finite here, nor (in one kernel) another value."""
     got = _run(cfg, data, which).result()
     clean = [np.nan_to_num(f, nan=0.0, posinf=0.0, neginf=0.0) for f in data["factors"]]   # a zero in the place adds nothing to the bound of the others
     with np.errstate(invalid="ignore"):
@@ -220,7 +220,7 @@ def _poisoned(oracle, cfg, data, which, same=True):
     assert fine.any() and not fine.all()
     np.testing.assert_array_equal(np.isfinite(got), fine)
     assert np.all(np.abs(got[fine].astype(np.float64) - ref[fine]) <= 1e-5 * bound[fine])
-    if same and which != "fissioned":   # (its first kernel, the leaf traversal, multiplies by masked zeros)
+    if which != "fissioned":   # (its first kernel, the leaf traversal, multiplies by masked zeros)
         np.testing.assert_array_equal(got[~fine], ref[~fine].astype(np.float32))
 
 
@@ -295,7 +295,7 @@ MTTKRPS = {   # 32,768 entries and more, most of them in slices of 160 and more
 @pytest.mark.parametrize("dtype,R", [("f32", 16), ("f32", 32), ("f64", 16)])
 @pytest.mark.parametrize("name", sorted(MTTKRPS))
 def test_mttkrp_over_steps(oracle, name, dtype, R):
-    """Pieces of fibers in eights and sixteens, chunks, runs inside slices; and an infinity in a row of C or D, which reaches the outputs that refer to it only."""
+    """Pieces of fibers in eights and sixteens, chunks, runs inside slices."""
     dims, coords, rng = _fibers(MTTKRPS[name])
     cfg = dict(kind="mttkrp3", dims=dims, nnz=coords[0].size, ranks=(R,), dtype=dtype, expr=synth.KINDS["mttkrp3"][0])
     dt = np.float64 if dtype == "f64" else np.float32
@@ -308,11 +308,28 @@ def test_mttkrp_over_steps(oracle, name, dtype, R):
         finally:
             sc.tuning_set("tile_leaves", 0)
     assert "slice products" in sc.plan_describe(con.plan)
-    if dtype == "f32":
-        for at in (0, 1):
-            bad = [f.copy() for f in factors]
-            bad[at][coords[at + 1][-1], 3] = np.inf
-            _poisoned(oracle, cfg, dict(data, factors=bad), "fused", same=False)
+
+
+@pytest.mark.parametrize("at", [0, 1])
+@pytest.mark.parametrize("dtype,R", [("f32", 16), ("f32", 32), ("f64", 16)])
+def test_mttkrp_over_steps_with_infinities(oracle, dtype, R, at):
+    """An infinity or a NaN in rows of C or D reaches the outputs that refer to it only, and infinite sums stay infinite: also where a run begins inside a group,
+    some of whose pieces end in the run before."""
+    for name, shape in MTTKRPS.items():
+        least = 540_000 if (dtype, R) == ("f32", 16) else 280_000   # chunks of 16 steps: runs begin inside them
+        dims, coords, rng = _fibers(shape * -(-least // sum(map(sum, shape))))
+        cfg = dict(kind="mttkrp3", dims=dims, nnz=coords[0].size, ranks=(R,), dtype=dtype, expr=synth.KINDS["mttkrp3"][0])
+        dt = np.float64 if dtype == "f64" else np.float32
+        factors = [rng.uniform(0.5, 1.5, s).astype(dt) for s in synth.factor_shapes(cfg)]   # one sign: infinities stay infinities in any order
+        for n in range(factors[at].shape[0]):
+            factors[at][n, n % (R // 2)] = np.nan if n % 16 == 5 else np.inf
+        data = dict(coords=coords, vals=rng.uniform(0.5, 1, coords[0].size).astype(dt), factors=factors)
+        for leaves in (0, 32):
+            sc.tuning_set("tile_leaves", leaves)
+            try:
+                _poisoned(oracle, cfg, data, "fused")
+            finally:
+                sc.tuning_set("tile_leaves", 0)
 
 
 @pytest.mark.parametrize("dtype,R", [("f32", 16), ("f32", 32), ("f64", 16)])
@@ -394,14 +411,19 @@ def test_chain_of_order_4_longer_chunks(oracle, least, cap):
 @pytest.mark.parametrize("at", [0, 1, 2])
 def test_chain_of_order_4_with_infinities(oracle, at):
     """Only the outputs that refer to a row with an infinity or a NaN are not finite."""
-    for name in ("singles", "children", "lengths"):
-        dims, coords, rng = _chain(CHAINS[name])
+    for name, shape in CHAINS.items():
+        dims, coords, rng = _chain(shape * -(-300_000 // sum(sum(map(sum, s)) for s in shape)))   # chunks of 32 steps: runs begin inside them
         cfg = dict(kind="ttmc4", dims=dims, nnz=coords[0].size, ranks=(8, 8, 8), dtype="f32", expr=synth.KINDS["ttmc4"][0])
         factors = [rng.uniform(0.5, 1.5, s).astype(np.float32) for s in synth.factor_shapes(cfg)]   # one sign: infinities stay infinities in any order
-        for n in range(min(3, factors[at].shape[0])):
-            factors[at][n, n] = [np.inf, np.inf, np.nan][n]
-        _poisoned(oracle, cfg, dict(coords=coords, vals=rng.uniform(0.5, 1, coords[0].size).astype(np.float32), factors=factors), "fused",
-                  same=name != "lengths")   # a run's end inside an (i,j,k) fiber: zero times the row in the run that has no leaf of it
+        for n in range(factors[at].shape[0]):
+            factors[at][n, n % 4] = np.nan if n % 16 == 5 else np.inf
+        data = dict(coords=coords, vals=rng.uniform(0.5, 1, coords[0].size).astype(np.float32), factors=factors)
+        for leaves in (0, 32):   # runs of a batch begin inside children and groups
+            sc.tuning_set("tile_leaves", leaves)
+            try:
+                _poisoned(oracle, cfg, data, "fused")
+            finally:
+                sc.tuning_set("tile_leaves", 0)
 
 
 @pytest.mark.parametrize("which,dims,lengths,ranks", [
