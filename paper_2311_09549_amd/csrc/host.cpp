@@ -1664,7 +1664,7 @@ static sc_status plan_ttmc_all(sc_plan *p, const char *expr, const Term &lhs, co
     p->k5_s_offset = variant <= 1 ? 0 : take((size_t)p->dims[0] * (size_t)(p->fcols[1] * p->fcols[2]) * esize(p->dtype));
     p->k5_inner_ws_offset = take(variant == 0 ? 0 : in->ws_bytes);
     p->k5_partials_offset = take((size_t)p->k5_nchunks * (size_t)p->out_elems * esize(p->dtype));
-    if (split) p->k5_split_offset = take((size_t)((units + 31) / 32 * 32) * (size_t)p->fcols[0] * 6);
+    if (split) p->k5_split_offset = take((size_t)((units + 31) / 32 * 32) * (size_t)p->fcols[0] * 6 + (size_t)((units + 31) / 32) * (size_t)p->fcols[0] / 64 * 4);   // parts, and a mark per workgroup that makes them
     p->ws_bytes = off;
 
     // temporaries as the caller can read them back after a FISSIONED execution: t rows (one per fiber) and

@@ -180,14 +180,29 @@ __global__ void __launch_bounds__(NT, 2) mode0_reduce_mfma_kernel(K5Args a)
 // first, by v_mfma_f32_16x16x32_bf16, which takes 32 slices at 16 times the fp32 rate.
 // C is split once by a launch of its own into rows of eight slices (k5_split_kernel), so that a lane reads operand A, eight slices of one l, with
 // one 16-byte load per part; S is read as it is, eight slices of four columns per lane, and split in registers: it passes once.
-// Infinities become NaN on the way (h = x, m = x - h), as do values past the largest bf16 (3.39e38), and a value below 2^-109 loses its last bits,
-// which bf16 cannot hold.
-// Repeated calls, the reduction alone, 40,000 slices, fp32 and this form: 128 x 128 x 128 1398 and 810 us (S alone takes 450), 128 x 64 x 64 366 and 228,
-// 64 x 64 x 64 198 and 155.  Error against double precision 1.31e-6 and 0.74e-6, 6.3e-7 and 4.1e-7, 6.4e-7 and 2.0e-7.
+// Parts hold values from 2^-109 on, below which the last bits are lost, to 2^127, past which h may be infinite.  A step of which C or S has smaller ones
+// (C's are marked by the launch that splits it) is left for products in fp32 after the others; where a sum turns out not to be finite the whole chunk is
+// added up again in fp32 (k5_again): infinities, NaN, values past the largest bf16 and small ones give what the fp32 form gives, in about five times its time.
+// The tests for it take 1 to 5 % of the reduction (64 x 64 x 64 154 us without, 158 with them; 128 x 64 x 64 222 and 234; 128 x 128 x 128 even).
+// Repeated calls, the reduction alone, 40,000 slices, fp32 and this form: 128 x 128 x 128 1398 and 810 us (S alone takes 450), 128 x 64 x 64 372 and 234,
+// 64 x 64 x 64 202 and 158.  Error against double precision 1.31e-6 and 0.74e-6, 6.4e-7 and 4.1e-7, 6.4e-7 and 2.0e-7; of inputs of one sign 4.2e-7 and
+// 1.4e-7, 1.3e-7 and 0.8e-7, 1.3e-7 and 0.6e-7; 3 million slices at 128 x 16 x 16, chunks of 5,900, 1.36e-6 and 1.16e-6, of one sign 1.2e-7 and 1.0e-7.
+// (Where all inputs are alike every slice is rounded the same way, and either form may be ahead: 10,000 slices at 128 x 128 x 128 3.1e-7 and 2.0e-6, 3 million
+// at 128 x 16 x 16 1.9e-5 and 5.2e-6.)
 // At L = 64 the six products of a step are added up apart from the sum they go to; at L = 128, whose registers are
 // full, that took longer (942 us for 765), and shorter chunks serve instead (plan_ttmc_all).
 constexpr int K5_K = 32;   // slices per step
 typedef __bf16 k5_bf16 __attribute__((ext_vector_type(8)));
+
+// whether some of N values are not zero but smaller than 2^-109
+template <int N>
+__device__ __forceinline__ bool k5_small(const float (&x)[N])
+{
+    uint32_t least = 0xffffffffu;
+#pragma unroll
+    for (int j = 0; j < N; ++j) least = min(least, (__builtin_bit_cast(uint32_t, x[j]) << 1) - 1);   // |x| doubled as an integer, less one: zero is the largest
+    return least < (18u << 24) - 1;
+}
 
 // the nearest bf16 of a (low half) and b
 __device__ __forceinline__ uint32_t k5_pack(float a, float b)
@@ -218,24 +233,88 @@ __device__ __forceinline__ void k5_parts(const float (&x)[8], uint4 (&part)[3])
     }
 }
 
-// C3[part][slices / 8][l][8], slices up to a multiple of 32; slices past the last are zero
-__global__ void __launch_bounds__(NT) k5_split_kernel(const float *__restrict__ C, int64_t ldC, int64_t rows, int L, int64_t groups, uint4 *__restrict__ C3)
+// C3[part][slices / 8][l][8], slices up to a multiple of 32; slices past the last are zero.  L is 64 or 128, so that a workgroup's values are those of a step or half of one, and there
+// are no threads past the last: marks[workgroup] says whether some are too small for the parts.
+__global__ void __launch_bounds__(NT) k5_split_kernel(const float *__restrict__ C, int64_t ldC, int64_t rows, int L, int64_t groups, uint4 *__restrict__ C3,
+                                                      uint32_t *__restrict__ marks)
 {
     const int64_t n = (int64_t)blockIdx.x * NT + threadIdx.x;
-    if (n >= groups * L) return;
     const int64_t g = n / L;
     const int l = (int)(n % L);
     float x[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) x[j] = 8 * g + j < rows ? C[(8 * g + j) * ldC + l] : 0.f;
+    const int small = __syncthreads_or(k5_small(x));
+    if (threadIdx.x == 0) marks[blockIdx.x] = small;
     uint4 part[3];
     k5_parts(x, part);
 #pragma unroll
     for (int p = 0; p < 3; ++p) C3[(int64_t)p * groups * L + n] = part[p];
 }
 
+// whether a step is left for fp32: the values of S that the lane has, and the marks of C
+template <int LT>
+__device__ __forceinline__ bool k5_leave(const k5_floatx4 (&raw)[8], const uint32_t *marks, int64_t step)
+{
+    uint32_t marked = marks[step * (LT / 4)];
+    if (LT == 8) marked |= marks[step * (LT / 4) + 1];
+    float least = 1.f;
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+        for (int j = 0; j < 8; j += 2) __asm__("v_min3_f32 %0, |%1|, |%2|, %0" : "+v"(least) : "v"(raw[j][x]), "v"(raw[j + 1][x]));
+    bool some = least < 0x1p-109f;
+    if (__any(some)) {   // zeros, which slices without an entry are full of, or others
+        float v[32];
+#pragma unroll
+        for (int j = 0; j < 32; ++j) v[j] = raw[j / 4][j % 4];
+        some = k5_small(v);
+    }
+    return marked || __any(some);
+}
+
+// Adds the steps of a chunk that were left (all) to (as) what is stored, an l tile at a time: four slices per v_mfma_f32_16x16x4_f32, whose sums lie as
+// those of the kernel below.
+template <int LT>
+__device__ __forceinline__ void k5_again(const K5Args &a, int64_t r0, int64_t r1, int c, int kk, int col, const uint32_t *marks, bool all)
+{
+    const float *S = static_cast<const float *>(a.S) + c;
+#pragma clang loop unroll(disable)
+    for (int l = 0; l < 16 * LT; l += 16) {
+        float *P = static_cast<float *>(a.partials) + ((int64_t)blockIdx.x * a.L + l + 4 * kk) * a.MN + c;
+        const float *C = static_cast<const float *>(a.C) + l + col;
+        k5_floatx4 sum[4] = {};
+        if (!all)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const k5_floatx4 was = *reinterpret_cast<const k5_floatx4 *>(P + (int64_t)q * a.MN);
+#pragma unroll
+                for (int x = 0; x < 4; ++x) sum[x][q] = was[x];
+            }
+#pragma clang loop unroll(disable)
+        for (int64_t r = r0; r < r1; r += K5_K) {
+            if (!all) {
+                k5_floatx4 raw[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) raw[j] = *reinterpret_cast<const k5_floatx4 *>(S + min(r + 8 * kk + j, a.rows - 1) * a.MN);
+                if (!k5_leave<LT>(raw, marks, r / K5_K)) continue;
+            }
+#pragma clang loop unroll(disable)
+            for (int64_t i = r + kk; i < r + K5_K; i += 4) {
+                const bool have = i < a.rows;
+                const k5_floatx4 v = *reinterpret_cast<const k5_floatx4 *>(S + min(i, a.rows - 1) * a.MN);
+                const float cl = have ? C[min(i, a.rows - 1) * a.ldC] : 0.f;
+#pragma unroll
+                for (int x = 0; x < 4; ++x) sum[x] = __builtin_amdgcn_mfma_f32_16x16x4f32(cl, have ? v[x] : 0.f, sum[x], 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) *reinterpret_cast<k5_floatx4 *>(P + (int64_t)q * a.MN) = k5_floatx4{sum[0][q], sum[1][q], sum[2][q], sum[3][q]};
+    }
+}
+
 template <int LT>   // L = 16 LT, an even number of tiles
-__global__ void __launch_bounds__(NT, 2) mode0_reduce_split_kernel(K5Args a, const uint4 *__restrict__ C3, int64_t groups)
+__global__ void __launch_bounds__(NT, 2) mode0_reduce_split_kernel(K5Args a, const uint4 *__restrict__ C3, int64_t groups, const uint32_t *__restrict__ marks)
 {
     constexpr bool APART = LT <= 4;   // a step's products are added up before they are added to the sum
     // The instruction's own sums are cut off, not rounded, and always to the same side, which adds up over the steps.  So S is taken with the other
@@ -263,20 +342,24 @@ __global__ void __launch_bounds__(NT, 2) mode0_reduce_split_kernel(K5Args a, con
 #pragma unroll
         for (int p = 0; p < 3; ++p) v[p] = Cl[p * part + r / 8 * a.L + 16 * lt];
     };
+    bool left = false;   // some steps are left for fp32
     load_s(r0);
     load_c(cv[0], r0, 0);
     float sign = 1.f;
     int to_turn = TURN;
     for (int64_t r = r0; r < r1; r += K5_K) {
+        const int64_t rn = min(r + K5_K, r1 - 1) / K5_K * K5_K;   // the next step, or this one again
+        const bool skip = k5_leave<LT>(raw, marks, r / K5_K);
+        left |= skip;
+        const float scale = skip ? 0.f : sign;
         uint4 s[4][3];
 #pragma unroll
         for (int x = 0; x < 4; ++x) {
             float v[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = r + 8 * kk + j < a.rows ? sign * raw[j][x] : 0.f;   // (slices past the last: zero times zero)
+            for (int j = 0; j < 8; ++j) v[j] = r + 8 * kk + j < a.rows ? scale * raw[j][x] : 0.f;   // (slices past the last: zero times zero)
             k5_parts(v, s[x]);
         }
-        const int64_t rn = min(r + K5_K, r1 - 1) / K5_K * K5_K;   // the next step, or this one again
         load_s(rn);
 #pragma unroll
         for (int lt = 0; lt < LT; ++lt) {
@@ -315,6 +398,12 @@ __global__ void __launch_bounds__(NT, 2) mode0_reduce_split_kernel(K5Args a, con
         for (int lt = 0; lt < LT; ++lt)
 #pragma unroll
             for (int x = 0; x < 4; ++x) acc[lt][x] *= sign;
+    k5_floatx4 none = {0.f, 0.f, 0.f, 0.f};   // ... if every sum is finite
+#pragma unroll
+    for (int lt = 0; lt < LT; ++lt)
+#pragma unroll
+        for (int x = 0; x < 4; ++x) none += acc[lt][x] * 0.f;
+    const bool again = __any(!(none[0] + none[1] + none[2] + none[3] == 0.f));
     // acc[lt][x][q] = partial(l = 16 lt + 4 kk + q, column c + x)
     float *P = static_cast<float *>(a.partials) + (int64_t)blockIdx.x * a.L * a.MN + c;
 #pragma unroll
@@ -322,6 +411,10 @@ __global__ void __launch_bounds__(NT, 2) mode0_reduce_split_kernel(K5Args a, con
 #pragma unroll
         for (int q = 0; q < 4; ++q)
             *reinterpret_cast<k5_floatx4 *>(P + (int64_t)(16 * lt + 4 * kk + q) * a.MN) = k5_floatx4{acc[lt][0][q], acc[lt][1][q], acc[lt][2][q], acc[lt][3][q]};
+    if (!left && !again) return;
+    int ln = lane;
+    __asm__ volatile("" : "+v"(ln));   // addresses are worked out here: kept over the loop above they cost registers, as `acc` would over this one
+    k5_again<LT>(a, r0, r1, ((int)blockIdx.y * ((int)blockDim.x / 64) + wave) * 64 + 4 * (ln % 16), ln / 16, ln % 16, marks, again);
 }
 
 // partial(b, l, (m,n)) = sum_{fibers f in chunk b} C(i_f,l) * D(j_f,m) * t(f,n); thread = (m,n)
@@ -519,12 +612,13 @@ sc_status run_ttmc_all(const sc_plan *p, const sc_csf_view *sp, const sc_dense_v
                     const int64_t groups = (a.rows + K5_K - 1) / K5_K * (K5_K / 8);
                     uint4 *C3 = reinterpret_cast<uint4 *>(wsb + p->k5_split_offset);
                     ln.begin("ttmc_all_split");
-                    k5_split_kernel<<<(unsigned)((groups * L + NT - 1) / NT), NT, 0, stream>>>(static_cast<const float *>(a.C), a.ldC, a.rows, L, groups, C3);
+                    uint32_t *marks = reinterpret_cast<uint32_t *>(C3 + 3 * groups * L);
+                    k5_split_kernel<<<(unsigned)(groups * L / NT), NT, 0, stream>>>(static_cast<const float *>(a.C), a.ldC, a.rows, L, groups, C3, marks);
                     ln.end();
                     const int strips = MN / 64, waves = strips % 4 == 0 ? 4 : strips % 2 == 0 ? 2 : 1;   // wavefronts per workgroup
                     const dim3 sgrid((unsigned)p->k5_nchunks, (unsigned)(strips / waves), 1);
                     ln.begin("ttmc_all_mode0_reduce_split");
-                    auto reduce = [&](auto lt) { mode0_reduce_split_kernel<decltype(lt)::value><<<sgrid, 64 * waves, 0, stream>>>(a, C3, groups); };
+                    auto reduce = [&](auto lt) { mode0_reduce_split_kernel<decltype(lt)::value><<<sgrid, 64 * waves, 0, stream>>>(a, C3, groups, marks); };
                     if (L == 64) reduce(std::integral_constant<int, 4>{});
                     else if (L == 128) reduce(std::integral_constant<int, 8>{});
                     else return SC_ERR_SCHED_UNSUPPORTED;

@@ -169,6 +169,44 @@ def test_core_tensor_reduction_in_parts(oracle, ranks, rows):
         np.testing.assert_array_equal(~np.isfinite(con.result()).all(axis=(1, 2)), bad)
 
 
+@pytest.mark.parametrize("what", ["positive", "constant", "infinite", "not a number", "largest", "small slices", "small C"])
+@pytest.mark.parametrize("ranks,n", [((64, 64, 64), 7650), ((128, 128, 128), 995)])
+def test_core_tensor_reduction_range(oracle, ranks, n, what):
+    """Products of 16 bits where the error could add up to one side, and where their parts cannot hold the values: infinities, values that the largest bf16 does not
+    reach, and values whose last bits are below the smallest (all alike, so that a lost bit is lost the same way in every slice)."""
+    cfg, data = _problem("ttmc_all", (n, 41, 97), [(i, 1 + i % 3 // 2) for i in range(1, n - n // 9)], ranks, "f32")
+    rng = np.random.default_rng(1)
+    C, D, E = (rng.uniform(0.5, 1.5, f.shape).astype(np.float32) for f in data["factors"])
+    if what not in ("positive", "infinite", "not a number", "largest"):
+        C[:], D[:], E[:] = 1.2345, 1.3456, 1.4567
+    vals = np.full(data["vals"].shape, 0.7, np.float32) if what != "positive" else rng.uniform(0.5, 1, data["vals"].shape).astype(np.float32)
+    i, j = int(data["coords"][0][-1]), int(data["coords"][1][0])
+    if what in ("infinite", "not a number"):
+        C[i, 5] = np.inf if what == "infinite" else np.nan
+        D[j, 3] = np.inf
+    elif what == "largest":
+        C[i - 40 : i, :] = np.float32(3.4e38)
+        D *= np.float32(2.0**-60)
+    elif what == "small slices":
+        D *= np.float32(2.0**-61)
+        E *= np.float32(2.0**-61)
+    elif what == "small C":
+        C *= np.float32(2.0**-121)
+    data = dict(data, vals=vals, factors=[C, D, E])
+    con = _run(cfg, data, "fused")
+    sc.plan_set_profiling(con.plan, True)
+    con.run()
+    got = con.result().astype(np.float64)
+    assert any(name == "ttmc_all_mode0_reduce_split" for name, _ in sc.plan_kernel_times(con.plan))
+    with np.errstate(invalid="ignore"):
+        ref = oracle.contract(cfg["kind"], data["coords"], vals, cfg["dims"], data["factors"])
+    fine = np.isfinite(ref)
+    np.testing.assert_array_equal(got[~fine], ref[~fine])
+    # one sign: |sum| is the sum of the absolute products.  2-norm: four roundings; alike in every slice, roundings add up over the steps of a chunk
+    err = np.linalg.norm(got[fine] - ref[fine]) / np.linalg.norm(ref[fine])
+    assert err <= (4 * 2.0**-24 if what not in ("constant", "small slices", "small C") else 4e-6), err
+
+
 # ---- slice products: steps, chunks (of 16 steps at these sizes, of 32 and 64 below), runs, sums over the runs of a workgroup ----
 def _fibers(shape, seed=0):
     """shape: per slice a list of fiber lengths; every fiber's entries start at a drawn place of the last mode."""
