@@ -33,8 +33,9 @@
  *   - fp32 sums are of fp32 products.  In the core tensor of a factor on every mode (fp32, large problems) each is the sum of six
  *     products of bf16 parts of its factors, exact but for what lies below 2^-26 of it; values that such parts do not hold
  *     (below 2^-109, above 2^127, infinities, NaN) are multiplied in fp32.
- *   - An infinity or a NaN reaches no output element that does not refer to it.  One that does is not finite: NaN instead of
- *     infinite where a schedule takes its sum in parts of both signs, or multiplies by masked zeros.
+ *   - An infinity or a NaN reaches no output element that does not refer to it (the core tensor of a factor on every
+ *     mode refers to every row of the first one).  One that does is not finite: NaN instead of infinite where a schedule takes
+ *     its sum in parts of both signs, or multiplies by masked zeros.
  *   - `on_device` says whether the pointers of a view are host (0) or device (1) memory.
  *   - sc_execute allocates nothing, never synchronises and launches only on the stream
  *     it is given.  sc_plan_create allocates the plan-owned device tables: tile records and,
