@@ -739,21 +739,36 @@ void list_steps(SliceSource src, int piece, int wide, int cap, const HostCsf &h,
 struct ChainPieces {
     struct Kid { int32_t z, len, k; };
     struct Piece { int32_t first, stride, n, j; };   // children kids[first], kids[first + stride] ...
+    struct At { int32_t z, f3, f2, nkids, npieces; };   // leaf, (i,j,k) fiber, (i,j) fiber; what was made of the leaves before
     Kid kids[256];
     Piece pieces[256];
-    uint64_t order[256];   // pieces by the number of children, then by their lengths: 4 bits each from the top, the piece below
-    int32_t nkids, npieces;
-    // where the leaves that were taken end: leaf, (i,j,k) fiber, (i,j) fiber
-    int32_t z, f3, f2;
+    uint64_t order[256];   // pieces, largest first, by a key of the number of children, then their lengths, 4 bits each from the top, then as they came (255 - piece)
+    At fibers[256];                   // where each (i,j) fiber begins
+    int32_t nkids, npieces, nfibers;
+    int32_t z, f3, f2;                // where the leaves that were taken end
 
-    // Takes the leaves [z, z1) of one slice, z in the (i,j,k) fiber f3 of the (i,j) fiber f2.
+    // At leaf z of the (i,j,k) fiber f3 of the (i,j) fiber f2.
+    void begin(int32_t leaf, int32_t fiber3, int32_t fiber2)
+    {
+        z = leaf, f3 = fiber3, f2 = fiber2;
+        nkids = npieces = nfibers = 0;
+    }
+    // Takes the leaves up to z1, all of one slice; gives back what was taken past it.
     void take(const HostCsf &h, int32_t z1)
     {
         const int32_t *pos2 = h.pos[2], *pos3 = h.pos[3], *crd1 = h.crd[1], *crd2 = h.crd[2];
-        nkids = npieces = 0;
-        uint64_t any = 0, all = ~0ull;   // bits that some (all) keys have
+        if (z1 < z) {
+            while (fibers[--nfibers].z >= z1) {}
+            const At &b = fibers[nfibers];
+            z = b.z, f3 = b.f3, f2 = b.f2, nkids = b.nkids, npieces = b.npieces;
+            int32_t kept = 0;
+            for (int32_t i = 0; kept < npieces; ++i)
+                if (255 - (int32_t)(order[i] & 255) < npieces) order[kept++] = order[i];
+        }
+        const int32_t old = npieces;
         while (z < z1) {
             const int32_t first = nkids, f_end = pos2[f2 + 1];
+            fibers[nfibers++] = At{z, f3, f2, nkids, npieces};
             bool equal = true;
             while (z < z1 && f3 < f_end) {
                 const int32_t z_end = pos3[f3 + 1], len = std::min(std::min(z_end, z1) - z, kSlicePiece);
@@ -774,14 +789,21 @@ struct ChainPieces {
             const int32_t np = (n + kChainPiece - 1) / kChainPiece;   // dealt out in turn
             for (int32_t i = 0; i < np; ++i) {
                 const Piece pc = {first + i, np, np == 1 ? n : (n - i + np - 1) / np, crd1[f2]};
-                uint64_t key = (uint64_t)pc.n << 60 | (uint64_t)npieces;
+                uint64_t key = (uint64_t)pc.n << 60 | (uint64_t)(255 - npieces);
                 for (int32_t u = 0; u < pc.n; ++u) key |= (uint64_t)(kids[pc.first + u * np].len - 1) << (56 - 4 * u);
-                any |= key;
-                all &= key;
-                order[npieces] = key;
+                int32_t at = npieces;
+                if (old > 0)   // few, into those in order
+                    for (; at > 0 && order[at - 1] < key; --at) order[at] = order[at - 1];
+                order[at] = key;
                 pieces[npieces++] = pc;
             }
             if (f3 == f_end) ++f2;
+        }
+        if (old > 0) return;
+        uint64_t any = 0, all = ~0ull;   // bits that some (all) keys have
+        for (int32_t i = 0; i < npieces; ++i) {
+            any |= order[i];
+            all &= order[i];
         }
         for (int shift = 64 - 4 * (kChainPiece + 1); shift < 64; shift += 4) {   // digit by digit, largest first, those alike as they came
             if (!((any & ~all) >> shift & 15)) continue;
@@ -792,7 +814,7 @@ struct ChainPieces {
             for (int32_t i = 0; i < npieces; ++i) order[at[was[i] >> shift & 15]++] = was[i];
         }
     }
-    const Piece &piece(int32_t n) const { return pieces[order[n] & 255]; }
+    const Piece &piece(int32_t n) const { return pieces[255 - (order[n] & 255)]; }
     int32_t longest(int32_t g, int32_t u) const   // leaves of the u-th children of the group that starts at the n-th piece, whose first piece has most children
     {
         uint64_t most = 0;
@@ -804,6 +826,12 @@ struct ChainPieces {
         int32_t s = from;
         for (int32_t g = 0; g < npieces; g += 4) {
             const int32_t n = (int32_t)(order[g] >> 60);
+            uint64_t any = 0;
+            for (int32_t q = g; q < std::min(g + 4, npieces); ++q) any |= order[q];
+            if (!(any & ((1ull << 60) - (1ull << (60 - 4 * kChainPiece))))) {   // single leaves
+                s += n;
+                continue;
+            }
             for (int32_t u = 0; u < n; ++u) {
                 const int32_t most = longest(g, u);
                 s = most > 1 ? (s + 1) / 2 * 2 + (most + 1) / 2 * 2 : s + 1;
@@ -872,21 +900,20 @@ void list_chain(int cap, const HostCsf &h, int64_t s0, int64_t s1, SlicePart &b)
     b.gk.reserve(kids * 5 / 4 + 1024);
     make_room();
     b.gj.reserve((size_t)(pos1[s1] - pos1[s0]) * 5 / 4 + kids / 8 + 1024);
-    ChainPieces w, next;
-    next.z = c.leaf0;
-    next.f3 = pos2[pos1[s0]];
-    next.f2 = pos1[s0];
+    ChainPieces w;
+    w.begin(c.leaf0, pos2[pos1[s0]], pos1[s0]);
     for (int64_t s = s0; s < s1; ++s) {
         const int32_t zend = pos3[pos2[pos1[s + 1]]];
         // a slice longer than what is left of a chunk starts the next one, unless much is left
-        if (cap - c.nsteps < 8 && (zend - next.z) / 4 >= cap - c.nsteps) flush(next.z, (int32_t)s);
-        while (next.z < zend) {
+        if (cap - c.nsteps < 8 && (zend - w.z) / 4 >= cap - c.nsteps) flush(w.z, (int32_t)s);
+        while (w.z < zend) {
             // as many leaves as make steps for what is left of the chunk
             const int32_t room = cap - c.nsteps;
-            int32_t n = std::min(zend - next.z, 4 * room), steps;
+            const int32_t z0 = w.z;
+            int32_t n = std::min(zend - z0, 4 * room), steps;
+            w.begin(z0, w.f3, w.f2);
             for (;;) {
-                w.z = next.z, w.f3 = next.f3, w.f2 = next.f2;
-                w.take(h, next.z + n);
+                w.take(h, z0 + n);
                 steps = w.steps(c.nsteps) - c.nsteps;
                 if (steps <= room) break;
                 n = std::max(1, std::min(n - 1, (int32_t)((int64_t)n * room / steps)));
@@ -923,11 +950,10 @@ void list_chain(int cap, const HostCsf &h, int64_t s0, int64_t s1, SlicePart &b)
                 c.gend |= 1ull << (c.nsteps - 1);
             }
             c.nleaves += n;
-            next.z = w.z, next.f3 = w.f3, next.f2 = w.f2;
-            if (next.z < zend) flush(next.z, (int32_t)s);
+            if (w.z < zend) flush(w.z, (int32_t)s);
         }
         c.send |= 1ull << (c.nsteps - 1);
-        if (c.nsteps == cap) flush(next.z, (int32_t)s + 1);
+        if (c.nsteps == cap) flush(w.z, (int32_t)s + 1);
     }
     flush(0, 0);
     b.leaf.resize(4 * (size_t)b.nsteps);
