@@ -969,14 +969,14 @@ void build_slices(const sc_plan *p, SliceSource src, int piece, const HostCsf &h
     const int wide = src == SLICE_MTTKRP ? (int)(1024 / (p->fcols[0] * (int64_t)esize(p->dtype))) : 4;   // leaves (children) per step
     int cap = std::min(64, 256 / wide);
     while (cap > std::max(8, 64 / wide) && (src == SLICE_ROWS ? children : p->nnz) < (int64_t)wide * cap * 8 * p->n_cu) cap /= 2;
-    // A thread per 256,000 leaves (children), 64,000 of an MTTKRP, 32,000 of a chain of order 4, whose listing takes longer, at most eight; ranges of
-    // slices with about equal numbers of them.  Plans made with 256,000 and so: MTTKRP of 400,000 entries 2.1 and 1.3 ms; order-4 chains of 100,000 3.5
-    // and 2.0 ms, of a million 11 and 8.6.
+    // A thread per 256,000 leaves (children), 32,000 of an MTTKRP, 16,000 of a chain of order 4, whose listing takes longer, at most eight; ranges of
+    // slices with about equal numbers of them.  Median plan with shares of twice, once, a half and a quarter of that, ms: MTTKRP of 100,000 entries 1.11,
+    // 1.00, 0.98 and 1.01, of 300,000 2.15, 1.67, 1.78 and 1.78; order-4 chains of 100,000 1.96, 1.50, 1.76 and 1.78, of a million 7.9, 7.5, 7.6 and 7.5.
     const int32_t *pos1 = h.pos[1], *pos2 = src == SLICE_ROWS ? nullptr : h.pos[2], *pos3 = src == SLICE_CHAIN ? h.pos[3] : nullptr;
     auto before = [&](int64_t s) { return (int64_t)(pos3 ? pos3[pos2[pos1[s]]] : pos2 ? pos2[pos1[s]] : pos1[s]); };
     const int64_t units = before(S);
     const int64_t most_threads = std::max<int64_t>(1, std::min<int64_t>(8, std::thread::hardware_concurrency()));
-    const int64_t nparts = std::max<int64_t>(1, std::min(units / (src == SLICE_CHAIN ? 32000 : src == SLICE_MTTKRP ? 64000 : 256000), most_threads));
+    const int64_t nparts = std::max<int64_t>(1, std::min(units / (src == SLICE_CHAIN ? 16000 : src == SLICE_MTTKRP ? 32000 : 256000), most_threads));
     std::vector<int64_t> from(1, 0);
     for (int64_t n = 1; n < nparts; ++n) {
         int64_t lo = from.back(), hi = S;   // first slice that begins at or after the n-th share
