@@ -271,7 +271,8 @@ sc_status sc_plan_kernel_time(const sc_plan *plan, int32_t index, char *name, si
  * the leaf range [n0, n1) and, for each CSF level above the leaves (a = parents of the
  * leaves, b = the level above, c = the one above that), the first node and the node count
  * the tile touches; flag bit 2*lvl is set when the first node of that level also has leaves
- * in an earlier tile, bit 2*lvl+1 when the last node also has leaves in a later tile. */
+ * in an earlier tile, bit 2*lvl+1 when the last node also has leaves in a later tile.  Plans whose
+ * kernel works through runs of steps (see sc_tuning_set) run none of these tiles. */
 sc_status sc_plan_tile_count(const sc_plan *plan, int64_t *count);
 sc_status sc_plan_tile(const sc_plan *plan, int64_t index, int32_t rec[9]);
 
@@ -283,9 +284,10 @@ sc_status sc_plan_tile(const sc_plan *plan, int64_t index, int32_t rec[9]);
  * (stride of the order in which tiles are handed to workgroups; 1 = tensor order),
  * "persistent_per_cu" (workgroups per compute unit launched by the kernels that loop over
  * tiles; 0 = as many as fit).  Plans whose kernel works through runs of steps instead (fp32 chains of
- * order 3 that need not be reproducible) have no work tiles: sc_plan_tile gives the tiles the caps
- * would make, "tile_leaves" bounds the length of a run (a quarter of it in steps, at least eight) and
- * "persistent_per_cu" the number of runs (four per workgroup).  Unknown names give
+ * order 3, of order 4 at 8 x 8 and MTTKRPs with long slices that need not be reproducible; sc_plan_describe
+ * says "slice products") have no work tiles: sc_plan_tile gives the tiles the caps
+ * would make, "tile_leaves" bounds the length of a run (a quarter of it in steps, at least eight, sixteen at
+ * order 4) and "persistent_per_cu" the number of runs (four per workgroup).  Unknown names give
  * SC_ERR_EXPR_PARSE; sc_plan_create rejects caps whose on-chip buffers would not fit a kernel over tiles. */
 sc_status sc_tuning_set(const char *name, int64_t value);
 

@@ -2166,12 +2166,13 @@ static sc_status plan_create_impl(sc_plan **out, const char *expr, const sc_csf_
     for (int t = 0; t < p->n_inter; ++t)
         appendf(tx, "temporary %d: %s, %lld x %lld, position-compressed along the sparse prefix%s\n", t, p->inter[t].name.c_str(),
                 (long long)p->inter[t].rows, (long long)p->inter[t].cols,
-                p->sched == SC_SCHED_FUSED ? ", live per tile only" : "");
+                p->sched != SC_SCHED_FUSED ? "" : src == SLICE_NONE ? ", live per tile only" : ", live in registers only");
     appendf(tx, "structure: nnz=%lld", (long long)p->nnz);
     for (int m = 0; m < d - 1; ++m) appendf(tx, " nodes[%d]=%lld", m, (long long)p->nfib[m]);
     appendf(tx, "\ntiles: %zu (<= %d leaves, <= %d level-a nodes", p->tiles.size(), p->caps.tn, p->caps.ta);
     if (d == 4) appendf(tx, ", <= %d level-b nodes", p->caps.tb);
-    appendf(tx, ")\nmodel: %.6g flops, %.6g compulsory HBM bytes, workspace %zu bytes\n", flops, bytes, p->ws_bytes);
+    appendf(tx, ")%s\nmodel: %.6g flops, %.6g compulsory HBM bytes, workspace %zu bytes\n", tiles_read ? "" : ", none of them run: the kernel works through runs of steps",
+            flops, bytes, p->ws_bytes);
     if (p->deterministic) {
         appendf(tx, "deterministic: %zu output rows span several tiles; their %lld pieces are stored in the workspace and added in tile order (%zu segments of at most %d)\n",
                 p->det_top.fix.size(), (long long)p->det_top.n_slots, p->det_top.segs.size(), kFixSegment);

@@ -182,8 +182,6 @@ __global__ void __launch_bounds__(NT, 4) chain4_kernel(ChainArgs a, const SliceR
         co[4] = row_at(st.j.z, a.rowC);
         co[6] = row_at(st.j.w, a.rowC);
         sl_lanes_meet();
-        // Where a run's end cuts a group, a child without a leaf (a piece without a child) in the one run has no row in it: its sum there is zero, and zero
-        // times a row with an infinity is no number.
         if (from > 0 && !(gm >> (from - 1) & 1)) {
             // The run begins inside a group: a child whose leaves (a piece whose children) all lie in the run before has no row in this one (its sum
             // here is zero, and zero times a row with an infinity is no number).

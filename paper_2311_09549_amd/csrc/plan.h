@@ -143,7 +143,7 @@ struct ChainChunk {
 static_assert(sizeof(ChainChunk) == 16, "ChainChunk layout");
 
 struct SliceRun {
-    int32_t chunk0, step;   // first chunk, and the run's first step in it (a multiple of 8)
+    int32_t chunk0, step;   // first chunk, and the run's first step in it (a multiple of 8, of kChainBatch in a chain of order 4)
     int32_t flags;          // bit 0: the slice of that step began in an earlier run
     int32_t pad;
 };
@@ -157,9 +157,10 @@ struct SliceTables {
     int32_t nruns = 0;
     SliceRun *d_runs = nullptr;       // nruns + 1
     SliceChunk *d_chunks = nullptr;
-    uint32_t *d_leaf = nullptr;       // from the leaves: 4 per step, last coordinate of the leaf of each child of the group (-1: none)
+    // G = 4 children per step, of an MTTKRP 8 (rows of 128 bytes) or 16 (of 64); a chunk holds at most 64 steps and 256 leaves, and a piece is no longer than a chunk's steps
+    uint32_t *d_leaf = nullptr;       // from the leaves: G per step, last coordinate of the leaf of each child of the group (-1: none)
     uint32_t *d_at = nullptr;         // ... a byte for each of these: the leaf's place in the chunk (255: none, unless the chunk has 256)
-    int32_t *d_gj = nullptr;          // ... 4 per group: coordinate of the child (-1: none)
+    int32_t *d_gj = nullptr;          // ... G per group: coordinate of the child (-1: none)
     int32_t *d_first = nullptr;       // from rows of T: first child of every step and the child count
     ChainChunk *d_kids = nullptr;     // chains of order 4: beside d_chunks
     int32_t *d_gk = nullptr;          // ... 8 for every pair of steps in which children end, 4 per step: coordinate of the (i,j,k) fiber (-1: none)

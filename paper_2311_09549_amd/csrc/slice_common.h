@@ -1,4 +1,4 @@
-// What the kernels that work in steps of four children share (kernels_slice.hip, kernels_chain4.hip): rows gathered through buffer
+// What the kernels that work in steps share (kernels_slice.hip, kernels_chain4.hip, kernels_mttkrp.hip): rows gathered through buffer
 // descriptors, exchange of values between the lanes of a wavefront, sums over the runs of a workgroup.
 #pragma once
 
