@@ -19,7 +19,7 @@
 //                                                                   (row = lane of the 16, k = kk), the lane's value of the row of C is operand B
 // so nothing passes through LDS from the leaves to the output.
 //
-// Bound by instruction issue: vector ALU 0.36 and matrix pipes 0.35 of the cycles at four wavefronts per SIMD, L1 address path 0.66.  Without the gathers 452
+// Bound by instruction issue: vector ALU 0.43 and matrix pipes 0.35 of the cycles at 3.6 wavefronts per SIMD, L1 address path 0.68.  Without the gathers 452
 // us, without the products of group ends as well 340.  Repeated calls, 50 M entries at 8 x 8 x 8, 921 us in the kernel over tiles that ran before
 // (both temporaries in LDS, three barriers per tile) and 550 now; a gather and a test per step and child, without the pairs, 605; rows of D gathered
 // only where children end 560.

@@ -3,7 +3,7 @@
 // G = 64 / LG lane groups of a wavefront take pieces of G fibers of a slice at a time, grouped by length, so that all of them end in the same
 // step: a row of C is gathered once per group of pieces, with every lane in use, where a walk of each lane group for itself gathers under the mask of the fibers that end at every step.  A
 // gather of 16 bytes per lane takes the L1 address path 16 cycles whatever its mask, and that path is what bounds these kernels.
-// 20 M entries at rank 32: 182 us in the kernel over tiles and 157 so; the path is 0.93 busy, at 21 cycles per gather where the rows that come
+// 20 M entries at rank 32: 182 us in the kernel over tiles and 157 so; the path is 0.92 busy, at 21 cycles per gather where the rows that come
 // from the L2 (2 cycles a line) are counted in; at rank 16 174 and 136.
 // A wavefront owns a run of steps; there is no barrier until its end.  The sum over a slice stays in registers, is added up over the lane groups where the
 // slice ends, and stored; a slice cut by a run's end is added to the zeroed row atomically,
