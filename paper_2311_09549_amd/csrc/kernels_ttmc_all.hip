@@ -187,8 +187,8 @@ __global__ void __launch_bounds__(NT, 2) mode0_reduce_mfma_kernel(K5Args a)
 // Repeated calls, the reduction alone, 40,000 slices, fp32 and this form: 128 x 128 x 128 1398 and 810 us (S alone takes 450), 128 x 64 x 64 372 and 234,
 // 64 x 64 x 64 202 and 158.  Error against double precision 1.31e-6 and 0.74e-6, 6.4e-7 and 4.1e-7, 6.4e-7 and 2.0e-7; of inputs of one sign 4.2e-7 and
 // 1.4e-7, 1.3e-7 and 0.8e-7, 1.3e-7 and 0.6e-7; 3 million slices at 128 x 16 x 16, chunks of 5,900, 1.36e-6 and 1.16e-6, of one sign 1.2e-7 and 1.0e-7.
-// (Where all inputs are alike every slice is rounded the same way, and either form may be ahead: 10,000 slices at 128 x 128 x 128 3.1e-7 and 2.0e-6, 3 million
-// at 128 x 16 x 16 1.9e-5 and 5.2e-6.)
+// (Where all inputs are alike every slice is rounded the same way, and either form may be ahead: at ten sizes, 995 to a million slices at L = 64 and 128, the
+// fp32 form is 1.3e-7 to 2.8e-5 off and this one 0.2e-7 to 2.9e-6, in three of them further than fp32.  Of random inputs and of one sign it is ahead at all ten.)
 // At L = 64 the six products of a step are added up apart from the sum they go to; at L = 128, whose registers are
 // full, that took longer (942 us for 765), and shorter chunks serve instead (plan_ttmc_all).
 constexpr int K5_K = 32;   // slices per step
